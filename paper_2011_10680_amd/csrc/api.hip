@@ -177,7 +177,8 @@ bool make_rp1_args(const ConvArgs &a, int x_hi, int xs_hi, Rp1Args &r) {
 
 hawq_status dispatch_conv(const ConvArgs &a, int x_hi, hipStream_t s) {
     if (a.M == 0) return HAWQ_OK;
-    if (a.x_dt == HAWQ_U8 && x_hi > 127 && gemm_splitk_eligible(a)) return launch_gemm_splitk(a, x_hi, s);
+    const bool sk = conv_sk_eligible(a, x_hi);
+    if (tile_override() == 0 && sk && conv_sk_small(a)) return launch_conv_sk(a, x_hi, s);
     if (conv_pw_eligible(a, x_hi)) return launch_conv_pw(a, s);
     if (tile_override() == 0 && conv_pws_eligible(a, x_hi)) return launch_conv_pws(a, s);
     if (tile_override() == 0 && conv3x3_c64_eligible(a, x_hi)) return launch_conv3x3_c64(a, s);
@@ -188,6 +189,7 @@ hawq_status dispatch_conv(const ConvArgs &a, int x_hi, hipStream_t s) {
         if (make_rp1_args(a, x_hi, 0, r1)) return launch_conv_rp1(r1, s);
     }
     if (conv_mfma_eligible(a, x_hi)) return launch_conv_mfma(a, s);
+    if (sk) return launch_conv_sk(a, x_hi, s);
     return launch_conv_direct(a, s);
 }
 
@@ -219,12 +221,15 @@ hawq_status make_dual_args(const hawq_conv_desc *d, const void *x, const void *w
 
 hawq_status dispatch_conv_dual(const ConvArgs &a, int x_hi, int xs_hi, hipStream_t s) {
     if (a.M == 0) return HAWQ_OK;
+    const bool sk = conv_sk_dual_eligible(a, x_hi, xs_hi);
+    if (tile_override() == 0 && sk && conv_sk_small(a)) return launch_conv_sk(a, x_hi, s);
     if (conv_pws_dual_eligible(a, x_hi, xs_hi)) return launch_conv_pws_dual(a, s);
     if (tile_override() == 0 && a.w_f != nullptr && a.ws_f != nullptr) {
         Rp1Args r1;
         if (make_rp1_args(a, x_hi, xs_hi, r1)) return launch_conv_rp1(r1, s);
     }
     if (conv_mfma_dual_eligible(a, x_hi, xs_hi)) return launch_conv_mfma_dual(a, s);
+    if (sk) return launch_conv_sk(a, x_hi, s);
     return launch_conv_direct(a, s);
 }
 

@@ -192,6 +192,11 @@ int tile_override();
 // 3x3 / stride 1 / pad 1, 64 -> 64 channels, INT8: weights resident in LDS, pixel operand kept across the taps
 bool conv3x3_c64_eligible(const ConvArgs &a, int x_hi);
 hawq_status launch_conv3x3_c64(const ConvArgs &a, hipStream_t s);
+// split-reduction kernel: small launches, channel counts that are a multiple of 16 only, unsigned bytes above 127
+bool conv_sk_eligible(const ConvArgs &a, int x_hi);
+bool conv_sk_dual_eligible(const ConvArgs &a, int x_hi, int xs_hi);
+hawq_status launch_conv_sk(const ConvArgs &a, int x_hi, hipStream_t s);
+bool conv_sk_small(const ConvArgs &a);   // preferred over the other kernels that take the shape
 hawq_status launch_conv_direct(const ConvArgs &a, hipStream_t s);   // any valid shape (also with a shortcut convolution)
 // matrix-core kernel for a block output with a convolution on both branches (ConvArgs::xs set)
 bool conv_mfma_dual_eligible(const ConvArgs &a, int x_hi, int xs_hi);
@@ -206,9 +211,6 @@ hawq_status launch_conv_pw(const ConvArgs &a, hipStream_t s);
 // same, for C = 256 with K >= 256 a multiple of 128: the activation stage is shared by a workgroup's four waves
 bool conv_pws_eligible(const ConvArgs &a, int x_hi);
 hawq_status launch_conv_pws(const ConvArgs &a, hipStream_t s);
-// few rows, long reduction (the fully connected layer): eight waves split the reduction, partial tiles meet in LDS
-bool gemm_splitk_eligible(const ConvArgs &a);
-hawq_status launch_gemm_splitk(const ConvArgs &a, int x_hi, hipStream_t s);
 // conv1 of the networks: 7x7/2 pad 3, C=3 -> 64, weights re-tiled to [64][8][8][4] and the
 // bias corrected for the -128 input offset by the host (see net.hip)
 hawq_status launch_conv_stem(const ConvArgs &a, hipStream_t s);
