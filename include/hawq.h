@@ -29,7 +29,7 @@
  *    keep |acc + bias| < 2^31.
  *  - Errors are return codes; argument validation happens on the host before any launch
  *    (so it can be exercised without a GPU): a call that fails validation has enqueued nothing.
- *    The entry points that issue several launches (hawq_concat_dyadic: one per branch;
+ *    The entry points that issue several launches (hawq_concat_dyadic: one per branch in its general form;
  *    hawq_forward_resnet: one per layer) validate everything they can first; should a later
  *    launch itself fail (HAWQ_ERR_DEVICE), the launches already issued stay enqueued, the
  *    streams are still joined, and the outputs are undefined.
@@ -236,7 +236,8 @@ hawq_status hawq_pool2d_sum_int(int32_t N, int32_t H, int32_t W, int32_t C, int3
  *   y[p, off_i + k] = clamp( rq(q_i[p,k], b_i[k], c_i[k]), y_lo, y_hi ),   off_i = K_0 + ... + K_(i-1)
  * `branches` is a HOST array of n_branches descriptors whose q / b / c are DEVICE pointers: q [n_pixels,K] of `dtype`
  * (HAWQ_S32 for an accumulator or pooled sum, or a stored low-bit tensor), b int32 [K], c uint8 [K].
- * y [n_pixels, sum K_i] of y_dt.  With a 4-bit type every K_i must be even.  One launch per branch.
+ * y [n_pixels, sum K_i] of y_dt.  With a 4-bit type every K_i must be even.  One launch for up to eight
+ * branches with INT32 or 8-bit elements, every K_i a multiple of four and 16-byte aligned arrays; else one per branch.
  */
 typedef struct {
     const void *q;

@@ -427,6 +427,7 @@ hawq_status hawq_concat_dyadic(int64_t n_pixels, int32_t n_branches, const hawq_
         Kt += br.K;
     }
     if (Kt > INT32_MAX || tensor_bytes(n_pixels * Kt, y_dt) >= kMaxBytes) return HAWQ_ERR_UNSUPPORTED;
+    if (launch_concat_all(n_pixels, n_branches, branches, (int)Kt, y_dt, y_lo, y_hi, y, (hipStream_t)stream, st)) return st;
     int64_t off = 0;
     for (int32_t i = 0; i < n_branches; ++i) {
         const hawq_concat_branch &br = branches[i];

@@ -226,6 +226,9 @@ hawq_status launch_maxpool(int N, int H, int W, int C, int x_dt, int y_dt, const
 
 hawq_status launch_pool_sum(int N, int H, int W, int C, int R, int S, int sh, int sw, int ph, int pw, int x_dt, int y_dt,
                             const void *x, const int32_t *b, const uint8_t *c, int lo, int hi, void *y, hipStream_t s);
+// every branch in one launch where shapes and types allow (false: nothing launched, use launch_concat_branch per branch)
+bool launch_concat_all(int64_t n_pixels, int n, const hawq_concat_branch *br, int Kt, int y_dt, int lo, int hi, void *y, hipStream_t s,
+                       hawq_status &st);
 hawq_status launch_concat_branch(int64_t n_pixels, int K, int Kt, int off, int q_dt, int y_dt, const void *q, const int32_t *b,
                                  const uint8_t *c, int lo, int hi, void *y, hipStream_t s);
 

@@ -32,10 +32,91 @@ residual_add_kernel(const int64_t units, const int K, const int per, const int m
     }
 }
 
+// Vector form: K % 4 == 0, 8-bit or INT32 operands and output.  A thread keeps one group of four channels (the grid's thread
+// count is a multiple of K / 4), so its parameters sit in registers, and has four pixels' loads in flight.  Bound: HBM
+// (m, r and y once); 32 x 56 x 56 x 256 INT32 + u8 -> u8 (154 MB): 103 us in the element-wise form above, whose sixteen
+// parameter loads per thread outnumbered its two data loads, 36 us (4.3 TB/s) here.
+template <int DT>
+__device__ __forceinline__ v4i load4(const void *p, int64_t unit) {   // elements 4 unit .. 4 unit + 3
+    if constexpr (DT == HAWQ_S32) {
+        return ((const v4i *)p)[unit];
+    } else {
+        const uint32_t w = ((const uint32_t *)p)[unit];
+        if constexpr (DT == HAWQ_U8) return (v4i){(int)(w & 0xff), (int)((w >> 8) & 0xff), (int)((w >> 16) & 0xff), (int)(w >> 24)};
+        else return (v4i){(int)(int8_t)w, (int)(int8_t)(w >> 8), (int)(int8_t)(w >> 16), (int)w >> 24};
+    }
+}
+template <int MD, int RD, bool Y32>
+__global__ void __launch_bounds__(256)
+residual_add_vec_kernel(const uint32_t units, const uint32_t groups, const void *m, const int32_t *__restrict__ m_b,
+                        const uint8_t *__restrict__ m_c, const void *r, const int32_t *__restrict__ r_b,
+                        const uint8_t *__restrict__ r_c, const int lo, const int hi, void *y) {
+    constexpr int U = 4;
+    const uint32_t T = gridDim.x * 256;
+    uint32_t u = blockIdx.x * 256 + threadIdx.x;
+    const uint32_t g = u % groups;
+    const v4i mb = ((const v4i *)m_b)[g], rb = ((const v4i *)r_b)[g];
+    const uint32_t mc = ((const uint32_t *)m_c)[g], rc = ((const uint32_t *)r_c)[g];
+    auto finish = [&](const v4i &a, const v4i &b, uint32_t at) {
+        v4i o;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            o[j] = clamp64(rq64(a[j], mb[j], (mc >> (8 * j)) & 0xff) + rq64(b[j], rb[j], (rc >> (8 * j)) & 0xff), lo, hi);
+        if (Y32) ((v4i *)y)[at] = o;
+        else ((uint32_t *)y)[at] = (o[0] & 0xff) | ((o[1] & 0xff) << 8) | ((o[2] & 0xff) << 16) | ((uint32_t)o[3] << 24);
+    };
+    for (; u + (U - 1) * T < units; u += U * T) {      // (units + U T stays far below 2^32: checked by the launcher)
+        v4i a[U], b[U];
+#pragma unroll
+        for (int i = 0; i < U; ++i) { a[i] = load4<MD>(m, u + i * T); b[i] = load4<RD>(r, u + i * T); }
+#pragma unroll
+        for (int i = 0; i < U; ++i) finish(a[i], b[i], u + i * T);
+    }
+    for (; u < units; u += T) {
+        const v4i a = load4<MD>(m, u), b = load4<RD>(r, u);
+        finish(a, b, u);
+    }
+}
+
+// Workgroups of 256 threads such that their threads are a multiple of `groups` (every thread keeps its channel group): a
+// multiple of groups / gcd(groups, 256), one unit per thread up to 1024 workgroups (four to a compute unit), about four per
+// thread beyond, at most 4096 workgroups.  0: no such grid.
+static uint32_t grouped_blocks(int64_t units, uint32_t groups) {
+    uint32_t a = groups, b = 256;
+    while (b) { const uint32_t t = a % b; a = b; b = t; }
+    const int64_t step = groups / a, one = (units + 255) / 256;
+    if (step > 4096) return 0;
+    int64_t want = one <= 1024 ? one : (one / 4 > 1024 ? one / 4 : 1024);
+    if (want > 4096) want = 4096;
+    const int64_t n = (want + step - 1) / step * step;
+    return (uint32_t)(n > 4096 ? n - step : n);
+}
+
 hawq_status launch_residual_add(int64_t n_pixels, int K, int m_dt, int r_dt, int y_dt, const void *m, const int32_t *m_b,
                                 const uint8_t *m_c, const void *r, const int32_t *r_b, const uint8_t *r_c, int lo, int hi,
                                 void *y, hipStream_t s) {
     const bool any4 = is4(m_dt) || is4(r_dt) || is4(y_dt);
+    const uintptr_t al = (uintptr_t)m | (uintptr_t)r | (uintptr_t)y | (uintptr_t)m_b | (uintptr_t)r_b;
+    if (!any4 && K % 4 == 0 && ((al & 15) | (((uintptr_t)m_c | (uintptr_t)r_c) & 3)) == 0 && n_pixels > 0) {
+        const int64_t vu = n_pixels * (K / 4);
+        const uint32_t nb = grouped_blocks(vu, K / 4);
+        if (nb != 0) {
+            auto go = [&](auto md, auto rd) {
+                constexpr int MD = decltype(md)::value, RD = decltype(rd)::value;
+                if (y_dt == HAWQ_S32) residual_add_vec_kernel<MD, RD, true><<<nb, 256, 0, s>>>((uint32_t)vu, K / 4, m, m_b, m_c, r, r_b, r_c, lo, hi, y);
+                else residual_add_vec_kernel<MD, RD, false><<<nb, 256, 0, s>>>((uint32_t)vu, K / 4, m, m_b, m_c, r, r_b, r_c, lo, hi, y);
+            };
+            auto on_r = [&](auto md) {
+                if (r_dt == HAWQ_S32) go(md, std::integral_constant<int, HAWQ_S32>{});
+                else if (r_dt == HAWQ_U8) go(md, std::integral_constant<int, HAWQ_U8>{});
+                else go(md, std::integral_constant<int, HAWQ_S8>{});
+            };
+            if (m_dt == HAWQ_S32) on_r(std::integral_constant<int, HAWQ_S32>{});
+            else if (m_dt == HAWQ_U8) on_r(std::integral_constant<int, HAWQ_U8>{});
+            else on_r(std::integral_constant<int, HAWQ_S8>{});
+            return check_launch();
+        }
+    }
     int per = (K % 4 == 0 && ((uintptr_t)y & 3) == 0) ? 4 : (any4 ? 2 : 1);
     const int64_t units = n_pixels * K / per;
     if (units == 0) return HAWQ_OK;
@@ -281,8 +362,6 @@ pool_sum_kernel(const int64_t units, const int H, const int W, const int C, cons
 
 // patch of output pixels per thread (measured at 128 x 35 x 35 x 288 INT32: 4x4 73.8 us, 4x8 76.8, 8x4 77.4, 8x8 78.2;
 // one row of eight, the previous form, 117.6 us)
-#define POOL_QT 4
-#define POOL_PT 4
 // fast path for the Inception pooling branch: 3x3 / stride 1 / pad 1 on INT32 (or unsigned 8-bit) data, C % 4 == 0.  One
 // thread = 4 channels of a QT-wide, PT-high patch of output pixels.  It walks the PT + 2 input rows under the patch once:
 // per row QT + 2 loads and the QT horizontal three-sums; an output row is the sum of the last three rows' horizontal sums
@@ -355,13 +434,21 @@ hawq_status launch_pool_sum(int N, int H, int W, int C, int R, int S, int sh, in
     const bool any4 = is4(x_dt) || is4(y_dt);
     if (R == 3 && S == 3 && sh == 1 && sw == 1 && ph == 1 && pw == 1 && C % 4 == 0 && (x_dt == HAWQ_S32 || x_dt == HAWQ_U8) &&
         (((uintptr_t)x | (uintptr_t)y) & 15) == 0) {
-        constexpr int QT = POOL_QT, PT = POOL_PT;
-        const int64_t units = (int64_t)N * ((H + PT - 1) / PT) * ((W + QT - 1) / QT) * (C / 4);
-        if (units == 0) return HAWQ_OK;
-        const int64_t blocks = (units + 255) / 256;
-        if (blocks > 0x7fffffff) return HAWQ_ERR_UNSUPPORTED;
-        if (x_dt == HAWQ_S32) pool_sum3x3_kernel<true, QT, PT><<<(uint32_t)blocks, 256, 0, s>>>(units, H, W, C, y_dt, x, b, c, lo, hi, y);
-        else pool_sum3x3_kernel<false, QT, PT><<<(uint32_t)blocks, 256, 0, s>>>(units, H, W, C, y_dt, x, b, c, lo, hi, y);
+        // patches of 4x4 outputs once they give every compute unit a workgroup, smaller ones below (17 x 17 x 64 at batch 4:
+        // 7 workgroups of 4x4 patches 7.4 us, 73 of single outputs 4.1)
+        auto blocks_of = [&](int t) { return ((int64_t)N * ((H + t - 1) / t) * ((W + t - 1) / t) * (C / 4) + 255) / 256; };
+        if (N == 0) return HAWQ_OK;
+        if (blocks_of(1) > 0x7fffffff) return HAWQ_ERR_UNSUPPORTED;
+        auto go = [&](auto tc) {
+            constexpr int PT = decltype(tc)::value;
+            const int64_t units = (int64_t)N * ((H + PT - 1) / PT) * ((W + PT - 1) / PT) * (C / 4);
+            const uint32_t blocks = (uint32_t)blocks_of(PT);
+            if (x_dt == HAWQ_S32) pool_sum3x3_kernel<true, PT, PT><<<blocks, 256, 0, s>>>(units, H, W, C, y_dt, x, b, c, lo, hi, y);
+            else pool_sum3x3_kernel<false, PT, PT><<<blocks, 256, 0, s>>>(units, H, W, C, y_dt, x, b, c, lo, hi, y);
+        };
+        if (blocks_of(4) >= 256) go(std::integral_constant<int, 4>{});
+        else if (blocks_of(2) >= 256) go(std::integral_constant<int, 2>{});
+        else go(std::integral_constant<int, 1>{});
         return check_launch();
     }
     const int per = (C % 4 == 0 && (((uintptr_t)x | (uintptr_t)y) & 15) == 0) ? 4 : (any4 ? 2 : 1);
@@ -402,6 +489,81 @@ concat_branch_kernel(const int64_t units, const int K, const int Kt, const int o
     } else {
         for (int j = 0; j < per; ++j) ((uint8_t *)y)[o + j] = (uint8_t)out[j];
     }
+}
+
+// Vector form, all branches in one launch: every K_i and offset a multiple of four, INT32 or 8-bit branches and outputs
+// (also packed 4-bit outputs).  A thread keeps one group of four output channels -- its branch and parameters are looked up
+// once -- and walks pixels with four loads in flight.  Bound: HBM (every branch and the output once).
+constexpr int kConcatMax = 8;
+struct ConcatArgs {
+    const void *q[kConcatMax];
+    const int32_t *b[kConcatMax];
+    const uint8_t *c[kConcatMax];
+    uint32_t end[kConcatMax];      // first channel group past the branch
+    int32_t dt[kConcatMax];
+};
+template <int YB>   // bits of an output element
+__global__ void __launch_bounds__(256)
+concat_vec_kernel(const ConcatArgs a, const int n, const uint32_t units, const uint32_t groups, const int lo, const int hi, void *y) {
+    constexpr int U = 4;
+    const uint32_t T = gridDim.x * 256;
+    uint32_t u = blockIdx.x * 256 + threadIdx.x;
+    const uint32_t px0 = u / groups, g = u - px0 * groups, dpx = T / groups;
+    int i = 0;
+    uint32_t begin = 0;
+#pragma unroll
+    for (int j = 0; j < kConcatMax - 1; ++j)
+        if (j < n - 1 && g >= a.end[j]) { i = j + 1; begin = a.end[j]; }
+    const void *q = a.q[0];
+    const int32_t *bp = a.b[0];
+    const uint8_t *cp = a.c[0];
+    int dt = a.dt[0];
+    uint32_t end = a.end[0];
+#pragma unroll
+    for (int j = 1; j < kConcatMax; ++j)
+        if (i == j) { q = a.q[j]; bp = a.b[j]; cp = a.c[j]; dt = a.dt[j]; end = a.end[j]; }
+    const uint32_t w = end - begin, k = g - begin;
+    const v4i b = ((const v4i *)bp)[k];
+    const uint32_t c = ((const uint32_t *)cp)[k];
+    auto load = [&](uint32_t at) { return dt == HAWQ_S32 ? load4<HAWQ_S32>(q, at) : dt == HAWQ_U8 ? load4<HAWQ_U8>(q, at) : load4<HAWQ_S8>(q, at); };
+    auto finish = [&](const v4i &v, uint32_t at) {
+        v4i o;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) o[j] = clamp64(rq64(v[j], b[j], (c >> (8 * j)) & 0xff), lo, hi);
+        if constexpr (YB == 32) ((v4i *)y)[at] = o;
+        else if constexpr (YB == 8) ((uint32_t *)y)[at] = (o[0] & 0xff) | ((o[1] & 0xff) << 8) | ((o[2] & 0xff) << 16) | ((uint32_t)o[3] << 24);
+        else ((uint16_t *)y)[at] = (uint16_t)((o[0] & 0xf) | ((o[1] & 0xf) << 4) | ((o[2] & 0xf) << 8) | ((o[3] & 0xf) << 12));
+    };
+    uint32_t e = px0 * w + k;
+    const uint32_t de = dpx * w;
+    for (; u + (U - 1) * T < units; u += U * T, e += U * de) {
+        v4i v[U];
+#pragma unroll
+        for (int j = 0; j < U; ++j) v[j] = load(e + j * de);
+#pragma unroll
+        for (int j = 0; j < U; ++j) finish(v[j], u + j * T);
+    }
+    for (; u < units; u += T, e += de) finish(load(e), u);
+}
+
+bool launch_concat_all(int64_t n_pixels, int n, const hawq_concat_branch *br, int Kt, int y_dt, int lo, int hi, void *y, hipStream_t s,
+                       hawq_status &st) {
+    if (n > kConcatMax || Kt % 4 != 0 || ((uintptr_t)y & 15) != 0 || n_pixels == 0) return false;
+    ConcatArgs a{};
+    uint32_t end = 0;
+    for (int i = 0; i < n; ++i) {
+        if (br[i].K % 4 != 0 || is4(br[i].dtype) || (((uintptr_t)br[i].q | (uintptr_t)br[i].b) & 15) || ((uintptr_t)br[i].c & 3)) return false;
+        end += br[i].K / 4;
+        a.q[i] = br[i].q; a.b[i] = br[i].b; a.c[i] = br[i].c; a.end[i] = end; a.dt[i] = br[i].dtype;
+    }
+    const int64_t units = n_pixels * (Kt / 4);
+    const uint32_t nb = grouped_blocks(units, Kt / 4);
+    if (nb == 0) return false;
+    if (y_dt == HAWQ_S32) concat_vec_kernel<32><<<nb, 256, 0, s>>>(a, n, (uint32_t)units, Kt / 4, lo, hi, y);
+    else if (is4(y_dt)) concat_vec_kernel<4><<<nb, 256, 0, s>>>(a, n, (uint32_t)units, Kt / 4, lo, hi, y);
+    else concat_vec_kernel<8><<<nb, 256, 0, s>>>(a, n, (uint32_t)units, Kt / 4, lo, hi, y);
+    st = check_launch();
+    return true;
 }
 
 hawq_status launch_concat_branch(int64_t n_pixels, int K, int Kt, int off, int q_dt, int y_dt, const void *q, const int32_t *b,
