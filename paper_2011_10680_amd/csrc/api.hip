@@ -103,8 +103,9 @@ hawq_status make_conv_args(const hawq_conv_desc *d, const void *x, const void *w
 }
 
 // The resident-pixel kernel's view of a validated 3x3 layer a1 (weights a1.w_f) and, when a2 is given, of the 1x1 layer
-// that consumes its output in the same launch (weights w2f; a2's x / y-of-a1 pointers are not used).
-bool make_rp_args(const ConvArgs &a1, int x_hi, const ConvArgs *a2, const void *w2f, RpArgs &r) {
+// that consumes its output in the same launch (weights w2f; a2's x / y-of-a1 pointers are not used).  any_shape: types and
+// alignment only, the shape is the caller's to check (conv_rpk.hip).
+bool make_rp_args(const ConvArgs &a1, int x_hi, const ConvArgs *a2, const void *w2f, RpArgs &r, bool any_shape) {
     if (a1.R != 3 || a1.S != 3 || a1.stride_h != 1 || a1.stride_w != 1 || a1.pad_h != 1 || a1.pad_w != 1) return false;
     if (a1.w_f == nullptr || a1.b == nullptr || a1.xs != nullptr) return false;
     if ((uintptr_t)a1.x & 15) return false;
@@ -117,16 +118,17 @@ bool make_rp_args(const ConvArgs &a1, int x_hi, const ConvArgs *a2, const void *
         if (a1.y_dt != HAWQ_U8 && a1.y_dt != HAWQ_S8 && a1.y_dt != HAWQ_U4) return false;
         if ((uintptr_t)a1.y & 15) return false;
         r.pk = 1; r.y4 = a1.y_dt == HAWQ_U4; r.y = a1.y; r.res_dt = HAWQ_U8;
-        return conv_rp_shape_ok(r, false);
+        return any_shape || conv_rp_shape_ok(r, false);
     }
     if (a1.w_dt != HAWQ_S8) return false;
     if (a1.x_dt == HAWQ_U8 ? x_hi > 127 : a1.x_dt != HAWQ_S8) return false;
-    if (a1.y_dt != HAWQ_U8 && a1.y_dt != HAWQ_S8) return false;
+    r.y4 = any_shape && a1.y_dt == HAWQ_U4 && a2 == nullptr && a1.res == nullptr;   // (conv_rpk.hip packs its output there too)
+    if (a1.y_dt != HAWQ_U8 && a1.y_dt != HAWQ_S8 && !r.y4) return false;
     if (a2 == nullptr) {
         if (a1.res != nullptr && a1.res_dt != HAWQ_U8 && a1.res_dt != HAWQ_S8) return false;
         if (((uintptr_t)a1.y | (uintptr_t)a1.res) & 15) return false;
         r.res = a1.res; r.res_b = a1.res_b; r.res_c = a1.res_c; r.res_dt = a1.res_dt; r.y = a1.y;
-        return conv_rp_shape_ok(r, false);
+        return any_shape || conv_rp_shape_ok(r, false);
     }
     // the intermediate tensor becomes the signed matrix operand of the second convolution
     if (a1.res != nullptr || a1.lo < -128 || a1.hi > 127) return false;
@@ -177,6 +179,10 @@ bool make_rp1_args(const ConvArgs &a, int x_hi, int xs_hi, Rp1Args &r) {
 
 hawq_status dispatch_conv(const ConvArgs &a, int x_hi, hipStream_t s) {
     if (a.M == 0) return HAWQ_OK;
+    if (tile_override() == 0 && a.w_f != nullptr) {
+        RpArgs r;
+        if (make_rp_args(a, x_hi, nullptr, nullptr, r, true) && conv_rpk_shape_ok(r)) return launch_conv_rpk(r, s);
+    }
     const bool sk = conv_sk_eligible(a, x_hi);
     if (tile_override() == 0 && sk && conv_sk_small(a)) return launch_conv_sk(a, x_hi, s);
     if (conv_pw_eligible(a, x_hi)) return launch_conv_pw(a, s);

@@ -235,7 +235,10 @@ hawq_status launch_concat_branch(int64_t n_pixels, int K, int Kt, int off, int q
 // resident-pixel 3x3 (+ fused 1x1) kernel: shape test and launch (operand types / alignment are the caller's to check)
 bool conv_rp_shape_ok(const RpArgs &a, bool fused);
 // RpArgs from a validated 3x3 layer (and, fused, the 1x1 layer that follows it); false if types, alignment or shape do not fit
-bool make_rp_args(const ConvArgs &a1, int x_hi, const ConvArgs *a2, const void *w2f, RpArgs &r);
+bool make_rp_args(const ConvArgs &a1, int x_hi, const ConvArgs *a2, const void *w2f, RpArgs &r, bool any_shape = false);
+// resident-pixel 3x3 kernel with the reduction split over the waves, for launches that do not fill the chip (RpArgs with any_shape)
+bool conv_rpk_shape_ok(const RpArgs &a);
+hawq_status launch_conv_rpk(const RpArgs &a, hipStream_t s);
 hawq_status launch_conv_rp(const RpArgs &a, bool fused, hipStream_t s);
 // resident-pixel 1x1 kernel (one convolution + optional shortcut tensor, or two convolutions when a.xs is set and the
 // caller vouches for a.dual16): Rp1Args from validated requests; false if types, alignment or shape do not fit

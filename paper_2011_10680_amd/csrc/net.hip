@@ -344,17 +344,15 @@ hawq_status hawq_net_create(int32_t arch, int32_t image_hw, int32_t num_classes,
     // kernel (64-byte K-steps: 8-bit form with C % 64 == 0, packed 4-bit form with C % 128 == 0)
     auto wrow = [&](int i) { return (int64_t)tensor_bytes((int64_t)L[i].R * L[i].S * L[i].C, is8(i) ? HAWQ_S8 : HAWQ_S4); };
     auto blocked = [&](int i) { return !L[i].is_stem && L[i].C % (is8(i) ? 64 : 128) == 0; };
-    // fragment-ordered copy: the 3x3 / 1 / 1 layers the resident-pixel kernel takes (128 or 256 input channels, 8-bit form)
-    // and the 1x1 layer that follows such a layer in a bottleneck (it may run fused behind it)
-    auto rp3x3 = [&](int i) { return L[i].R == 3 && L[i].S == 3 && L[i].stride == 1 && L[i].pad == 1 && is8(i) && (L[i].C == 128 || L[i].C == 256 || (L[i].C == 512 && L[i].W <= 14)) && L[i].K % L[i].C == 0; };
-    // ... and the same layers with packed 4-bit operands (the kernel's packed form)
-    auto rp3x3pk = [&](int i) { return L[i].R == 3 && L[i].S == 3 && L[i].stride == 1 && L[i].pad == 1 && !is8(i) && L[i].W <= 28 && (L[i].C == 128 || L[i].C == 256 || (L[i].C == 512 && L[i].W <= 14)) && L[i].K % L[i].C == 0; };
-    // ... and the 1x1 layers of the resident-pixel 1x1 kernel (main branches and transition convolutions alike)
+    // fragment-ordered copy: the 3x3 / 1 / 1 layers of the resident-pixel kernels (8-bit form or packed) ...
+    auto rp3x3 = [&](int i) { return L[i].R == 3 && L[i].S == 3 && L[i].stride == 1 && L[i].pad == 1 && (L[i].C == 64 || L[i].C == 128 || L[i].C == 256 || L[i].C == 512) && L[i].K % L[i].C == 0; };
+    // ... the 1x1 layers of the resident-pixel 1x1 kernel (main branches and transition convolutions alike), and the 1x1 layer
+    // that follows such a 3x3 in a bottleneck (it may run fused behind it)
     auto rp1x1 = [&](int i) { return L[i].R == 1 && L[i].S == 1 && L[i].pad == 0 && is8(i) && L[i].K % 256 == 0 && (L[i].C == 256 || L[i].C == 512 || L[i].C == 1024 || L[i].C == 2048); };
     auto fragmented = [&](int i) {
         if (L[i].is_stem || L[i].is_fc) return false;
-        if (rp3x3(i) || rp3x3pk(i) || rp1x1(i)) return true;
-        return i > 0 && L[i].R == 1 && L[i].has_residual && is8(i) && rp3x3(i - 1) && L[i - 1].block == L[i].block && L[i].C == L[i - 1].K;
+        if (rp3x3(i) || rp1x1(i)) return true;
+        return i > 0 && L[i].R == 1 && L[i].has_residual && is8(i) && is8(i - 1) && rp3x3(i - 1) && L[i - 1].block == L[i].block && L[i].C == L[i - 1].K;
     };
     std::vector<Off> off(nl);
     size_t total = 0;
@@ -362,8 +360,6 @@ hawq_status hawq_net_create(int32_t arch, int32_t image_hw, int32_t num_classes,
     for (int i = 0; i < nl; ++i) {
         const int64_t nw = (int64_t)L[i].K * L[i].R * L[i].S * L[i].C;
         off[i].w = take((size_t)tensor_bytes(nw, is8(i) ? HAWQ_S8 : HAWQ_S4));
-        off[i].wt = blocked(i) ? take((size_t)((L[i].K + 63) / 64) * (size_t)wrow(i) * 64) : 0;
-        off[i].wf = fragmented(i) ? take((size_t)((L[i].K + 31) / 32) * 32 * (size_t)L[i].R * L[i].S * L[i].C) : 0;   // (always bytes: 4-bit weights are expanded)
         off[i].bias = take(4 * (size_t)L[i].K);
         off[i].b = take(4 * (size_t)L[i].K);
         off[i].c = take((size_t)L[i].K);
@@ -372,7 +368,12 @@ hawq_status hawq_net_create(int32_t arch, int32_t image_hw, int32_t num_classes,
     }
     const size_t off_pb = take(4 * (size_t)c_last), off_pc = take((size_t)c_last);
     const size_t off_ws = take(64 * 256), off_bs = take(4 * 64);
-    std::vector<uint8_t> host(total, 0);
+    const size_t host_bytes = total;   // the reordered copies behind this are made on the device
+    for (int i = 0; i < nl; ++i) {
+        off[i].wt = blocked(i) ? take((size_t)((L[i].K + 63) / 64) * (size_t)wrow(i) * 64) : 0;
+        off[i].wf = fragmented(i) ? take((size_t)((L[i].K + 31) / 32) * 32 * (size_t)L[i].R * L[i].S * L[i].C) : 0;   // (always bytes: 4-bit weights are expanded)
+    }
+    std::vector<uint8_t> host(host_bytes, 0);
     for (int i = 0; i < nl; ++i) {
         const int64_t nw = (int64_t)L[i].K * L[i].R * L[i].S * L[i].C;
         if (lp[i].bits == 4 && expand[i]) {   // nibbles -> sign-extended bytes (even element in the low nibble)
@@ -384,36 +385,6 @@ hawq_status hawq_net_create(int32_t arch, int32_t image_hw, int32_t num_classes,
             }
         } else {
             memcpy(&host[off[i].w], lp[i].w, (size_t)tensor_bytes(nw, lp[i].bits == 4 ? HAWQ_S4 : HAWQ_S8));
-        }
-        if (blocked(i)) {   // [K][row] -> [K/64][row/64][64][64], rows past K stay zero
-            const int64_t row = wrow(i), nsteps = row / 64;
-            const uint8_t *src = &host[off[i].w];
-            uint8_t *dst = &host[off[i].wt];
-            for (int k = 0; k < L[i].K; ++k)
-                for (int64_t st = 0; st < nsteps; ++st)
-                    memcpy(dst + (((int64_t)(k >> 6) * nsteps + st) * 64 + (k & 63)) * 64, src + k * row + st * 64, 64);
-        }
-        if (fragmented(i)) {   // [K][row] -> [K/32][row/64][2][64 lanes][16]: see launch_fragment_weights for the order
-            const bool four = !is8(i);                 // packed rows: expanded to bytes, even elements of every 32 first
-            const int64_t rowp = wrow(i), nsteps = (four ? 2 * rowp : rowp) / 64;
-            const uint8_t *src = &host[off[i].w];
-            uint8_t *dst = &host[off[i].wf];
-            for (int g = 0; g < (L[i].K + 31) / 32; ++g)
-                for (int64_t st = 0; st < nsteps; ++st)
-                    for (int kk = 0; kk < 2; ++kk)
-                        for (int lane = 0; lane < 64; ++lane) {
-                            const int rho = lane & 31, khalf = lane >> 5;
-                            const int k = g * 32 + ((rho >> 2) & 1) * 16 + (rho >> 3) * 4 + (rho & 3);
-                            uint8_t *d = dst + ((((int64_t)g * nsteps + st) * 2 + kk) * 64 + lane) * 16;
-                            if (k >= L[i].K) continue;
-                            const int64_t ci = st * 4 + kk * 2 + khalf;
-                            if (!four) { memcpy(d, src + k * rowp + ci * 16, 16); continue; }
-                            const uint8_t *p = src + k * rowp + (ci >> 1) * 16;
-                            for (int j = 0; j < 16; ++j) {
-                                const int v = (ci & 1) ? (p[j] >> 4) : (p[j] & 0xF);
-                                d[j] = (uint8_t)(int8_t)(v >= 8 ? v - 16 : v);
-                            }
-                        }
         }
         memcpy(&host[off[i].bias], lp[i].bias, 4 * (size_t)L[i].K);
         if (!L[i].is_fc) {
@@ -439,13 +410,22 @@ hawq_status hawq_net_create(int32_t arch, int32_t image_hw, int32_t num_classes,
     memcpy(&host[off_pc], pool_c, (size_t)c_last);
     if (scratch_base() == nullptr) return fail(HAWQ_ERR_DEVICE);   // (address of the fixed workspace on this device, for hawq_forward_resnet_noalloc)
     if (hipMalloc(&net->arena, total) != hipSuccess) return fail(HAWQ_ERR_DEVICE);
-    if (hipMemcpy(net->arena, host.data(), total, hipMemcpyHostToDevice) != hipSuccess) return fail(HAWQ_ERR_DEVICE);
+    if (hipMemcpy(net->arena, host.data(), host_bytes, hipMemcpyHostToDevice) != hipSuccess) return fail(HAWQ_ERR_DEVICE);
     // second stream (default priority) and the events that order it against the caller's stream
     if (hipStreamCreateWithFlags(&net->aux_stream, hipStreamNonBlocking) != hipSuccess ||
         hipEventCreateWithFlags(&net->fork_ev, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&net->join_ev, hipEventDisableTiming) != hipSuccess)
         return fail(HAWQ_ERR_DEVICE);
     const uint8_t *A = (const uint8_t *)net->arena;
+    // the weights' reordered copies (see launch_block_weights / launch_fragment_weights), from the uploaded ones
+    for (int i = 0; i < nl; ++i) {
+        hawq_status st = HAWQ_OK;
+        if (blocked(i)) st = launch_block_weights(A + off[i].w, (uint8_t *)net->arena + off[i].wt, L[i].K, wrow(i), net->aux_stream);
+        if (st == HAWQ_OK && fragmented(i))
+            st = launch_fragment_weights(A + off[i].w, (uint8_t *)net->arena + off[i].wf, L[i].K, wrow(i), !is8(i), net->aux_stream);
+        if (st != HAWQ_OK) return fail(st);
+    }
+    if (hipStreamSynchronize(net->aux_stream) != hipSuccess) return fail(HAWQ_ERR_DEVICE);
 
     // ---- steps ----
     auto new_tensor = [&](int P, int Q, int K, int dt) {
