@@ -240,6 +240,9 @@ bool make_rp_args(const ConvArgs &a1, int x_hi, const ConvArgs *a2, const void *
 bool conv_rpk_shape_ok(const RpArgs &a);
 hawq_status launch_conv_rpk(const RpArgs &a, hipStream_t s);
 hawq_status launch_conv_rp(const RpArgs &a, bool fused, hipStream_t s);
+// resident-pixel 1x1 kernel with the reduction split over the waves (fragment-ordered weights, launches that do not fill the chip)
+bool conv_rp1k_eligible(const ConvArgs &a, int x_hi);
+hawq_status launch_conv_rp1k(const ConvArgs &a, hipStream_t s);
 // resident-pixel 1x1 kernel (one convolution + optional shortcut tensor, or two convolutions when a.xs is set and the
 // caller vouches for a.dual16): Rp1Args from validated requests; false if types, alignment or shape do not fit
 bool conv_rp1_shape_ok(const Rp1Args &a);

@@ -167,58 +167,14 @@ __global__ void __launch_bounds__(64 * WC * WK) conv_rpk_kernel(const RpArgs a) 
     });
 
     // ---- the partial tiles meet where the patch was ----
-    v4i *red = (v4i *)lds;                            // [channel group][partial][tile][4 registers' quad][lane]
-    auto at = [&](int part, int tp, int q) -> v4i & { return red[(((wc * R + part) * TP + tp) * 4 + q) * 64 + lane]; };
-    auto quad = [&](const v16i &v, int q) { return (v4i){v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]}; };
-    __syncthreads();
-    if constexpr (WK > R) {
-        if (wk >= R)
-#pragma unroll
-            for (int tp = 0; tp < TP; ++tp)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) at(wk - R, tp, q) = quad(acc[tp], q);
-        __syncthreads();
-        if (wk < R)
-#pragma unroll
-            for (int tp = 0; tp < TP; ++tp)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const v4i v = at(wk, tp, q);
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) acc[tp][4 * q + i] += v[i];
-                }
-    }
-    if constexpr (R > 1) {
-        if (wk < R)                                   // (a wave re-uses the region only it has read)
-#pragma unroll
-            for (int tp = 0; tp < TP; ++tp)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) at(wk, tp, q) = quad(acc[tp], q);
-        __syncthreads();
-    }
+    v16i fin[NF];
+    rpk_reduce<TP, WC, WK, R, NF>(lds, lane, wk, wc, acc, fin);
     if (wk >= R || wk >= TP) return;
     const __amdgpu_buffer_rsrc_t rsrc_y = __builtin_amdgcn_make_buffer_rsrc((void *)a.y, 0, (int)(((int64_t)a.M * a.K1) >> ysh), 0x00020000);
 #pragma unroll
     for (int j = 0; j < NF; ++j) {
-        const int t = wk + j * R;
-        if (t >= TP) break;
-        v16i s;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            v4i v = at(0, t, q);
-#pragma unroll
-            for (int p = 1; p < R; ++p) v += at(p, t, q);
-            s[4 * q] = v[0]; s[4 * q + 1] = v[1]; s[4 * q + 2] = v[2]; s[4 * q + 3] = v[3];
-        }
-        const uint32_t rw[2][4] = {{resw[j][0], resw[j][1], resw[j][2], resw[j][3]}, {0, 0, 0, 0}};
-        uint32_t o[2][4];
-        rp_epilogue<1>(s, s, par + chl, pres + chl, has_res, a.res_dt == HAWQ_S8, rw, wide, a.lo1, a.hi1, o);
-        if (a.y4) {
-            auto nib = [](uint32_t d) { return (d & 0xfu) | ((d >> 4) & 0xf0u) | ((d >> 8) & 0xf00u) | ((d >> 12) & 0xf000u); };
-            __builtin_amdgcn_raw_buffer_store_b64((v2i){(int)(nib(o[0][0]) | (nib(o[0][1]) << 16)), (int)(nib(o[0][2]) | (nib(o[0][3]) << 16))}, rsrc_y, (int)yoff[j], 0, 0);
-        } else {
-            __builtin_amdgcn_raw_buffer_store_b128((v4i){(int)o[0][0], (int)o[0][1], (int)o[0][2], (int)o[0][3]}, rsrc_y, (int)yoff[j], 0, 0);
-        }
+        if (wk + j * R >= TP) break;
+        rpk_store(fin[j], par + chl, pres + chl, has_res, a.res_dt == HAWQ_S8, resw[j], wide, a.lo1, a.hi1, ysh != 0, rsrc_y, yoff[j]);
     }
 }
 

@@ -346,14 +346,9 @@ hawq_status hawq_net_create(int32_t arch, int32_t image_hw, int32_t num_classes,
     auto blocked = [&](int i) { return !L[i].is_stem && L[i].C % (is8(i) ? 64 : 128) == 0; };
     // fragment-ordered copy: the 3x3 / 1 / 1 layers of the resident-pixel kernels (8-bit form or packed) ...
     auto rp3x3 = [&](int i) { return L[i].R == 3 && L[i].S == 3 && L[i].stride == 1 && L[i].pad == 1 && (L[i].C == 64 || L[i].C == 128 || L[i].C == 256 || L[i].C == 512) && L[i].K % L[i].C == 0; };
-    // ... the 1x1 layers of the resident-pixel 1x1 kernel (main branches and transition convolutions alike), and the 1x1 layer
-    // that follows such a 3x3 in a bottleneck (it may run fused behind it)
-    auto rp1x1 = [&](int i) { return L[i].R == 1 && L[i].S == 1 && L[i].pad == 0 && is8(i) && L[i].K % 256 == 0 && (L[i].C == 256 || L[i].C == 512 || L[i].C == 1024 || L[i].C == 2048); };
-    auto fragmented = [&](int i) {
-        if (L[i].is_stem || L[i].is_fc) return false;
-        if (rp3x3(i) || rp1x1(i)) return true;
-        return i > 0 && L[i].R == 1 && L[i].has_residual && is8(i) && is8(i - 1) && rp3x3(i - 1) && L[i - 1].block == L[i].block && L[i].C == L[i - 1].K;
-    };
+    // ... and the 1x1 layers of the resident-pixel 1x1 kernels (main branches and transition convolutions alike)
+    auto rp1x1 = [&](int i) { return L[i].R == 1 && L[i].S == 1 && L[i].pad == 0 && L[i].C % 64 == 0 && L[i].K % 64 == 0; };
+    auto fragmented = [&](int i) { return !L[i].is_stem && !L[i].is_fc && (rp3x3(i) || rp1x1(i)); };
     std::vector<Off> off(nl);
     size_t total = 0;
     auto take = [&](size_t bytes) { size_t o = total; total = align_up(total + bytes, 256); return o; };

@@ -97,4 +97,71 @@ __device__ __forceinline__ void rp_epilogue(const v16i &acc0, const v16i &acc1, 
     if (NT == 1) out[1][0] = out[1][1] = out[1][2] = out[1][3] = 0;   // (every element written on every path keeps the array in registers)
 }
 
+// ---- the split-reduction forms (conv_rpk.hip, conv_rp1k.hip) ----
+
+// The partial tiles of WK waves per channel group meet in LDS (`lds`: WC * R * TP * 4 KB, free once every wave is here).  First
+// exchange (WK > R): waves R .. hand theirs to waves 0 .. R - 1; second: every remaining wave lays out its sums and wave wk
+// collects tiles wk, wk + R, ... into fin.  Quads of four registers x 64 lanes: every access is 1 KB of consecutive LDS.
+template <int TP, int WC, int WK, int R, int NF>
+__device__ __forceinline__ void rpk_reduce(uint8_t *lds, int lane, int wk, int wc, v16i (&acc)[TP], v16i (&fin)[NF]) {
+    v4i *red = (v4i *)lds;
+    auto at = [&](int part, int tp, int q) -> v4i & { return red[(((wc * R + part) * TP + tp) * 4 + q) * 64 + lane]; };
+    auto quad = [&](const v16i &v, int q) { return (v4i){v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]}; };
+    if constexpr (WK == 1) {
+#pragma unroll
+        for (int j = 0; j < NF; ++j) fin[j] = acc[j];
+        return;
+    }
+    __syncthreads();
+    if constexpr (WK > R) {
+        if (wk >= R)
+#pragma unroll
+            for (int tp = 0; tp < TP; ++tp)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) at(wk - R, tp, q) = quad(acc[tp], q);
+        __syncthreads();
+        if (wk < R)
+#pragma unroll
+            for (int tp = 0; tp < TP; ++tp)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const v4i v = at(wk, tp, q);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) acc[tp][4 * q + i] += v[i];
+                }
+    }
+    if (wk < R)                                   // (a wave re-uses the region only it has read)
+#pragma unroll
+        for (int tp = 0; tp < TP; ++tp)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) at(wk, tp, q) = quad(acc[tp], q);
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < NF; ++j) {
+        const int t = wk + j * R < TP ? wk + j * R : TP - 1;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            v4i v = at(0, t, q);
+#pragma unroll
+            for (int p = 1; p < R; ++p) v += at(p, t, q);
+            fin[j][4 * q] = v[0]; fin[j][4 * q + 1] = v[1]; fin[j][4 * q + 2] = v[2]; fin[j][4 * q + 3] = v[3];
+        }
+    }
+}
+
+// One pixel's 16 channels: requantise (+ shortcut), store as 16 bytes or as 16 nibbles
+__device__ __forceinline__ void rpk_store(const v16i &s, const RpChan *pc, const RpRes *pr, bool has_res, bool res_signed,
+                                          const uint32_t (&resw)[4], int wide, int lo, int hi, bool y4,
+                                          __amdgpu_buffer_rsrc_t rsrc_y, uint32_t yoff) {
+    const uint32_t rw[2][4] = {{resw[0], resw[1], resw[2], resw[3]}, {0, 0, 0, 0}};
+    uint32_t o[2][4];
+    rp_epilogue<1>(s, s, pc, pr, has_res, res_signed, rw, wide, lo, hi, o);
+    if (y4) {
+        auto nib = [](uint32_t d) { return (d & 0xfu) | ((d >> 4) & 0xf0u) | ((d >> 8) & 0xf00u) | ((d >> 12) & 0xf000u); };
+        __builtin_amdgcn_raw_buffer_store_b64((v2i){(int)(nib(o[0][0]) | (nib(o[0][1]) << 16)), (int)(nib(o[0][2]) | (nib(o[0][3]) << 16))}, rsrc_y, (int)yoff, 0, 0);
+    } else {
+        __builtin_amdgcn_raw_buffer_store_b128((v4i){(int)o[0][0], (int)o[0][1], (int)o[0][2], (int)o[0][3]}, rsrc_y, (int)yoff, 0, 0);
+    }
+}
+
 }  // namespace hawq
