@@ -179,6 +179,7 @@ bool make_rp1_args(const ConvArgs &a, int x_hi, int xs_hi, Rp1Args &r) {
 
 hawq_status dispatch_conv(const ConvArgs &a, int x_hi, hipStream_t s) {
     if (a.M == 0) return HAWQ_OK;
+    if (tile_override() == 0 && conv3x3_rows_eligible(a, x_hi)) return launch_conv3x3_rows(a, s);
     if (tile_override() == 0 && a.w_f != nullptr) {
         RpArgs r;
         if (make_rp_args(a, x_hi, nullptr, nullptr, r, true) && conv_rpk_shape_ok(r)) return launch_conv_rpk(r, s);

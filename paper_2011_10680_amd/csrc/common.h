@@ -197,6 +197,9 @@ bool conv_sk_eligible(const ConvArgs &a, int x_hi);
 bool conv_sk_dual_eligible(const ConvArgs &a, int x_hi, int xs_hi);
 hawq_status launch_conv_sk(const ConvArgs &a, int x_hi, hipStream_t s);
 bool conv_sk_small(const ConvArgs &a);   // preferred over the other kernels that take the shape
+// 3x3, 64 input channels, stride 1 or 2, on whole output rows (fragment-ordered weights in registers)
+bool conv3x3_rows_eligible(const ConvArgs &a, int x_hi);
+hawq_status launch_conv3x3_rows(const ConvArgs &a, hipStream_t s);
 hawq_status launch_conv_direct(const ConvArgs &a, hipStream_t s);   // any valid shape (also with a shortcut convolution)
 // matrix-core kernel for a block output with a convolution on both branches (ConvArgs::xs set)
 bool conv_mfma_dual_eligible(const ConvArgs &a, int x_hi, int xs_hi);
