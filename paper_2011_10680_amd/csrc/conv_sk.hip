@@ -362,7 +362,8 @@ bool conv_sk_eligible(const ConvArgs &a, int x_hi) {
     if (four ? (a.x_dt != HAWQ_U4 || a.w_dt != HAWQ_S4) : (a.w_dt != HAWQ_S8 || (a.x_dt != HAWQ_U8 && a.x_dt != HAWQ_S8))) return false;
     if (((uintptr_t)a.x | (uintptr_t)a.w) & 15) return false;
     const int64_t red = (int64_t)a.R * a.S * a.C;
-    if (red >= (1 << 23) || (int64_t)a.H + a.R >= (1 << 29) || (int64_t)a.W + a.S >= (1 << 29)) return false;   // (16 w * 15 * red < 2^31; bounds test)
+    // packed sums are kept times sixteen: |16 w x| <= 16 * 8 * 15 and red < 2^20 stay below 2^31; the spatial limits are the bounds test's
+    if (red >= (four ? 1 << 20 : 1 << 23) || (int64_t)a.H + a.R >= (1 << 29) || (int64_t)a.W + a.S >= (1 << 29)) return false;
     if ((int64_t)((a.K + 63) / 64 * 64) * (red + 64) >= ((int64_t)1 << 31)) return false;   // the blocked copy below the out-of-range offset
     (void)x_hi;
     return a.xs == nullptr;

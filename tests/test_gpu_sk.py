@@ -61,6 +61,19 @@ def test_split_reduction_shapes(hawq, shape):
         assert 0.02 < (v > 0).mean() and len(np.unique(v)) > 5
 
 
+@pytest.mark.parametrize("C", [(1 << 20) - 32, 1 << 20, 1200000])
+def test_longest_packed_reductions(hawq, C):
+    """Sums of all-extreme packed operands on both sides of the length up to which sixteen times a sum fits 32 bits."""
+    from gpu_util import run_conv_gpu, assert_same
+    case = wl.conv_case(seed=5, N=1, H=1, W=1, C=32, K=16, R=1, S=1, stride=1, pad=0, bits=4)
+    case["C"] = C
+    case["x"] = np.full(case["x"].shape[:-1] + (C // 2,), 0xFF, dtype=case["x"].dtype)                    # 15
+    case["w"] = np.full(case["w"].shape[:-1] + (C // 2,), 0x88, dtype=np.uint8).view(case["w"].dtype)     # -8
+    got, want = run_conv_gpu(case, hawq.U4, hawq.S4, hawq.S32, raw=True, x_hi=0, y_lo=0, y_hi=0, relu=0)
+    assert_same(got, want, str(C))
+    assert (np.abs(want.astype(np.int64) + 120 * C) < 1 << 28).all()
+
+
 @pytest.mark.parametrize("N,H,C,K,R,pad", [(2, 9, 64, 48, 3, 1), (24, 20, 176, 272, 3, 1), (3, 8, 16, 16, 1, 0)])
 def test_unsigned_bytes_over_the_whole_range_with_padding(hawq, N, H, C, K, R, pad):
     """x - 128 on the matrix cores: padding taps and the chunks past the reduction's end must cancel exactly."""
