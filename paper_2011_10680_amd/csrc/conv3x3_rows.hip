@@ -318,6 +318,9 @@ bool conv3x3_rows_eligible(const ConvArgs &a, int x_hi) {
     if (a.y_dt != HAWQ_U8 && a.y_dt != HAWQ_S8 && a.y_dt != HAWQ_U4) return false;
     if (a.res != nullptr && a.res_dt != HAWQ_U8 && a.res_dt != HAWQ_S8 && a.res_dt != HAWQ_U4) return false;
     if (((uintptr_t)a.x | (uintptr_t)a.y | (uintptr_t)a.res) & 15) return false;
+    // element offsets of the output (and of the shortcut) stay below 2^31, the value that marks a pixel past the tile; a row
+    // of more than 1024 pixels fits no LDS buffer (and rows_plan's byte counts stay 32-bit)
+    if ((int64_t)a.M * a.K >= ((int64_t)1 << 31) || a.W > 1024) return false;
     RowsArgs g;
     return rows_plan(a, g);
 }
