@@ -747,12 +747,18 @@ hawq_status launch_conv_pws(const ConvArgs &a, hipStream_t s) {
 hawq_status launch_conv_pw(const ConvArgs &a, hipStream_t s) {
     if (a.M == 0) return HAWQ_OK;
     // measured: at C = 64 one pixel tile per group and four waves per SIMD hide the epilogue's integer work
-    // behind the memory stream best; at C = 128 two tiles per group (two waves per SIMD) are as good as any
-    // deeper or wider arrangement
+    // behind the memory stream best; at C = 128 without a shortcut two tiles per group (two waves per SIMD) are as good as
+    // any deeper or wider arrangement.  With a shortcut single tiles win at every size (28x28x128 -> 512): their groups
+    // divide more evenly over the waves, and the epilogue of one tile covers the next one's loads.  8-bit, two waves per SIMD:
+    // 11.4 -> 10.4 us at batch 24, 13.2 -> 12.7 at 37, 19.0 -> 18.0 at 64, 46.6 -> 43.2 at 128 (three waves: 10.9, 13.3, 19.2,
+    // 47.4); packed 4-bit, whose stages are half as large, three: 9.8 -> 9.1, 11.7 -> 11.1, 16.4 -> 15.5, 26.0 -> 25.0 (two:
+    // 9.2, 11.4, 16.2, 26.7).  Beside another part's kernels (corun) nothing is left to even out: ResNet50 at batch 128 as 64 + 64
+    // 1062 us with two tiles, 1067 with one, the mixed network at 256 1789 / 1793; the two-tile form stays there.
     // (with a shortcut: three waves per SIMD, whose register budget holds all of a lane's epilogue parameters -- 52 -> 47.5 us
     // for 56x56x64 -> 256 at batch 128 against four waves that read bias and shortcut multiplier from LDS)
     if (a.C == 64) return a.res != nullptr ? launch_pw<1, 1, 2, 3>(a, s) : launch_pw<1, 1, 2, 4>(a, s);
     if (a.C == 256) return launch_pw<4, 1, 2, 2>(a, s);
+    if (a.res != nullptr && !a.corun) return is4(a.x_dt) ? launch_pw_res<2, 1, 2, 3, true>(a, s) : launch_pw_res<2, 1, 2, 2, true>(a, s);
     return launch_pw<2, 2, 2, 2>(a, s);
 }
 
