@@ -16,17 +16,10 @@
 //     even columns of a row before the odd ones, so that a tap's pixels are consecutive again.
 // Two buffers of rows: the next tile's are fetched while this one is multiplied, one barrier per tile.
 // PK: packed 4-bit operands; pixels stay packed in LDS (32 bytes), a lane takes its half's nibbles on the way into the MFMA.
+#include "conv3x3_rows_plan.h"
 #include "rp.h"
 
 namespace hawq {
-
-struct RowsArgs {
-    int32_t R, tpi, n_tiles;      // output rows of a tile, tiles per image, tiles in all
-    int32_t PW, PWh;              // pixels of an LDS row; stride 2: index of the first odd column in it
-    int32_t nt;                   // MFMA column tiles (32 pixels) of a tile
-    uint32_t mq;                  // i / Q for i < 32 nt: umulhi(i, mq), mq = ceil(2^32 / Q)
-    int32_t buf;                  // bytes of one LDS buffer
-};
 
 // WC: channel groups of 32 (waves along channels), 4 / WC waves along pixels.
 template <int WC, bool S2, bool PK, bool RES>
@@ -133,7 +126,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))
                 }
             }
             const int ic = i < n_px ? i : n_px - 1;
-            const int row = (int)__umulhi((uint32_t)ic, g.mq);
+            const int row = rows_row((uint32_t)ic, g.mq);
             const uint32_t p = (uint32_t)((S2 ? 2 * row : row) * g.PW + (ic - row * a.Q)) << PSH;
             // the three columns of the window (stride 2: even plane at +0 and +1, odd plane PWh pixels on)
 #pragma unroll
@@ -273,30 +266,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))
 
 // ---- host side ----
 
-// Rows per tile and LDS layout for a layer; false: no tile fits
 static bool rows_plan(const ConvArgs &a, RowsArgs &g) {
-    const bool s2 = a.stride_h == 2;
-    const int pxb = is4(a.x_dt) ? 32 : 64, al = is4(a.x_dt) ? 32 : 16;
-    if (s2) {
-        g.PWh = (a.Q + 1 + 15) / 16 * 16;                     // even columns -1, 1, ..., 2 Q - 1; as many odd ones, 0, 2, ...
-        g.PW = (2 * g.PWh + al - 1) / al * al;
-    } else {
-        g.PWh = 0;
-        g.PW = (a.W + 2 + al - 1) / al * al;
-    }
-    // the tile that wastes least: whole 32-pixel column tiles against R rows, rows against the image height
-    double best = 0;
-    g.R = 0;
-    for (int R = 1; R <= 16 && R <= a.P; ++R) {
-        const int rows = s2 ? 2 * R + 1 : R + 2;
-        if (2 * rows * g.PW * pxb > (s2 ? 76 << 10 : 50 << 10)) break;
-        const int tpi = (a.P + R - 1) / R, nt = (R * a.Q + 31) / 32;
-        const double eff = (double)a.P * a.Q / ((double)tpi * nt * 32) * (nt >= 6 ? 1.0 : nt >= 4 ? 0.97 : 0.9);
-        if (eff > best + 1e-9) { best = eff; g.R = R; g.tpi = tpi; g.nt = nt; g.buf = rows * g.PW * pxb; }
-    }
-    g.mq = (uint32_t)(((1ull << 32) + a.Q - 1) / a.Q);
-    g.n_tiles = a.N * g.tpi;
-    return g.R > 0;
+    return rows_plan(a.N, a.W, a.P, a.Q, a.stride_h == 2, is4(a.x_dt), g);
 }
 
 // Where this form is preferred, at 56x56 (this kernel against the one it replaces: conv3x3_c64.hip for stride 1, the tiled
@@ -318,9 +289,8 @@ bool conv3x3_rows_eligible(const ConvArgs &a, int x_hi) {
     if (a.y_dt != HAWQ_U8 && a.y_dt != HAWQ_S8 && a.y_dt != HAWQ_U4) return false;
     if (a.res != nullptr && a.res_dt != HAWQ_U8 && a.res_dt != HAWQ_S8 && a.res_dt != HAWQ_U4) return false;
     if (((uintptr_t)a.x | (uintptr_t)a.y | (uintptr_t)a.res) & 15) return false;
-    // element offsets of the output (and of the shortcut) stay below 2^31, the value that marks a pixel past the tile; a row
-    // of more than 1024 pixels fits no LDS buffer (and rows_plan's byte counts stay 32-bit)
-    if ((int64_t)a.M * a.K >= ((int64_t)1 << 31) || a.W > 1024) return false;
+    // element offsets of the output (and of the shortcut) stay below 2^31, the value that marks a pixel past the tile
+    if ((int64_t)a.M * a.K >= ((int64_t)1 << 31)) return false;
     RowsArgs g;
     return rows_plan(a, g);
 }

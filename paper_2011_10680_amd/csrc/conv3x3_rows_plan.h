@@ -1,0 +1,48 @@
+// Tiles of the whole-row 3x3 kernel (conv3x3_rows.hip): the arithmetic that its launcher and its device code share.  Plain C++
+// (constexpr functions serve the host and the device), so that a program without a GPU can walk it over every size.
+#pragma once
+#include <stdint.h>
+
+namespace hawq {
+
+struct RowsArgs {
+    int32_t R, tpi, n_tiles;      // output rows of a tile, tiles per image, tiles in all
+    int32_t PW, PWh;              // pixels of an LDS row; stride 2: index of the first odd column in it
+    int32_t nt;                   // MFMA column tiles (32 pixels) of a tile
+    uint32_t mq;                  // i / Q for i < 32 nt: see rows_row
+    int32_t buf;                  // bytes of one LDS buffer
+};
+
+// i / Q for an output pixel i of a tile, with mq = ceil(2^32 / Q).  Exact for Q >= 2 (i Q < 2^32); for Q = 1 the reciprocal
+// does not fit 32 bits, rows_plan takes no such layer.
+constexpr int rows_row(uint32_t i, uint32_t mq) { return (int)(((uint64_t)i * mq) >> 32); }
+
+// Rows per tile and LDS layout for N images of W columns with P x Q outputs (s2: stride 2, else 1; packed: 4-bit operands);
+// false: the kernel does not take the layer
+constexpr bool rows_plan(int32_t N, int32_t W, int32_t P, int32_t Q, bool s2, bool packed, RowsArgs &g) {
+    // a row of more than 1024 pixels fits no LDS buffer (and the byte counts below stay 32-bit)
+    if (W > 1024 || Q < 2) return false;
+    const int pxb = packed ? 32 : 64, al = packed ? 32 : 16;
+    if (s2) {
+        g.PWh = (Q + 1 + 15) / 16 * 16;                       // even columns -1, 1, ..., 2 Q - 1; as many odd ones, 0, 2, ...
+        g.PW = (2 * g.PWh + al - 1) / al * al;
+    } else {
+        g.PWh = 0;
+        g.PW = (W + 2 + al - 1) / al * al;
+    }
+    // the tile that wastes least: whole 32-pixel column tiles against R rows, rows against the image height
+    double best = 0;
+    g.R = 0;
+    for (int R = 1; R <= 16 && R <= P; ++R) {
+        const int rows = s2 ? 2 * R + 1 : R + 2;
+        if (2 * rows * g.PW * pxb > (s2 ? 76 << 10 : 50 << 10)) break;
+        const int tpi = (P + R - 1) / R, nt = (R * Q + 31) / 32;
+        const double eff = (double)P * Q / ((double)tpi * nt * 32) * (nt >= 6 ? 1.0 : nt >= 4 ? 0.97 : 0.9);
+        if (eff > best + 1e-9) { best = eff; g.R = R; g.tpi = tpi; g.nt = nt; g.buf = rows * g.PW * pxb; }
+    }
+    g.mq = (uint32_t)(((1ull << 32) + Q - 1) / Q);
+    g.n_tiles = N * g.tpi;
+    return g.R > 0;
+}
+
+}  // namespace hawq

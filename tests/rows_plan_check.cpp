@@ -1,0 +1,36 @@
+// Walks the whole-row 3x3 kernel's plan over every output width on the host: the row division of every pixel a lane may ask
+// for, and the LDS bytes that the pixel's window then reads.  Prints the first fault and returns 1, or the number of plans taken.
+#include <cstdio>
+
+#include "../paper_2011_10680_amd/csrc/conv3x3_rows_plan.h"
+
+using namespace hawq;
+
+int main() {
+    const int heights[] = {1, 2, 3, 7, 16, 17, 56, 200};
+    int taken = 0;
+    for (int s2 = 0; s2 < 2; ++s2)
+        for (int packed = 0; packed < 2; ++packed)
+            for (int W = 1; W <= 2100; ++W)
+                for (const int H : heights) {
+                    const int P = s2 ? (H - 1) / 2 + 1 : H, Q = s2 ? (W - 1) / 2 + 1 : W;
+                    RowsArgs g{};
+                    if (!rows_plan(3, W, P, Q, s2, packed, g)) continue;
+                    ++taken;
+                    const int n_px = g.R * Q, pxb = packed ? 32 : 64;
+                    const int rows = s2 ? 2 * g.R + 1 : g.R + 2;
+                    bool ok = g.R >= 1 && g.R <= P && g.tpi * g.R >= P && (g.tpi - 1) * g.R < P && g.n_tiles == 3 * g.tpi && g.nt * 32 >= n_px &&
+                              g.PW % (packed ? 32 : 16) == 0 && g.buf == rows * g.PW * pxb && 2 * g.buf <= 76 << 10;
+                    for (int i = 0; ok && i < 32 * g.nt; ++i) {
+                        const int ic = i < n_px ? i : n_px - 1, row = rows_row((uint32_t)ic, g.mq), q = ic - row * Q;
+                        // stride 2: columns q and q + 1 of the even plane, q of the odd one; stride 1: columns q .. q + 2
+                        const int last = s2 ? g.PWh + q : q + 2;
+                        ok = row == ic / Q && q >= 0 && q < Q && last < g.PW && (!s2 || (q + 1 < g.PWh && g.PWh + q < 2 * g.PWh)) &&
+                             ((s2 ? 2 * row : row) + 2) * g.PW + last < rows * g.PW;
+                        if (!ok) std::printf("pixel %d (row %d, column %d): ", ic, row, q);
+                    }
+                    if (!ok) { std::printf("stride %d packed %d W %d H %d R %d\n", 1 + s2, packed, W, H, g.R); return 1; }
+                }
+    std::printf("%d plans\n", taken);
+    return 0;
+}

@@ -57,3 +57,12 @@ def test_whole_rows_64_channels(hawq, N, H, W, K, stride, bits, res, y4):
         assert_same(y.cpu().numpy(), want, str((N, H, W, K, stride, bits, wide)))
     v = oracle.unpack(want, oracle.U4) if y4 else want.astype(np.int32)
     assert 0.02 < (v > 0).mean() and (v == hi).mean() < 0.7
+
+
+@pytest.mark.parametrize("N,H,W,K,stride,bits,res,y4", [
+    (1024, 64, 1, 64, 1, 8, None, False), (300, 101, 2, 64, 1, 8, 0, False), (250, 67, 3, 64, 1, 8, 1, False),
+    (500, 50, 1, 64, 2, 8, None, False), (200, 200, 2, 64, 2, 8, 0, False), (150, 91, 3, 128, 2, 8, None, True), (600, 177, 2, 64, 2, 4, None, True),
+])
+def test_outputs_one_to_three_pixels_wide(hawq, N, H, W, K, stride, bits, res, y4):
+    """An output one pixel wide has no 32-bit reciprocal of its width: those layers run on the general kernels."""
+    test_whole_rows_64_channels(hawq, N, H, W, K, stride, bits, res, y4)
