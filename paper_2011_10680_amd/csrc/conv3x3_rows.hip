@@ -41,11 +41,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))
     const int chl = wc * 32 + khalf * 16;
     const int ysh = is4(a.y_dt) ? 1 : 0;
     const bool r4 = RES && is4(a.res_dt);
-    // tiles of this workgroup: XCD b % 8 owns a contiguous eighth of them (rows shared by neighbours stay in its L2)
-    const uint32_t per = (uint32_t)(g.n_tiles + 7) / 8, xcd = blockIdx.x & 7;
-    const int step = (int)((gridDim.x + 7 - xcd) / 8);
-    const int t_end = (int)((xcd + 1) * per < (uint32_t)g.n_tiles ? (xcd + 1) * per : (uint32_t)g.n_tiles);
-    int tile = (int)(xcd * per + (blockIdx.x >> 3));
+    const RowsWalk walk = rows_walk(blockIdx.x, gridDim.x, g.n_tiles);
+    const int step = walk.step, t_end = walk.end;
+    int tile = walk.first;
 
     const __amdgpu_buffer_rsrc_t rs_x = __builtin_amdgcn_make_buffer_rsrc((void *)a.x, 0, a.N * a.H * a.W * PXB, 0x00020000);
     const int rowb = g.PW * PXB;                             // bytes of an LDS row
@@ -291,17 +289,16 @@ bool conv3x3_rows_eligible(const ConvArgs &a, int x_hi) {
     if (((uintptr_t)a.x | (uintptr_t)a.y | (uintptr_t)a.res) & 15) return false;
     // element offsets of the output (and of the shortcut) stay below 2^31, the value that marks a pixel past the tile
     if ((int64_t)a.M * a.K >= ((int64_t)1 << 31)) return false;
-    RowsArgs g;
-    return rows_plan(a, g);
+    RowsArgs g{};
+    int wc = 0, ncg = 0, gx = 0;
+    return rows_plan(a, g) && rows_grid(a.K, g.n_tiles, wc, ncg, gx);
 }
 
 hawq_status launch_conv3x3_rows(const ConvArgs &a, hipStream_t s) {
     RowsArgs g{};
-    if (!rows_plan(a, g)) return HAWQ_ERR_UNSUPPORTED;
+    int wc = 0, ncg = 0, gx = 0;
+    if (!rows_plan(a, g) || !rows_grid(a.K, g.n_tiles, wc, ncg, gx)) return HAWQ_ERR_UNSUPPORTED;
     const bool s2 = a.stride_h == 2, pk = is4(a.x_dt), res = a.res != nullptr;
-    const int wc = a.K % 128 == 0 ? 4 : 2, ncg = a.K / (32 * wc);
-    int gx = 512 / ncg;                                        // two workgroups per compute unit (registers)
-    if (gx > g.n_tiles) gx = g.n_tiles;
     const dim3 grid(gx, ncg);
     const size_t lds = 2 * (size_t)g.buf;
     auto go = [&](auto wcc, auto s2c, auto pkc, auto rc) {

@@ -45,4 +45,23 @@ constexpr bool rows_plan(int32_t N, int32_t W, int32_t P, int32_t Q, bool s2, bo
     return g.R > 0;
 }
 
+// Tiles of workgroup b of gx: first, first + step, ... below end.  Workgroup b runs on XCD b % 8, which owns a contiguous
+// eighth of the tiles (rows shared by neighbours stay in its L2); its workgroups divide them.
+struct RowsWalk { int32_t first, end, step; };
+constexpr RowsWalk rows_walk(uint32_t b, uint32_t gx, int32_t n_tiles) {
+    const uint32_t per = (uint32_t)(n_tiles + 7) / 8, xcd = b & 7;
+    const uint32_t end = (xcd + 1) * per < (uint32_t)n_tiles ? (xcd + 1) * per : (uint32_t)n_tiles;
+    return {(int32_t)(xcd * per + (b >> 3)), (int32_t)end, (int32_t)((gx + 7 - xcd) / 8)};
+}
+
+// Workgroups along the tiles (gx) for K output channels in groups of 32 wc: two workgroups per compute unit (registers).
+// false: too many channel groups -- with fewer than eight workgroups, and fewer than tiles, an XCD's share has no owner.
+constexpr bool rows_grid(int32_t K, int32_t n_tiles, int32_t &wc, int32_t &ncg, int32_t &gx) {
+    wc = K % 128 == 0 ? 4 : 2;
+    ncg = K / (32 * wc);
+    gx = 512 / ncg;
+    if (gx > n_tiles) gx = n_tiles;
+    return gx >= 8 || (gx > 0 && gx == n_tiles);
+}
+
 }  // namespace hawq

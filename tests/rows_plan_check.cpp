@@ -1,6 +1,8 @@
 // Walks the whole-row 3x3 kernel's plan over every output width on the host: the row division of every pixel a lane may ask
-// for, and the LDS bytes that the pixel's window then reads.  Prints the first fault and returns 1, or the number of plans taken.
+// for, and the LDS bytes that the pixel's window then reads; and the workgroups' tiles over every channel count: each tile
+// exactly once in every grid.  Prints the first fault and returns 1, or the numbers of plans and grids taken.
 #include <cstdio>
+#include <vector>
 
 #include "../paper_2011_10680_amd/csrc/conv3x3_rows_plan.h"
 
@@ -31,6 +33,23 @@ int main() {
                     }
                     if (!ok) { std::printf("stride %d packed %d W %d H %d R %d\n", 1 + s2, packed, W, H, g.R); return 1; }
                 }
-    std::printf("%d plans\n", taken);
+    int grids = 0;
+    const int tile_counts[] = {1, 7, 8, 9, 20, 63, 126, 448, 896, 1793};
+    for (int K = 64; K <= 70000; K += 64)
+        for (const int n : tile_counts) {
+            int32_t wc = 0, ncg = 0, gx = 0;
+            if (!rows_grid(K, n, wc, ncg, gx)) continue;
+            ++grids;
+            std::vector<int> owners(n, 0);
+            bool ok = gx > 0 && 32 * wc * ncg == K;
+            for (int b = 0; b < gx; ++b) {
+                const RowsWalk w = rows_walk((uint32_t)b, (uint32_t)gx, n);
+                ok = ok && w.step > 0 && w.first >= 0 && w.end <= n;
+                for (int t = w.first; ok && t < w.end; t += w.step) ++owners[t];
+            }
+            for (int t = 0; t < n; ++t) ok = ok && owners[t] == 1;
+            if (!ok) { std::printf("K %d: %d tiles on %d workgroups are not covered once each\n", K, n, gx); return 1; }
+        }
+    std::printf("%d plans %d grids\n", taken, grids);
     return 0;
 }

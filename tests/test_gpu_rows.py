@@ -66,3 +66,9 @@ def test_whole_rows_64_channels(hawq, N, H, W, K, stride, bits, res, y4):
 def test_outputs_one_to_three_pixels_wide(hawq, N, H, W, K, stride, bits, res, y4):
     """An output one pixel wide has no 32-bit reciprocal of its width: those layers run on the general kernels."""
     test_whole_rows_64_channels(hawq, N, H, W, K, stride, bits, res, y4)
+
+
+@pytest.mark.parametrize("N,H,W,K,stride", [(9, 74, 73, 4160, 2), (8, 78, 80, 8320, 2), (9, 74, 73, 4096, 2)])
+def test_many_output_channels(hawq, N, H, W, K, stride):
+    """More than 64 groups of output channels leave the kernel too few workgroups along the pixels: the general kernels."""
+    test_whole_rows_64_channels(hawq, N, H, W, K, stride, 8, None, False)
