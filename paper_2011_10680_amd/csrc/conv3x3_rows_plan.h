@@ -54,14 +54,16 @@ constexpr RowsWalk rows_walk(uint32_t b, uint32_t gx, int32_t n_tiles) {
     return {(int32_t)(xcd * per + (b >> 3)), (int32_t)end, (int32_t)((gx + 7 - xcd) / 8)};
 }
 
-// Workgroups along the tiles (gx) for K output channels in groups of 32 wc: two workgroups per compute unit (registers).
-// false: too many channel groups -- with fewer than eight workgroups, and fewer than tiles, an XCD's share has no owner.
+// Workgroups along the tiles (gx) for K output channels in groups of 32 wc: two workgroups per compute unit (registers), or
+// one per tile.  A multiple of eight: every XCD then has as many workgroups as the others, and as its share has tiles (with one
+// per tile and 238 tiles, two XCDs had 29 workgroups for 30 tiles: one tile's time more, 7.4 -> 10.0 us at 17 x 56 x 56).
+// false: too many channel groups -- with fewer than eight workgroups an XCD's share has no owner.
 constexpr bool rows_grid(int32_t K, int32_t n_tiles, int32_t &wc, int32_t &ncg, int32_t &gx) {
     wc = K % 128 == 0 ? 4 : 2;
     ncg = K / (32 * wc);
-    gx = 512 / ncg;
-    if (gx > n_tiles) gx = n_tiles;
-    return gx >= 8 || (gx > 0 && gx == n_tiles);
+    gx = 512 / ncg / 8 * 8;
+    if (gx > (n_tiles + 7) / 8 * 8) gx = (n_tiles + 7) / 8 * 8;
+    return gx >= 8;
 }
 
 }  // namespace hawq

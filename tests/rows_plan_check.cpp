@@ -1,6 +1,6 @@
 // Walks the whole-row 3x3 kernel's plan over every output width on the host: the row division of every pixel a lane may ask
 // for, and the LDS bytes that the pixel's window then reads; and the workgroups' tiles over every channel count: each tile
-// exactly once in every grid.  Prints the first fault and returns 1, or the numbers of plans and grids taken.
+// exactly once, and evenly, in every grid.  Prints the first fault and returns 1, or the numbers of plans and grids taken.
 #include <cstdio>
 #include <vector>
 
@@ -42,13 +42,18 @@ int main() {
             ++grids;
             std::vector<int> owners(n, 0);
             bool ok = gx > 0 && 32 * wc * ncg == K;
+            // no workgroup has more tiles than an even division of an XCD's share gives its workgroups
+            const int share = (n + 7) / 8, room = 512 / ncg / 8, per_xcd = room < 1 ? 1 : room < share ? room : share;
+            const int most = (share + per_xcd - 1) / per_xcd;
             for (int b = 0; b < gx; ++b) {
                 const RowsWalk w = rows_walk((uint32_t)b, (uint32_t)gx, n);
                 ok = ok && w.step > 0 && w.first >= 0 && w.end <= n;
-                for (int t = w.first; ok && t < w.end; t += w.step) ++owners[t];
+                int mine = 0;
+                for (int t = w.first; ok && t < w.end; t += w.step, ++mine) ++owners[t];
+                ok = ok && mine <= most;
             }
             for (int t = 0; t < n; ++t) ok = ok && owners[t] == 1;
-            if (!ok) { std::printf("K %d: %d tiles on %d workgroups are not covered once each\n", K, n, gx); return 1; }
+            if (!ok) { std::printf("K %d: %d tiles on %d workgroups are not covered once each, or unevenly\n", K, n, gx); return 1; }
         }
     std::printf("%d plans %d grids\n", taken, grids);
     return 0;
