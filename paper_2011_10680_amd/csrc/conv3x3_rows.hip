@@ -252,11 +252,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))
         const int n = tile / g.tpi, h0 = (tile - n * g.tpi) * g.R;
         const int64_t m0 = ((int64_t)n * a.P + h0) * a.Q;
         const int rows = a.P - h0 < g.R ? a.P - h0 : g.R, valid = rows * a.Q, nt = (valid + 31) >> 5;
-        // this wave's column tiles: the first or second half of the pairs
-        const int pairs = (nt + 1) >> 1, p0 = WP == 1 ? 0 : (wp == 0 ? 0 : (pairs + 1) >> 1), p1 = WP == 1 ? pairs : (wp == 0 ? (pairs + 1) >> 1 : pairs);
-        for (int p = p0; p < p1; ++p) {
-            if (2 * p + 1 < nt) compute(std::integral_constant<int, 2>{}, 2 * p, buf, m0, valid);
-            else compute(std::integral_constant<int, 1>{}, 2 * p, buf, m0, valid);
+        // this wave's column tiles: the first or second half (of five: three and two, not two pairs and a single)
+        const int half = (nt + 1) >> 1, t0 = WP == 1 || wp == 0 ? 0 : half, t1 = WP == 1 || wp == 1 ? nt : half;
+        for (int t = t0; t < t1; t += 2) {
+            if (t + 1 < t1) compute(std::integral_constant<int, 2>{}, t, buf, m0, valid);
+            else compute(std::integral_constant<int, 1>{}, t, buf, m0, valid);
         }
         cur ^= 1;
     }
@@ -268,19 +268,51 @@ static bool rows_plan(const ConvArgs &a, RowsArgs &g) {
     return rows_plan(a.N, a.W, a.P, a.Q, a.stride_h == 2, is4(a.x_dt), g);
 }
 
-// Where this form is preferred, at 56x56 (this kernel against the one it replaces: conv3x3_c64.hip for stride 1, the tiled
-// kernel for stride 2): with a shortcut 17.1 us (20.0) at batch 64, 25.8 (31.2) at 128; without 9.7 (10.5) at 32, 15.5 (15.1)
-// at 64, 22.4 (24.9) at 128; stride 2, 64 -> 128: 7.3 (7.8) at 32, 11.5 (12.8) at 64, 17.8 (22.1) at 128; images wider than
-// conv3x3_c64's 62 pixels: 18.7 (33.8) at 112x112.  Fewer pixels: the split-reduction forms.  Packed operands cost eight
-// vector operations per fragment here: stride 1 stays with conv3x3_c64 (14.7 against 17.9 us at batch 64), stride 2 comes here
-// from 50000 output pixels on (11.2 against 13.1 us at batch 64, 10.6 against 9.2 at 32).
+// Where this form is preferred, against the kernel that takes the layer otherwise (conv3x3_c64.hip for 64 -> 64 at stride 1 and
+// up to 62 columns, else the tiled kernel), swept over images of 20x20 to 112x112 and 9000 to 400000 output pixels.  Either
+// kernel's time climbs in steps of a round of workgroups; the lines lie where the other one needs its next round.
+//   Stride 1, 64 -> 64, up to 62 columns: with a shortcut from 65536 pixels on (56x56 at batch 22 10.5 us against 12.4, 64 18.4
+//   against 22.1, 128 27.2 against 35.9; at 19 10.3 against 9.4).  Without one the two are near each other, and conv3x3_c64 does
+//   not care how rows divide into column tiles: it keeps the layer below six of its rounds (56x56 at batch 40 11.2 there, 12.5
+//   here) and below 48 columns (28x28 at 192 12.3 and 14.4, 40x40 at 251 24.2 and 26.6).  Beyond, 56x56 at batch 64 15.1 and 15.6 by
+//   itself, at 128 25.6 and 24.1; inside the networks this kernel is ahead at 64 too (ResNet50 at batch 128 as 64 + 64 1077 us with it,
+//   1085 without, ResNet18 at 64 262 and 264).
+//   Stride 1, more columns (112x112: 7.2 us against 8.6 at batch 4, 24.0 against 45.0 at 32) or more channels (128 at 56x56: 16.7
+//   against 18.1 at batch 22, 33.7 against 48.2 at 96): from 50000 pixels and 2^23 outputs (64 channels: any) on; 128 channels
+//   below 65536 pixels 0.89 to 1.10 of the tiled kernel's time.
+//   Packed operands cost eight vector operations per fragment here: stride 1 up to 62 columns stays with conv3x3_c64 (14.7
+//   against 17.9 us at batch 64), all else comes here from 65536 pixels on (stride 2, 56x56 64 -> 128: 13.9 us against 17.2 at
+//   batch 85, 14.2 against 12.8 at 66).
+//   Stride 2, 8-bit: by the two estimates of rows_faster_s2.
+// Fewer pixels: the split-reduction forms.
 // (Measured and dropped: three workgroups per compute unit -- the registers allow two; reading fragments two or three
-// half-steps ahead with a fixed schedule; requantising a pair of column tiles between the next pair's MFMAs: a tile's 2.8 us
-// are near its MFMA time for two waves per SIMD, what remains is start-up (3 us) and the fetch's issue (0.7 us a tile).)
+// half-steps ahead with a fixed schedule; requantising a pair of column tiles between the next pair's MFMAs.  What a tile costs
+// beside its MFMAs is its start-up (3 us) and the fetch's issue (0.7 us).)
+
+// Stride 2, 8-bit operands: microseconds of this kernel and of the tiled one, fitted to 386 layers (64 to 256 output channels; 5 % rms,
+// single layers up to 17 %).  Here: rounds of 256 workgroups times the column tiles of a wave and the bytes of a tile's rows;
+// there: rounds of its 128 x 128 (64 channels: 64 x 128) tiles.  The estimate is worst where channel groups of 64 share no pixels
+// (K % 128 == 64: 192 channels) and on outputs of less than 12 columns: those have to be clearly faster.  By pixels alone (from
+// 12000 on) such layers took up to 1.55 times the tiled kernel's time, 64 -> 128 up to 1.16 times.
+static bool rows_faster_s2(const ConvArgs &a, const RowsArgs &g, int wc, int ncg) {
+    const int64_t rounds = ((int64_t)g.n_tiles * ncg + 255) / 256, px_tiles = ((int64_t)a.M + 127) / 128;
+    const double here = 4.8 + (double)rounds * (0.62 * (wc == 4 ? g.nt : (g.nt + 1) / 2) + 0.016 / 1024 * g.buf);
+    const double tiled = a.K == 64 ? 1.5 + 7.1 * (double)((px_tiles + 511) / 512) : 3.8 + 4.15 * (double)((px_tiles * ((a.K + 127) / 128) + 255) / 256);
+    return here < ((a.K != 64 && wc == 2) || a.Q < 12 ? 0.88 : a.K > 128 ? 0.97 : 1.0) * tiled;
+}
+
 bool conv3x3_rows_eligible(const ConvArgs &a, int x_hi) {
-    const bool s2 = a.stride_h == 2;
-    if (is4(a.x_dt) ? a.M < 50000 || (!s2 && a.W <= 62) : a.M < (s2 ? 12000 : 50000)) return false;
     if (a.R != 3 || a.S != 3 || a.C != 64 || a.pad_h != 1 || a.pad_w != 1 || a.stride_h != a.stride_w || (a.stride_h != 1 && a.stride_h != 2)) return false;
+    const bool s2 = a.stride_h == 2;
+    if (is4(a.x_dt)) {
+        if (a.M <= 65536 || (!s2 && a.W <= 62)) return false;
+    } else if (s2) {
+        if (a.M < 12000) return false;
+    } else if (a.K == 64 && a.W <= 62) {
+        if (a.M <= 65536 || (a.res == nullptr && (a.M < 6 * 32768 || a.W < 48))) return false;
+    } else {
+        if (a.M < 50000 || (a.K != 64 && (int64_t)a.M * a.K <= (1 << 23))) return false;
+    }
     if (a.w_f == nullptr || a.b == nullptr || a.xs != nullptr || a.K % 64 != 0) return false;
     if (a.x_dt == HAWQ_U4) { if (a.w_dt != HAWQ_S4) return false; }
     else if (a.w_dt != HAWQ_S8 || (a.x_dt == HAWQ_U8 ? x_hi > 127 : a.x_dt != HAWQ_S8)) return false;
@@ -291,7 +323,8 @@ bool conv3x3_rows_eligible(const ConvArgs &a, int x_hi) {
     if ((int64_t)a.M * a.K >= ((int64_t)1 << 31)) return false;
     RowsArgs g{};
     int wc = 0, ncg = 0, gx = 0;
-    return rows_plan(a, g) && rows_grid(a.K, g.n_tiles, wc, ncg, gx);
+    if (!rows_plan(a, g) || !rows_grid(a.K, g.n_tiles, wc, ncg, gx)) return false;
+    return !s2 || is4(a.x_dt) || rows_faster_s2(a, g, wc, ncg);
 }
 
 hawq_status launch_conv3x3_rows(const ConvArgs &a, hipStream_t s) {
