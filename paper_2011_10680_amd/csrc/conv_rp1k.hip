@@ -176,20 +176,30 @@ static hawq_status rp1k_launch(const ConvArgs &a, hipStream_t s) {
 //   256 -> 1024 + shortcut at 14x14: batch 4 4.7 (5.5), 8 5.6 (6.7), 16 7.5 (7.2); 128 -> 512 + shortcut: batch 4 5.0 (6.4), 8 6.7 (6.8)
 //   256 -> 128 / 2: batch 8 4.5 (5.4), 16 4.9 (6.1), 32 6.5 (7.5), 64 11.1 (10.3); 256 -> 64: batch 4 4.2 (4.6), 8 5.2 (6.1), 32 11.7 (11.4)
 // The variant: tiles of 64 channels (32 at C = 2048) and 64 pixels (32 from C = 1024 on) while they are at most one
-// workgroup per compute unit, the next larger tile beyond.
+// workgroup per compute unit, the next larger tile beyond -- that one as far as it is the faster, which depends on what takes the
+// layer otherwise.  In workgroups of 64 x 64, against the kernel that takes over:
+//   C = 256, no shortcut, 8-bit, K >= 256: to 512 (256 -> 512: 0.92 of the tiled kernel's time at 384, 1.02 at 512, 1.19 at 600; one round
+//     of its tiles reaches to 1024).  Packed or K = 128: to 1024 (0.89 to 1.0).  K not a multiple of 128: 64 x 64 to 256 (192 channels:
+//     1.07 to 1.12 beyond), packed or K = 64 to 512 (0.79 to 0.93, 0.82 to 0.92).
+//   C = 512: to 512 (packed 1.13 to 1.23 at 600 to 704, 8-bit with K = 128 or stride 2 1.04 to 1.11) -- to 800 where the resident-pixel
+//     kernel would take the layer, which is no faster there (0.88 to 1.01).
+//   C = 1024: to 256 against the tiled kernel (1.0 to 1.10 beyond), to 400 against the resident-pixel one (0.75 to 0.95).
+//   C = 128, packed, no shortcut: below the streaming kernel's 8192 pixels (1.03 beyond).
 static int rp1k_variant(const ConvArgs &a) {
     if (a.K % 64 != 0 || a.M <= 0) return 0;
     const int64_t out = (int64_t)a.M * a.K;
-    if (out <= (is4(a.x_dt) ? 1 << 19 : a.C >= 2048 ? 3 << 15 : a.C >= 1024 ? 1 << 17 : 1 << 18)) return 0;
+    const bool pk = is4(a.x_dt), res = a.res != nullptr, k128 = a.K % 128 == 0;
+    if (out <= (pk ? 1 << 19 : a.C >= 2048 ? 3 << 15 : a.C >= 1024 ? 1 << 17 : 1 << 18)) return 0;
     const int64_t t64 = ((int64_t)a.M + 63) / 64, t32 = ((int64_t)a.M + 31) / 32, g = a.K / 64;
-    const bool k128 = a.K % 128 == 0;
+    // (the layer is conv_rp1.hip's otherwise: see make_rp1_args)
+    const bool rp1 = !pk && a.K % 256 == 0 && a.stride_h == 1 && a.stride_w == 1 && !is4(a.y_dt) && !(res && is4(a.res_dt));
     switch (a.C) {
-    case 128: return k128 && t64 * (g / 2) <= 256 ? 1 : 0;
+    case 128: return k128 && t64 * (g / 2) <= 256 && !(pk && !res && a.M >= 8192) ? 1 : 0;
     case 256:
-        if (t64 * g <= (k128 || a.res != nullptr ? 256 : 512)) return 2;
-        return k128 && t64 * (g / 2) <= (a.res != nullptr ? 256 : 512) ? 3 : 0;
-    case 512: return t64 * g <= 256 ? 4 : k128 && t64 * (g / 2) <= 400 ? 5 : 0;
-    case 1024: return t32 * g <= 256 ? 6 : t64 * g <= 400 ? 7 : 0;
+        if (t64 * g <= (!k128 && !res && (pk || a.K == 64) ? 512 : 256)) return 2;
+        return k128 && t64 * (g / 2) <= (!res && (pk || a.K == 128 || a.K >= 2048) ? 512 : 256) ? 3 : 0;
+    case 512: return t64 * g <= 256 ? 4 : k128 && t64 * (g / 2) <= (rp1 ? 400 : 256) ? 5 : 0;
+    case 1024: return t32 * g <= 256 ? 6 : t64 * g <= (rp1 ? 400 : 256) ? 7 : 0;
     case 2048: return t32 * (2 * g) <= 256 ? 8 : t64 * (2 * g) <= 256 ? 9 : 0;
     default: return 0;
     }
