@@ -659,7 +659,8 @@ static hawq_status launch_pw_res(const ConvArgs &a, hipStream_t s) {
     const int n_groups = (a.M + 32 * TP - 1) / (32 * TP);
     // fill every SIMD of the 256 CUs with as many waves as the register budget allows, each walking over
     // several pixel groups
-    int n_seq = (WPE * 4 * 256 + n_ct - 1) / n_ct;
+    int n_seq = (WPE * 4 * 256) / n_ct;   // (rounded down: one workgroup past the last slot would be a round of its own)
+    if (n_seq < 1) n_seq = 1;
     if (n_seq > n_groups) n_seq = n_groups;
     const int waves = n_seq * n_ct;
     const uint32_t blocks = (uint32_t)((waves + 3) / 4);
@@ -753,12 +754,20 @@ hawq_status launch_conv_pw(const ConvArgs &a, hipStream_t s) {
     // 11.4 -> 10.4 us at batch 24, 13.2 -> 12.7 at 37, 19.0 -> 18.0 at 64, 46.6 -> 43.2 at 128 (three waves: 10.9, 13.3, 19.2,
     // 47.4); packed 4-bit, whose stages are half as large, three: 9.8 -> 9.1, 11.7 -> 11.1, 16.4 -> 15.5, 26.0 -> 25.0 (two:
     // 9.2, 11.4, 16.2, 26.7).  Beside another part's kernels (corun) nothing is left to even out: ResNet50 at batch 128 as 64 + 64
-    // 1062 us with two tiles, 1067 with one, the mixed network at 256 1789 / 1793; the two-tile form stays there.
+    // 1062 us with two tiles, 1067 with one, the mixed network at 256 1789 / 1793; the two-tile form stays there.  So it does
+    // where its groups fill whole rounds of its waves and the single tiles just do not: in one round against two (packed 128 -> 256 at
+    // 16366 pixels 6.8 us with two tiles, 8.3 with one; 8-bit 128 -> 192 at 12789 7.6 and 8.4), and, packed, whose single-tile
+    // round takes seven tenths of a two-tile one, two against three (9.5 and 10.0 at 32732).
     // (with a shortcut: three waves per SIMD, whose register budget holds all of a lane's epilogue parameters -- 52 -> 47.5 us
     // for 56x56x64 -> 256 at batch 128 against four waves that read bias and shortcut multiplier from LDS)
     if (a.C == 64) return a.res != nullptr ? launch_pw<1, 1, 2, 3>(a, s) : launch_pw<1, 1, 2, 4>(a, s);
     if (a.C == 256) return launch_pw<4, 1, 2, 2>(a, s);
-    if (a.res != nullptr && !a.corun) return is4(a.x_dt) ? launch_pw_res<2, 1, 2, 3, true>(a, s) : launch_pw_res<2, 1, 2, 2, true>(a, s);
+    if (a.res != nullptr && !a.corun) {
+        const bool four = is4(a.x_dt);
+        const int64_t n_ct = (a.K + 31) / 32, wpe = four ? 3 : 2;
+        const int64_t single = (((int64_t)a.M + 31) / 32 * n_ct + 1024 * wpe - 1) / (1024 * wpe), pairs = (((int64_t)a.M + 63) / 64 * n_ct + 2047) / 2048;
+        if (!(four ? 10 * pairs <= 7 * single : pairs == 1 && single == 2)) return four ? launch_pw_res<2, 1, 2, 3, true>(a, s) : launch_pw_res<2, 1, 2, 2, true>(a, s);
+    }
     return launch_pw<2, 2, 2, 2>(a, s);
 }
 

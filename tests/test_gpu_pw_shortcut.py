@@ -26,3 +26,8 @@ def test_128_channels_with_shortcut(N, H, W, K, bits, res):
     assert_same(got, want, str((N, H, W, K, bits, res)))
     v = want.astype(np.int32) if bits == 8 else oracle.unpack(want, oracle.U4)
     assert 0.02 < (v > 0).mean() and len(np.unique(v)) > 5
+
+
+@pytest.mark.parametrize("N,H,W,K,bits,res", [(1, 167, 98, 256, 4, 2), (1, 87, 147, 192, 8, 0), (1, 103, 129, 176, 8, 1), (1, 121, 137, 192, 4, 2)])
+def test_128_channels_with_shortcut_in_one_round_of_tile_pairs(N, H, W, K, bits, res):
+    test_128_channels_with_shortcut(N, H, W, K, bits, res)
