@@ -408,7 +408,14 @@ static hawq_status sk_launch(const ConvArgs &a, SkArgs e, bool xf, hipStream_t s
 // against the one it replaces): 7x7 3x3 512 -> 512 at batch 1 / 4 5.2 / 7.2 us (14.6 / 15.2), 14x14 3x3 256 -> 256 4.2 / 6.3
 // (9.4 / 9.7), 28x28 3x3 128 -> 128 4.1 / 6.2 (7.1 / 8.6), 14x14 1x1 1024 -> 256 3.7 / 4.8 (8.7 / 9.0).  Above the line the
 // streaming and resident-pixel kernels win: 56x56 1x1 64 -> 256 + shortcut at batch 4 16.3 (6.1), 28x28 128 -> 512 9.5 (6.5).
-bool conv_sk_small(const ConvArgs &a) { return (int64_t)a.M * a.K <= (1 << 19); }
+// One kind above 2^18 outputs is the tiled kernel's: a long 8-bit reduction over fewer than 1024 pixels, where that one takes 64 x 64
+// tiles with a ring of eight -- unless the blocked copy of the weights, which both read, is there (without it, 7x7 2048 -> 512 at
+// batch 16 9.7 us here, 8.6 there; 14x14 1024 -> 512 at 4 7.6 and 6.9; 128 x 4096 -> 4096 14.8 and 13.5).
+bool conv_sk_small(const ConvArgs &a) {
+    const int64_t out = (int64_t)a.M * a.K;
+    const bool tiled = !is4(a.x_dt) && a.xs == nullptr && a.w_t == nullptr && a.M < 1024 && (int64_t)a.R * a.S * a.C >= 1024 && a.C % 64 == 0 && a.K % 16 == 0;
+    return out <= (tiled ? 1 << 18 : 1 << 19);
+}
 
 hawq_status launch_conv_sk(const ConvArgs &a_in, int x_hi, hipStream_t s) {
     ConvArgs a = a_in;
