@@ -270,49 +270,47 @@ static bool rows_plan(const ConvArgs &a, RowsArgs &g) {
 
 // Where this form is preferred, against the kernel that takes the layer otherwise (conv3x3_c64.hip for 64 -> 64 at stride 1 and
 // up to 62 columns, else the tiled kernel), swept over images of 20x20 to 112x112 and 9000 to 400000 output pixels.  Either
-// kernel's time climbs in steps of a round of workgroups; the lines lie where the other one needs its next round.
-//   Stride 1, 64 -> 64, up to 62 columns: with a shortcut from 65536 pixels on (56x56 at batch 22 10.5 us against 12.4, 64 18.4
-//   against 22.1, 128 27.2 against 35.9; at 19 10.3 against 9.4).  Without one the two are near each other, and conv3x3_c64 does
-//   not care how rows divide into column tiles: it keeps the layer below six of its rounds (56x56 at batch 40 11.2 there, 12.5
-//   here) and below 48 columns (28x28 at 192 12.3 and 14.4, 40x40 at 251 24.2 and 26.6).  Beyond, 56x56 at batch 64 15.1 and 15.6 by
-//   itself, at 128 25.6 and 24.1; inside the networks this kernel is ahead at 64 too (ResNet50 at batch 128 as 64 + 64 1077 us with it,
-//   1085 without, ResNet18 at 64 262 and 264).
-//   Stride 1, more columns (112x112: 7.2 us against 8.6 at batch 4, 24.0 against 45.0 at 32) or more channels (128 at 56x56: 16.7
-//   against 18.1 at batch 22, 33.7 against 48.2 at 96): from 50000 pixels and 2^23 outputs (64 channels: any) on; 128 channels
-//   below 65536 pixels 0.89 to 1.10 of the tiled kernel's time.
-//   Packed operands cost eight vector operations per fragment here: stride 1 up to 62 columns stays with conv3x3_c64 (14.7
-//   against 17.9 us at batch 64), all else comes here from 65536 pixels on (stride 2, 56x56 64 -> 128: 13.9 us against 17.2 at
-//   batch 85, 14.2 against 12.8 at 66).
-//   Stride 2, 8-bit: by the two estimates of rows_faster_s2.
-// Fewer pixels: the split-reduction forms.
+// kernel's time climbs in steps, a round of workgroups each, so no line by pixels alone holds for every image size (with one,
+// from 50000 pixels and for stride 2 from 12000 on, layers were up to 1.7 times slower than before: 28x28 at batch 66 7.4 us ->
+// 12.5).  The estimates of rows_faster place the steps:
+//   stride 1, 64 -> 64, up to 62 columns, with a shortcut: 56x56 at batch 17 8.7 us against 9.2, 19 10.3 against 9.4 (left), 64 18.4
+//   against 22.1, 128 27.2 against 35.9; without: 32 9.8 against 10.7, 40 12.5 against 11.2 (left), 64 15.6 against 15.1 alone,
+//   but inside the networks ahead (ResNet50 at batch 128 as 64 + 64 1077 us with it, 1085 without), 128 24.1 against 25.6;
+//   stride 2, 56x56 64 -> 128: batch 32 8.3 against 8.8, 48 10.4 against 11.7, 128 16.0 against 21.0; packed, 64 12.2 against 14.0, 66
+//   14.2 against 12.8 (left).
+//   stride 1, 64 -> 128: 112x112 batch 4 9.7 against 11.5, 56x56 19 16.5 against 14.0 (left), 96 33.7 against 48.2.
+// More columns at 64 channels (112x112: 7.2 us against 8.6 at batch 4, 24.0 against 45.0 at 32; packed 7.8 against 10.5 at 4) come here
+// from 50000 pixels on.  Packed operands cost eight vector operations per fragment here: up to 62 columns stride 1 stays with
+// conv3x3_c64 (14.7 against 17.9 us at batch 64).  Fewer pixels: the split-reduction forms.
 // (Measured and dropped: three workgroups per compute unit -- the registers allow two; reading fragments two or three
 // half-steps ahead with a fixed schedule; requantising a pair of column tiles between the next pair's MFMAs.  What a tile costs
 // beside its MFMAs is its start-up (3 us) and the fetch's issue (0.7 us).)
 
-// Stride 2, 8-bit operands: microseconds of this kernel and of the tiled one, fitted to 386 layers (64 to 256 output channels; 5 % rms,
-// single layers up to 17 %).  Here: rounds of 256 workgroups times the column tiles of a wave and the bytes of a tile's rows;
-// there: rounds of its 128 x 128 (64 channels: 64 x 128) tiles.  The estimate is worst where channel groups of 64 share no pixels
-// (K % 128 == 64: 192 channels) and on outputs of less than 12 columns: those have to be clearly faster.  By pixels alone (from
-// 12000 on) such layers took up to 1.55 times the tiled kernel's time, 64 -> 128 up to 1.16 times.
-static bool rows_faster_s2(const ConvArgs &a, const RowsArgs &g, int wc, int ncg) {
-    const int64_t rounds = ((int64_t)g.n_tiles * ncg + 255) / 256, px_tiles = ((int64_t)a.M + 127) / 128;
-    const double here = 4.8 + (double)rounds * (0.62 * (wc == 4 ? g.nt : (g.nt + 1) / 2) + 0.016 / 1024 * g.buf);
-    const double tiled = a.K == 64 ? 1.5 + 7.1 * (double)((px_tiles + 511) / 512) : 3.8 + 4.15 * (double)((px_tiles * ((a.K + 127) / 128) + 255) / 256);
-    return here < ((a.K != 64 && wc == 2) || a.Q < 12 ? 0.88 : a.K > 128 ? 0.97 : 1.0) * tiled;
+// Microseconds of this kernel and of the other one, fitted to 2400 layers of 64 to 512 output channels (each row 2 to 5 % rms).  Here:
+// rounds of 256 workgroups, times the column tiles of a wave and the KB of a tile's rows, and the MB that move; there: rounds of
+// workgroups, and the MB.  `margin`: how far below the other estimate this one has to be.
+struct RowsCost { double start, tile, kb, mb, o_start, o_round, o_mb, margin; };
+
+static bool rows_faster(const ConvArgs &a, const RowsArgs &g, int wc, int ncg) {
+    const bool s2 = a.stride_h == 2, four = is4(a.x_dt), res = a.res != nullptr;
+    const RowsCost c = !s2 && a.K == 64 ? (res ? RowsCost{5.23, 0.491, 0.0, 0.123, 4.67, 2.363, 0.0, a.M > 65536 ? 1.0 : 0.94}     // conv3x3_c64
+                                               : RowsCost{4.66, 0.351, 0.005, 0.168, 4.6, 1.255, 0.067, 1.0})
+                     : !s2              ? (res ? RowsCost{6.09, 0.51, 0.016, 0.08, 4.55, 3.35, 0.163, 1.0} : RowsCost{5.08, 0.51, 0.012, 0.075, 3.64, 3.2, 0.198, 1.0})
+                     : four             ? (a.K == 64 ? RowsCost{5.33, 0.57, 0.008, 0.103, 3.43, 4.0, 0.394, 1.0} : RowsCost{5.22, 0.74, 0.008, 0.035, 4.57, 4.13, 0.154, 1.0})
+                     : a.K == 64        ? RowsCost{4.75, 0.41, 0.015, 0.052, 3.0, 3.93, 0.172, 0.97}
+                     : wc == 4          ? RowsCost{4.99, 0.553, 0.02, 0.013, 3.66, 3.74, 0.083, 0.97}
+                                        : RowsCost{4.65, 0.505, 0.024, 0.0, 3.89, 2.84, 0.196, 0.97};
+    const int64_t px_tiles = ((int64_t)a.M + 127) / 128;      // 256 of them are a round of conv3x3_c64, 512 one of the tiled kernel's 64 x 128 tiles
+    const int64_t o_rounds = a.K != 64 ? (px_tiles * ((a.K + 127) / 128) + 255) / 256 : s2 ? (px_tiles + 511) / 512 : (px_tiles + 255) / 256;
+    const double rounds = (double)(((int64_t)g.n_tiles * ncg + 255) / 256), tiles = wc == 4 ? g.nt : (g.nt + 1) / 2;
+    const double mb = 1e-6 / (four ? 2 : 1) * a.M * (64 * a.stride_h * a.stride_w + a.K * (res ? 2 : 1));
+    return c.start + rounds * (c.tile * tiles + c.kb / 1024 * g.buf) + c.mb * mb < c.margin * (c.o_start + c.o_round * (double)o_rounds + c.o_mb * mb);
 }
 
 bool conv3x3_rows_eligible(const ConvArgs &a, int x_hi) {
     if (a.R != 3 || a.S != 3 || a.C != 64 || a.pad_h != 1 || a.pad_w != 1 || a.stride_h != a.stride_w || (a.stride_h != 1 && a.stride_h != 2)) return false;
-    const bool s2 = a.stride_h == 2;
-    if (is4(a.x_dt)) {
-        if (a.M <= 65536 || (!s2 && a.W <= 62)) return false;
-    } else if (s2) {
-        if (a.M < 12000) return false;
-    } else if (a.K == 64 && a.W <= 62) {
-        if (a.M <= 65536 || (a.res == nullptr && (a.M < 6 * 32768 || a.W < 48))) return false;
-    } else {
-        if (a.M < 50000 || (a.K != 64 && (int64_t)a.M * a.K <= (1 << 23))) return false;
-    }
+    const bool s2 = a.stride_h == 2, four = is4(a.x_dt), wide_image = !s2 && a.W > 62 && (a.K == 64 || four);
+    if (a.M < (s2 && !four ? 12000 : 50000) || (!s2 && four && !wide_image)) return false;
     if (a.w_f == nullptr || a.b == nullptr || a.xs != nullptr || a.K % 64 != 0) return false;
     if (a.x_dt == HAWQ_U4) { if (a.w_dt != HAWQ_S4) return false; }
     else if (a.w_dt != HAWQ_S8 || (a.x_dt == HAWQ_U8 ? x_hi > 127 : a.x_dt != HAWQ_S8)) return false;
@@ -324,7 +322,7 @@ bool conv3x3_rows_eligible(const ConvArgs &a, int x_hi) {
     RowsArgs g{};
     int wc = 0, ncg = 0, gx = 0;
     if (!rows_plan(a, g) || !rows_grid(a.K, g.n_tiles, wc, ncg, gx)) return false;
-    return !s2 || is4(a.x_dt) || rows_faster_s2(a, g, wc, ncg);
+    return wide_image || rows_faster(a, g, wc, ncg);
 }
 
 hawq_status launch_conv3x3_rows(const ConvArgs &a, hipStream_t s) {

@@ -62,7 +62,7 @@ def test_whole_rows_64_channels(hawq, N, H, W, K, stride, bits, res, y4):
 @pytest.mark.parametrize("N,H,W,K,stride,bits,res,y4", [
     # 64 -> 64 up to 62 columns: with a shortcut past 65536 pixels; column tiles of a tile odd and even in number, ragged last tiles
     (22, 56, 56, 64, 1, 8, 0, False), (29, 47, 49, 64, 1, 8, 1, True), (73, 30, 31, 64, 1, 8, 2, True), (242, 16, 17, 64, 1, 8, 1, False), (52, 33, 39, 64, 1, 8, 0, False),
-    (76, 51, 51, 64, 1, 8, None, True),                                                    # without one, past 196608
+    (64, 56, 56, 64, 1, 8, None, True), (33, 56, 55, 64, 1, 8, None, False),               # without one
     (9, 73, 77, 64, 1, 8, None, False), (8, 93, 101, 128, 1, 8, 1, False), (17, 56, 56, 192, 1, 8, None, True), (6, 112, 111, 64, 1, 4, 2, True),
     (20, 75, 63, 128, 2, 8, None, False), (200, 31, 29, 128, 2, 8, 0, False), (48, 61, 61, 192, 2, 8, None, True), (110, 45, 47, 256, 2, 8, 1, False),
     (90, 56, 55, 128, 2, 4, None, True), (30, 93, 95, 64, 2, 4, 2, True),
