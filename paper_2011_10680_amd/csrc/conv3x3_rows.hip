@@ -288,13 +288,16 @@ static bool rows_plan(const ConvArgs &a, RowsArgs &g) {
 
 // Microseconds of this kernel and of the other one, fitted to 2400 layers of 64 to 512 output channels (each row 2 to 5 % rms).  Here:
 // rounds of 256 workgroups, times the column tiles of a wave and the KB of a tile's rows, and the MB that move; there: rounds of
-// workgroups, and the MB.  `margin`: how far below the other estimate this one has to be.
+// workgroups, and the MB.  `margin`: how far below the other estimate this one has to be (64 -> 64 without a shortcut may be 3 %
+// above it: inside a network, with its input still in cache, it gains that: ResNet18 at batch 26 208 us without, 203 with it).
+// Beside another stream's kernels (corun) the end of a round idles nothing, and this kernel's fewer bytes per output decide: ResNet18 at
+// batch 103 as 56 + 47 354 us by the estimates, 338 with it throughout; at 206 514 and 493; ResNet50 at 96 894 and 879.
 struct RowsCost { double start, tile, kb, mb, o_start, o_round, o_mb, margin; };
 
 static bool rows_faster(const ConvArgs &a, const RowsArgs &g, int wc, int ncg) {
     const bool s2 = a.stride_h == 2, four = is4(a.x_dt), res = a.res != nullptr;
     const RowsCost c = !s2 && a.K == 64 ? (res ? RowsCost{5.23, 0.491, 0.0, 0.123, 4.67, 2.363, 0.0, a.M > 65536 ? 1.0 : 0.94}     // conv3x3_c64
-                                               : RowsCost{4.66, 0.351, 0.005, 0.168, 4.6, 1.255, 0.067, 1.0})
+                                               : RowsCost{4.66, 0.351, 0.005, 0.168, 4.6, 1.255, 0.067, a.M > 65536 ? 1.03 : 1.0})
                      : !s2              ? (res ? RowsCost{6.09, 0.51, 0.016, 0.08, 4.55, 3.35, 0.163, 1.0} : RowsCost{5.08, 0.51, 0.012, 0.075, 3.64, 3.2, 0.198, 1.0})
                      : four             ? (a.K == 64 ? RowsCost{5.33, 0.57, 0.008, 0.103, 3.43, 4.0, 0.394, 1.0} : RowsCost{5.22, 0.74, 0.008, 0.035, 4.57, 4.13, 0.154, 1.0})
                      : a.K == 64        ? RowsCost{4.75, 0.41, 0.015, 0.052, 3.0, 3.93, 0.172, 0.97}
@@ -322,7 +325,7 @@ bool conv3x3_rows_eligible(const ConvArgs &a, int x_hi) {
     RowsArgs g{};
     int wc = 0, ncg = 0, gx = 0;
     if (!rows_plan(a, g) || !rows_grid(a.K, g.n_tiles, wc, ncg, gx)) return false;
-    return wide_image || rows_faster(a, g, wc, ncg);
+    return wide_image || a.corun || rows_faster(a, g, wc, ncg);
 }
 
 hawq_status launch_conv3x3_rows(const ConvArgs &a, hipStream_t s) {
