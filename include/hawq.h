@@ -73,17 +73,23 @@ typedef struct {
     int32_t x_hi;                  /* largest |activation| the caller guarantees; 0 = the type's maximum.
                                       Used by the overflow bound; HAWQ_U8 data with x_hi <= 127 (the
                                       post-ReLU 8-bit range of the workloads) runs on the signed INT8
-                                      matrix cores, larger values take a slower exact kernel.   */
+                                      matrix cores; larger values cost one more product per
+                                      reduction step (C % 16 == 0; else a slower exact kernel).  */
     const void *w_blocked;         /* optional (NULL: none): device copy of the same weights made by
                                       hawq_conv_block_weights; the implicit-GEMM kernel then reads it instead of w
                                       (whole cache lines per fetch).  w is still required: other kernels read it. */
     const void *w_fragments;       /* optional (NULL: none): device copy of the same weights made by
-                                      hawq_conv_fragment_weights; a 3x3 / stride 1 / pad 1 layer with 128, 256 or 512
-                                      input channels (8-bit or packed 4-bit operands), or a 1x1 / stride 1 layer with
-                                      512, 1024 or 2048 input channels and K % 256 == 0 (8-bit operands), then runs on
-                                      a kernel that keeps its pixels in LDS and streams these; so do launches of a
-                                      middling size of the 3x3 layers with 64 channels and of the 1x1 layers (any
-                                      stride) with 128 to 2048 channels and K % 64 == 0, in both operand widths.
+                                      hawq_conv_fragment_weights.  Kernels that keep their pixels in LDS and read the
+                                      weights in this order then take (requantised outputs, 16-byte aligned x, y and
+                                      residual, x_hi <= 127 for HAWQ_U8 data; each in a range of sizes where it is
+                                      the faster kernel):
+                                       - 3x3 / pad 1 with 64 input channels, stride 1 or 2, K % 64 == 0;
+                                       - 3x3 / stride 1 / pad 1 with 128, 256 or 512 input channels, K % 64 == 0
+                                         (large launches: K % 128 == 0, from 256 channels on K % 256 == 0);
+                                       - 1x1 of any stride with 128 (K % 128 == 0), 256, 512, 1024 or 2048 input
+                                         channels, K % 64 == 0 (large launches: 8-bit, stride 1, 512 channels or
+                                         more, K % 256 == 0).
+                                      Other layers do not read the copy.
                                       (hawq_conv2d_dual_int ignores the field: that kernel's two-convolution form needs
                                       a bound on the main branch's values that only hawq_net_create, which sees the
                                       weights on the host, can establish.) */
@@ -103,9 +109,10 @@ typedef struct {
  * bias, b, res_b: int32 [K]; c, res_c: uint8 [K].  b == c == NULL is allowed only with
  * y_dtype == HAWQ_S32 and no residual: y = t (raw accumulator + bias).
  * The INT32 accumulator never goes to memory; x and y must not overlap.
- * Every valid request is served; the matrix-core kernels need C a multiple of 64, 16-byte aligned x and w,
- * at most 304 reduction steps (R*S*C/64) and, for their vector epilogue, K a multiple of 16 with 16-byte aligned
- * y / residual / bias / b arrays -- anything else runs on a slower exact kernel with the same results.
+ * Every valid request is served; the matrix-core kernels need C a multiple of 16 (large launches are fastest with
+ * a multiple of 64), 16-byte aligned x and w, a reduction R*S*C below 2^23 (packed 4-bit: 2^20) and, for their
+ * vector epilogue, K a multiple of 16 (small launches: 4) with 16-byte aligned y / residual / bias / b arrays --
+ * anything else runs on a slower exact kernel with the same results.
  */
 hawq_status hawq_conv2d_int(const hawq_conv_desc *desc, const void *x, const void *w, const int32_t *bias,
                             const int32_t *b, const uint8_t *c, const void *residual, const int32_t *res_b,

@@ -185,7 +185,7 @@ hawq_status dispatch_conv(const ConvArgs &a, int x_hi, hipStream_t s) {
         if (make_rp_args(a, x_hi, nullptr, nullptr, r, true) && conv_rpk_shape_ok(r)) return launch_conv_rpk(r, s);
     }
     if (tile_override() == 0 && conv_rp1k_eligible(a, x_hi)) return launch_conv_rp1k(a, s);
-    const bool sk = conv_sk_eligible(a, x_hi);
+    const bool sk = conv_sk_eligible(a);
     if (tile_override() == 0 && sk && conv_sk_small(a)) return launch_conv_sk(a, x_hi, s);
     if (conv_pw_eligible(a, x_hi)) return launch_conv_pw(a, s);
     if (tile_override() == 0 && conv_pws_eligible(a, x_hi)) return launch_conv_pws(a, s);

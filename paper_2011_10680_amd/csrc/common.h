@@ -193,7 +193,7 @@ int tile_override();
 bool conv3x3_c64_eligible(const ConvArgs &a, int x_hi);
 hawq_status launch_conv3x3_c64(const ConvArgs &a, hipStream_t s);
 // split-reduction kernel: small launches, channel counts that are a multiple of 16 only, unsigned bytes above 127
-bool conv_sk_eligible(const ConvArgs &a, int x_hi);
+bool conv_sk_eligible(const ConvArgs &a);
 bool conv_sk_dual_eligible(const ConvArgs &a, int x_hi, int xs_hi);
 hawq_status launch_conv_sk(const ConvArgs &a, int x_hi, hipStream_t s);
 bool conv_sk_small(const ConvArgs &a);   // preferred over the other kernels that take the shape

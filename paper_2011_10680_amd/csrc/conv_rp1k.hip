@@ -157,7 +157,7 @@ static hawq_status rp1k_launch(const ConvArgs &a, hipStream_t s) {
     const int bp = 32 * TP;
     const uint32_t nb = (uint32_t)((a.M + bp - 1) / bp) * (uint32_t)(a.K / (32 * WC));
     size_t lds = (size_t)bp * (pk ? 32 * CCH : 64 * CCH);
-    const size_t red = WK > 1 ? (size_t)WC * R * TP * 4096 : 0;
+    const size_t red = (size_t)WC * R * TP * 4096;
     if (red > lds) lds = red;
     if (lds < 1024) lds = 1024;
     if (pk) conv_rp1k_kernel<CCH, TP, WC, WK, true><<<nb, 64 * WC * WK, lds, s>>>(a);

@@ -184,7 +184,7 @@ static hawq_status rpk_launch(const RpArgs &a, hipStream_t s) {
     const int cb = a.pk ? 32 * CCH : 64 * CCH, bp = 32 * TP;
     const uint32_t nb = (uint32_t)((a.M + bp - 1) / bp) * (uint32_t)(a.K1 / (32 * WC));
     size_t lds = ((size_t)(bp + 2 * a.W + 3) * cb + 1023) / 1024 * 1024;
-    const size_t red = WK > 1 ? (size_t)WC * R * TP * 4096 : 0;
+    const size_t red = (size_t)WC * R * TP * 4096;
     if (red > lds) lds = red;
     if (a.pk) conv_rpk_kernel<CCH, TP, WC, WK, true><<<nb, 64 * WC * WK, lds, s>>>(a);
     else conv_rpk_kernel<CCH, TP, WC, WK, false><<<nb, 64 * WC * WK, lds, s>>>(a);

@@ -146,7 +146,8 @@ __global__ void __launch_bounds__(WK *WM * 64) conv_sk_kernel(const ConvArgs a, 
     constexpr int D = TC + TP <= 2 ? 8 : TC + TP <= 4 ? 5 : TC + TP <= 6 ? 4 : 3;   // steps in flight per wave
     constexpr int SLOTS = WM * TC * TP * 64, NT = WK * WM * 64, E = (SLOTS + NT - 1) / NT;
     constexpr uint32_t kInvalid = 0x80000000u;              // beyond every tensor: the load returns zeros
-    __shared__ v4i red[WK > 1 ? WM * WK * TC * TP * 64 : 1];
+    static_assert(WK > 1, "the partial tiles meet in LDS, and two convolutions need two waves");
+    __shared__ v4i red[WM * WK * TC * TP * 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wk = wave % WK, wp = wave / WK;
     const int row16 = lane & 15, kg = lane >> 4;
@@ -316,31 +317,24 @@ __global__ void __launch_bounds__(WK *WM * 64) conv_sk_kernel(const ConvArgs a, 
         }
 
     // ---- the partial tiles meet; every thread finishes four channels of a pixel ----
-    if constexpr (WK > 1) {
 #pragma unroll
-        for (int tp = 0; tp < TP; ++tp)
+    for (int tp = 0; tp < TP; ++tp)
 #pragma unroll
-            for (int tc = 0; tc < TC; ++tc) red[((wp * WK + wk) * TC * TP + tp * TC + tc) * 64 + lane] = acc[tp][tc];
-        __syncthreads();
-    }
+        for (int tc = 0; tc < TC; ++tc) red[((wp * WK + wk) * TC * TP + tp * TC + tc) * 64 + lane] = acc[tp][tc];
+    __syncthreads();
     static_for<0, E>([&](auto jc) {
         constexpr int j = decltype(jc)::value;
-        int s = tid + j * NT;
-        if constexpr (WK == 1) s = (wp * TC * TP + j) * 64 + lane;       // its own tiles
+        const int s = tid + j * NT;
         if (SLOTS % NT != 0 && s >= SLOTS) return;
         uint32_t m; int ch;
         slot_mk(s, m, ch);
         if (m >= (uint32_t)a.M || ch >= a.K) return;
         v4i t = {0, 0, 0, 0}, ts = {0, 0, 0, 0};
-        if constexpr (WK == 1) {
-            t = acc[j / TC][j % TC];
-        } else {
-            const int w = s / (64 * TC * TP), in_tile = s % (64 * TC * TP);
+        const int w = s / (64 * TC * TP), in_tile = s % (64 * TC * TP);
 #pragma unroll
-            for (int k = 0; k < WK; ++k) {
-                const v4i u = red[(w * WK + k) * (64 * TC * TP) + in_tile];
-                if (!DUAL || k < e.wk_main) t += u; else ts += u;
-            }
+        for (int k = 0; k < WK; ++k) {
+            const v4i u = red[(w * WK + k) * (64 * TC * TP) + in_tile];
+            if (!DUAL || k < e.wk_main) t += u; else ts += u;
         }
         if constexpr (E <= 2) {
             sk_store<DUAL>(a, e.vec, m, ch, t, ts, par[j]);
@@ -356,7 +350,7 @@ __global__ void __launch_bounds__(WK *WM * 64) conv_sk_kernel(const ConvArgs a, 
 
 static int sk_form(const ConvArgs &a) { return !is4(a.x_dt) ? 0 : a.C % 32 == 0 ? 1 : 2; }
 
-bool conv_sk_eligible(const ConvArgs &a, int x_hi) {
+bool conv_sk_eligible(const ConvArgs &a) {
     const bool four = is4(a.x_dt);
     if (a.C % 16 != 0 || four != is4(a.w_dt)) return false;
     if (four ? (a.x_dt != HAWQ_U4 || a.w_dt != HAWQ_S4) : (a.w_dt != HAWQ_S8 || (a.x_dt != HAWQ_U8 && a.x_dt != HAWQ_S8))) return false;
@@ -365,7 +359,6 @@ bool conv_sk_eligible(const ConvArgs &a, int x_hi) {
     // packed sums are kept times sixteen: |16 w x| <= 16 * 8 * 15 and red < 2^20 stay below 2^31; the spatial limits are the bounds test's
     if (red >= (four ? 1 << 20 : 1 << 23) || (int64_t)a.H + a.R >= (1 << 29) || (int64_t)a.W + a.S >= (1 << 29)) return false;
     if ((int64_t)((a.K + 63) / 64 * 64) * (red + 64) >= ((int64_t)1 << 31)) return false;   // the blocked copy below the out-of-range offset
-    (void)x_hi;
     return a.xs == nullptr;
 }
 
@@ -374,7 +367,7 @@ bool conv_sk_dual_eligible(const ConvArgs &a, int x_hi, int xs_hi) {
     if (a.mid_s8 && (a.res_b == nullptr || a.res_c == nullptr)) return false;
     ConvArgs m = a;
     m.xs = nullptr;
-    if (!conv_sk_eligible(m, x_hi) || is4(a.x_dt) || is4(a.xs_dt) || a.Cs % 16 != 0 || a.ws_dt != HAWQ_S8) return false;
+    if (!conv_sk_eligible(m) || is4(a.x_dt) || is4(a.xs_dt) || a.Cs % 16 != 0 || a.ws_dt != HAWQ_S8) return false;
     if ((a.x_dt == HAWQ_U8 && x_hi > 127) || (a.xs_dt == HAWQ_U8 && xs_hi > 127)) return false;
     if (((uintptr_t)a.xs | (uintptr_t)a.ws) & 15) return false;
     return (int64_t)a.Hs < (1 << 29) && (int64_t)a.Ws < (1 << 29) && (int64_t)((a.K + 63) / 64 * 64) * (a.Cs + 64) < ((int64_t)1 << 31);
@@ -387,12 +380,10 @@ static hawq_status sk_launch(const ConvArgs &a, SkArgs e, bool xf, hipStream_t s
     constexpr int T = WK * WM * 64;
     e.wk_main = WK;
     if (a.xs != nullptr) {
-        if constexpr (WK > 1) {
-            const int s1 = a.R * a.S * (a.C / 16), s2 = a.Cs / 16;
-            int w2 = (2 * WK * s2 + s1 + s2) / (2 * (s1 + s2));
-            e.wk_main = WK - (w2 < 1 ? 1 : w2 > WK - 1 ? WK - 1 : w2);
-            conv_sk_kernel<TC, TP, WK, WM, 0, false, true><<<nb, T, 0, s>>>(a, e);
-        }
+        const int s1 = a.R * a.S * (a.C / 16), s2 = a.Cs / 16;
+        const int w2 = (2 * WK * s2 + s1 + s2) / (2 * (s1 + s2));
+        e.wk_main = WK - (w2 < 1 ? 1 : w2 > WK - 1 ? WK - 1 : w2);
+        conv_sk_kernel<TC, TP, WK, WM, 0, false, true><<<nb, T, 0, s>>>(a, e);
         return check_launch();
     }
     const int form = sk_form(a);

@@ -65,7 +65,7 @@ residual_add_vec_kernel(const uint32_t units, const uint32_t groups, const void 
         if (Y32) ((v4i *)y)[at] = o;
         else ((uint32_t *)y)[at] = (o[0] & 0xff) | ((o[1] & 0xff) << 8) | ((o[2] & 0xff) << 16) | ((uint32_t)o[3] << 24);
     };
-    for (; u + (U - 1) * T < units; u += U * T) {      // (units + U T stays far below 2^32: checked by the launcher)
+    for (; u + (U - 1) * T < units; u += U * T) {      // (units + U T stays far below 2^32: the interface takes fewer than 2^31 elements)
         v4i a[U], b[U];
 #pragma unroll
         for (int i = 0; i < U; ++i) { a[i] = load4<MD>(m, u + i * T); b[i] = load4<RD>(r, u + i * T); }
@@ -360,8 +360,6 @@ pool_sum_kernel(const int64_t units, const int H, const int W, const int C, cons
     }
 }
 
-// patch of output pixels per thread (measured at 128 x 35 x 35 x 288 INT32: 4x4 73.8 us, 4x8 76.8, 8x4 77.4, 8x8 78.2;
-// one row of eight, the previous form, 117.6 us)
 // fast path for the Inception pooling branch: 3x3 / stride 1 / pad 1 on INT32 (or unsigned 8-bit) data, C % 4 == 0.  One
 // thread = 4 channels of a QT-wide, PT-high patch of output pixels.  It walks the PT + 2 input rows under the patch once:
 // per row QT + 2 loads and the QT horizontal three-sums; an output row is the sum of the last three rows' horizontal sums
@@ -434,8 +432,9 @@ hawq_status launch_pool_sum(int N, int H, int W, int C, int R, int S, int sh, in
     const bool any4 = is4(x_dt) || is4(y_dt);
     if (R == 3 && S == 3 && sh == 1 && sw == 1 && ph == 1 && pw == 1 && C % 4 == 0 && (x_dt == HAWQ_S32 || x_dt == HAWQ_U8) &&
         (((uintptr_t)x | (uintptr_t)y) & 15) == 0) {
-        // patches of 4x4 outputs once they give every compute unit a workgroup, smaller ones below (17 x 17 x 64 at batch 4:
-        // 7 workgroups of 4x4 patches 7.4 us, 73 of single outputs 4.1)
+        // patches of 4x4 outputs once they give every compute unit a workgroup (128 x 35 x 35 x 288 INT32: 4x4 73.8 us, 4x8 76.8,
+        // 8x4 77.4, 8x8 78.2; one row of eight 117.6), smaller ones below (17 x 17 x 64 at batch 4: 7 workgroups of 4x4 patches
+        // 7.4 us, 73 of single outputs 4.1)
         auto blocks_of = [&](int t) { return ((int64_t)N * ((H + t - 1) / t) * ((W + t - 1) / t) * (C / 4) + 255) / 256; };
         if (N == 0) return HAWQ_OK;
         if (blocks_of(1) > 0x7fffffff) return HAWQ_ERR_UNSUPPORTED;

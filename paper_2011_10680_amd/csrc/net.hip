@@ -347,7 +347,7 @@ hawq_status hawq_net_create(int32_t arch, int32_t image_hw, int32_t num_classes,
     // fragment-ordered copy: the 3x3 / 1 / 1 layers of the resident-pixel kernels (8-bit form or packed) ...
     auto rp3x3 = [&](int i) { return L[i].R == 3 && L[i].S == 3 && (L[i].stride == 1 || L[i].C == 64) && L[i].pad == 1 && (L[i].C == 64 || L[i].C == 128 || L[i].C == 256 || L[i].C == 512) && L[i].K % L[i].C == 0; };
     // ... and the 1x1 layers of the resident-pixel 1x1 kernels (main branches and transition convolutions alike)
-    auto rp1x1 = [&](int i) { return L[i].R == 1 && L[i].S == 1 && L[i].pad == 0 && L[i].C % 64 == 0 && L[i].K % 64 == 0; };
+    auto rp1x1 = [&](int i) { return L[i].R == 1 && L[i].S == 1 && L[i].pad == 0 && L[i].C % 128 == 0 && L[i].K % 64 == 0; };
     auto fragmented = [&](int i) { return !L[i].is_stem && !L[i].is_fc && (rp3x3(i) || rp1x1(i)); };
     std::vector<Off> off(nl);
     size_t total = 0;

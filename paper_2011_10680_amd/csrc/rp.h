@@ -107,11 +107,6 @@ __device__ __forceinline__ void rpk_reduce(uint8_t *lds, int lane, int wk, int w
     v4i *red = (v4i *)lds;
     auto at = [&](int part, int tp, int q) -> v4i & { return red[(((wc * R + part) * TP + tp) * 4 + q) * 64 + lane]; };
     auto quad = [&](const v16i &v, int q) { return (v4i){v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]}; };
-    if constexpr (WK == 1) {
-#pragma unroll
-        for (int j = 0; j < NF; ++j) fin[j] = acc[j];
-        return;
-    }
     __syncthreads();
     if constexpr (WK > R) {
         if (wk >= R)
