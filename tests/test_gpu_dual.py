@@ -106,6 +106,29 @@ def test_matrix_core_form(hawq, shape):
     assert (want < 0).any() and (want > 0).any()
 
 
+# the same forms past 2^19 outputs, where the tiled kernel takes over from the split-reduction one
+_LARGE = [(9, 28, 64, 256, 1, 64, 1), (9, 14, 128, 512, 1, 256, 2), (6, 7, 512, 2048, 1, 1024, 2), (27, 14, 128, 128, 3, 64, 2), (40, 9, 64, 192, 1, 128, 1),
+          (17, 16, 256, 144, 3, 192, 1), (22, 7, 512, 512, 3, 256, 2), (19, 7, 512, 608, 3, 320, 2), (70, 7, 512, 512, 3, 256, 2)]
+
+
+@pytest.mark.parametrize("shape", _LARGE)
+def test_matrix_core_form_large_launches(hawq, shape):
+    test_matrix_core_form(hawq, shape)
+
+
+@pytest.mark.parametrize("shape", [(11, 14, 128, 256, 1, 256, 2), (23, 7, 512, 512, 3, 256, 2)])
+def test_wide_multipliers_and_4bit_output_large_launches(hawq, shape):
+    from gpu_util import assert_same
+    N, H, C, K, R, Cs, ss = shape
+    t, tw = _case(99, N, H, C, K, R, Cs, ss), _case(99, N, H, C, K, R, Cs, ss, wide=True)
+    ref, _ = _run(hawq, t, hawq.U8, 1, 0, 127)
+    for case, y_dt, hi in ((tw, hawq.U8, 127), (t, hawq.U4, 15), (tw, hawq.U4, 15)):
+        got, want = _run(hawq, case, y_dt, 1, 0, hi)
+        assert_same(got, want, str((shape, y_dt)))
+        if y_dt == hawq.U8:
+            assert_same(got, ref, "scaling numerator and shift together changes nothing")
+
+
 def test_wide_multipliers_and_4bit_output(hawq):
     from gpu_util import assert_same
     t = _case(99, 3, 14, 128, 256, 1, 256, 2)

@@ -91,3 +91,35 @@ def test_conv1x1_signed_output_and_clamp_window(hawq):
                                  pad=0, x_dt=oracle.U8, w_dt=oracle.S8, y_dt=o_dt, relu=relu, y_lo=lo, y_hi=hi)
         got = y.cpu().numpy()
         assert_same(got.view(np.int8) if y_dt == hawq.S8 else got, want)
+
+
+# the same at sizes that reach this kernel: past the split-reduction kernels' lines
+LARGE = [(33, 7, 7, 512, 2048, "u8", False), (66, 7, 7, 512, 1024, "s8", True), (9, 37, 39, 512, 256, None, True),
+         (33, 14, 14, 1024, 256, None, False), (17, 14, 14, 1024, 512, "u8", True), (67, 7, 7, 1024, 512, "s8", False),
+         (21, 7, 7, 2048, 512, None, False), (11, 7, 7, 2048, 1024, "s8", True), (42, 7, 7, 2048, 256, "u8", False), (43, 7, 7, 2048, 512, None, True)]
+
+
+@pytest.mark.parametrize("N,H,W,C,K,res,wide", LARGE)
+def test_conv1x1_with_fragment_weights_large_launches(hawq, N, H, W, C, K, res, wide):
+    test_conv1x1_with_fragment_weights(hawq, N, H, W, C, K, res, wide)
+
+
+@pytest.mark.parametrize("N,C,K", [(34, 512, 2048), (67, 1024, 512), (22, 2048, 512)])
+def test_conv1x1_signed_output_and_clamp_window_large_launches(hawq, N, C, K):
+    import torch
+    from gpu_util import to_dev, assert_same
+    case = _centre(wl.conv_case(seed=78, N=N, H=7, W=7, C=C, K=K, R=1, S=1, stride=1, pad=0, bits=8), C, K)
+    for y_dt, relu, lo, hi in ((hawq.S8, 0, -128, 127), (hawq.S8, 0, -100, 90), (hawq.U8, 1, 3, 200)):
+        d = hawq.ConvDesc(N=N, H=7, W=7, C=C, K=K, R=1, S=1, stride_h=1, stride_w=1, pad_h=0, pad_w=0, x_dtype=hawq.U8, w_dtype=hawq.S8,
+                          y_dtype=y_dt, res_dtype=hawq.U8, relu=relu, y_lo=lo, y_hi=hi, x_hi=127)
+        w = to_dev(case["w"])
+        wf = torch.zeros((hawq.hawq_conv_fragment_weights_bytes(d),), dtype=torch.uint8, device="cuda")
+        hawq.hawq_conv_fragment_weights(d, w, wf)
+        d.w_fragments = wf.data_ptr()
+        y = torch.full((N, 7, 7, K), 0x5A, dtype=torch.uint8, device="cuda")
+        hawq.hawq_conv2d_int(d, to_dev(case["x"]), w, to_dev(case["bias"]), to_dev(case["b"]), to_dev(case["c"]), None, None, None, y)
+        torch.cuda.synchronize()
+        want = oracle.conv2d_int(case["x"], case["w"], case["bias"], case["b"], case["c"], N=N, H=7, W=7, C=C, K=K, R=1, S=1, stride=1,
+                                 pad=0, x_dt=oracle.U8, w_dt=oracle.S8, y_dt=y_dt, relu=relu, y_lo=lo, y_hi=hi)
+        got = y.cpu().numpy()
+        assert_same(got.view(np.int8) if y_dt == hawq.S8 else got, want, str((C, lo, hi)))

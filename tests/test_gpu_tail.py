@@ -209,3 +209,47 @@ def test_bottleneck_tail_refuses_other_shapes(hawq):
         with pytest.raises(hawq.HawqError) as e:
             call(d2, d3)
         assert e.value.status == status, (e.value.status, status)
+
+
+# the same at sizes that reach this kernel: past the split-reduction kernels' lines.  128 channels: 256-pixel tiles up to 71680 pixels,
+# 448-pixel ones beyond; 256: half the channels per workgroup below 160 tiles of 128 pixels; ragged last tiles, several images in one
+LARGE = [(21, 28, 28, 128, 128, None, False), (23, 27, 27, 128, 256, "s8", False), (65, 13, 21, 128, 128, "u8", True), (92, 28, 28, 128, 128, "u8", False),
+         (93, 28, 28, 128, 128, None, True), (21, 14, 14, 256, 256, None, False), (22, 13, 15, 256, 512, "u8", False), (6, 28, 26, 256, 256, "s8", True),
+         (106, 14, 14, 256, 256, "u8", True), (106, 14, 14, 256, 256, "s8", False), (42, 7, 7, 512, 512, None, True), (43, 7, 7, 512, 512, "u8", False),
+         (59, 5, 14, 512, 256, "s8", True), (150, 7, 7, 512, 512, "s8", False)]
+
+
+@pytest.mark.parametrize("N,H,W,C,K,res,wide", LARGE)
+def test_conv3x3_with_fragment_weights_large_launches(hawq, N, H, W, C, K, res, wide):
+    test_conv3x3_with_fragment_weights(hawq, N, H, W, C, K, res, wide)
+
+
+LARGE_PACKED = [(21, 28, 28, 128, 128, "u4", False), (92, 28, 28, 128, 128, "u4", True), (21, 14, 14, 256, 256, "u4", True), (35, 13, 11, 256, 512, "u8", False),
+                (106, 14, 14, 256, 256, "u4", False), (42, 7, 7, 512, 512, "u4", False), (59, 5, 14, 512, 256, "u8", True), (150, 7, 7, 512, 512, "u4", True)]
+
+
+@pytest.mark.parametrize("N,H,W,C,K,ydt,wide", LARGE_PACKED)
+def test_conv3x3_packed_4bit_large_launches(hawq, N, H, W, C, K, ydt, wide):
+    test_conv3x3_packed_4bit_with_fragment_weights(hawq, N, H, W, C, K, ydt, wide)
+
+
+@pytest.mark.parametrize("C,K,N", [(128, 128, 21), (256, 256, 22), (512, 512, 43)])
+def test_conv3x3_signed_output_and_clamp_window_large_launches(hawq, C, K, N):
+    """Signed 8-bit output without ReLU and clamp windows inside the type's range."""
+    import torch
+    from gpu_util import to_dev, assert_same
+    H = {128: 28, 256: 14, 512: 7}[C]
+    case = _centre(wl.conv_case(seed=C, N=N, H=H, W=H, C=C, K=K, R=3, S=3, stride=1, pad=1, bits=8))
+    for y_dt, relu, lo, hi in ((hawq.S8, 0, -128, 127), (hawq.S8, 0, -100, 90), (hawq.U8, 1, 3, 200)):
+        d = hawq.ConvDesc(N=N, H=H, W=H, C=C, K=K, R=3, S=3, stride_h=1, stride_w=1, pad_h=1, pad_w=1, x_dtype=hawq.U8, w_dtype=hawq.S8,
+                          y_dtype=y_dt, res_dtype=hawq.U8, relu=relu, y_lo=lo, y_hi=hi, x_hi=127)
+        w = to_dev(case["w"])
+        wf = _frag(hawq, d, w)
+        d.w_fragments = wf.data_ptr()
+        y = torch.full((N, H, H, K), 0x5A, dtype=torch.uint8, device="cuda")
+        hawq.hawq_conv2d_int(d, to_dev(case["x"]), w, to_dev(case["bias"]), to_dev(case["b"]), to_dev(case["c"]), None, None, None, y)
+        torch.cuda.synchronize()
+        want = oracle.conv2d_int(case["x"], case["w"], case["bias"], case["b"], case["c"], N=N, H=H, W=H, C=C, K=K, R=3, S=3, stride=1,
+                                 pad=1, x_dt=oracle.U8, w_dt=oracle.S8, y_dt=y_dt, relu=relu, y_lo=lo, y_hi=hi)
+        got = y.cpu().numpy()
+        assert_same(got.view(np.int8) if y_dt == hawq.S8 else got, want, str((C, lo, hi)))
