@@ -320,8 +320,7 @@ bool conv3x3_rows_eligible(const ConvArgs &a, int x_hi) {
     if (a.y_dt != HAWQ_U8 && a.y_dt != HAWQ_S8 && a.y_dt != HAWQ_U4) return false;
     if (a.res != nullptr && a.res_dt != HAWQ_U8 && a.res_dt != HAWQ_S8 && a.res_dt != HAWQ_U4) return false;
     if (((uintptr_t)a.x | (uintptr_t)a.y | (uintptr_t)a.res) & 15) return false;
-    // element offsets of the output (and of the shortcut) stay below 2^31, the value that marks a pixel past the tile
-    if ((int64_t)a.M * a.K >= ((int64_t)1 << 31)) return false;
+    if (!rows_offsets_fit(a.M, a.K)) return false;
     RowsArgs g{};
     int wc = 0, ncg = 0, gx = 0;
     if (!rows_plan(a, g) || !rows_grid(a.K, g.n_tiles, wc, ncg, gx)) return false;

@@ -45,6 +45,9 @@ constexpr bool rows_plan(int32_t N, int32_t W, int32_t P, int32_t Q, bool s2, bo
     return g.R > 0;
 }
 
+// Element offsets of the output (and of the shortcut) stay below 2^31, the value that marks a pixel past the tile
+constexpr bool rows_offsets_fit(int64_t M, int32_t K) { return M * K < ((int64_t)1 << 31); }
+
 // Tiles of workgroup b of gx: first, first + step, ... below end.  Workgroup b runs on XCD b % 8, which owns a contiguous
 // eighth of the tiles (rows shared by neighbours stay in its L2); its workgroups divide them.
 struct RowsWalk { int32_t first, end, step; };

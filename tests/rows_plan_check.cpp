@@ -33,6 +33,11 @@ int main() {
                     }
                     if (!ok) { std::printf("stride %d packed %d W %d H %d R %d\n", 1 + s2, packed, W, H, g.R); return 1; }
                 }
+    // every element offset below the marker 0x80000000, also those the kernel forms in 32 bits
+    for (int64_t M = 1; M < ((int64_t)1 << 31); M = M * 3 / 2 + 1)
+        for (int K = 64; K <= 65536; K *= 2)
+            if (rows_offsets_fit(M, K) != ((uint64_t)M * (uint64_t)K - 1 < 0x7fffffffu)) { std::printf("M %lld K %d\n", (long long)M, K); return 1; }
+    if (rows_offsets_fit((int64_t)1 << 25, 64) || !rows_offsets_fit(((int64_t)1 << 25) - 1, 64)) { std::printf("2^31 elements\n"); return 1; }
     int grids = 0;
     const int tile_counts[] = {1, 7, 8, 9, 20, 63, 126, 448, 896, 1793};
     for (int K = 64; K <= 70000; K += 64)
