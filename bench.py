@@ -98,6 +98,21 @@ def profiled_dominant_kernel(workload):
     return best
 
 
+def profiled_kernels(workload):
+    """Kernel families of one forward, in order of first use, from the committed launch-by-launch summary; [] if there is none."""
+    path = os.path.join(os.path.dirname(os.path.abspath(__file__)), "profiles", "per_layer_%s.md" % workload)
+    if not os.path.exists(path):
+        return []
+    names = []
+    for line in open(path):
+        c = [x.strip() for x in line.strip().strip("|").split("|")]
+        if len(c) >= 5 and c[0].isdigit():
+            name = re.sub(r"(_kernel)?(<.*)?$", "", c[3].strip("`"))
+            if name not in names:
+                names.append(name)
+    return names
+
+
 def dominant_kernel_layers(workload, kernel):
     """Names of the layers that the committed launch-by-launch summary (profiles/per_layer_<workload>.md) shows on `kernel`."""
     path = os.path.join(os.path.dirname(os.path.abspath(__file__)), "profiles", "per_layer_%s.md" % workload)
@@ -336,8 +351,8 @@ def main():
             dom["live_tops"] = 2 * sum(r["gmac"] for r in live) * 1e9 / (live_us * 1e-6) / 1e12
             dom["live_frac_int8_mfma_peak"] = dom["live_tops"] / PEAK_INT8_TOPS
     roof.update(traffic=profiled_traffic(args.workload),
-                kernel="one forward = %s%d launches (conv_stem_pool, conv3x3_c64, conv_rp, conv_mfma, conv_pw, conv_pws, conv_pws_dual, avgpool)"
-                       % ("2 x " if first else "", sum(r["mbytes"] > 0 for r in rows)),
+                kernel="one forward = %s%d launches (%s)" % ("2 x " if first else "", sum(r["mbytes"] > 0 for r in rows),
+                                                             ", ".join(profiled_kernels(args.workload)) or "no committed profile"),
                 dominant_kernel=dom,
                 launch_ms=ev_ms_per_step, algorithmic_bytes=total_bytes, t_hbm_ms=t_mem * 1e3, t_mfma_ms=t_mfma * 1e3,
                 mfma_tops=achieved_tops, mfma_frac=achieved_tops / PEAK_INT8_TOPS,

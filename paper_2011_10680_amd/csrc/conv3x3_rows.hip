@@ -12,8 +12,10 @@
 //     in the tile only, and output pixels of a tile are consecutive in memory.  The LDS-DMA that fetches the rows writes the
 //     zeros by itself (out-of-range offsets);
 //   * an LDS row is PW pixels long, a multiple of 16, so that a row step leaves the chunk permutation alone (pixel p keeps
-//     chunk c at c ^ (p >> 2): sixteen consecutive pixels of one chunk lie in sixteen different banks).  Stride 2 keeps the
-//     even columns of a row before the odd ones, so that a tap's pixels are consecutive again.
+//     chunk c at c ^ (p >> 2): sixteen consecutive pixels of one LDS row lie in sixteen different banks; a column tile that
+//     crosses a row end continues PW - Q pixels further, 8 of 16 for 56 columns, and collides: 0.20 to 0.33 of the LDS-active
+//     cycles are conflicts there).  Stride 2 keeps the even columns of a row before the odd ones, so that a tap's pixels are
+//     consecutive again.
 // Two buffers of rows: the next tile's are fetched while this one is multiplied, one barrier per tile.
 // PK: packed 4-bit operands; pixels stay packed in LDS (32 bytes), a lane takes its half's nibbles on the way into the MFMA.
 #include "conv3x3_rows_plan.h"
@@ -284,7 +286,8 @@ static bool rows_plan(const ConvArgs &a, RowsArgs &g) {
 // conv3x3_c64 (14.7 against 17.9 us at batch 64).  Fewer pixels: the split-reduction forms.
 // (Measured and dropped: three workgroups per compute unit -- the registers allow two; reading fragments two or three
 // half-steps ahead with a fixed schedule; requantising a pair of column tiles between the next pair's MFMAs.  What a tile costs
-// beside its MFMAs is its start-up (3 us) and the fetch's issue (0.7 us).)
+// beside its MFMAs -- the matrix pipe is busy 0.20 to 0.36 of the time -- is its start-up (3 us), the fetch's issue (0.7 us), the bank
+// conflicts at row ends and the epilogue, which nothing overlaps within a wave.)
 
 // Microseconds of this kernel and of the other one, fitted to 2400 layers of 64 to 512 output channels (each row 2 to 5 % rms).  Here:
 // rounds of 256 workgroups, times the column tiles of a wave and the KB of a tile's rows, and the MB that move; there: rounds of
