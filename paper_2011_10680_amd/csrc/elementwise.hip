@@ -434,7 +434,9 @@ hawq_status launch_pool_sum(int N, int H, int W, int C, int R, int S, int sh, in
         (((uintptr_t)x | (uintptr_t)y) & 15) == 0) {
         // patches of 4x4 outputs once they give every compute unit a workgroup (128 x 35 x 35 x 288 INT32: 4x4 73.8 us, 4x8 76.8,
         // 8x4 77.4, 8x8 78.2; one row of eight 117.6), smaller ones below (17 x 17 x 64 at batch 4: 7 workgroups of 4x4 patches
-        // 7.4 us, 73 of single outputs 4.1)
+        // 7.4 us, 73 of single outputs 4.1).  INT32 maps of many channels, whose rows the smaller patches read more often from
+        // beyond the L2s, from fewer workgroups on (35 x 35 x 768 at batch 4, 243 workgroups of 4x4: 10.0 us, 2x2 11.7; 28 x 28 x 1024,
+        // 196: 9.6 and 11.2; at 183 9.5 and 8.8)
         auto blocks_of = [&](int t) { return ((int64_t)N * ((H + t - 1) / t) * ((W + t - 1) / t) * (C / 4) + 255) / 256; };
         if (N == 0) return HAWQ_OK;
         if (blocks_of(1) > 0x7fffffff) return HAWQ_ERR_UNSUPPORTED;
@@ -445,7 +447,8 @@ hawq_status launch_pool_sum(int N, int H, int W, int C, int R, int S, int sh, in
             if (x_dt == HAWQ_S32) pool_sum3x3_kernel<true, PT, PT><<<blocks, 256, 0, s>>>(units, H, W, C, y_dt, x, b, c, lo, hi, y);
             else pool_sum3x3_kernel<false, PT, PT><<<blocks, 256, 0, s>>>(units, H, W, C, y_dt, x, b, c, lo, hi, y);
         };
-        if (blocks_of(4) >= 256) go(std::integral_constant<int, 4>{});
+        const int64_t large = x_dt != HAWQ_S32 || C < 512 ? 256 : C < 768 ? 240 : 192;
+        if (blocks_of(4) >= large) go(std::integral_constant<int, 4>{});
         else if (blocks_of(2) >= 256) go(std::integral_constant<int, 2>{});
         else go(std::integral_constant<int, 1>{});
         return check_launch();

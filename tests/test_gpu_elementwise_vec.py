@@ -75,3 +75,8 @@ def test_pool3x3_patch_sizes(hawq, N, H, W, C):
     torch.cuda.synchronize()
     want = oracle.pool2d_sum_int(x, None, None, N=N, H=H, W=W, C=C, R=3, S=3, stride=1, pad=1, x_dt=oracle.S32, y_dt=oracle.S32)
     assert_same(y.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("N,H,W,C", [(4, 35, 34, 768), (3, 29, 28, 1024), (4, 37, 38, 640)])
+def test_pool3x3_patch_sizes_many_channels(hawq, N, H, W, C):
+    test_pool3x3_patch_sizes(hawq, N, H, W, C)
