@@ -80,3 +80,10 @@ def test_pool3x3_patch_sizes(hawq, N, H, W, C):
 @pytest.mark.parametrize("N,H,W,C", [(4, 35, 34, 768), (3, 29, 28, 1024), (4, 37, 38, 640)])
 def test_pool3x3_patch_sizes_many_channels(hawq, N, H, W, C):
     test_pool3x3_patch_sizes(hawq, N, H, W, C)
+
+
+@pytest.mark.parametrize("P", [4095, 4097])
+@pytest.mark.parametrize("y_dt", [oracle.U8, oracle.U4])
+def test_one_branch_on_both_sides_of_its_line(hawq, P, y_dt):
+    """2^19 groups of four channels: one group per thread below, the walking form from there on."""
+    test_concat_in_one_launch(hawq, P, [(512, oracle.S32)], y_dt)
