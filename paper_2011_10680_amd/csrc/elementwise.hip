@@ -35,11 +35,13 @@ residual_add_kernel(const int64_t units, const int K, const int per, const int m
 // Vector form: K % 4 == 0, 8-bit or INT32 operands and output.  A thread keeps one group of four channels (the grid's thread
 // count is a multiple of K / 4), so its parameters sit in registers, and has four pixels' loads in flight.  Bound: HBM
 // (m, r and y once); 32 x 56 x 56 x 256 INT32 + u8 -> u8 (154 MB): 103 us in the element-wise form above, whose sixteen
-// parameter loads per thread outnumbered its two data loads, 36 us (4.3 TB/s) here.
-template <int DT>
+// parameter loads per thread outnumbered its two data loads, 37 us (4.2 TB/s) in the exact 64-bit form below, 25.5 us (6.0 TB/s)
+// in the streaming form after it.
+template <int DT, bool NT = false>
 __device__ __forceinline__ v4i load4(const void *p, int64_t unit) {   // elements 4 unit .. 4 unit + 3
     if constexpr (DT == HAWQ_S32) {
-        return ((const v4i *)p)[unit];
+        if constexpr (NT) return __builtin_nontemporal_load((const v4i *)p + unit);
+        else return ((const v4i *)p)[unit];
     } else {
         const uint32_t w = ((const uint32_t *)p)[unit];
         if constexpr (DT == HAWQ_U8) return (v4i){(int)(w & 0xff), (int)((w >> 8) & 0xff), (int)((w >> 16) & 0xff), (int)(w >> 24)};
@@ -78,16 +80,111 @@ residual_add_vec_kernel(const uint32_t units, const uint32_t groups, const void 
     }
 }
 
+// rq(t, b, c) of four channels whose parameters a thread keeps.  Narrow evaluation, exact like the 64-bit one, where the
+// parameters allow it: INT32 operands (c <= 32, b < 2^(c-1)): high word of t * (b << (32 - c)) + 2^31, one instruction;
+// 8-bit operands (c <= 31, b < 2^22): (t * b + 2^(c-1)) >> c in 32 bits, two.  Results then stay below 2^30, so two of them
+// add up in 32 bits.  (The 64-bit form's shifts and comparisons, some 28 instructions per output of a residual addition, were
+// 23 us of vector arithmetic next to 30 us of memory traffic in the case above; the narrow form's are 5.)
+template <int DT>
+struct Rescale4 {
+    v4i b, k, rnd;     // k: b << (32 - c) (INT32) or c (8 bits)
+    uint32_t c;
+    __device__ __forceinline__ bool init(const v4i &b_, uint32_t c_) {
+        b = b_; c = c_;
+        bool ok = true;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t cj = (c >> (8 * j)) & 0xff;
+            if constexpr (DT == HAWQ_S32) {
+                ok &= cj <= 32 && ((uint32_t)b[j] >> ((cj - 1) & 31)) == 0;
+                k[j] = (int32_t)((uint32_t)b[j] << ((32 - cj) & 31));
+            } else {
+                ok &= cj <= 31 && b[j] < (1 << 22);
+                k[j] = (int32_t)(cj & 31);
+                rnd[j] = (int32_t)(1u << ((cj - 1) & 31));
+            }
+        }
+        return ok;
+    }
+    __device__ __forceinline__ int32_t narrow(int32_t t, int j, int64_t half) const {
+        if constexpr (DT == HAWQ_S32) return (int32_t)(((int64_t)t * (int64_t)k[j] + half) >> 32);
+        else return (__mul24(t, b[j]) + rnd[j]) >> k[j];
+    }
+    __device__ __forceinline__ int64_t wide(int32_t t, int j) const { return rq64(t, b[j], (c >> (8 * j)) & 0xff); }
+};
+__device__ __forceinline__ int32_t med3(int32_t v, int32_t lo, int32_t hi) {   // lo <= hi is validated by the interface
+    int32_t t;
+    asm("v_med3_i32 %0, %1, %2, %3" : "=v"(t) : "v"(v), "v"(lo), "v"(hi));
+    return t;
+}
+__device__ __forceinline__ uint32_t pack4(const v4i &o) {   // low bytes of four values
+    return __builtin_amdgcn_perm((uint32_t)o[1], (uint32_t)o[0], 0x0c0c0400u) | __builtin_amdgcn_perm((uint32_t)o[3], (uint32_t)o[2], 0x04000c0cu);
+}
+
+// The form for tensors that many rounds of the grid stream through: narrow evaluation, non-temporal loads and stores (nothing here
+// is read twice), three workgroups a compute unit.
+template <int MD, int RD, bool Y32>
+__global__ void __launch_bounds__(256)
+residual_add_stream_kernel(const uint32_t units, const uint32_t groups, const void *m, const int32_t *__restrict__ m_b,
+                        const uint8_t *__restrict__ m_c, const void *r, const int32_t *__restrict__ r_b,
+                        const uint8_t *__restrict__ r_c, const int lo, const int hi, void *y) {
+    constexpr int U = 4;
+    const uint32_t T = gridDim.x * 256;
+    uint32_t u = blockIdx.x * 256 + threadIdx.x;
+    const uint32_t g = u % groups;
+    const v4i mb = ((const v4i *)m_b)[g], rb = ((const v4i *)r_b)[g];
+    const uint32_t mc = ((const uint32_t *)m_c)[g], rc = ((const uint32_t *)r_c)[g];
+    v4i a[U], b[U];
+    auto fetch = [&]() -> bool {       // four pixels' operands (units + U T stays far below 2^32: the interface takes fewer than 2^31 elements)
+        const bool four = u + (U - 1) * T < units;
+        if (four)
+#pragma unroll
+            for (int i = 0; i < U; ++i) { a[i] = load4<MD, true>(m, u + i * T); b[i] = load4<RD, true>(r, u + i * T); }
+        return four;
+    };
+    bool four = fetch();               // (in flight while the parameters arrive and their form is decided)
+    Rescale4<MD> pm;
+    Rescale4<RD> pr;
+    const bool ok_m = pm.init(mb, mc), narrow = pr.init(rb, rc) & ok_m;
+    int32_t vlo = lo, vhi = hi;
+    int64_t half = (int64_t)1 << 31;
+    asm volatile("" : "+v"(vlo), "+v"(vhi), "+v"(half));   // (an addend that the compiler knows makes it split the multiply-add)
+    auto walk = [&](auto nc) {
+        auto finish = [&](const v4i &a, const v4i &b, uint32_t at) {
+            v4i o;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if constexpr (decltype(nc)::value) o[j] = med3(pm.narrow(a[j], j, half) + pr.narrow(b[j], j, half), vlo, vhi);
+                else o[j] = clamp64(pm.wide(a[j], j) + pr.wide(b[j], j), lo, hi);
+            }
+            if (Y32) __builtin_nontemporal_store(o, (v4i *)y + at);
+            else __builtin_nontemporal_store(pack4(o), (uint32_t *)y + at);
+        };
+        while (four) {
+#pragma unroll
+            for (int i = 0; i < U; ++i) finish(a[i], b[i], u + i * T);
+            u += U * T;
+            four = fetch();
+        }
+        for (; u < units; u += T) {
+            const v4i a1 = load4<MD, true>(m, u), b1 = load4<RD, true>(r, u);
+            finish(a1, b1, u);
+        }
+    };
+    if (__all(narrow)) walk(std::true_type{});
+    else walk(std::false_type{});
+}
+
 // Workgroups of 256 threads such that their threads are a multiple of `groups` (every thread keeps its channel group): a
-// multiple of groups / gcd(groups, 256), one unit per thread up to 1024 workgroups (four to a compute unit), about four per
-// thread beyond, at most 4096 workgroups.  0: no such grid.
-static uint32_t grouped_blocks(int64_t units, uint32_t groups) {
+// multiple of groups / gcd(groups, 256), one unit per thread up to `large` workgroups (four to a compute unit), which then walk:
+// a grid of more, one to each four units up to 4096, has its last round half empty (32 x 35 x 35 x 288 INT32 to 4 bits 11.1 us,
+// with 1024 workgroups 10.2; four branches of 512 channels in all to 8 bits 19.9 and 18.7).  At most 4096.  0: no such grid.
+static uint32_t grouped_blocks(int64_t units, uint32_t groups, int64_t large = 1024) {
     uint32_t a = groups, b = 256;
     while (b) { const uint32_t t = a % b; a = b; b = t; }
     const int64_t step = groups / a, one = (units + 255) / 256;
     if (step > 4096) return 0;
-    int64_t want = one <= 1024 ? one : (one / 4 > 1024 ? one / 4 : 1024);
-    if (want > 4096) want = 4096;
+    const int64_t want = one <= large ? one : large;
     const int64_t n = (want + step - 1) / step * step;
     return (uint32_t)(n > 4096 ? n - step : n);
 }
@@ -99,12 +196,17 @@ hawq_status launch_residual_add(int64_t n_pixels, int K, int m_dt, int r_dt, int
     const uintptr_t al = (uintptr_t)m | (uintptr_t)r | (uintptr_t)y | (uintptr_t)m_b | (uintptr_t)r_b;
     if (!any4 && K % 4 == 0 && ((al & 15) | (((uintptr_t)m_c | (uintptr_t)r_c) & 3)) == 0 && n_pixels > 0) {
         const int64_t vu = n_pixels * (K / 4);
-        const uint32_t nb = grouped_blocks(vu, K / 4);
+        // The streaming form from the size on at which its few, long-lived workgroups are no slower (operands not in L2, this form
+        // against the other): with an INT32 operand 23 / 27 / 36 / 72 MB 6.5 / 7.3 / 7.8 / 13.5 us (7.0 / 7.6 / 9.0 / 16.2), but
+        // 14 / 19 MB 5.3 / 5.6 (4.7 / 5.5); 8 bits both 4.8 / 9.6 / 19 MB 3.19 / 4.3 / 5.8 (3.26 / 4.75 / 7.1), 1.2 MB 2.70 (2.57).
+        const bool stream = vu >= (m_dt == HAWQ_S32 || r_dt == HAWQ_S32 ? 900000 : 400000);
+        const uint32_t nb = grouped_blocks(vu, K / 4, stream ? 768 : 1024);
         if (nb != 0) {
             auto go = [&](auto md, auto rd) {
                 constexpr int MD = decltype(md)::value, RD = decltype(rd)::value;
-                if (y_dt == HAWQ_S32) residual_add_vec_kernel<MD, RD, true><<<nb, 256, 0, s>>>((uint32_t)vu, K / 4, m, m_b, m_c, r, r_b, r_c, lo, hi, y);
-                else residual_add_vec_kernel<MD, RD, false><<<nb, 256, 0, s>>>((uint32_t)vu, K / 4, m, m_b, m_c, r, r_b, r_c, lo, hi, y);
+                auto run = [&](auto kernel) { kernel<<<nb, 256, 0, s>>>((uint32_t)vu, K / 4, m, m_b, m_c, r, r_b, r_c, lo, hi, y); };
+                if (stream) y_dt == HAWQ_S32 ? run(residual_add_stream_kernel<MD, RD, true>) : run(residual_add_stream_kernel<MD, RD, false>);
+                else y_dt == HAWQ_S32 ? run(residual_add_vec_kernel<MD, RD, true>) : run(residual_add_vec_kernel<MD, RD, false>);
             };
             auto on_r = [&](auto md) {
                 if (r_dt == HAWQ_S32) go(md, std::integral_constant<int, HAWQ_S32>{});
@@ -525,27 +627,55 @@ concat_vec_kernel(const ConcatArgs a, const int n, const uint32_t units, const u
     for (int j = 1; j < kConcatMax; ++j)
         if (i == j) { q = a.q[j]; bp = a.b[j]; cp = a.c[j]; dt = a.dt[j]; end = a.end[j]; }
     const uint32_t w = end - begin, k = g - begin;
+    auto load = [&](uint32_t at) { return dt == HAWQ_S32 ? load4<HAWQ_S32>(q, at) : dt == HAWQ_U8 ? load4<HAWQ_U8>(q, at) : load4<HAWQ_S8>(q, at); };
     const v4i b = ((const v4i *)bp)[k];
     const uint32_t c = ((const uint32_t *)cp)[k];
-    auto load = [&](uint32_t at) { return dt == HAWQ_S32 ? load4<HAWQ_S32>(q, at) : dt == HAWQ_U8 ? load4<HAWQ_U8>(q, at) : load4<HAWQ_S8>(q, at); };
-    auto finish = [&](const v4i &v, uint32_t at) {
-        v4i o;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) o[j] = clamp64(rq64(v[j], b[j], (c >> (8 * j)) & 0xff), lo, hi);
-        if constexpr (YB == 32) ((v4i *)y)[at] = o;
-        else if constexpr (YB == 8) ((uint32_t *)y)[at] = (o[0] & 0xff) | ((o[1] & 0xff) << 8) | ((o[2] & 0xff) << 16) | ((uint32_t)o[3] << 24);
-        else ((uint16_t *)y)[at] = (uint16_t)((o[0] & 0xf) | ((o[1] & 0xf) << 4) | ((o[2] & 0xf) << 8) | ((o[3] & 0xf) << 12));
-    };
     uint32_t e = px0 * w + k;
     const uint32_t de = dpx * w;
-    for (; u + (U - 1) * T < units; u += U * T, e += U * de) {
-        v4i v[U];
+    v4i v[U];
+    auto fetch = [&]() -> bool {       // four pixels' values, or the one that is left
+        const bool four = u + (U - 1) * T < units;
+        if (u < units) v[0] = load(e);
+        if (four)
 #pragma unroll
-        for (int j = 0; j < U; ++j) v[j] = load(e + j * de);
+            for (int j = 1; j < U; ++j) v[j] = load(e + j * de);
+        return four;
+    };
+    bool four = fetch();               // (in flight while the parameters arrive and their form is decided)
+    // narrow evaluation in its INT32 form for either operand width (see Rescale4)
+    Rescale4<HAWQ_S32> pq;
+    const bool narrow = pq.init(b, c);
+    int32_t vlo = lo, vhi = hi;
+    int64_t half = (int64_t)1 << 31;
+    asm volatile("" : "+v"(vlo), "+v"(vhi), "+v"(half));
+    auto walk = [&](auto nc) {
+        auto finish = [&](const v4i &v, uint32_t at) {
+            v4i o;
 #pragma unroll
-        for (int j = 0; j < U; ++j) finish(v[j], u + j * T);
-    }
-    for (; u < units; u += T, e += de) finish(load(e), u);
+            for (int j = 0; j < 4; ++j) {
+                if constexpr (decltype(nc)::value) o[j] = med3(pq.narrow(v[j], j, half), vlo, vhi);
+                else o[j] = clamp64(pq.wide(v[j], j), lo, hi);
+            }
+            if constexpr (YB == 32) ((v4i *)y)[at] = o;
+            else if constexpr (YB == 8) ((uint32_t *)y)[at] = pack4(o);
+            else ((uint16_t *)y)[at] = (uint16_t)((o[0] & 0xf) | ((o[1] & 0xf) << 4) | ((o[2] & 0xf) << 8) | ((o[3] & 0xf) << 12));
+        };
+        while (four) {
+#pragma unroll
+            for (int j = 0; j < U; ++j) finish(v[j], u + j * T);
+            u += U * T;
+            e += U * de;
+            four = fetch();
+        }
+        while (u < units) {
+            finish(v[0], u);
+            u += T;
+            e += de;
+            if (u < units) v[0] = load(e);
+        }
+    };
+    if (__all(narrow)) walk(std::true_type{});
+    else walk(std::false_type{});
 }
 
 bool launch_concat_all(int64_t n_pixels, int n, const hawq_concat_branch *br, int Kt, int y_dt, int lo, int hi, void *y, hipStream_t s,

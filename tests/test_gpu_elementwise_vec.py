@@ -40,6 +40,52 @@ def test_residual_add_vector_form(hawq, P, K, m_dt, r_dt, y_dt):
     assert_same(y.cpu().numpy(), want.reshape(P, K))
 
 
+# both sides of the streaming form's line (400000 or, with an INT32 operand, 900000 groups of four), a channel group count that does
+# not divide the grid, in narrow parameters, with one channel outside the INT32 form's range (c > 32) and outside the 8-bit form's (b >= 2^22)
+@pytest.mark.parametrize("P,K,m_dt,r_dt,y_dt", [(56249, 64, oracle.S32, oracle.U8, oracle.U8), (56251, 64, oracle.S32, oracle.U8, oracle.U8),
+                                                (11689, 4 * 77, oracle.S32, oracle.S32, oracle.S32), (3127, 512, oracle.U8, oracle.S8, oracle.S8),
+                                                (5201, 4 * 77, oracle.S8, oracle.U8, oracle.U8)])
+@pytest.mark.parametrize("wide", [None, "c", "b"])
+def test_residual_add_streaming_form(hawq, P, K, m_dt, r_dt, y_dt, wide):
+    import torch
+    from gpu_util import to_dev, assert_same
+    g = np.random.default_rng(P + K)
+    m, r = _draw(g, (P, K), m_dt), _draw(g, (P, K), r_dt)
+    dn = lambda dt: (g.integers(1 << 14, 1 << 15, size=K).astype(np.int32), (g.integers(0, 2, size=K) + (27 if dt == oracle.S32 else 15)).astype(np.uint8))
+    (mb, mc), (rb, rc) = dn(m_dt), dn(r_dt)
+    if wide == "c":
+        mb[K // 2], mc[K // 2] = (1 << 31) - 1, 43
+    if wide == "b":
+        rb[5], rc[5] = 3 << 22, 24
+    lo, hi = {oracle.U8: (0, 127), oracle.S8: (-128, 127), oracle.S32: (-1000, 1000)}[y_dt]
+    y = torch.full((P, K), 0x5A, dtype={oracle.U8: torch.uint8, oracle.S8: torch.int8, oracle.S32: torch.int32}[y_dt], device="cuda")
+    hawq.hawq_residual_add_dyadic(P, K, m_dt, r_dt, y_dt, to_dev(m), to_dev(mb), to_dev(mc), to_dev(r), to_dev(rb), to_dev(rc), 0, lo, hi, y)
+    torch.cuda.synchronize()
+    want = oracle.residual_add_dyadic(m, mb, mc, r, rb, rc, n_pixels=P, K=K, m_dt=m_dt, r_dt=r_dt, y_dt=y_dt, relu=0, y_lo=lo, y_hi=hi)
+    assert_same(y.cpu().numpy(), want.reshape(P, K))
+
+
+# narrow parameters, and one channel with c > 32; fewer units than threads, several rounds of four and a remainder
+@pytest.mark.parametrize("P", [3, 30011])
+def test_concat_wide_parameters(hawq, P):
+    import torch
+    from gpu_util import to_dev, assert_same
+    g = np.random.default_rng(P)
+    host, dev = [], []
+    for K, dt in ((64, oracle.S32), (12, oracle.U8)):
+        q = _draw(g, (P, K), dt)
+        b = g.integers(1 << 14, 1 << 15, size=K).astype(np.int32)
+        c = np.full(K, 27 if dt == oracle.S32 else 15, dtype=np.uint8)
+        b[7], c[7] = (1 << 30) + 12345, 44 if dt == oracle.S32 else 31
+        host.append((q, dt, b, c))
+        dev.append((to_dev(q), dt, to_dev(b), to_dev(c)))
+    y = torch.full((P, 76), 0x5A, dtype=torch.uint8, device="cuda")
+    hawq.hawq_concat_dyadic(P, dev, oracle.U8, 0, 127, y)
+    torch.cuda.synchronize()
+    want = oracle.concat_dyadic(host, n_pixels=P, y_dt=oracle.U8, y_lo=0, y_hi=127)
+    assert_same(y.cpu().numpy(), np.asarray(want).reshape(tuple(y.shape)))
+
+
 @pytest.mark.parametrize("P,spec,y_dt", [(1, [(4, oracle.S32)], oracle.U8), (777, [(64, oracle.S32), (12, oracle.U8), (4, oracle.S8)], oracle.U8),
                                          (9000, [(64, oracle.S32), (64, oracle.S32), (96, oracle.S32), (288, oracle.S32)], oracle.U8),
                                          (50, [(4, oracle.S32)] * 8, oracle.S32), (50, [(8, oracle.U8)] * 9, oracle.U8),
