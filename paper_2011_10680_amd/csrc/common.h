@@ -6,6 +6,7 @@
 #include <type_traits>
 
 #include "../../include/hawq.h"
+#include "xcd_walk.h"
 
 namespace hawq {
 

@@ -45,6 +45,8 @@ conv3x3_c64_kernel(const ConvArgs a, const int n_tiles) {
     const int W = a.W, HW = a.H * a.W;
     const int n_in = a.N * HW;                  // input pixels = output pixels
     const int prows = BP + 2 * W + 2;           // rows in use (<= PROWS - 1, checked by the host)
+    const TileWalk walk = xcd_walk(blockIdx.x, gridDim.x, n_tiles);
+    if (walk.first >= walk.end) return;         // (the whole workgroup, before any barrier: its XCD's eighth has fewer tiles than workgroups)
 
     const __amdgpu_buffer_rsrc_t rsrc_w = __builtin_amdgcn_make_buffer_rsrc((void *)a.w, 0, 64 * 9 * ROWB, 0x00020000);
     const __amdgpu_buffer_rsrc_t rsrc_x = __builtin_amdgcn_make_buffer_rsrc((void *)a.x, 0, n_in * ROWB, 0x00020000);
@@ -99,7 +101,7 @@ conv3x3_c64_kernel(const ConvArgs a, const int n_tiles) {
             const int row = inst * RPI + p_row0;
             const int ch = INT4 ? (lane & 1) : ((lane & 3) ^ ((row >> 2) & 3));
             const int f = f0 + row;
-            const bool ok = tile < n_tiles && row < prows && f >= 0 && f < n_in;   // other rows are filled with zeros
+            const bool ok = tile < walk.end && row < prows && f >= 0 && f < n_in;   // other rows are filled with zeros
             __builtin_amdgcn_raw_ptr_buffer_load_lds(
                 rsrc_x, (__attribute__((address_space(3))) void *)(buf + inst * 1024), 16,
                 ok ? f * ROWB + ch * 16 : (int)kInvalid, 0, 0, 0);
@@ -113,7 +115,7 @@ conv3x3_c64_kernel(const ConvArgs a, const int n_tiles) {
 #pragma unroll
         for (int tc = 0; tc < TC; ++tc) {
             const int64_t e = m * 64 + chl + 16 * tc;
-            const uint32_t ro = (tile < n_tiles && m < a.M) ? (uint32_t)(r4 ? (e >> 1) : e) : kInvalid;
+            const uint32_t ro = (tile < walk.end && m < a.M) ? (uint32_t)(r4 ? (e >> 1) : e) : kInvalid;
             const v4i t = __builtin_amdgcn_raw_buffer_load_b128(rsrc_r, (int)ro, 0, 0);
             rw[0][tc][0] = (uint32_t)t[0]; rw[0][tc][1] = (uint32_t)t[1];
             rw[0][tc][2] = (uint32_t)t[2]; rw[0][tc][3] = (uint32_t)t[3];
@@ -203,18 +205,18 @@ conv3x3_c64_kernel(const ConvArgs a, const int n_tiles) {
         if (wide) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     };
 
-    const int gstride = gridDim.x;
-    int tile = blockIdx.x;                       // < n_tiles by construction of the grid
+    const int gstride = walk.step;
+    int tile = walk.first;
     uint32_t rw0[TP][TC][4] = {}, rw1[TP][TC][4] = {};
     fetch_patch(tile, pa);
     if (has_res) fetch_res(tile, rw0);
     wide = __syncthreads_or(wide);   // parameters staged by all waves; `wide` is workgroup-uniform from here
     do_tile(tile, pa, pb, rw0, rw1, gstride, std::true_type{});
     tile += gstride;
-    while (tile < n_tiles) {
+    while (tile < walk.end) {
         do_tile(tile, pb, pa, rw1, rw0, gstride, std::false_type{});
         tile += gstride;
-        if (tile >= n_tiles) break;
+        if (tile >= walk.end) break;
         do_tile(tile, pa, pb, rw0, rw1, gstride, std::false_type{});
         tile += gstride;
     }
@@ -239,7 +241,7 @@ bool conv3x3_c64_eligible(const ConvArgs &a, int x_hi) {
 hawq_status launch_conv3x3_c64(const ConvArgs &a, hipStream_t s) {
     if (a.M == 0) return HAWQ_OK;
     const int n_tiles = (a.M + 127) / 128;
-    const int grid = n_tiles < 512 ? n_tiles : 512;   // two workgroups per CU
+    const uint32_t grid = xcd_walk_grid(n_tiles, 512);   // two workgroups per CU
     const bool four = is4(a.x_dt);
     if (a.res != nullptr) {
         if (four) conv3x3_c64_kernel<true, true><<<grid, 256, 0, s>>>(a, n_tiles);

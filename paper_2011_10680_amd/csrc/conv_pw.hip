@@ -44,9 +44,10 @@ conv_pw_kernel(const ConvArgs a, const int n_ct, const int n_seq, const int n_gr
 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     // workgroups that share pixels (consecutive channel tiles of one sequence) stay on one XCD and its L2
-    const int g = (int)xcd_remap(blockIdx.x, gridDim.x) * 4 + wave;
+    const int g = (int)(blockIdx.x >> 3) * 4 + wave;
     const int ct = g % n_ct, seq = g / n_ct;
-    if (seq >= n_seq) return;                        // whole wave; the kernel has no workgroup barrier
+    const TileWalk gr = xcd_walk(blockIdx.x & 7 | (uint32_t)seq << 3, (uint32_t)n_seq, n_groups);   // (seq: within the XCD)
+    if (seq >= n_seq >> 3 || gr.first >= gr.end) return;   // whole wave; the kernel has no workgroup barrier
     const int rho = lane & 31, khalf = lane >> 5;
     const int k0 = ct * 32;
     const int Cb = INT4 ? a.C / 2 : a.C;
@@ -116,7 +117,7 @@ conv_pw_kernel(const ConvArgs a, const int n_ct, const int n_seq, const int n_gr
     const bool unit = a.stride_h == 1 && a.stride_w == 1;   // 1x1, no padding: output pixel m reads input pixel m
     const int PQ = a.P * a.Q;
     auto pixel_offset = [&](int grp, int64_t m) -> uint32_t {   // byte offset of output pixel m's input row
-        if (grp >= n_groups || m >= a.M) return kInvalid;
+        if (grp >= gr.end || m >= a.M) return kInvalid;
         if (unit) return (uint32_t)m * (uint32_t)Cb;
         const int mi = (int)m;
         const int n = mi / PQ, pq = mi - n * PQ;
@@ -152,7 +153,7 @@ conv_pw_kernel(const ConvArgs a, const int n_ct, const int n_seq, const int n_gr
             if (RES) {
                 // the lane's 16 channels of pixel m: 16 bytes (8 for 4-bit data)
                 const int64_t m = mbase + rho;
-                const bool ok = grp < n_groups && m < a.M;
+                const bool ok = grp < gr.end && m < a.M;
                 const int64_t e = m * (int64_t)a.K + k0 + khalf * 16;
                 const uint32_t ro = (ok && k0 + khalf * 16 < a.K) ? (uint32_t)(r4 ? (e >> 1) : e) : kInvalid;
                 // one 16-byte load for either width (4-bit data uses the first 8 bytes; bytes past the end of the
@@ -213,7 +214,7 @@ conv_pw_kernel(const ConvArgs a, const int n_ct, const int n_seq, const int n_gr
         }
     };
 
-    // Ring of NS stages: while group i is processed, groups i + n_seq .. i + (NS-1) n_seq are landing
+    // Ring of NS stages: while group i is processed, the next NS - 1 groups of the wave's walk are landing
     // (issue() past the last group presents out-of-range offsets and fetches nothing, but still counts).
     // Operations issued after a stage's own loads when its turn comes: the loads of the NS-1 later stages and
     // the stores of the groups processed since -- none for the first group, up to NS-1 groups' worth later.
@@ -223,43 +224,43 @@ conv_pw_kernel(const ConvArgs a, const int n_ct, const int n_seq, const int n_gr
     using W0 = std::integral_constant<int, (NS - 1) * (D + R)>;
     using W1 = std::integral_constant<int, (NS - 1) * (D + R) + S>;
     using WN = std::integral_constant<int, (NS - 1) * (D + R) + (NS - 1) * S>;
-    int grp = seq;
+    int grp = gr.first;
     if constexpr (NS == 2) {
         issue(grp, xs0, st0);
-        issue(grp + n_seq, xs1, st1);
+        issue(grp + gr.step, xs1, st1);
         process(fastc, grp, xs0, st0, W0{});
-        grp += n_seq;
-        while (grp < n_groups) {
-            issue(grp + n_seq, xs0, st0);
+        grp += gr.step;
+        while (grp < gr.end) {
+            issue(grp + gr.step, xs0, st0);
             process(fastc, grp, xs1, st1, WN{});
-            grp += n_seq;
-            if (grp >= n_groups) break;
-            issue(grp + n_seq, xs1, st1);
+            grp += gr.step;
+            if (grp >= gr.end) break;
+            issue(grp + gr.step, xs1, st1);
             process(fastc, grp, xs0, st0, WN{});
-            grp += n_seq;
+            grp += gr.step;
         }
     } else {
         issue(grp, xs0, st0);
-        issue(grp + n_seq, xs1, st1);
-        issue(grp + 2 * n_seq, xs2, st2);
+        issue(grp + gr.step, xs1, st1);
+        issue(grp + 2 * gr.step, xs2, st2);
         process(fastc, grp, xs0, st0, W0{});
-        grp += n_seq;
-        if (grp >= n_groups) return;
-        issue(grp + 2 * n_seq, xs0, st0);
+        grp += gr.step;
+        if (grp >= gr.end) return;
+        issue(grp + 2 * gr.step, xs0, st0);
         process(fastc, grp, xs1, st1, W1{});
-        grp += n_seq;
-        while (grp < n_groups) {
-            issue(grp + 2 * n_seq, xs1, st1);
+        grp += gr.step;
+        while (grp < gr.end) {
+            issue(grp + 2 * gr.step, xs1, st1);
             process(fastc, grp, xs2, st2, WN{});
-            grp += n_seq;
-            if (grp >= n_groups) break;
-            issue(grp + 2 * n_seq, xs2, st2);
+            grp += gr.step;
+            if (grp >= gr.end) break;
+            issue(grp + 2 * gr.step, xs2, st2);
             process(fastc, grp, xs0, st0, WN{});
-            grp += n_seq;
-            if (grp >= n_groups) break;
-            issue(grp + 2 * n_seq, xs0, st0);
+            grp += gr.step;
+            if (grp >= gr.end) break;
+            issue(grp + 2 * gr.step, xs0, st0);
             process(fastc, grp, xs1, st1, WN{});
-            grp += n_seq;
+            grp += gr.step;
         }
     }
     };
@@ -291,8 +292,9 @@ conv_pws_kernel(const ConvArgs a, const int n_ct, const int n_seq, const int n_g
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // the launch makes n_ct a multiple of 4 and the grid exactly n_seq * n_ct / 4 workgroups: the four waves
     // of a workgroup share `seq` (so every wave reaches every barrier the same number of times)
-    const int g = (int)xcd_remap(blockIdx.x, gridDim.x) * 4 + wave;
+    const int g = (int)(blockIdx.x >> 3) * 4 + wave;
     const int ct = g % n_ct, seq = g / n_ct;
+    const TileWalk gr = xcd_walk(blockIdx.x & 7 | (uint32_t)seq << 3, (uint32_t)n_seq, n_groups);   // (seq: within the XCD)
     const int rho = lane & 31, khalf = lane >> 5;
     const int k0 = ct * 32;
     const int Cb = a.C;
@@ -360,7 +362,7 @@ conv_pws_kernel(const ConvArgs a, const int n_ct, const int n_seq, const int n_g
     const bool unit = a.stride_h == 1 && a.stride_w == 1;
     const int PQ = a.P * a.Q;
     auto pixel_offset = [&](int grp, int64_t m) -> uint32_t {
-        if (grp >= n_groups || m >= a.M) return kInvalid;
+        if (grp >= gr.end || m >= a.M) return kInvalid;
         if (unit) return (uint32_t)m * (uint32_t)Cb;
         const int mi = (int)m;
         const int n = mi / PQ, pq = mi - n * PQ;
@@ -387,7 +389,7 @@ conv_pws_kernel(const ConvArgs a, const int n_ct, const int n_seq, const int n_g
         }
         if (RES) {
             const int64_t m = mbase + rho;
-            const bool ok = grp < n_groups && m < a.M;
+            const bool ok = grp < gr.end && m < a.M;
             const int64_t e = m * (int64_t)a.K + k0 + khalf * 16;
             const uint32_t ro = (ok && k0 + khalf * 16 < a.K) ? (uint32_t)(r4 ? (e >> 1) : e) : kInvalid;
             const v4i t = __builtin_amdgcn_raw_buffer_load_b128(rsrc_r, (int)ro, 0, 0);
@@ -435,18 +437,18 @@ conv_pws_kernel(const ConvArgs a, const int n_ct, const int n_seq, const int n_g
     };
     auto walk = [&](auto fastc) {   // once per epilogue form (see conv_pw_kernel)
     Stage st0, st1, st2, st3;
-    int grp = seq, it = 0;
+    int grp = gr.first, it = 0;
     issue(grp, xs0, st0);
-    issue(grp + n_seq, xs1, st1);
-    issue(grp + 2 * n_seq, xs2, st2);
+    issue(grp + gr.step, xs1, st1);
+    issue(grp + 2 * gr.step, xs2, st2);
 #define HAWQ_PWS_STEP(curx, curs, nxtx, nxts)        \
     arrive(it);                                      \
-    issue(grp + 3 * n_seq, nxtx, nxts);              \
+    issue(grp + 3 * gr.step, nxtx, nxts);            \
     compute(fastc, grp, curx, curs);                 \
-    grp += n_seq;                                    \
+    grp += gr.step;                                  \
     ++it;                                            \
-    if (grp >= n_groups) break;
-    while (grp < n_groups) {
+    if (grp >= gr.end) break;
+    while (grp < gr.end) {
         HAWQ_PWS_STEP(xs0, st0, xs3, st3)
         HAWQ_PWS_STEP(xs1, st1, xs0, st0)
         HAWQ_PWS_STEP(xs2, st2, xs1, st1)
@@ -482,8 +484,9 @@ conv_pws_dual_kernel(const ConvArgs a, const int n_ct, const int n_seq, const in
     __shared__ __attribute__((aligned(1024))) uint8_t xs3[STAGE];
 
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int g = (int)xcd_remap(blockIdx.x, gridDim.x) * 4 + wave;
+    const int g = (int)(blockIdx.x >> 3) * 4 + wave;
     const int ct = g % n_ct, seq = g / n_ct;        // the four waves of a workgroup share `seq` (n_ct is a multiple of 4)
+    const TileWalk gr = xcd_walk(blockIdx.x & 7 | (uint32_t)seq << 3, (uint32_t)n_seq, n_groups);   // (seq: within the XCD)
     const int rho = lane & 31, khalf = lane >> 5;
     const int k0 = ct * 32;
 
@@ -537,9 +540,9 @@ conv_pws_dual_kernel(const ConvArgs a, const int n_ct, const int n_seq, const in
     const int d_row = lane >> 2;
     const int d_chunk = (lane & 3) ^ ((d_row >> 2) & 3);
     // Where a lane's shortcut fetch reads (image, row, column of its output pixel) is found by division once, for the wave's
-    // first group; successive calls of issue() are one sequence stride (32 n_seq pixels) apart, so the byte offset then
+    // first group; successive calls of issue() are one step (32 gr.step pixels) apart, so the byte offset then
     // advances by wave-uniform increments with two carries -- no division in the loop.
-    const int step_px = 32 * n_seq;
+    const int step_px = 32 * gr.step;
     const int dn = step_px / PQ, drem = step_px - dn * PQ, dp = drem / a.Q, dq = drem - dp * a.Q;
     const uint32_t row_b = (uint32_t)(a.stride_sh * a.Ws * a.Cs), col_b = (uint32_t)(a.stride_sw * a.Cs);
     const uint32_t inc_q = (uint32_t)dq * col_b, inc_p = (uint32_t)dp * row_b;
@@ -552,7 +555,7 @@ conv_pws_dual_kernel(const ConvArgs a, const int n_ct, const int n_seq, const in
     for (int j = 0; j < DW; ++j) {
         const int inst = wave + 4 * j;
         const int kc = inst >> 1, h = inst & 1;
-        const int mi = seq * 32 + h * 16 + d_row;
+        const int mi = gr.first * 32 + h * 16 + d_row;
         const int n = mi / PQ, pq = mi - n * PQ;
         s_p[j] = pq / a.Q;
         s_q[j] = pq - s_p[j] * a.Q;
@@ -561,7 +564,7 @@ conv_pws_dual_kernel(const ConvArgs a, const int n_ct, const int n_seq, const in
     }
     const __amdgpu_buffer_rsrc_t rsrc_xm = __builtin_amdgcn_make_buffer_rsrc((void *)a.x, 0, (int)((int64_t)a.N * a.H * a.W * a.C), 0x00020000);
     const __amdgpu_buffer_rsrc_t rsrc_xs = __builtin_amdgcn_make_buffer_rsrc((void *)a.xs, 0, (int)((int64_t)a.N * a.Hs * a.Ws * a.Cs), 0x00020000);
-    // (calls must come in the order of the walk below: grp = seq, seq + n_seq, seq + 2 n_seq, ...)
+    // (calls must come in the order of the walk below: gr.first, gr.first + gr.step, ...)
     auto issue = [&](int grp, uint8_t *xs) {
         const int64_t mbase = (int64_t)grp * 32;
 #pragma unroll
@@ -570,7 +573,7 @@ conv_pws_dual_kernel(const ConvArgs a, const int n_ct, const int n_seq, const in
             const int kc = inst >> 1, h = inst & 1;
             const bool main_branch = kc < KC1;      // wave-uniform
             const int64_t m = mbase + h * 16 + d_row;
-            const bool ok = grp < n_groups && m < a.M;
+            const bool ok = grp < gr.end && m < a.M;
             auto *dst = (__attribute__((address_space(3))) void *)(xs + inst * 1024);
             if (main_branch) {                      // a scalar branch: each side names its own descriptor
                 const uint32_t off = ok ? (uint32_t)m * (uint32_t)a.C + kc * 64 + d_chunk * 16 : kInvalid;
@@ -619,18 +622,18 @@ conv_pws_dual_kernel(const ConvArgs a, const int n_ct, const int n_seq, const in
         else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(L + 3 * S) : "memory");
         __builtin_amdgcn_s_barrier();
     };
-    int grp = seq, it = 0;
+    int grp = gr.first, it = 0;
     issue(grp, xs0);
-    issue(grp + n_seq, xs1);
-    issue(grp + 2 * n_seq, xs2);
+    issue(grp + gr.step, xs1);
+    issue(grp + 2 * gr.step, xs2);
 #define HAWQ_PWSD_STEP(curx, nxtx)                   \
     arrive(it);                                      \
-    issue(grp + 3 * n_seq, nxtx);                    \
+    issue(grp + 3 * gr.step, nxtx);                  \
     compute(grp, curx);                              \
-    grp += n_seq;                                    \
+    grp += gr.step;                                  \
     ++it;                                            \
-    if (grp >= n_groups) break;
-    while (grp < n_groups) {
+    if (grp >= gr.end) break;
+    while (grp < gr.end) {
         HAWQ_PWSD_STEP(xs0, xs3)
         HAWQ_PWSD_STEP(xs1, xs0)
         HAWQ_PWSD_STEP(xs2, xs1)
@@ -660,10 +663,10 @@ static hawq_status launch_pw_res(const ConvArgs &a, hipStream_t s) {
     // fill every SIMD of the 256 CUs with as many waves as the register budget allows, each walking over
     // several pixel groups
     int n_seq = (WPE * 4 * 256) / n_ct;   // (rounded down: one workgroup past the last slot would be a round of its own)
-    if (n_seq < 1) n_seq = 1;
-    if (n_seq > n_groups) n_seq = n_groups;
-    const int waves = n_seq * n_ct;
-    const uint32_t blocks = (uint32_t)((waves + 3) / 4);
+    n_seq = n_seq < 8 ? 8 : n_seq / 8 * 8;
+    if (n_seq > (n_groups + 7) / 8 * 8) n_seq = (n_groups + 7) / 8 * 8;
+    const int waves = n_seq / 8 * n_ct;                  // of an XCD
+    const uint32_t blocks = (uint32_t)((waves + 3) / 4) * 8;
     if (is4(a.x_dt)) conv_pw_kernel<KC, TP, NS, WPE, RES, true><<<blocks, 256, 0, s>>>(a, n_ct, n_seq, n_groups);
     else conv_pw_kernel<KC, TP, NS, WPE, RES, false><<<blocks, 256, 0, s>>>(a, n_ct, n_seq, n_groups);
     return check_launch();
@@ -691,8 +694,8 @@ static hawq_status launch_pws(const ConvArgs &a, hipStream_t s) {
     const int n_ct = a.K / 32;                           // a multiple of 4
     const int n_groups = (a.M + 31) / 32;
     int n_seq = (WPE * 4 * 256) / n_ct;
-    if (n_seq < 1) n_seq = 1;
-    if (n_seq > n_groups) n_seq = n_groups;
+    n_seq = n_seq < 8 ? 8 : n_seq / 8 * 8;
+    if (n_seq > (n_groups + 7) / 8 * 8) n_seq = (n_groups + 7) / 8 * 8;
     const uint32_t blocks = (uint32_t)(n_seq * (n_ct / 4));   // exactly: every wave of the grid has work
     if (a.res != nullptr) conv_pws_kernel<KC, WPE, true><<<blocks, 256, 0, s>>>(a, n_ct, n_seq, n_groups);
     else conv_pws_kernel<KC, WPE, false><<<blocks, 256, 0, s>>>(a, n_ct, n_seq, n_groups);
@@ -724,8 +727,8 @@ static hawq_status launch_pws_dual(const ConvArgs &a, hipStream_t s) {
     const int n_ct = a.K / 32;                           // a multiple of 4
     const int n_groups = (a.M + 31) / 32;
     int n_seq = (WPE * 4 * 256) / n_ct;
-    if (n_seq < 1) n_seq = 1;
-    if (n_seq > n_groups) n_seq = n_groups;
+    n_seq = n_seq < 8 ? 8 : n_seq / 8 * 8;
+    if (n_seq > (n_groups + 7) / 8 * 8) n_seq = (n_groups + 7) / 8 * 8;
     const uint32_t blocks = (uint32_t)(n_seq * (n_ct / 4));
     if (a.mid_s8) conv_pws_dual_kernel<KC1, KC2, WPE, true><<<blocks, 256, 0, s>>>(a, n_ct, n_seq, n_groups);
     else conv_pws_dual_kernel<KC1, KC2, WPE, false><<<blocks, 256, 0, s>>>(a, n_ct, n_seq, n_groups);

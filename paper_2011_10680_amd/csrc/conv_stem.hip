@@ -189,6 +189,7 @@ conv_stem_pool_kernel(const ConvArgs a, const int pool_P, const int pool_Q, cons
     // and tid + 256 of the FUSE_ROWS * FUSE_GROUPS groups.
     constexpr int NITEM = (FUSE_ROWS * FUSE_GROUPS + 255) / 256;
     uint32_t raw[NITEM][3];
+    const TileWalk walk = xcd_walk(blockIdx.x, gridDim.x, n_tiles);
     auto fetch = [&](int tile) {
         int t = tile;
         const int tq = t % tiles_q; t /= tiles_q;
@@ -202,7 +203,7 @@ conv_stem_pool_kernel(const ConvArgs a, const int pool_P, const int pool_Q, cons
             const int ih = 4 * tp_ * FUSE_PT - 5 + rl;
             const int iw = 4 * tq * FUSE_PT - 8 + 4 * g;
             raw[it][0] = raw[it][1] = raw[it][2] = 0;
-            if (tile < n_tiles && i < FUSE_ROWS * FUSE_GROUPS && (unsigned)ih < (unsigned)a.H && iw >= 0 && iw + 3 < a.W) {
+            if (tile < walk.end && i < FUSE_ROWS * FUSE_GROUPS && (unsigned)ih < (unsigned)a.H && iw >= 0 && iw + 3 < a.W) {
                 const uint32_t *src = (const uint32_t *)(img + ((int64_t)ih * a.W + iw) * 3);
                 raw[it][0] = src[0]; raw[it][1] = src[1]; raw[it][2] = src[2];
             }
@@ -236,16 +237,16 @@ conv_stem_pool_kernel(const ConvArgs a, const int pool_P, const int pool_Q, cons
     int32_t lo_c = a.lo, hi_c = a.hi, lo_p = pool_lo, hi_p = pool_hi;
     asm volatile("" : "+v"(lo_c), "+v"(hi_c), "+v"(lo_p), "+v"(hi_p));
 
-    int tile = blockIdx.x;            // < n_tiles by construction of the grid
+    int tile = walk.first;
     fetch(tile);
-    for (; tile < n_tiles; tile += gridDim.x) {
+    for (; tile < walk.end; tile += walk.step) {
         int t = tile;
         const int tq = t % tiles_q; t /= tiles_q;
         const int tp_ = t % tiles_p;
         const int n = t / tiles_p;
         const int pp0 = tp_ * FUSE_PT, pq0 = tq * FUSE_PT;       // pooled tile origin
         stage();
-        fetch(tile + gridDim.x);
+        fetch(tile + walk.step);
         __syncthreads();              // patch complete; the previous tile's output reads are done
 
         // ---- wave w: MFMA tiles 4w .. 4w + 3, one after the other; tile wt = pooled row wt / 2 of the pooled tile, column
@@ -344,11 +345,11 @@ hawq_status launch_conv_stem_pool(const ConvArgs &a, int pool_y_dt, int pool_lo,
     const int tiles_p = (pool_P + FUSE_PT - 1) / FUSE_PT, tiles_q = (pool_Q + FUSE_PT - 1) / FUSE_PT;
     const int64_t n_tiles = (int64_t)a.N * tiles_p * tiles_q;
     if (n_tiles > 0x7fffffff) return HAWQ_ERR_UNSUPPORTED;
-    const int64_t grid = n_tiles < 3 * 256 ? n_tiles : 3 * 256;    // persistent: three workgroups per CU
+    const uint32_t grid = xcd_walk_grid(n_tiles, 3 * 256);         // persistent: three workgroups per CU
     // the pooled bytes are unsigned: bounds outside 0..255 never bind
     pool_lo = pool_lo < 0 ? 0 : pool_lo;
     pool_hi = pool_hi > 255 ? 255 : pool_hi;
-    conv_stem_pool_kernel<<<(uint32_t)grid, 256, 0, s>>>(a, pool_P, pool_Q, pool_y_dt, pool_lo, pool_hi, (uint8_t *)pool_y,
+    conv_stem_pool_kernel<<<grid, 256, 0, s>>>(a, pool_P, pool_Q, pool_y_dt, pool_lo, pool_hi, (uint8_t *)pool_y,
                                                           tiles_q, tiles_p, (int)n_tiles);
     return check_launch();
 }

@@ -273,7 +273,9 @@ __global__ void __launch_bounds__(256)
 avgpool_u8_kernel(const int HW, const int C, const uint8_t *__restrict__ x, const int32_t *__restrict__ b,
                   const uint8_t *__restrict__ c, const int lo, const int hi, uint8_t *__restrict__ y) {
     __shared__ int32_t part[16][256 + 8];
-    const int n = blockIdx.y, cbase = blockIdx.x * 256;
+    // (the XCDs take contiguous images, as the kernel that wrote them did)
+    const uint32_t L = xcd_remap(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
+    const int n = (int)(L / gridDim.x), cbase = (int)(L % gridDim.x) * 256;
     const int g = threadIdx.x & 15, sl = threadIdx.x >> 4;
     int32_t sum[16];
 #pragma unroll
