@@ -1,4 +1,5 @@
-"""ctypes binding with the same names as the C entry points.  Argument marshalling only.
+"""Python binding with the same names as the C entry points.  Argument marshalling only: ctypes, and for the per-layer entry
+points on tensors of the usual types the same in C (``_fastcall.so``, csrc/fastcall.cpp).
 
 Tensors are ``torch`` CUDA (HIP) tensors; the binding passes ``data_ptr()`` and the current
 stream handle.  The library is loaded from ``libhawq.so`` next to this file; if it is missing
@@ -141,6 +142,7 @@ def _p(t):
 
 
 _raw_stream = None
+_fast = None      # the native marshalling module once the device and stream queries it uses are known to work; else None
 
 
 def _stream(stream):
@@ -156,51 +158,99 @@ def _stream(stream):
         get_device, get_stream = getattr(torch._C, "_cuda_getDevice", None), getattr(torch._C, "_cuda_getCurrentRawStream", None)
         if get_device is not None and get_stream is not None:
             _raw_stream = lambda: get_stream(get_device())
+            _use_fastcall(torch, get_device, get_stream)
         else:
             _raw_stream = lambda: torch.cuda.current_stream().cuda_stream
         return handle
     return _raw_stream()
 
 
+def _use_fastcall(torch, get_device, get_stream):
+    """Calls go through the native marshalling from now on, where it is built for this interpreter and torch's methods have the
+    form it calls."""
+    global _fast
+    try:
+        from . import _fastcall
+    except ImportError:
+        return
+    lib = load_library()
+    names = ("conv2d_int", "conv2d_dual_int", "gemm_int", "residual_add_dyadic", "avgpool_int", "maxpool_int", "pool2d_sum_int", "concat_dyadic")
+    addresses = tuple(ctypes.cast(getattr(lib, "hawq_" + n), ctypes.c_void_p).value for n in names)
+    if _fastcall.setup(addresses, torch.Tensor, torch.nn.Parameter, ConvDesc, get_device, get_stream):
+        _fast = _fastcall
+
+
 def hawq_conv2d_int(desc, x, w, bias, b, c, residual, res_b, res_c, y, stream=None):
+    if _fast is not None:
+        st = _fast.conv2d(desc, x, w, bias, b, c, residual, res_b, res_c, y, stream)
+        if st is not None:
+            return _check(st, "hawq_conv2d_int") if st else None
     _check(load_library().hawq_conv2d_int(ctypes.byref(desc), _p(x), _p(w), _p(bias), _p(b), _p(c), _p(residual),
                                            _p(res_b), _p(res_c), _p(y), _stream(stream)), "hawq_conv2d_int")
 
 
 def hawq_conv2d_dual_int(desc, x, w, bias, b, c, desc_s, xs, ws, bias_s, b_s, c_s, y, stream=None):
+    if _fast is not None:
+        st = _fast.dual(desc, x, w, bias, b, c, desc_s, xs, ws, bias_s, b_s, c_s, y, stream)
+        if st is not None:
+            return _check(st, "hawq_conv2d_dual_int") if st else None
     _check(load_library().hawq_conv2d_dual_int(ctypes.byref(desc), _p(x), _p(w), _p(bias), _p(b), _p(c), ctypes.byref(desc_s),
                                                 _p(xs), _p(ws), _p(bias_s), _p(b_s), _p(c_s), _p(y), _stream(stream)),
            "hawq_conv2d_dual_int")
 
 
 def hawq_gemm_int(M, N, Kdim, x_dt, w_dt, y_dt, x, w, bias, b, c, relu, y_lo, y_hi, y, stream=None):
+    if _fast is not None:
+        st = _fast.gemm(M, N, Kdim, x_dt, w_dt, y_dt, x, w, bias, b, c, relu, y_lo, y_hi, y, stream)
+        if st is not None:
+            return _check(st, "hawq_gemm_int") if st else None
     _check(load_library().hawq_gemm_int(M, N, Kdim, x_dt, w_dt, y_dt, _p(x), _p(w), _p(bias), _p(b), _p(c), relu, y_lo,
                                          y_hi, _p(y), _stream(stream)), "hawq_gemm_int")
 
 
 def hawq_residual_add_dyadic(n_pixels, K, m_dt, r_dt, y_dt, m, m_b, m_c, r, r_b, r_c, relu, y_lo, y_hi, y, stream=None):
+    if _fast is not None:
+        st = _fast.residual_add(n_pixels, K, m_dt, r_dt, y_dt, m, m_b, m_c, r, r_b, r_c, relu, y_lo, y_hi, y, stream)
+        if st is not None:
+            return _check(st, "hawq_residual_add_dyadic") if st else None
     _check(load_library().hawq_residual_add_dyadic(n_pixels, K, m_dt, r_dt, y_dt, _p(m), _p(m_b), _p(m_c), _p(r), _p(r_b),
                                                     _p(r_c), relu, y_lo, y_hi, _p(y), _stream(stream)),
            "hawq_residual_add_dyadic")
 
 
 def hawq_avgpool_int(N, H, W, C, x_dt, y_dt, x, b, c, y_lo, y_hi, y, stream=None):
+    if _fast is not None:
+        st = _fast.avgpool(N, H, W, C, x_dt, y_dt, x, b, c, y_lo, y_hi, y, stream)
+        if st is not None:
+            return _check(st, "hawq_avgpool_int") if st else None
     _check(load_library().hawq_avgpool_int(N, H, W, C, x_dt, y_dt, _p(x), _p(b), _p(c), y_lo, y_hi, _p(y), _stream(stream)),
            "hawq_avgpool_int")
 
 
 def hawq_maxpool_int(N, H, W, C, x_dt, y_dt, x, y_lo, y_hi, y, stream=None):
+    if _fast is not None:
+        st = _fast.maxpool(N, H, W, C, x_dt, y_dt, x, y_lo, y_hi, y, stream)
+        if st is not None:
+            return _check(st, "hawq_maxpool_int") if st else None
     _check(load_library().hawq_maxpool_int(N, H, W, C, x_dt, y_dt, _p(x), y_lo, y_hi, _p(y), _stream(stream)),
            "hawq_maxpool_int")
 
 
 def hawq_pool2d_sum_int(N, H, W, C, R, S, stride_h, stride_w, pad_h, pad_w, x_dt, y_dt, x, b, c, y_lo, y_hi, y, stream=None):
+    if _fast is not None:
+        st = _fast.pool2d_sum(N, H, W, C, R, S, stride_h, stride_w, pad_h, pad_w, x_dt, y_dt, x, b, c, y_lo, y_hi, y, stream)
+        if st is not None:
+            return _check(st, "hawq_pool2d_sum_int") if st else None
     _check(load_library().hawq_pool2d_sum_int(N, H, W, C, R, S, stride_h, stride_w, pad_h, pad_w, x_dt, y_dt, _p(x), _p(b), _p(c),
                                                y_lo, y_hi, _p(y), _stream(stream)), "hawq_pool2d_sum_int")
 
 
 def hawq_concat_dyadic(n_pixels, branches, y_dt, y_lo, y_hi, y, stream=None):
     """branches: list of (q, dtype, b, c) device tensors; K is taken from b."""
+    if _fast is not None:
+        st = _fast.concat(n_pixels, branches, y_dt, y_lo, y_hi, y, stream)
+        if st is not None:
+            return _check(st, "hawq_concat_dyadic") if st else None
     arr = (ConcatBranch * len(branches))()
     for i, (q, dt, b, c) in enumerate(branches):
         arr[i].q, arr[i].b, arr[i].c = q.data_ptr(), b.data_ptr(), c.data_ptr()

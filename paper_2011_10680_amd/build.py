@@ -1,11 +1,13 @@
-"""Compile the HIP sources into ``libhawq.so`` for gfx950 (in-tree, with hipcc)."""
+"""Compile the HIP sources into ``libhawq.so`` for gfx950 (in-tree, with hipcc), and the Python binding's native half."""
 import os
 import subprocess
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libhawq.so")
+FASTCALL = os.path.join(HERE, "_fastcall.so")     # CPython module: argument marshalling in C (host code only)
 OBJ_DIR = os.path.join(HERE, "_build")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -17,9 +19,9 @@ def sources():
 
 
 def is_stale():
-    if not os.path.exists(LIB):
+    if not (os.path.exists(LIB) and os.path.exists(FASTCALL)):
         return True
-    t = os.path.getmtime(LIB)
+    t = min(os.path.getmtime(LIB), os.path.getmtime(FASTCALL))
     deps = [os.path.join(CSRC, f) for f in os.listdir(CSRC)] + [os.path.join(HERE, "..", "include", "hawq.h")]
     return any(os.path.getmtime(d) > t for d in deps)
 
@@ -33,13 +35,20 @@ def _compile(src):
     return obj
 
 
+def _compile_fastcall():
+    subprocess.check_call(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-I", sysconfig.get_paths()["include"],
+                           "-o", FASTCALL, os.path.join(CSRC, "fastcall.cpp")])
+
+
 def build(force=True, jobs=8):
     """Compile every .hip source and link the shared library.  Returns its path."""
     if not force and not is_stale():
         return LIB
     os.makedirs(OBJ_DIR, exist_ok=True)
     with ThreadPoolExecutor(max_workers=jobs) as ex:
+        fast = ex.submit(_compile_fastcall)
         objs = list(ex.map(_compile, sources()))
+        fast.result()
     subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs)
     return LIB
 
