@@ -186,7 +186,8 @@ hawq_status dispatch_conv(const ConvArgs &a, int x_hi, hipStream_t s) {
     }
     if (tile_override() == 0 && conv_rp1k_eligible(a, x_hi)) return launch_conv_rp1k(a, s);
     const bool sk = conv_sk_eligible(a);
-    if (tile_override() == 0 && sk && conv_sk_small(a)) return launch_conv_sk(a, x_hi, s);
+    const bool tile = tile_override() == 0 && conv_tile_eligible(a, x_hi);
+    if (tile_override() == 0 && sk && conv_sk_small(a)) return tile && conv_tile_over_sk(a) ? launch_conv_tile(a, x_hi, s) : launch_conv_sk(a, x_hi, s);
     if (conv_pw_eligible(a, x_hi)) return launch_conv_pw(a, s);
     if (tile_override() == 0 && conv_pws_eligible(a, x_hi)) return launch_conv_pws(a, s);
     if (tile_override() == 0 && conv3x3_c64_eligible(a, x_hi)) return launch_conv3x3_c64(a, s);
@@ -196,7 +197,9 @@ hawq_status dispatch_conv(const ConvArgs &a, int x_hi, hipStream_t s) {
         Rp1Args r1;
         if (make_rp1_args(a, x_hi, 0, r1)) return launch_conv_rp1(r1, s);
     }
-    if (conv_mfma_eligible(a, x_hi)) return launch_conv_mfma(a, s);
+    const bool mfma = conv_mfma_eligible(a, x_hi);
+    if (tile && conv_tile_preferred(a, mfma)) return launch_conv_tile(a, x_hi, s);
+    if (mfma) return launch_conv_mfma(a, s);
     if (sk) return launch_conv_sk(a, x_hi, s);
     return launch_conv_direct(a, s);
 }

@@ -21,11 +21,9 @@
 // and cancels.
 // A block output with two convolutions (ConvArgs::xs) divides the waves between them in proportion to their steps.
 #include "common.h"
+#include "fastdiv.h"
 
 namespace hawq {
-
-// n / d for 0 <= n < 2^31: umulhi(n, mul) >> sh, mul = ceil(2^(31 + s) / d), s = ceil(log2 d), sh = s - 1; d = 1: mul = 0
-struct FastDiv { uint32_t mul, sh; };
 
 struct SkArgs {
     FastDiv ch, S, PQ, Q;      // 16-byte (8-byte) chunks of a tap, filter width, output pixels of an image, output width
@@ -35,21 +33,30 @@ struct SkArgs {
     int32_t vec;               // K % 4 == 0 and aligned arrays: vector loads and stores in the epilogue
 };
 
-static FastDiv fast_div(uint32_t d) {
-    if (d <= 1) return {0, 0};
-    uint32_t s = 0;
-    while ((1ull << s) < d) ++s;
-    return {(uint32_t)(((1ull << (31 + s)) + d - 1) / d), s - 1};
-}
-__device__ __forceinline__ uint32_t fdiv(uint32_t n, FastDiv f) { return f.mul ? __umulhi(n, f.mul) >> f.sh : n; }
-
 struct SkParams { int32_t bias[4], b[4], rb[4]; uint32_t c, rc, res; int32_t bias_s[4], b_s[4]; uint32_t c_s; };
 
-// Parameters (and shortcut values) of channels ch .. ch + 3 at pixel m
-template <bool DUAL>
-__device__ __forceinline__ void sk_load_params(const ConvArgs &a, int vec, uint32_t m, int ch, SkParams &p) {
-    const bool rq = a.b != nullptr, has_res = a.res != nullptr;
+// Shortcut values of channels ch .. ch + 3 at pixel m
+__device__ __forceinline__ uint32_t sk_load_res(const ConvArgs &a, int vec, uint32_t m, int ch) {
     const int res_dt = a.res_dt;
+    if (vec) {
+        const uint32_t o = m * (uint32_t)a.K + ch;
+        return is4(res_dt) ? *(const uint16_t *)(a.res + (o >> 1)) : *(const uint32_t *)(a.res + o);
+    }
+    uint32_t v = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int k = ch + j < a.K ? ch + j : a.K - 1;
+        const int bits = is4(res_dt) ? 4 : 8;
+        v |= ((uint32_t)load_elem(a.res, res_dt, (int64_t)m * a.K + k) & ((1u << bits) - 1)) << (bits * j);
+    }
+    return v;
+}
+
+// Parameters of channels ch .. ch + 3; RES: also the shortcut values at pixel m
+template <bool DUAL, bool RES>
+__device__ __forceinline__ void sk_load_params(const ConvArgs &a, int vec, uint32_t m, int ch, SkParams &p) {
+    const bool rq = a.b != nullptr;
+    if (RES && a.res != nullptr) p.res = sk_load_res(a, vec, m, ch);
     if (vec) {
         const v4i t = *(const v4i *)(a.bias + ch);
 #pragma unroll
@@ -66,10 +73,6 @@ __device__ __forceinline__ void sk_load_params(const ConvArgs &a, int vec, uint3
             for (int j = 0; j < 4; ++j) p.rb[j] = u[j];
             p.rc = *(const uint32_t *)(a.res_c + ch);
         }
-        if (has_res) {
-            const uint32_t o = m * (uint32_t)a.K + ch;
-            p.res = is4(res_dt) ? *(const uint16_t *)(a.res + (o >> 1)) : *(const uint32_t *)(a.res + o);
-        }
         if constexpr (DUAL) {
             const v4i u = *(const v4i *)(a.bias_s + ch), v = *(const v4i *)(a.b_s + ch);
 #pragma unroll
@@ -77,17 +80,13 @@ __device__ __forceinline__ void sk_load_params(const ConvArgs &a, int vec, uint3
             p.c_s = *(const uint32_t *)(a.c_s + ch);
         }
     } else {
-        p.c = p.rc = p.res = p.c_s = 0;
+        p.c = p.rc = p.c_s = 0;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int k = ch + j < a.K ? ch + j : a.K - 1;
             p.bias[j] = a.bias[k];
             if (rq) { p.b[j] = a.b[k]; p.c |= (uint32_t)a.c[k] << (8 * j); }
             if (a.res_b != nullptr) { p.rb[j] = a.res_b[k]; p.rc |= (uint32_t)a.res_c[k] << (8 * j); }
-            if (has_res) {
-                const int bits = is4(res_dt) ? 4 : 8;
-                p.res |= ((uint32_t)load_elem(a.res, res_dt, (int64_t)m * a.K + k) & ((1u << bits) - 1)) << (bits * j);
-            }
             if constexpr (DUAL) { p.bias_s[j] = a.bias_s[k]; p.b_s[j] = a.b_s[k]; p.c_s |= (uint32_t)a.c_s[k] << (8 * j); }
         }
     }
@@ -193,7 +192,10 @@ __global__ void __launch_bounds__(WK *WM * 64) conv_sk_kernel(const ConvArgs a, 
         xoff[tp] = (uint32_t)((((int)nn * H + ih0[tp]) * W + iw0[tp]) * Cb);
         if (m >= (uint32_t)a.M) ih0[tp] = 1 << 30;          // (fails the bounds test of every tap)
     }
-    // ---- parameters and shortcut values of the outputs this thread will finish: requested before the operands ----
+    // ---- parameters and shortcut values of the outputs this thread will finish: requested before the operands.  Of more than
+    // two slots only the parameters, once: the slots lie whole rows of channel tiles apart and share them (loaded again for each
+    // slot they cannot pass the stores before them: 39200 pixels of 1x1 288 -> 64 17.1 us, once 13.0) ----
+    static_assert(E <= 2 || NT / 64 % TC == 0, "one set of channels per thread");
     SkParams par[E <= 2 ? E : 1];
     auto slot_mk = [&](int s, uint32_t &m, int &ch) {       // slot -> pixel, first of four channels
         const int l = s & 63, t = (s >> 6) % (TC * TP), w = s / (64 * TC * TP);
@@ -205,8 +207,12 @@ __global__ void __launch_bounds__(WK *WM * 64) conv_sk_kernel(const ConvArgs a, 
         for (int j = 0; j < E; ++j) {
             uint32_t m; int ch;
             slot_mk(tid + j * NT, m, ch);
-            if ((SLOTS % NT == 0 || tid + j * NT < SLOTS) && m < (uint32_t)a.M && ch < a.K) sk_load_params<DUAL>(a, e.vec, m, ch, par[j]);
+            if ((SLOTS % NT == 0 || tid + j * NT < SLOTS) && m < (uint32_t)a.M && ch < a.K) sk_load_params<DUAL, true>(a, e.vec, m, ch, par[j]);
         }
+    } else {
+        uint32_t m; int ch;
+        slot_mk(tid, m, ch);
+        if (ch < a.K) sk_load_params<DUAL, false>(a, e.vec, m, ch, par[0]);
     }
 
     v4i acc[TP][TC], accx[XF ? TC : 1];
@@ -339,9 +345,8 @@ __global__ void __launch_bounds__(WK *WM * 64) conv_sk_kernel(const ConvArgs a, 
         if constexpr (E <= 2) {
             sk_store<DUAL>(a, e.vec, m, ch, t, ts, par[j]);
         } else {
-            SkParams p;
-            sk_load_params<DUAL>(a, e.vec, m, ch, p);
-            sk_store<DUAL>(a, e.vec, m, ch, t, ts, p);
+            if (a.res != nullptr) par[0].res = sk_load_res(a, e.vec, m, ch);
+            sk_store<DUAL>(a, e.vec, m, ch, t, ts, par[0]);
         }
     });
 }
@@ -430,19 +435,18 @@ hawq_status launch_conv_sk(const ConvArgs &a_in, int x_hi, hipStream_t s) {
     // (~1.6 us) more.  7x7 3x3 512 -> 512 at batch 1: 16x16 tiles (128 workgroups) 5.2 us, 32x32 (32) 8.0; 14x14 3x3
     // 256 -> 256 at batch 4: 32x32 (200) 6.3, 16x32 (400) 7.9, 16x16 (784) 9.1.  A 32x64 tile of few steps splits them
     // over four waves instead of eight (28x28 1x1 512 -> 128 at batch 4: 4.9 against 5.1 us), one of many over eight (7x7
-    // 3x3 at batch 16: 12.4 against 13.9).  Past one round every operand byte counts: 64x128, or 32x128 where the last
-    // 64 channels would be half empty.
+    // 3x3 at batch 16: 12.4 against 13.9).  Past one round the number of waves in flight counts more than the operand bytes:
+    // four waves a tile for long reductions (64 x 64; packed 5x5 240 -> 208 at 3267 pixels 22.4 us, with two 26.0), else two, 32 channels x
+    // 64 pixels a workgroup, from 512 of those on 32 x 128 (packed 1x1 272 -> 288 at 39200 pixels 24 us,
+    // with 64 x 128 tiles or four waves a tile 27 to 42; packed 3x3 48 -> 64 8.3 and 9.8).
     auto tiles = [&](int tc, int tp) { return (int64_t)((a.K + 16 * tc - 1) / (16 * tc)) * ((a.M + 16 * tp - 1) / (16 * tp)); };
     if (tiles(1, 1) <= 256) return sk_launch<1, 1, 8, 1>(a, e, xf, s);
     if (tiles(1, 2) <= 256) return sk_launch<1, 2, 8, 1>(a, e, xf, s);
     if (tiles(2, 2) <= 256) return sk_launch<2, 2, 8, 1>(a, e, xf, s);
-    if (tiles(2, 4) <= 256) {
-        const int steps = (a.R * a.S * (is4(a.x_dt) ? a.C / 2 : a.C) + 63) / 64;
-        return steps < 32 ? sk_launch<2, 2, 4, 2>(a, e, xf, s) : sk_launch<2, 4, 8, 1>(a, e, xf, s);
-    }
-    if (tiles(4, 4) <= 512) return sk_launch<4, 2, 4, 2>(a, e, xf, s);
-    if ((a.K & 63) >= 1 && (a.K & 63) <= 32) return sk_launch<2, 4, 4, 2>(a, e, xf, s);
-    return sk_launch<4, 4, 2, 2>(a, e, xf, s);
+    const int steps = (a.R * a.S * (is4(a.x_dt) ? a.C / 2 : a.C) + 63) / 64;
+    if (tiles(2, 4) <= 256) return steps < 32 ? sk_launch<2, 2, 4, 2>(a, e, xf, s) : sk_launch<2, 4, 8, 1>(a, e, xf, s);
+    if (tiles(4, 4) <= 512 && steps >= 16) return sk_launch<4, 2, 4, 2>(a, e, xf, s);
+    return tiles(2, 4) <= 512 ? sk_launch<2, 2, 2, 2>(a, e, xf, s) : sk_launch<2, 4, 2, 2>(a, e, xf, s);
 }
 
 }  // namespace hawq

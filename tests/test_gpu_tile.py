@@ -1,0 +1,109 @@
+"""GPU parity of the tiled kernel with channels along the lanes: ragged channel counts, unsigned bytes above 127, INT32 results, at
+the edges of every tile it chooses from, bit-exact."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def hawq():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import paper_2011_10680_amd as h
+    h.load_library()
+    return h
+
+
+# (M, N, K): 64x32 tiles; 64x64 with a remainder in every direction and 1, 5 and 6 steps of the four-deep ring; 128x64; 128x128;
+# 256x256; N % 4 of 0 .. 3; one row past a tile
+_PRODUCTS = [(300, 1003, 1024), (769, 1002, 64), (1030, 1001, 320), (1025, 1000, 384), (3000, 301, 192), (4099, 999, 768), (4097, 1004, 256),
+             (2100, 4002, 1024)]
+
+
+@pytest.mark.parametrize("M,N,K", _PRODUCTS)
+@pytest.mark.parametrize("x_dt,y_dt", [(oracle.U8, oracle.S32), (oracle.S8, oracle.S32), (oracle.U8, oracle.U8), (oracle.S8, oracle.S8)])
+def test_matrix_product(hawq, M, N, K, x_dt, y_dt):
+    import torch
+    from gpu_util import to_dev, assert_same
+    g = np.random.default_rng(M + N + K)
+    x = g.integers(0, 256, size=(M, K)).astype(np.uint8) if x_dt == oracle.U8 else g.integers(-128, 128, size=(M, K)).astype(np.int8)
+    w = g.integers(-127, 128, size=(N, K)).astype(np.int8)
+    w[0], w[N - 1] = -128, 127
+    bias = g.integers(-(1 << 15), 1 << 15, size=N).astype(np.int32)
+    raw = y_dt == oracle.S32
+    b = c = None
+    if not raw:
+        s = np.sqrt(K) * 74 * (148 if x_dt == oracle.U8 else 74) / 42
+        b = g.integers(1 << 14, 1 << 15, size=N).astype(np.int32)
+        c = (int(np.log2(1.5 * (1 << 14) * s)) + g.integers(0, 2, size=N)).astype(np.uint8)
+    lo, hi = (0, 0) if raw else {oracle.U8: (0, 255), oracle.S8: (-128, 127)}[y_dt]
+    y = torch.full((M, N), 0x5A, dtype={oracle.U8: torch.uint8, oracle.S8: torch.int8, oracle.S32: torch.int32}[y_dt], device="cuda")
+    hawq.hawq_gemm_int(M, N, K, x_dt, hawq.S8, y_dt, to_dev(x), to_dev(w), to_dev(bias), to_dev(b), to_dev(c), 0, lo, hi, y)
+    torch.cuda.synchronize()
+    want = oracle.conv2d_int(x.reshape(1, 1, M, K), w, bias, b, c, N=1, H=1, W=M, C=K, K=N, R=1, S=1, stride=1, pad=0, x_dt=x_dt, w_dt=oracle.S8,
+                             y_dt=y_dt, relu=0, y_lo=lo, y_hi=hi)
+    assert_same(y.cpu().numpy(), np.asarray(want).reshape(M, N), str((M, N, K)))
+
+
+# (N, H, W, C, K, R, S, stride, pad, bits, what): windows and channel counts whose 64-byte steps hold several taps, or parts of them;
+# what: "raw", "wide" (one channel outside the narrow evaluation's range), "byte" (unsigned bytes above 127), "s" (signed result)
+_WINDOWS = [
+    (9, 35, 34, 96, 96, 3, 3, 1, 1, 8, ""), (9, 35, 34, 96, 97, 3, 3, 1, 1, 8, "raw"), (8, 34, 33, 112, 90, 3, 3, 1, 1, 8, "wide"),
+    (23, 35, 35, 16, 32, 5, 3, 1, 2, 8, "raw"), (30, 41, 39, 48, 66, 3, 3, 2, 1, 8, "s"), (14, 33, 35, 64, 80, 3, 3, 1, 1, 8, ""),
+    (9, 35, 34, 80, 96, 3, 3, 1, 1, 8, "byte"), (12, 61, 60, 144, 275, 1, 1, 2, 0, 8, "byte"),
+    (13, 35, 35, 288, 64, 1, 1, 1, 0, 4, "raw"), (13, 35, 35, 288, 70, 1, 1, 1, 0, 4, ""), (9, 35, 34, 96, 100, 3, 3, 1, 1, 4, ""),
+    (15, 35, 33, 32, 62, 5, 5, 1, 2, 4, "s"), (9, 35, 34, 160, 98, 3, 3, 1, 1, 4, "wide"), (14, 33, 35, 128, 96, 3, 3, 1, 1, 4, ""),
+    (40, 35, 35, 224, 300, 1, 1, 1, 0, 4, ""),
+]
+
+
+@pytest.mark.parametrize("shape", _WINDOWS)
+def test_convolution_windows(hawq, shape):
+    from gpu_util import run_conv_gpu, assert_same
+    from test_gpu_conv import _scale_c
+    N, H, W, C, K, R, S, stride, pad, bits, what = shape
+    case = _scale_c(wl.conv_case(seed=sum(shape[:10]), N=N, H=H, W=W, C=C, K=K, R=R, S=S, stride=stride, pad=pad, bits=bits), bits)
+    if what == "byte":
+        case["x"] = np.random.default_rng(K).integers(0, 256, size=case["x"].shape).astype(np.uint8)
+        case["c"] = case["c"] + np.uint8(1)
+    if what == "wide":
+        case["b"][K // 2], case["c"][K // 2] = (1 << 31) - 1, case["c"][K // 2] + 16
+    if bits == 4:
+        wu = oracle.unpack(case["w"], oracle.S4).reshape(K, R, S, C)
+        wu[0], wu[K - 1] = -8, 7
+        case["w"] = wl.pack_nibbles(wu).reshape(case["w"].shape)
+    raw = what == "raw"
+    x_dt, w_dt = (hawq.U8, hawq.S8) if bits == 8 else (hawq.U4, hawq.S4)
+    y_dt = hawq.S32 if raw else {(8, True): hawq.S8, (8, False): hawq.U8, (4, True): hawq.S4, (4, False): hawq.U4}[bits, what == "s"]
+    lo, hi = {(8, True): (-128, 127), (8, False): (0, 127), (4, True): (-8, 7), (4, False): (0, 15)}[bits, what == "s"]
+    got, want = run_conv_gpu(case, x_dt, w_dt, y_dt, y_lo=lo, y_hi=hi, raw=raw, relu=0 if raw or what == "s" else 1, x_hi=127 if bits == 8 and what != "byte" else 0)
+    assert_same(got, want, str(shape))
+    if not raw:
+        v = want.astype(np.int32) if bits == 8 else oracle.unpack(want, y_dt)
+        assert len(np.unique(v)) > 8
+
+
+def test_blocked_weights(hawq):
+    """The blocked copy in place of the weights' rows, whole and ragged channel tiles."""
+    import torch
+    from gpu_util import to_dev, assert_same
+    from test_gpu_conv import _scale_c
+    for bits, C, K in ((8, 192, 96), (4, 128, 100)):
+        case = _scale_c(wl.conv_case(seed=K, N=9, H=35, W=34, C=C, K=K, R=3, S=3, stride=1, pad=1, bits=bits), bits)
+        x_dt, w_dt, hi = (hawq.U8, hawq.S8, 127) if bits == 8 else (hawq.U4, hawq.S4, 15)
+        d = hawq.ConvDesc(N=9, H=35, W=34, C=C, K=K, R=3, S=3, stride_h=1, stride_w=1, pad_h=1, pad_w=1, x_dtype=x_dt, w_dtype=w_dt,
+                          y_dtype=x_dt, res_dtype=hawq.U8, relu=1, y_lo=0, y_hi=hi, x_hi=127 if bits == 8 else 0)
+        w = to_dev(case["w"])
+        blocked = torch.empty(hawq.hawq_conv_blocked_weights_bytes(d), dtype=torch.uint8, device="cuda")
+        hawq.hawq_conv_block_weights(d, w, blocked)
+        d.w_blocked = blocked.data_ptr()
+        y = torch.full((9, 35, 34, K * bits // 8), 0x5A, dtype=torch.uint8, device="cuda")
+        hawq.hawq_conv2d_int(d, to_dev(case["x"]), w, to_dev(case["bias"]), to_dev(case["b"]), to_dev(case["c"]), None, None, None, y)
+        torch.cuda.synchronize()
+        want = oracle.conv2d_int(case["x"], case["w"], case["bias"], case["b"], case["c"], N=9, H=35, W=34, C=C, K=K, R=3, S=3, stride=1, pad=1,
+                                 x_dt=x_dt, w_dt=w_dt, y_dt=x_dt, relu=1, y_lo=0, y_hi=hi)
+        assert_same(y.cpu().numpy(), want, str((bits, C, K)))
