@@ -1,6 +1,7 @@
 // Tiled implicit GEMM for the large launches whose channel counts or operands the other tiled kernel (conv_mfma.hip) does not
 // suit: input channels a multiple of 16 only (packed 4-bit: of 32), any number of output channels, unsigned bytes above 127, INT32
-// results.  The matrix product of hawq_gemm_int and the convolutions of Inception-style modules.
+// results; and the middling ones, a few 64 x 64 tiles per CU.  The matrix product of hawq_gemm_int, the convolutions of
+// Inception-style modules, residual networks' layers at small and middling batches.
 //
 // Two things differ from conv_mfma.hip.  Pixels are the MFMA's row operand and channels its column operand, so a lane holds one
 // output channel and sixteen pixels: its parameters are a handful of registers, and a store instruction writes 32 consecutive
@@ -33,7 +34,7 @@ struct TileArgs {
 };
 
 // BM x BN (pixels x channels) per workgroup of WM x WN waves
-template <int BM, int BN, int WM, int WN, int FORM, bool XF, bool TAPS>
+template <int BM, int BN, int WM, int WN, int FORM, bool XF, bool TAPS, bool RES>
 __global__ void __launch_bounds__(WM *WN * 64) __attribute__((amdgpu_waves_per_eu(BM * BN / (WM * WN) >= 64 * 64 ? 2 : 3)))
 conv_tile_kernel(const ConvArgs a, const TileArgs e) {
     constexpr int NW = WM * WN;                             // waves
@@ -117,15 +118,43 @@ conv_tile_kernel(const ConvArgs a, const TileArgs e) {
     };
     static_for<0, NBUF - 1>([&](auto ic) { fetch(decltype(ic)::value, ic); });
 
-    // ---- the lane's channels' parameters ----
+    // ---- the shortcut, in the form the results are stored in: of pixel 8 j + 4 half + q, the four channels of the lane's quad ----
     const int col = lane & 31, half = lane >> 5;
-    int32_t bias[TN], pb[TN], pcs[TN];
+    const int q = lane & 3;                               // position in its quad of lanes = of four consecutive channels
+    uint32_t resw[RES ? TM : 1][RES ? TN : 1][4];
+    if constexpr (RES) {
+        const bool r4 = is4(a.res_dt);
+        const __amdgpu_buffer_rsrc_t rs_r = __builtin_amdgcn_make_buffer_rsrc((void *)a.res, 0, (int)tensor_bytes((int64_t)a.M * a.K, a.res_dt), 0x00020000);
+#pragma unroll
+        for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+            for (int tn = 0; tn < TN; ++tn) {
+                const int ch4 = n0 + (wn * TN + tn) * 32 + (col & ~3);
+                const uint32_t o = (uint32_t)(m0 + (wm * TM + tm) * 32 + 4 * half + q) * (uint32_t)a.K + (uint32_t)ch4;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const uint32_t at = ch4 < a.K ? o + (uint32_t)(8 * j * a.K) : kInvalid;
+                    if (r4) {
+                        const uint32_t h = __builtin_amdgcn_raw_buffer_load_b16(rs_r, (int)(ch4 < a.K ? at >> 1 : kInvalid), 0, 0);
+                        resw[tm][tn][j] = (h & 0xfu) | ((h & 0xf0u) << 4) | ((h & 0xf00u) << 8) | ((h & 0xf000u) << 12);
+                    } else {
+                        resw[tm][tn][j] = __builtin_amdgcn_raw_buffer_load_b32(rs_r, (int)at, 0, 0);
+                    }
+                }
+            }
+    }
+    // ---- the lane's channels' parameters ----
+    int32_t bias[TN], pb[TN], pcs[TN], prb[TN], prc[TN];
 #pragma unroll
     for (int tn = 0; tn < TN; ++tn) {
         const int ch = n0 + (wn * TN + tn) * 32 + col;
         bias[tn] = ch < a.K ? a.bias[ch] : 0;
         pb[tn] = a.b != nullptr && ch < a.K ? a.b[ch] : 0;
         pcs[tn] = a.b != nullptr && ch < a.K ? a.c[ch] : 1;
+        if constexpr (RES) {
+            prb[tn] = ch < a.K ? a.res_b[ch] : 0;
+            prc[tn] = ch < a.K ? a.res_c[ch] : 1;
+        }
     }
 
     // ---- fragment addresses within a stage ----
@@ -229,6 +258,7 @@ conv_tile_kernel(const ConvArgs a, const TileArgs e) {
         }
         narrow &= pcs[tn] <= 32 && ((uint32_t)pb[tn] >> ((pcs[tn] - 1) & 31)) == 0;
         bs[tn] = (int32_t)((uint32_t)pb[tn] << ((32 - pcs[tn]) & 31));
+        if constexpr (RES) narrow &= prc[tn] <= 31 && (uint32_t)prb[tn] < 1u << 22;   // (r rb + 2^(rc-1)) >> rc in 32 bits
     }
     narrow = __all(narrow);
     int32_t lo = a.lo, hi = a.hi;
@@ -236,13 +266,25 @@ conv_tile_kernel(const ConvArgs a, const TileArgs e) {
     asm volatile("" : "+v"(lo), "+v"(hi), "+v"(round));   // (opaque addend and bounds: one multiply-add, one median per output)
     const int y_dt = a.y_dt, K = a.K;
     const __amdgpu_buffer_rsrc_t rs_y = __builtin_amdgcn_make_buffer_rsrc((void *)a.y, 0, (int)tensor_bytes((int64_t)a.M * K, y_dt), 0x00020000);
-    const int q = lane & 3;                               // position in its quad of lanes = of four consecutive channels
+    // four x four bytes change places within a quad of lanes: byte k of lane q <-> byte q of lane k
     const uint32_t sel01 = (uint32_t)(q | (4 + q) << 8) | 0x0c0c0000u, sel23 = (uint32_t)(q << 16 | (4 + q) << 24) | 0x00000c0cu;
+    auto quad_transpose = [&](uint32_t p) -> uint32_t {
+        const uint32_t t0 = (uint32_t)__builtin_amdgcn_mov_dpp((int)p, 0x00, 0xf, 0xf, true);
+        const uint32_t t1 = (uint32_t)__builtin_amdgcn_mov_dpp((int)p, 0x55, 0xf, 0xf, true);
+        const uint32_t t2 = (uint32_t)__builtin_amdgcn_mov_dpp((int)p, 0xaa, 0xf, 0xf, true);
+        const uint32_t t3 = (uint32_t)__builtin_amdgcn_mov_dpp((int)p, 0xff, 0xf, 0xf, true);
+        return __builtin_amdgcn_perm(t1, t0, sel01) | __builtin_amdgcn_perm(t3, t2, sel23);
+    };
+    const bool res_signed = RES && a.res_dt == HAWQ_S8;
 #pragma unroll
     for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
         for (int tn = 0; tn < TN; ++tn) {
             v16i v = acc[tm][tn];
+            uint32_t rw[4] = {0, 0, 0, 0};                // shortcut bytes of the lane's channel, pixels 8 j + 4 half + 0 .. 3
+            if constexpr (RES)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) rw[j] = quad_transpose(resw[tm][tn][j]);
             if constexpr (FORM != 0) v >>= 4;
 #pragma unroll
             for (int i = 0; i < 16; ++i) v[i] += bias[tn];
@@ -252,13 +294,23 @@ conv_tile_kernel(const ConvArgs a, const TileArgs e) {
                     asm volatile("" : "+v"(s));           // (a hoisted 64-bit sign extension would make it a 64 x 32 product)
 #pragma unroll
                     for (int i = 0; i < 16; ++i) {
-                        const int32_t y = (int32_t)(((int64_t)v[i] * (int64_t)s + round) >> 32);
+                        int32_t y = (int32_t)(((int64_t)v[i] * (int64_t)s + round) >> 32);
+                        if constexpr (RES) {
+                            const int32_t r = res_signed ? __builtin_amdgcn_sbfe((int32_t)rw[i >> 2], 8 * (i & 3), 8) : (int32_t)__builtin_amdgcn_ubfe(rw[i >> 2], 8 * (i & 3), 8);
+                            y += (__mul24(r, prb[tn]) + (int32_t)(1u << ((prc[tn] - 1) & 31))) >> prc[tn];
+                        }
                         asm("v_med3_i32 %0, %1, %2, %3" : "=v"(v[i]) : "v"(y), "v"(lo), "v"(hi));
                     }
                 } else {
 #pragma unroll 1
                     for (int i = 0; i < 16; ++i) {        // element 0, then all move down by one
-                        const int32_t y = clamp64(rq64(v[0], pb[tn], pcs[tn]), a.lo, a.hi);
+                        int64_t w = rq64(v[0], pb[tn], pcs[tn]);
+                        if constexpr (RES) {
+                            w += rq64(res_signed ? (int32_t)(int8_t)rw[0] : (int32_t)(rw[0] & 0xff), prb[tn], prc[tn]);
+                            rw[0] = rw[0] >> 8 | rw[1] << 24; rw[1] = rw[1] >> 8 | rw[2] << 24;
+                            rw[2] = rw[2] >> 8 | rw[3] << 24; rw[3] >>= 8;
+                        }
+                        const int32_t y = clamp64(w, a.lo, a.hi);
                         v = __builtin_shufflevector(v, v, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15, 0);
                         v[15] = y;
                     }
@@ -278,18 +330,14 @@ conv_tile_kernel(const ConvArgs a, const TileArgs e) {
                 for (int i = 0; i < 16; ++i)
                     __builtin_amdgcn_raw_buffer_store_b8((uint8_t)v[i], rs_y, (int)(o + (uint32_t)((8 * (i >> 2) + (i & 3)) * K)), 0, 0);
             } else {
-                // four pixels x four channels change places within the quad: a lane then has four channels of pixel q
+                // a lane then has the four channels of its quad, of pixel q
                 const int ch4 = ch & ~3;
                 const uint32_t o = (uint32_t)(mb + q) * (uint32_t)K + (uint32_t)ch4;
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     const uint32_t p = __builtin_amdgcn_perm((uint32_t)v[4 * j + 1], (uint32_t)v[4 * j], 0x0c0c0400u) |
                                        __builtin_amdgcn_perm((uint32_t)v[4 * j + 3], (uint32_t)v[4 * j + 2], 0x04000c0cu);
-                    const uint32_t t0 = (uint32_t)__builtin_amdgcn_mov_dpp((int)p, 0x00, 0xf, 0xf, true);
-                    const uint32_t t1 = (uint32_t)__builtin_amdgcn_mov_dpp((int)p, 0x55, 0xf, 0xf, true);
-                    const uint32_t t2 = (uint32_t)__builtin_amdgcn_mov_dpp((int)p, 0xaa, 0xf, 0xf, true);
-                    const uint32_t t3 = (uint32_t)__builtin_amdgcn_mov_dpp((int)p, 0xff, 0xf, 0xf, true);
-                    const uint32_t w = __builtin_amdgcn_perm(t1, t0, sel01) | __builtin_amdgcn_perm(t3, t2, sel23);
+                    const uint32_t w = quad_transpose(p);
                     const uint32_t at = o + (uint32_t)(8 * j * K);
                     if (!is4(y_dt)) {
                         __builtin_amdgcn_raw_buffer_store_b32(w, rs_y, (int)(ch4 < K ? at : kInvalid), 0, 0);
@@ -311,11 +359,14 @@ conv_tile_kernel(const ConvArgs a, const TileArgs e) {
 
 bool conv_tile_eligible(const ConvArgs &a, int x_hi) {
     const bool four = is4(a.x_dt);
-    if (a.C % (four ? 32 : 16) != 0 || four != is4(a.w_dt) || a.xs != nullptr || a.res != nullptr) return false;
+    if (a.C % (four ? 32 : 16) != 0 || four != is4(a.w_dt) || a.xs != nullptr) return false;
     if (four ? (a.x_dt != HAWQ_U4 || a.w_dt != HAWQ_S4) : (a.w_dt != HAWQ_S8 || (a.x_dt != HAWQ_U8 && a.x_dt != HAWQ_S8))) return false;
     if (((uintptr_t)a.x | (uintptr_t)a.w) & 15) return false;
     if (((uintptr_t)a.bias | (uintptr_t)a.b) & 3) return false;
     if (a.y_dt == HAWQ_S32 && ((uintptr_t)a.y & 3)) return false;
+    // a shortcut: whole groups of four channels on both sides, operands within the signed range
+    if (a.res != nullptr && (a.b == nullptr || a.K % 4 != 0 || (((uintptr_t)a.res | (uintptr_t)a.y) & 3) || ((uintptr_t)a.res_b & 3) ||
+                             a.res_dt == HAWQ_S4 || a.y_dt == HAWQ_S32 || (a.x_dt == HAWQ_U8 && x_hi > 127))) return false;
     const int64_t red = (int64_t)a.R * a.S * a.C;
     // packed sums are kept times sixteen (16 * 15 * 8 * red < 2^31), chunk numbers (red / 16 and some steps) well below 2^31, rows of
     // the tiles that reach past M * K and offsets past a row's last chunk below the mark of an invalid one
@@ -325,16 +376,18 @@ bool conv_tile_eligible(const ConvArgs &a, int x_hi) {
     return (int64_t)a.N * a.H * a.W * a.C + 4 * red < edge;
 }
 
-template <int BM, int BN, int WM, int WN>
+template <int BM, int BN, int WM, int WN, bool RES>
 static hawq_status tile_launch(const ConvArgs &a, TileArgs e, int x_hi, hipStream_t s) {
     e.n_nt = (a.K + BN - 1) / BN;
     const uint32_t nb = e.n_nt * (uint32_t)((a.M + BM - 1) / BM);
     constexpr int T = WM * WN * 64;
     const bool xf = a.x_dt == HAWQ_U8 && x_hi > 127, taps = a.R * a.S > 1 || a.pad_h != 0 || a.pad_w != 0;
     auto go = [&](auto kernel) { kernel<<<nb, T, 0, s>>>(a, e); };
-    if (is4(a.x_dt)) taps ? go(conv_tile_kernel<BM, BN, WM, WN, 1, false, true>) : go(conv_tile_kernel<BM, BN, WM, WN, 1, false, false>);
-    else if (xf) taps ? go(conv_tile_kernel<BM, BN, WM, WN, 0, true, true>) : go(conv_tile_kernel<BM, BN, WM, WN, 0, true, false>);
-    else taps ? go(conv_tile_kernel<BM, BN, WM, WN, 0, false, true>) : go(conv_tile_kernel<BM, BN, WM, WN, 0, false, false>);
+    if (is4(a.x_dt)) taps ? go(conv_tile_kernel<BM, BN, WM, WN, 1, false, true, RES>) : go(conv_tile_kernel<BM, BN, WM, WN, 1, false, false, RES>);
+    else if constexpr (!RES) {
+        if (xf) taps ? go(conv_tile_kernel<BM, BN, WM, WN, 0, true, true, RES>) : go(conv_tile_kernel<BM, BN, WM, WN, 0, true, false, RES>);
+        else taps ? go(conv_tile_kernel<BM, BN, WM, WN, 0, false, true, RES>) : go(conv_tile_kernel<BM, BN, WM, WN, 0, false, false, RES>);
+    } else taps ? go(conv_tile_kernel<BM, BN, WM, WN, 0, false, true, RES>) : go(conv_tile_kernel<BM, BN, WM, WN, 0, false, false, RES>);
     return check_launch();
 }
 
@@ -363,25 +416,46 @@ static int tile_choice(const ConvArgs &a) {
 }
 
 // Over the split-reduction kernel below its line of 2^19 outputs: matrix products and 1x1 layers of no more than 24 steps.  From
-// 2^18 outputs on with 8 steps or more or ragged rows (300 x 1000 x 1024 6.7 -> 4.6 us, 300 x 1003 x 256 4.9 -> 3.4; with 64 steps 14.4
-// and 15.1), from 3 * 2^17 on with fewer (8670 pixels of packed 288 -> 48 4.6 -> 4.2; 7350 3.8 and 4.1).  A 3x3 window stays there
-// (4624 pixels of 64 -> 96 4.2 us, here 5.8).
+// 2^18 outputs on with 8-bit operands and 8 steps or more, or with ragged rows (300 x 1000 x 1024 6.7 -> 4.6 us, 300 x 1003 x 256 4.9 ->
+// 3.4; with 64 steps 14.4 and 15.1), from 3 * 2^17 on with fewer (8670 pixels of packed 288 -> 48 4.6 -> 4.2; 7350 3.8 and 4.1).  A 3x3
+// window stays there (4624 pixels of 64 -> 96 4.2 us, here 5.8), and so do
+// longer packed reductions (1024 -> 2048 / 2 at 196 pixels 5.3 us, here 6.3; 2048 -> 512 at 784 7.4 and 8.2).
 bool conv_tile_over_sk(const ConvArgs &a) {
+    if (a.res != nullptr) return false;
     const int64_t out = (int64_t)a.M * a.K, steps = tile_steps(a);
-    return a.R * a.S == 1 && steps <= 24 && out > (steps >= 8 || a.K % 4 != 0 ? 1 << 18 : 3 << 17);
+    const bool ragged = a.K % 4 != 0;
+    if (a.R * a.S != 1 || steps > 24 || (is4(a.x_dt) && steps >= 8 && !ragged)) return false;
+    return out > (steps >= 8 || ragged ? 1 << 18 : 3 << 17);
+}
+
+// Launches of no more than two or three 64 x 64 tiles per CU: those tiles, three workgroups side by side on a CU, whose fetches,
+// products and epilogues overlap (shortcut, 64 -> 256 at 56 x 56, packed, batch 2: 5.0 us, with 128 x 64 6.2; 3x3 / 2 64 -> 128, batch
+// 16: 6.2 and 6.6).  With more tiles or steps the larger tiles' fewer bytes count (512 x 4096 x 4096 22.7 us, with 64 x 64 23.8; shortcut,
+// packed 3x3 256 -> 256 at 14 x 14, batch 48, 588 tiles of 18 steps: 16.9, conv_mfma.hip 16.4).
+static bool few_tiles(const ConvArgs &a) {
+    const int64_t steps = tile_steps(a), tiles = ((int64_t)a.M + 63) / 64 * ((a.K + 63) / 64);
+    return tiles <= (steps < 16 ? 768 : steps < 32 ? 512 : 0);
 }
 
 // Over the tiled kernel with pixels along the lanes (mfma: that kernel takes the launch) or, above its line, the split-reduction
-// kernel.  The former keeps whole groups of 16 channels with 8-bit results and no quarter of a 128-channel tile to spare: its
-// epilogue stores 16 bytes a lane (1x1 512 -> 128 at 28x28, batch 64 11.2 us, here 10.8; 3x3 / 2 256 -> 512 at 14x14, batch 128 13.3
-// and 14.8); this one takes INT32 results (4096 x 1000 x 256 25 -> 7.3), ragged ones (19 -> 5.5), 96 or 192 channels (3x3 64 -> 96 at
-// 35x35, batch 32 12.9 -> 9.3) and products large enough for 256 x 256 tiles.  The split-reduction kernel keeps long packed reductions
-// just above its line (5x5 224 -> 112 at 7350 pixels 13.0 us, here 16.0; at 8670 24.3 and 20.2).
+// kernel.  The former's tiles are 128 channels wide and its workgroups of eight waves, one or two on a CU: a launch of few tiles is
+// faster here (56 x 56, 64 -> 256 with its shortcut, batch 1, 5.7 -> 3.9 us, batch 4 5.6 and 5.6; packed 3x3 / 2 64 -> 128, batch 8 9.1 ->
+// 5.3; packed 3x3 256 -> 256 at 14 x 14 with its shortcut, batch 16 14.2 -> 9.7), from seven tiles of rows on (1024 -> 2048 / 2 at 196
+// pixels 7.0 us, here 7.4; at 588 8.9 and 8.2) and for packed shortcut layers up to 1024 channels (512 -> 2048 at 784 pixels 7.5
+// and 8.1; 256 -> 1024 at 784 5.9 and 5.3).  Of the larger launches it keeps those with whole groups of 16 channels, 8-bit
+// results and no quarter of a 128-channel tile to spare, and every shortcut: its epilogue stores 16 bytes a lane (1x1 512 -> 128 at
+// 28x28, batch 64 11.2 us, here 10.8; 3x3 / 2 256 -> 512 at 14x14, batch 128 13.3 and 14.8); this one takes INT32 results
+// (4096 x 1000 x 256 25 -> 7.3), ragged ones (19 -> 5.5), 96 or 192 channels (3x3 64 -> 96 at 35x35, batch 32 12.9 -> 9.3) and products
+// large enough for 256 x 256 tiles.  The split-reduction kernel keeps long packed reductions just above its line (5x5 224 -> 112 at
+// 7350 pixels 13.0 us, here 16.0; at 8670 24.3 and 20.2).
 bool conv_tile_preferred(const ConvArgs &a, bool mfma) {
     const int64_t steps = tile_steps(a);
-    const int64_t quarter = ((int64_t)a.M + 63) / 64 * ((a.K + 63) / 64);
-    if (mfma && a.K % 16 == 0 && a.M < 1024 && quarter <= 256 && steps >= 32) return false;
-    if (mfma) return a.K % 16 != 0 || a.y_dt == HAWQ_S32 || (a.K > 64 && (a.K < 128 || (a.R * a.S == 1 && (a.K + 127) / 128 * 512 >= 5 * a.K))) || (steps >= 16 && tile_choice(a) == 0);
+    if (mfma) {
+        if (a.y_dt != HAWQ_S32 && a.M >= 448 && few_tiles(a) && !(is4(a.x_dt) && a.res != nullptr && a.K > 1024)) return true;
+        if (a.res != nullptr) return false;
+        if (a.K % 16 == 0 && a.M < 1024 && steps >= 32 && ((int64_t)a.M + 63) / 64 * ((a.K + 63) / 64) <= 256) return false;
+        return a.K % 16 != 0 || a.y_dt == HAWQ_S32 || (a.K > 64 && (a.K < 128 || (a.R * a.S == 1 && (a.K + 127) / 128 * 512 >= 5 * a.K))) || (steps >= 16 && tile_choice(a) == 0);
+    }
     return !(is4(a.x_dt) ? steps >= 20 && (int64_t)a.M * a.K <= 7 << 17 : steps >= 32 && (int64_t)a.M * a.K <= 5 << 17);
 }
 
@@ -395,12 +469,14 @@ hawq_status launch_conv_tile(const ConvArgs &a_in, int x_hi, hipStream_t s) {
     e.PQ = fast_div(a.P * a.Q);
     e.Q = fast_div(a.Q);
     e.vec = a.K % 4 == 0 && ((uintptr_t)a.y & 3) == 0;
-    switch (tile_choice(a)) {
-    case 0: return tile_launch<256, 256, 2, 4>(a, e, x_hi, s);
-    case 1: return tile_launch<128, 128, 4, 2>(a, e, x_hi, s);
-    case 2: return tile_launch<128, 64, 2, 2>(a, e, x_hi, s);
-    case 3: return tile_launch<64, 64, 2, 2>(a, e, x_hi, s);
-    default: return tile_launch<64, 32, 2, 1>(a, e, x_hi, s);
+    if (a.res != nullptr) return tile_launch<64, 64, 2, 2, true>(a, e, x_hi, s);   // (one form: larger launches stay with conv_mfma.hip)
+    const int choice = tile_choice(a);
+    switch (choice < 3 && few_tiles(a) ? 3 : choice) {
+    case 0: return tile_launch<256, 256, 2, 4, false>(a, e, x_hi, s);
+    case 1: return tile_launch<128, 128, 4, 2, false>(a, e, x_hi, s);
+    case 2: return tile_launch<128, 64, 2, 2, false>(a, e, x_hi, s);
+    case 3: return tile_launch<64, 64, 2, 2, false>(a, e, x_hi, s);
+    default: return tile_launch<64, 32, 2, 1, false>(a, e, x_hi, s);
     }
 }
 

@@ -1,5 +1,5 @@
-"""GPU parity of the tiled kernel with channels along the lanes: ragged channel counts, unsigned bytes above 127, INT32 results, at
-the edges of every tile it chooses from, bit-exact."""
+"""GPU parity of the tiled kernel with channels along the lanes: ragged channel counts, unsigned bytes above 127, INT32 results,
+identity shortcuts, at the edges of every tile it chooses from, bit-exact."""
 import numpy as np
 import pytest
 
@@ -107,3 +107,41 @@ def test_blocked_weights(hawq):
         want = oracle.conv2d_int(case["x"], case["w"], case["bias"], case["b"], case["c"], N=9, H=35, W=34, C=C, K=K, R=3, S=3, stride=1, pad=1,
                                  x_dt=x_dt, w_dt=w_dt, y_dt=x_dt, relu=1, y_lo=0, y_hi=hi)
         assert_same(y.cpu().numpy(), want, str((bits, C, K)))
+
+
+# (N, H, W, C, K, R, stride, bits, shortcut's type, what): 64x64 tiles with remainders in pixels and channels, one K-step and
+# many, channel counts of 4, 8 and 12 past a group of 16, results of either sign and width; what: "wide" (one channel's main and
+# another's shortcut parameters outside the narrow evaluation's range), "s" (signed result)
+_SHORTCUTS = [
+    (1, 56, 56, 64, 256, 1, 1, 8, oracle.U8, ""), (1, 56, 55, 64, 256, 1, 1, 8, oracle.S8, "wide"), (7, 29, 31, 128, 128, 3, 1, 8, oracle.U8, "s"),
+    (16, 35, 34, 96, 68, 1, 1, 8, oracle.U8, "wide"), (9, 33, 33, 48, 84, 3, 1, 8, oracle.S8, ""), (14, 33, 35, 80, 44, 1, 1, 8, oracle.U4, ""),
+    (1, 56, 56, 64, 256, 1, 1, 4, oracle.U4, ""), (5, 56, 55, 64, 64, 3, 1, 4, oracle.U4, "wide"), (12, 14, 14, 256, 256, 3, 1, 4, oracle.U8, ""),
+    (24, 35, 35, 96, 76, 1, 1, 4, oracle.S8, "s"), (20, 35, 35, 96, 92, 3, 2, 4, oracle.U4, "s"),
+]
+
+
+@pytest.mark.parametrize("shape", _SHORTCUTS)
+def test_identity_shortcut(hawq, shape):
+    from gpu_util import run_conv_gpu, assert_same
+    from test_gpu_conv import _scale_c
+    N, H, W, C, K, R, stride, bits, res_dt, what = shape
+    case = _scale_c(wl.conv_case(seed=sum(shape[:8]), N=N, H=H, W=W, C=C, K=K, R=R, S=R, stride=stride, pad=R // 2, bits=bits), bits)
+    g = np.random.default_rng(K + N)
+    P, Q = (H + 2 * (R // 2) - R) // stride + 1, (W + 2 * (R // 2) - R) // stride + 1
+    rl, rh = {oracle.U8: (0, 255), oracle.S8: (-128, 127), oracle.U4: (0, 15)}[res_dt]
+    res = g.integers(rl, rh + 1, size=(N, P, Q, K))
+    case["residual"] = wl.pack_nibbles(res) if res_dt == oracle.U4 else res.astype(np.int8 if res_dt == oracle.S8 else np.uint8)
+    # a shortcut of about the range of the result: rescaled by 1/2 .. 1 (8-bit results), to a quarter of that for packed ones
+    case["res_b"] = g.integers(1 << 14, 1 << 15, size=K).astype(np.int32)
+    case["res_c"] = np.full(K, {(8, oracle.U4): 12, (4, oracle.U8): 19, (4, oracle.S8): 19}.get((bits, res_dt), 15), np.uint8)
+    if what == "wide":
+        case["b"][K // 2], case["c"][K // 2] = (1 << 31) - 1, case["c"][K // 2] + 16
+        case["res_b"][1], case["res_c"][1] = (1 << 31) - 1, 31
+    signed = what == "s"
+    x_dt, w_dt = (hawq.U8, hawq.S8) if bits == 8 else (hawq.U4, hawq.S4)
+    y_dt = {(8, True): hawq.S8, (8, False): hawq.U8, (4, True): hawq.S4, (4, False): hawq.U4}[bits, signed]
+    lo, hi = {(8, True): (-128, 127), (8, False): (0, 255), (4, True): (-8, 7), (4, False): (0, 15)}[bits, signed]
+    got, want = run_conv_gpu(case, x_dt, w_dt, y_dt, res_dt=res_dt, y_lo=lo, y_hi=hi, relu=0 if signed else 1, x_hi=127 if bits == 8 else 0)
+    assert_same(got, want, str(shape))
+    v = want.astype(np.int32) if bits == 8 else oracle.unpack(want, y_dt)
+    assert len(np.unique(v)) > 8
