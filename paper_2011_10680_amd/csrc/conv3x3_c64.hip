@@ -45,7 +45,7 @@ conv3x3_c64_kernel(const ConvArgs a, const int n_tiles) {
     const int W = a.W, HW = a.H * a.W;
     const int n_in = a.N * HW;                  // input pixels = output pixels
     const int prows = BP + 2 * W + 2;           // rows in use (<= PROWS - 1, checked by the host)
-    const TileWalk walk = xcd_walk(blockIdx.x, gridDim.x, n_tiles);
+    const TileWalk walk = xcd_walk(blockIdx.x, gridDim.x, n_tiles, xcd_eighths(a.M));
     if (walk.first >= walk.end) return;         // (the whole workgroup, before any barrier: its XCD's eighth has fewer tiles than workgroups)
 
     const __amdgpu_buffer_rsrc_t rsrc_w = __builtin_amdgcn_make_buffer_rsrc((void *)a.w, 0, 64 * 9 * ROWB, 0x00020000);

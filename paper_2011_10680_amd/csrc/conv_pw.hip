@@ -46,7 +46,7 @@ conv_pw_kernel(const ConvArgs a, const int n_ct, const int n_seq, const int n_gr
     // workgroups that share pixels (consecutive channel tiles of one sequence) stay on one XCD and its L2
     const int g = (int)(blockIdx.x >> 3) * 4 + wave;
     const int ct = g % n_ct, seq = g / n_ct;
-    const TileWalk gr = xcd_walk(blockIdx.x & 7 | (uint32_t)seq << 3, (uint32_t)n_seq, n_groups);   // (seq: within the XCD)
+    const TileWalk gr = xcd_walk(blockIdx.x & 7 | (uint32_t)seq << 3, (uint32_t)n_seq, n_groups, xcd_eighths(a.M));   // (seq: within the XCD)
     if (seq >= n_seq >> 3 || gr.first >= gr.end) return;   // whole wave; the kernel has no workgroup barrier
     const int rho = lane & 31, khalf = lane >> 5;
     const int k0 = ct * 32;
@@ -294,7 +294,7 @@ conv_pws_kernel(const ConvArgs a, const int n_ct, const int n_seq, const int n_g
     // of a workgroup share `seq` (so every wave reaches every barrier the same number of times)
     const int g = (int)(blockIdx.x >> 3) * 4 + wave;
     const int ct = g % n_ct, seq = g / n_ct;
-    const TileWalk gr = xcd_walk(blockIdx.x & 7 | (uint32_t)seq << 3, (uint32_t)n_seq, n_groups);   // (seq: within the XCD)
+    const TileWalk gr = xcd_walk(blockIdx.x & 7 | (uint32_t)seq << 3, (uint32_t)n_seq, n_groups, xcd_eighths(a.M));   // (seq: within the XCD)
     const int rho = lane & 31, khalf = lane >> 5;
     const int k0 = ct * 32;
     const int Cb = a.C;
@@ -486,7 +486,7 @@ conv_pws_dual_kernel(const ConvArgs a, const int n_ct, const int n_seq, const in
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g = (int)(blockIdx.x >> 3) * 4 + wave;
     const int ct = g % n_ct, seq = g / n_ct;        // the four waves of a workgroup share `seq` (n_ct is a multiple of 4)
-    const TileWalk gr = xcd_walk(blockIdx.x & 7 | (uint32_t)seq << 3, (uint32_t)n_seq, n_groups);   // (seq: within the XCD)
+    const TileWalk gr = xcd_walk(blockIdx.x & 7 | (uint32_t)seq << 3, (uint32_t)n_seq, n_groups, xcd_eighths(a.M));   // (seq: within the XCD)
     const int rho = lane & 31, khalf = lane >> 5;
     const int k0 = ct * 32;
 

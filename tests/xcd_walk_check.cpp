@@ -25,6 +25,14 @@ int main() {
             }
             for (int t = 0; t < n; ++t)
                 if (owner[t] < 0 || (t > 0 && owner[t] < owner[t - 1])) { std::printf("tile %d of %d, grid %u\n", t, n, gx); return 1; }
+            std::vector<int> turns(n, 0);   // the other map: each tile once, in as many rounds
+            for (uint32_t b = 0; b < gx; ++b) {
+                const TileWalk w = xcd_walk(b, gx, n, false);
+                for (int t = w.first; t < w.end; t += w.step)
+                    if (t < 0 || t >= n || turns[t]++ != 0) { std::printf("turns: tile %d of %d, workgroup %u of %u\n", t, n, b, gx); return 1; }
+            }
+            for (int t = 0; t < n; ++t)
+                if (turns[t] != 1) { std::printf("turns: tile %d of %d, grid %u\n", t, n, gx); return 1; }
             ++walked;
         }
     std::printf("%d\n", walked);
