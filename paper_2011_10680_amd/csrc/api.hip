@@ -235,12 +235,15 @@ hawq_status dispatch_conv_dual(const ConvArgs &a, int x_hi, int xs_hi, hipStream
     const bool sk = conv_sk_dual_eligible(a, x_hi, xs_hi);
     if (tile_override() == 0 && sk && conv_sk_small(a)) return launch_conv_sk(a, x_hi, s);
     if (conv_pws_dual_eligible(a, x_hi, xs_hi)) return launch_conv_pws_dual(a, s);
+    const bool tile = tile_override() == 0 && conv_tile_dual_eligible(a, x_hi, xs_hi);
     if (tile_override() == 0 && a.w_f != nullptr && a.ws_f != nullptr) {
         Rp1Args r1;
         if (make_rp1_args(a, x_hi, xs_hi, r1)) return launch_conv_rp1(r1, s);
     }
+    if (tile && conv_tile_dual_preferred(a)) return launch_conv_tile(a, x_hi, s);
     if (conv_mfma_dual_eligible(a, x_hi, xs_hi)) return launch_conv_mfma_dual(a, s);
     if (sk) return launch_conv_sk(a, x_hi, s);
+    if (tile) return launch_conv_tile(a, x_hi, s);
     return launch_conv_direct(a, s);
 }
 

@@ -13,7 +13,8 @@
 // (row >> 2) & 3 on the source side, which makes every fragment read free of bank conflicts.  One barrier per step.  Chunks past
 // the reduction's end read as zeros on the pixel side, so what the weight side then holds does not matter.
 //
-// XF: unsigned bytes above 127 are multiplied as x - 128 (one XOR per dword of a fragment); 128 times the sum of a channel's weights
+// RES, DUAL: an identity shortcut, read as the results are stored; a second convolution (1x1) whose steps follow the first one's, with
+// sums of its own.  XF: unsigned bytes above 127 are multiplied as x - 128 (one XOR per dword of a fragment); 128 times the sum of a channel's weights
 // is added at the end, the sums formed by dot products on the vector ALU from the fragments the MFMAs read (so that padding and
 // ragged ends cancel exactly).  FORM 1: packed 4-bit operands, split into nibbles between fragment read and MFMA, weights kept as 16 w.
 //
@@ -34,7 +35,7 @@ struct TileArgs {
 };
 
 // BM x BN (pixels x channels) per workgroup of WM x WN waves
-template <int BM, int BN, int WM, int WN, int FORM, bool XF, bool TAPS, bool RES>
+template <int BM, int BN, int WM, int WN, int FORM, bool XF, bool TAPS, bool RES, bool DUAL>
 __global__ void __launch_bounds__(WM *WN * 64) __attribute__((amdgpu_waves_per_eu(BM * BN / (WM * WN) >= 64 * 64 ? 2 : 3)))
 conv_tile_kernel(const ConvArgs a, const TileArgs e) {
     constexpr int NW = WM * WN;                             // waves
@@ -70,9 +71,16 @@ conv_tile_kernel(const ConvArgs a, const TileArgs e) {
     const int wstep = tiled ? 4096 : 64;
     const __amdgpu_buffer_rsrc_t rs_w = __builtin_amdgcn_make_buffer_rsrc((void *)(tiled ? a.w_t : a.w), 0, tiled ? (a.K + 63) / 64 * steps * 4096 : a.K * row_b, 0x00020000);
 
+    // DUAL: the steps after the main branch's are the shortcut convolution's, a 1x1 window without padding
+    const int Csb = DUAL ? (FORM == 0 ? a.Cs : a.Cs / 2) : 0;
+    const int n_chs = Csb >> 4, steps_s = (n_chs + 3) >> 2, total = steps + steps_s;
+    const __amdgpu_buffer_rsrc_t rs_xs = __builtin_amdgcn_make_buffer_rsrc((void *)(DUAL ? a.xs : a.x), 0, DUAL ? a.N * a.Hs * a.Ws * Csb : 0, 0x00020000);
+    const bool tiled_s = DUAL && a.ws_t != nullptr;
+    const __amdgpu_buffer_rsrc_t rs_ws = __builtin_amdgcn_make_buffer_rsrc((void *)(DUAL ? (tiled_s ? a.ws_t : a.ws) : a.w), 0, tiled_s ? (a.K + 63) / 64 * steps_s * 4096 : a.K * Csb, 0x00020000);
+
     // ---- this lane's rows of a stage: instruction i fills rows 16 i .. 16 i + 15, four lanes each ----
     const int c4 = (lane & 3) ^ ((lane >> 4) & 3);          // the chunk the swizzle places at the lane's position
-    uint32_t xoff[NX], woff[NB];
+    uint32_t xoff[NX], woff[NB], xsoff[DUAL ? NX : 1], wsoff[DUAL ? NB : 1];
     int ih0[NX], iw0[NX];
 #pragma unroll
     for (int j = 0; j < NX; ++j) {
@@ -86,13 +94,31 @@ conv_tile_kernel(const ConvArgs a, const TileArgs e) {
             if (TAPS) ih0[j] = 1 << 30;                     // (fails the bounds test of every tap)
             else xoff[j] = kInvalid;
         }
+        if constexpr (DUAL)
+            xsoff[j] = m >= (uint32_t)a.M ? kInvalid : (uint32_t)((((int)nn * a.Hs + (int)p * a.stride_sh) * a.Ws + (int)q * a.stride_sw) * Csb);
     }
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
         const int n = n0 + (j * NW + wave) * 16 + (lane >> 2);
         woff[j] = n >= a.K ? kInvalid : tiled ? (uint32_t)((n >> 6) * steps * 4096 + (n & 63) * 64 + c4 * 16) : (uint32_t)(n * row_b + c4 * 16);
+        if constexpr (DUAL)
+            wsoff[j] = n >= a.K ? kInvalid : tiled_s ? (uint32_t)((n >> 6) * steps_s * 4096 + (n & 63) * 64 + c4 * 16) : (uint32_t)(n * Csb + c4 * 16);
     }
     auto fetch = [&](int step, auto bc) {
+        if (DUAL && step >= steps) {
+            if constexpr (DUAL) {
+                const uint32_t ks = (uint32_t)((step - steps) * 4 + c4);
+#pragma unroll
+                for (int j = 0; j < NX; ++j)
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_xs, (__attribute__((address_space(3))) void *)(buf(bc) + (j * NW + wave) * 1024), 16,
+                                                             (int)(ks < (uint32_t)n_chs && xsoff[j] != kInvalid ? xsoff[j] + ks * 16 : kInvalid), 0, 0, 0);
+#pragma unroll
+                for (int j = 0; j < NB; ++j)
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_ws, (__attribute__((address_space(3))) void *)(buf(bc) + BM * 64 + (j * NW + wave) * 1024), 16,
+                                                             (int)(wsoff[j] == kInvalid ? kInvalid : wsoff[j] + (step - steps) * (tiled_s ? 4096 : 64)), 0, 0, 0);
+            }
+            return;
+        }
         const uint32_t kc = (uint32_t)(step * 4 + c4);
         const bool in = kc < (uint32_t)n_chunks;
         uint32_t off, r = 0, s = 0;
@@ -144,7 +170,8 @@ conv_tile_kernel(const ConvArgs a, const TileArgs e) {
             }
     }
     // ---- the lane's channels' parameters ----
-    int32_t bias[TN], pb[TN], pcs[TN], prb[TN], prc[TN];
+    int32_t bias[TN], pb[TN], pcs[TN], prb[TN], prc[TN], sbias[DUAL ? TN : 1], sb[DUAL ? TN : 1], scs[DUAL ? TN : 1];
+    const bool mid = DUAL && a.mid_s8;                    // the shortcut's own INT8 result, rescaled once more
 #pragma unroll
     for (int tn = 0; tn < TN; ++tn) {
         const int ch = n0 + (wn * TN + tn) * 32 + col;
@@ -154,6 +181,13 @@ conv_tile_kernel(const ConvArgs a, const TileArgs e) {
         if constexpr (RES) {
             prb[tn] = ch < a.K ? a.res_b[ch] : 0;
             prc[tn] = ch < a.K ? a.res_c[ch] : 1;
+        }
+        if constexpr (DUAL) {
+            sbias[tn] = ch < a.K ? a.bias_s[ch] : 0;
+            sb[tn] = ch < a.K ? a.b_s[ch] : 0;
+            scs[tn] = ch < a.K ? a.c_s[ch] : 1;
+            prb[tn] = mid && ch < a.K ? a.res_b[ch] : 0;
+            prc[tn] = mid && ch < a.K ? a.res_c[ch] : 1;
         }
     }
 
@@ -172,7 +206,7 @@ conv_tile_kernel(const ConvArgs a, const TileArgs e) {
             wf[tn][kk] = BM * 64 + row * 64 + (((kk * 2 + half) ^ ((row >> 2) & 3)) << 4);
         }
     }
-    v16i acc[TM][TN];
+    v16i acc[TM][TN], accm[DUAL ? TM : 1][DUAL ? TN : 1];   // (DUAL: the main branch's sums move to accm when its steps are done)
     int32_t wsum[XF ? TN : 1] = {};
 #pragma unroll
     for (int tm = 0; tm < TM; ++tm)
@@ -222,6 +256,18 @@ conv_tile_kernel(const ConvArgs a, const TileArgs e) {
     auto iteration = [&](int step, auto ic) {
         constexpr int ph = decltype(ic)::value;
         v4i x1[TM], w1[TN];
+        if constexpr (DUAL) {
+            if (step == steps) {
+#pragma unroll
+                for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+                    for (int tn = 0; tn < TN; ++tn) {
+                        accm[tm][tn] = acc[tm][tn];
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) acc[tm][tn][i] = 0;
+                    }
+            }
+        }
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm) x1[tm] = *(const v4i *)(buf(ic) + xf[tm][1]);
 #pragma unroll
@@ -237,19 +283,19 @@ conv_tile_kernel(const ConvArgs a, const TileArgs e) {
     };
     for (int step = 0;; step += NBUF) {
         iteration(step, std::integral_constant<int, 0>{});
-        if (step + 1 >= steps) break;
+        if (step + 1 >= total) break;
         iteration(step + 1, std::integral_constant<int, 1>{});
-        if (step + 2 >= steps) break;
+        if (step + 2 >= total) break;
         iteration(step + 2, std::integral_constant<int, 2>{});
-        if (step + 3 >= steps) break;
+        if (step + 3 >= total) break;
         iteration(step + 3, std::integral_constant<int, 3>{});
-        if (step + 4 >= steps) break;
+        if (step + 4 >= total) break;
     }
 
     // ---- epilogue: a lane has channel `col` of each tile and, of half h, pixels 8 j + 4 h + k (register 4 j + k) ----
     const bool rq = a.b != nullptr;
     bool narrow = true;
-    int32_t bs[TN];
+    int32_t bs[TN], ss[DUAL ? TN : 1];
 #pragma unroll
     for (int tn = 0; tn < TN; ++tn) {
         if constexpr (XF) {
@@ -259,6 +305,10 @@ conv_tile_kernel(const ConvArgs a, const TileArgs e) {
         narrow &= pcs[tn] <= 32 && ((uint32_t)pb[tn] >> ((pcs[tn] - 1) & 31)) == 0;
         bs[tn] = (int32_t)((uint32_t)pb[tn] << ((32 - pcs[tn]) & 31));
         if constexpr (RES) narrow &= prc[tn] <= 31 && (uint32_t)prb[tn] < 1u << 22;   // (r rb + 2^(rc-1)) >> rc in 32 bits
+        if constexpr (DUAL) {
+            narrow &= scs[tn] <= 32 && ((uint32_t)sb[tn] >> ((scs[tn] - 1) & 31)) == 0 && prc[tn] <= 31 && (uint32_t)prb[tn] < 1u << 22;
+            ss[tn] = (int32_t)((uint32_t)sb[tn] << ((32 - scs[tn]) & 31));
+        }
     }
     narrow = __all(narrow);
     int32_t lo = a.lo, hi = a.hi;
@@ -280,7 +330,8 @@ conv_tile_kernel(const ConvArgs a, const TileArgs e) {
     for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
         for (int tn = 0; tn < TN; ++tn) {
-            v16i v = acc[tm][tn];
+            v16i v = DUAL ? accm[DUAL ? tm : 0][DUAL ? tn : 0] : acc[tm][tn];
+            v16i u = acc[tm][tn];                         // (DUAL: the shortcut's sums)
             uint32_t rw[4] = {0, 0, 0, 0};                // shortcut bytes of the lane's channel, pixels 8 j + 4 half + 0 .. 3
             if constexpr (RES)
 #pragma unroll
@@ -288,6 +339,11 @@ conv_tile_kernel(const ConvArgs a, const TileArgs e) {
             if constexpr (FORM != 0) v >>= 4;
 #pragma unroll
             for (int i = 0; i < 16; ++i) v[i] += bias[tn];
+            if constexpr (DUAL) {
+                if constexpr (FORM != 0) u >>= 4;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) u[i] += sbias[tn];
+            }
             if (rq) {
                 if (__builtin_expect(narrow, 1)) {
                     int32_t s = bs[tn];
@@ -299,6 +355,16 @@ conv_tile_kernel(const ConvArgs a, const TileArgs e) {
                             const int32_t r = res_signed ? __builtin_amdgcn_sbfe((int32_t)rw[i >> 2], 8 * (i & 3), 8) : (int32_t)__builtin_amdgcn_ubfe(rw[i >> 2], 8 * (i & 3), 8);
                             y += (__mul24(r, prb[tn]) + (int32_t)(1u << ((prc[tn] - 1) & 31))) >> prc[tn];
                         }
+                        if constexpr (DUAL) {
+                            int32_t z = ss[tn];
+                            asm volatile("" : "+v"(z));
+                            int32_t r = (int32_t)(((int64_t)u[i] * (int64_t)z + round) >> 32);
+                            if (mid) {
+                                r = r < -128 ? -128 : r > 127 ? 127 : r;
+                                r = (__mul24(r, prb[tn]) + (int32_t)(1u << ((prc[tn] - 1) & 31))) >> prc[tn];
+                            }
+                            y += r;
+                        }
                         asm("v_med3_i32 %0, %1, %2, %3" : "=v"(v[i]) : "v"(y), "v"(lo), "v"(hi));
                     }
                 } else {
@@ -309,6 +375,12 @@ conv_tile_kernel(const ConvArgs a, const TileArgs e) {
                             w += rq64(res_signed ? (int32_t)(int8_t)rw[0] : (int32_t)(rw[0] & 0xff), prb[tn], prc[tn]);
                             rw[0] = rw[0] >> 8 | rw[1] << 24; rw[1] = rw[1] >> 8 | rw[2] << 24;
                             rw[2] = rw[2] >> 8 | rw[3] << 24; rw[3] >>= 8;
+                        }
+                        if constexpr (DUAL) {
+                            int64_t r = rq64(u[0], sb[tn], scs[tn]);
+                            if (mid) r = rq64(clamp64(r, -128, 127), prb[tn], prc[tn]);
+                            w += r;
+                            u = __builtin_shufflevector(u, u, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15, 0);
                         }
                         const int32_t y = clamp64(w, a.lo, a.hi);
                         v = __builtin_shufflevector(v, v, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15, 0);
@@ -376,18 +448,32 @@ bool conv_tile_eligible(const ConvArgs &a, int x_hi) {
     return (int64_t)a.N * a.H * a.W * a.C + 4 * red < edge;
 }
 
-template <int BM, int BN, int WM, int WN, bool RES>
+bool conv_tile_dual_eligible(const ConvArgs &a, int x_hi, int xs_hi) {
+    if (a.xs == nullptr || a.res != nullptr || a.b == nullptr || a.y_dt == HAWQ_S32 || a.K % 4 != 0) return false;
+    if (a.mid_s8 && (a.res_b == nullptr || a.res_c == nullptr)) return false;
+    ConvArgs m = a, t = a;                                  // each branch as a layer of its own
+    m.xs = t.xs = nullptr;
+    t.x = a.xs; t.w = a.ws; t.bias = a.bias_s; t.b = a.b_s; t.H = a.Hs; t.W = a.Ws; t.C = a.Cs; t.R = t.S = 1; t.x_dt = a.xs_dt; t.w_dt = a.ws_dt;
+    if (is4(a.x_dt) != is4(a.xs_dt) || (a.x_dt == HAWQ_U8 && x_hi > 127) || (a.xs_dt == HAWQ_U8 && xs_hi > 127)) return false;
+    if (((uintptr_t)a.y | (uintptr_t)a.bias_s | (uintptr_t)a.b_s | (uintptr_t)(a.mid_s8 ? a.res_b : nullptr)) & 3) return false;
+    return conv_tile_eligible(m, x_hi) && conv_tile_eligible(t, xs_hi);
+}
+
+template <int BM, int BN, int WM, int WN, bool RES, bool DUAL = false>
 static hawq_status tile_launch(const ConvArgs &a, TileArgs e, int x_hi, hipStream_t s) {
     e.n_nt = (a.K + BN - 1) / BN;
     const uint32_t nb = e.n_nt * (uint32_t)((a.M + BM - 1) / BM);
     constexpr int T = WM * WN * 64;
     const bool xf = a.x_dt == HAWQ_U8 && x_hi > 127, taps = a.R * a.S > 1 || a.pad_h != 0 || a.pad_w != 0;
     auto go = [&](auto kernel) { kernel<<<nb, T, 0, s>>>(a, e); };
-    if (is4(a.x_dt)) taps ? go(conv_tile_kernel<BM, BN, WM, WN, 1, false, true, RES>) : go(conv_tile_kernel<BM, BN, WM, WN, 1, false, false, RES>);
+    if constexpr (DUAL) {
+        if (is4(a.x_dt)) taps ? go(conv_tile_kernel<BM, BN, WM, WN, 1, false, true, false, true>) : go(conv_tile_kernel<BM, BN, WM, WN, 1, false, false, false, true>);
+        else taps ? go(conv_tile_kernel<BM, BN, WM, WN, 0, false, true, false, true>) : go(conv_tile_kernel<BM, BN, WM, WN, 0, false, false, false, true>);
+    } else if (is4(a.x_dt)) taps ? go(conv_tile_kernel<BM, BN, WM, WN, 1, false, true, RES, false>) : go(conv_tile_kernel<BM, BN, WM, WN, 1, false, false, RES, false>);
     else if constexpr (!RES) {
-        if (xf) taps ? go(conv_tile_kernel<BM, BN, WM, WN, 0, true, true, RES>) : go(conv_tile_kernel<BM, BN, WM, WN, 0, true, false, RES>);
-        else taps ? go(conv_tile_kernel<BM, BN, WM, WN, 0, false, true, RES>) : go(conv_tile_kernel<BM, BN, WM, WN, 0, false, false, RES>);
-    } else taps ? go(conv_tile_kernel<BM, BN, WM, WN, 0, false, true, RES>) : go(conv_tile_kernel<BM, BN, WM, WN, 0, false, false, RES>);
+        if (xf) taps ? go(conv_tile_kernel<BM, BN, WM, WN, 0, true, true, RES, false>) : go(conv_tile_kernel<BM, BN, WM, WN, 0, true, false, RES, false>);
+        else taps ? go(conv_tile_kernel<BM, BN, WM, WN, 0, false, true, RES, false>) : go(conv_tile_kernel<BM, BN, WM, WN, 0, false, false, RES, false>);
+    } else taps ? go(conv_tile_kernel<BM, BN, WM, WN, 0, false, true, RES, false>) : go(conv_tile_kernel<BM, BN, WM, WN, 0, false, false, RES, false>);
     return check_launch();
 }
 
@@ -459,6 +545,18 @@ bool conv_tile_preferred(const ConvArgs &a, bool mfma) {
     return !(is4(a.x_dt) ? steps >= 20 && (int64_t)a.M * a.K <= 7 << 17 : steps >= 32 && (int64_t)a.M * a.K <= 5 << 17);
 }
 
+// Two convolutions in one launch.  Packed operands always, the direct kernel is what else takes them (56 x 56, 64 -> 256 plus 64, batch
+// 1 267 us, here 5.4, batch 64 11700 and 63).  Bytes with few tiles, as few_tiles counts them over both branches' steps; conv_mfma.hip
+// keeps a larger tile's sums twice and has one workgroup of it on a CU (56 x 56, 64 -> 256 plus 64, batch 1 8.2 -> 5.2 us; 28 x 28, 128 ->
+// 512 plus 256 / 2, batch 2 9.5 -> 6.2, 8 10.6 -> 9.4; 3x3 256 -> 256 at 14 x 14 plus 128 / 2, batch 16 24.2 -> 19.1, 48 24.4 and 26.4).
+// Where the main branch's term fits 16 bits its eight-wave form stays (ResNet18 at batch 32 207 us, 213 with this one).
+bool conv_tile_dual_preferred(const ConvArgs &a) {
+    if (is4(a.x_dt)) return true;
+    if (a.dual16) return false;
+    const int64_t steps = tile_steps(a) + (a.Cs + 63) / 64, tiles = ((int64_t)a.M + 63) / 64 * ((a.K + 63) / 64);
+    return tiles <= (steps < 16 ? 768 : steps < 64 ? 512 : 0);
+}
+
 hawq_status launch_conv_tile(const ConvArgs &a_in, int x_hi, hipStream_t s) {
     ConvArgs a = a_in;
     if (a.M == 0) return HAWQ_OK;
@@ -469,6 +567,10 @@ hawq_status launch_conv_tile(const ConvArgs &a_in, int x_hi, hipStream_t s) {
     e.PQ = fast_div(a.P * a.Q);
     e.Q = fast_div(a.Q);
     e.vec = a.K % 4 == 0 && ((uintptr_t)a.y & 3) == 0;
+    if (a.xs != nullptr) {
+        if (a.Cs % (is4(a.x_dt) ? 128 : 64) != 0) a.ws_t = nullptr;
+        return tile_launch<64, 64, 2, 2, false, true>(a, e, x_hi, s);
+    }
     if (a.res != nullptr) return tile_launch<64, 64, 2, 2, true>(a, e, x_hi, s);   // (one form: larger launches stay with conv_mfma.hip)
     const int choice = tile_choice(a);
     switch (choice < 3 && few_tiles(a) ? 3 : choice) {

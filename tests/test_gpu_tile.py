@@ -1,5 +1,5 @@
 """GPU parity of the tiled kernel with channels along the lanes: ragged channel counts, unsigned bytes above 127, INT32 results,
-identity shortcuts, at the edges of every tile it chooses from, bit-exact."""
+identity shortcuts, a second convolution, at the edges of every tile it chooses from, bit-exact."""
 import numpy as np
 import pytest
 
@@ -144,4 +144,26 @@ def test_identity_shortcut(hawq, shape):
     got, want = run_conv_gpu(case, x_dt, w_dt, y_dt, res_dt=res_dt, y_lo=lo, y_hi=hi, relu=0 if signed else 1, x_hi=127 if bits == 8 else 0)
     assert_same(got, want, str(shape))
     v = want.astype(np.int32) if bits == 8 else oracle.unpack(want, y_dt)
+    assert len(np.unique(v)) > 8
+
+
+# (N, H, C, K, R, Cs, stride of the shortcut, bits, wide, result): one and several steps of either branch, remainders in pixels and
+# channels, chunks that end within a step, signed results
+_DUAL = [
+    (1, 56, 64, 256, 1, 64, 1, 8, False, oracle.U8), (3, 28, 128, 512, 1, 256, 2, 8, True, oracle.U8), (7, 28, 128, 128, 3, 64, 2, 8, False, oracle.S8),
+    (9, 23, 80, 116, 1, 48, 2, 8, False, oracle.U8), (9, 31, 48, 84, 3, 16, 1, 8, True, oracle.U4), (1, 56, 64, 256, 1, 64, 1, 4, False, oracle.U4),
+    (2, 14, 256, 1024, 1, 512, 2, 4, True, oracle.U4), (2, 5, 32, 36, 1, 32, 2, 4, False, oracle.U8), (3, 17, 96, 76, 3, 160, 2, 4, True, oracle.S4),
+]
+
+
+@pytest.mark.parametrize("shape", _DUAL)
+def test_two_convolutions(hawq, shape):
+    from gpu_util import assert_same
+    from test_gpu_dual import _case, _run
+    N, H, C, K, R, Cs, ss, bits, wide, y_dt = shape
+    t = _case(sum(shape[:8]), N, H, C, K, R, Cs, ss, bits=bits, wide=wide)
+    lo, hi = {oracle.U8: (0, 255), oracle.S8: (-128, 127), oracle.U4: (0, 15), oracle.S4: (-8, 7)}[y_dt]
+    got, want = _run(hawq, t, y_dt, 0 if lo else 1, lo, hi)
+    assert_same(got, want, str(shape))
+    v = want.astype(np.int32) if y_dt in (oracle.U8, oracle.S8) else oracle.unpack(want, y_dt)
     assert len(np.unique(v)) > 8
