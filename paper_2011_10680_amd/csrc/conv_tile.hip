@@ -549,12 +549,12 @@ bool conv_tile_preferred(const ConvArgs &a, bool mfma) {
 // 1 267 us, here 5.4, batch 64 11700 and 63).  Bytes with few tiles, as few_tiles counts them over both branches' steps; conv_mfma.hip
 // keeps a larger tile's sums twice and has one workgroup of it on a CU (56 x 56, 64 -> 256 plus 64, batch 1 8.2 -> 5.2 us; 28 x 28, 128 ->
 // 512 plus 256 / 2, batch 2 9.5 -> 6.2, 8 10.6 -> 9.4; 3x3 256 -> 256 at 14 x 14 plus 128 / 2, batch 16 24.2 -> 19.1, 48 24.4 and 26.4).
-// Where the main branch's term fits 16 bits its eight-wave form stays (ResNet18 at batch 32 207 us, 213 with this one).
+// Where the main branch's term fits 16 bits its eight-wave form is better than that: up to a tile per CU (ResNet50 at batch 1 223.4 ->
+// 221.0 us, ResNet18 at 8 140.3 -> 138.1; at 32, with 392 tiles of 38 steps, 207 and 213).
 bool conv_tile_dual_preferred(const ConvArgs &a) {
     if (is4(a.x_dt)) return true;
-    if (a.dual16) return false;
     const int64_t steps = tile_steps(a) + (a.Cs + 63) / 64, tiles = ((int64_t)a.M + 63) / 64 * ((a.K + 63) / 64);
-    return tiles <= (steps < 16 ? 768 : steps < 64 ? 512 : 0);
+    return tiles <= (a.dual16 ? (steps < 32 ? 256 : 0) : steps < 16 ? 768 : steps < 64 ? 512 : 0);
 }
 
 hawq_status launch_conv_tile(const ConvArgs &a_in, int x_hi, hipStream_t s) {
