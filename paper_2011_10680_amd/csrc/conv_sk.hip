@@ -1,5 +1,6 @@
-// Split-reduction implicit GEMM: the kernel for launches too small to fill the chip, and for the shapes whose channel
-// count no 64-channel K-step divides.
+// Split-reduction implicit GEMM: the kernel for launches too small to fill the chip (and for a packed channel count that is a
+// multiple of 16 only, and long packed reductions just above its line, at any size; conv_tile.hip takes the other large launches whose
+// channel count no 64-channel K-step divides).
 //
 // Same GEMM view as conv_mfma.hip (rows = output channels, columns = output pixels, reduction index = (r, s, c)), another
 // division of labour.  What bounds a small layer is latency: with few output tiles every workgroup walks its whole
@@ -406,7 +407,8 @@ static hawq_status sk_launch(const ConvArgs &a, SkArgs e, bool xf, hipStream_t s
 // streaming and resident-pixel kernels win: 56x56 1x1 64 -> 256 + shortcut at batch 4 16.3 (6.1), 28x28 128 -> 512 9.5 (6.5).
 // One kind above 2^18 outputs is the tiled kernel's: a long 8-bit reduction over fewer than 1024 pixels, where that one takes 64 x 64
 // tiles with a ring of eight -- unless the blocked copy of the weights, which both read, is there (without it, 7x7 2048 -> 512 at
-// batch 16 9.7 us here, 8.6 there; 14x14 1024 -> 512 at 4 7.6 and 6.9; 128 x 4096 -> 4096 14.8 and 13.5).
+// batch 16 9.7 us here, 8.6 there; 14x14 1024 -> 512 at 4 7.6 and 6.9; 128 x 4096 -> 4096 14.8 and 13.5).  Others are conv_tile.hip's
+// (conv_tile_over_sk).
 bool conv_sk_small(const ConvArgs &a) {
     const int64_t out = (int64_t)a.M * a.K;
     const bool tiled = !is4(a.x_dt) && a.xs == nullptr && a.w_t == nullptr && a.M < 1024 && (int64_t)a.R * a.S * a.C >= 1024 && a.C % 64 == 0 && a.K % 16 == 0;

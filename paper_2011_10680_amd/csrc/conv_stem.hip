@@ -133,7 +133,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) c
 // never written to or read from HBM -- and never requantised either.  Requantisation (Section 3.1) and the clamps are
 // non-decreasing in the accumulator for every multiplier the interface admits (b >= 0), so the maximum commutes with
 // them exactly: the kernel takes the maximum over a window's INT32 accumulators (+ the channel's bias, the same for every
-// pixel) and requantises once per *pooled* output, 4.5 times fewer quarter-rate 64-bit multiplies than conv1 has outputs.
+// pixel) and requantises once per *pooled* output, 4.5 times fewer 64-bit multiplies than conv1 has outputs.
 //
 // For that a pooling window's nine accumulators must meet in one lane.  The MFMA leaves a lane with one column and
 // sixteen rows of the 32x32 result, so here the *pixels* are the row operand and the channels the column operand (the
