@@ -57,7 +57,7 @@ def solve(omega, size=None, bops=None, latency=None, size_limit=None, bops_limit
     from scipy.optimize import Bounds, LinearConstraint, milp
     omega = np.asarray(omega, dtype=np.float64)
     L, B = omega.shape
-    A, lo, hi = [], [], []
+    A, lo, hi, limits = [], [], [], []
     for i in range(L):                                   # exactly one choice per group
         row = np.zeros(L * B)
         row[i * B:(i + 1) * B] = 1
@@ -67,17 +67,25 @@ def solve(omega, size=None, bops=None, latency=None, size_limit=None, bops_limit
             continue
         if tab is None:
             raise ValueError("a limit needs its cost table")
-        A.append(np.asarray(tab, dtype=np.float64).reshape(-1)); lo.append(-np.inf); hi.append(float(lim))
+        tab = np.asarray(tab, dtype=np.float64).reshape(-1)
+        limits.append((tab.reshape(L, B), float(lim)))
+        scale = 1e3 / max(np.abs(tab).max(), 1e-300)     # (the solver's feasibility tolerance is absolute, 1e-6)
+        A.append(tab * scale); lo.append(-np.inf); hi.append(float(lim) * scale)
     ub = np.ones(L * B)
     lb = np.zeros(L * B)
     for i, j in (fixed or {}).items():
         lb[i * B + j] = 1
-    res = milp(c=omega.reshape(-1), integrality=np.ones(L * B), bounds=Bounds(lb, ub),
-               constraints=LinearConstraint(np.array(A), np.array(lo), np.array(hi)))
-    if not res.success:
-        raise ValueError("bit selection infeasible under the given limits: " + str(res.message))
-    x = np.rint(res.x).reshape(L, B)
-    choice = x.argmax(axis=1)
+    while True:
+        res = milp(c=omega.reshape(-1), integrality=np.ones(L * B), bounds=Bounds(lb, ub),
+                   constraints=LinearConstraint(np.array(A), np.array(lo), np.array(hi)))
+        if not res.success:
+            raise ValueError("bit selection infeasible under the given limits: " + str(res.message))
+        choice = np.rint(res.x).reshape(L, B).argmax(axis=1)
+        if all(tab[np.arange(L), choice].sum() <= lim + 1e-12 * abs(lim) for tab, lim in limits):
+            break
+        row = np.zeros((L, B))                           # over a limit by less than the tolerance: anything but this choice
+        row[np.arange(L), choice] = 1
+        A.append(row.reshape(-1)); lo.append(0); hi.append(L - 1)
     return choice, float(omega[np.arange(L), choice].sum())
 
 

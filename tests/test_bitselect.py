@@ -97,3 +97,24 @@ def test_latency_table_measured_on_the_gpu_and_selection_under_a_latency_limit()
     assert Q[np.arange(len(names)), choice].sum() <= limit + 1e-9
     for hn in nets.values():
         hn.close()
+
+
+def test_a_limit_half_a_nanosecond_below_the_best_choice():
+    """Limits in milliseconds, closer to a choice's cost than a solver's absolute tolerance: held, and the best that holds it."""
+    import itertools
+    g = np.random.default_rng(0)
+    for _ in range(12):
+        L = int(g.integers(4, 9))
+        Q = np.round(g.uniform(0.004, 0.014, (L, 2)), 9)
+        omega = np.stack([np.linspace(2, 1, L), np.zeros(L)], axis=1)
+        first, _ = bs.solve(omega, latency=Q, latency_limit=0.5 * (Q.min(axis=1).sum() + Q.max(axis=1).sum()))
+        limit = Q[np.arange(L), first].sum() - 5e-7
+        costs = [(omega[np.arange(L), list(ch)].sum(), Q[np.arange(L), list(ch)].sum()) for ch in itertools.product((0, 1), repeat=L)]
+        best = min((o for o, q in costs if q <= limit), default=None)
+        if best is None:
+            with pytest.raises(ValueError):
+                bs.solve(omega, latency=Q, latency_limit=limit)
+            continue
+        choice, obj = bs.solve(omega, latency=Q, latency_limit=limit)
+        assert Q[np.arange(L), choice].sum() <= limit + 1e-12
+        assert abs(obj - best) < 1e-9
