@@ -179,14 +179,17 @@ residual_add_stream_kernel(const uint32_t units, const uint32_t groups, const vo
 // multiple of groups / gcd(groups, 256), one unit per thread up to `large` workgroups (four to a compute unit), which then walk:
 // a grid of more, one to each four units up to 4096, has its last round half empty (32 x 35 x 35 x 288 INT32 to 4 bits 11.1 us,
 // with 1024 workgroups 10.2; four branches of 512 channels in all to 8 bits 19.9 and 18.7).  At most 4096.  0: no such grid.
-static uint32_t grouped_blocks(int64_t units, uint32_t groups, int64_t large = 1024) {
+// stream: no more than `large` where a multiple at most an eighth below it exists, for a few compute units with one workgroup more than
+// the others set the end (200704 pixels of 100 channels, INT32 and bytes, 775 workgroups 23.6 us, 750 21.2; 60000 of 300 21.7 and
+// 19.6; 25088 of 1028 771 workgroups 29.2 us, 514 31.5).  The concatenation gains nothing from it (288 channels to 4 bits 10.7, 10.9).
+static uint32_t grouped_blocks(int64_t units, uint32_t groups, int64_t large = 1024, bool stream = false) {
     uint32_t a = groups, b = 256;
     while (b) { const uint32_t t = a % b; a = b; b = t; }
     const int64_t step = groups / a, one = (units + 255) / 256;
     if (step > 4096) return 0;
     const int64_t want = one <= large ? one : large;
     const int64_t n = (want + step - 1) / step * step;
-    return (uint32_t)(n > 4096 ? n - step : n);
+    return (uint32_t)(n > 4096 || (stream && n > large && 8 * (n - step) >= 7 * large) ? n - step : n);
 }
 
 hawq_status launch_residual_add(int64_t n_pixels, int K, int m_dt, int r_dt, int y_dt, const void *m, const int32_t *m_b,
@@ -200,7 +203,7 @@ hawq_status launch_residual_add(int64_t n_pixels, int K, int m_dt, int r_dt, int
         // against the other): with an INT32 operand 23 / 27 / 36 / 72 MB 6.5 / 7.3 / 7.8 / 13.5 us (7.0 / 7.6 / 9.0 / 16.2), but
         // 14 / 19 MB 5.3 / 5.6 (4.7 / 5.5); 8 bits both 4.8 / 9.6 / 19 MB 3.19 / 4.3 / 5.8 (3.26 / 4.75 / 7.1), 1.2 MB 2.70 (2.57).
         const bool stream = vu >= (m_dt == HAWQ_S32 || r_dt == HAWQ_S32 ? 900000 : 400000);
-        const uint32_t nb = grouped_blocks(vu, K / 4, stream ? 768 : 1024);
+        const uint32_t nb = grouped_blocks(vu, K / 4, stream ? 768 : 1024, stream);
         if (nb != 0) {
             auto go = [&](auto md, auto rd) {
                 constexpr int MD = decltype(md)::value, RD = decltype(rd)::value;

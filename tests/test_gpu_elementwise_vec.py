@@ -44,7 +44,9 @@ def test_residual_add_vector_form(hawq, P, K, m_dt, r_dt, y_dt):
 # not divide the grid, in narrow parameters, with one channel outside the INT32 form's range (c > 32) and outside the 8-bit form's (b >= 2^22)
 @pytest.mark.parametrize("P,K,m_dt,r_dt,y_dt", [(56249, 64, oracle.S32, oracle.U8, oracle.U8), (56251, 64, oracle.S32, oracle.U8, oracle.U8),
                                                 (11689, 4 * 77, oracle.S32, oracle.S32, oracle.S32), (3127, 512, oracle.U8, oracle.S8, oracle.S8),
-                                                (5201, 4 * 77, oracle.S8, oracle.U8, oracle.U8)])
+                                                (5201, 4 * 77, oracle.S8, oracle.U8, oracle.U8),
+                                                # grids of 750 workgroups (the next multiple, 775, above 768) and of 771 (the one below is 514)
+                                                (36011, 100, oracle.S32, oracle.U8, oracle.U8), (3503, 1028, oracle.S32, oracle.S8, oracle.U8)])
 @pytest.mark.parametrize("wide", [None, "c", "b"])
 def test_residual_add_streaming_form(hawq, P, K, m_dt, r_dt, y_dt, wide):
     import torch
