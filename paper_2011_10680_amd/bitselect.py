@@ -53,11 +53,17 @@ def quantization_perturbation(W, bits):
 def solve(omega, size=None, bops=None, latency=None, size_limit=None, bops_limit=None, latency_limit=None, fixed=None):
     """Exact solution of the selection problem.  omega, size, bops, latency: [L, B] arrays (row = layer group, column =
     bit choice); a limit of None drops that constraint.  fixed: {row: column} choices imposed beforehand.
-    Returns (choice [L] column indices, objective) or raises ValueError if the limits cannot be met."""
+    Returns (choice [L] column indices, objective) or raises ValueError if the limits cannot be met.
+
+    No limit is exceeded by more than the rounding of its sum.  The solver itself takes a choice within its tolerance of a limit for one that holds it; such a
+    choice is excluded and the problem solved again, sixteen times at most.  Where equal rows make more of them than that, the
+    limit is lowered by that tolerance (doubled as long as it takes): the result then still holds every limit, and only a
+    choice within a few parts in 10^9 of one may have been passed over."""
     from scipy.optimize import Bounds, LinearConstraint, milp
     omega = np.asarray(omega, dtype=np.float64)
     L, B = omega.shape
-    A, lo, hi, limits = [], [], [], []
+    tolerance = 1e-6                                     # of the solver, on a row's sum
+    A, lo, hi, limits = [], [], [], []                   # limits: [table, limit, row of A, margin below it]
     for i in range(L):                                   # exactly one choice per group
         row = np.zeros(L * B)
         row[i * B:(i + 1) * B] = 1
@@ -68,24 +74,36 @@ def solve(omega, size=None, bops=None, latency=None, size_limit=None, bops_limit
         if tab is None:
             raise ValueError("a limit needs its cost table")
         tab = np.asarray(tab, dtype=np.float64).reshape(-1)
-        limits.append((tab.reshape(L, B), float(lim)))
-        scale = 1e3 / max(np.abs(tab).max(), 1e-300)     # (the solver's feasibility tolerance is absolute, 1e-6)
+        if not np.isfinite(tab).all():
+            raise ValueError("a cost table must be finite")
+        limits.append([tab.reshape(L, B), float(lim), len(A), tolerance])
+        # the tolerance is absolute: small tables are scaled up to a largest entry of 1000, large ones stay as they are
+        scale = max(1.0, 1e3 / max(np.abs(tab).max(), 1e-30))
         A.append(tab * scale); lo.append(-np.inf); hi.append(float(lim) * scale)
     ub = np.ones(L * B)
     lb = np.zeros(L * B)
     for i, j in (fixed or {}).items():
         lb[i * B + j] = 1
+    rows, singly = len(A), 16
     while True:
         res = milp(c=omega.reshape(-1), integrality=np.ones(L * B), bounds=Bounds(lb, ub),
                    constraints=LinearConstraint(np.array(A), np.array(lo), np.array(hi)))
         if not res.success:
             raise ValueError("bit selection infeasible under the given limits: " + str(res.message))
         choice = np.rint(res.x).reshape(L, B).argmax(axis=1)
-        if all(tab[np.arange(L), choice].sum() <= lim + 1e-12 * abs(lim) for tab, lim in limits):
+        over = [l for l in limits if l[0][np.arange(L), choice].sum() > l[1] + 1e-12 * abs(l[1])]
+        if not over:
             break
-        row = np.zeros((L, B))                           # over a limit by less than the tolerance: anything but this choice
-        row[np.arange(L), choice] = 1
-        A.append(row.reshape(-1)); lo.append(0); hi.append(L - 1)
+        if singly > 0:
+            singly -= 1
+            row = np.zeros((L, B))                       # anything but this choice
+            row[np.arange(L), choice] = 1
+            A.append(row.reshape(-1)); lo.append(0); hi.append(L - 1)
+        else:
+            del A[rows:], lo[rows:], hi[rows:]           # (the lower limit excludes those too)
+            for l in over:
+                hi[l[2]] -= l[3]
+                l[3] *= 2
     return choice, float(omega[np.arange(L), choice].sum())
 
 

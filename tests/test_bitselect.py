@@ -118,3 +118,43 @@ def test_a_limit_half_a_nanosecond_below_the_best_choice():
         choice, obj = bs.solve(omega, latency=Q, latency_limit=limit)
         assert Q[np.arange(L), choice].sum() <= limit + 1e-12
         assert abs(obj - best) < 1e-9
+
+
+@pytest.mark.parametrize("L", [8, 20, 54])
+@pytest.mark.parametrize("unit", [1.0, 1e-3, 1e10])
+def test_equal_groups_just_above_the_limit(monkeypatch, L, unit):
+    """Every choice of half the groups lies over the limit by less than the solver's tolerance, and there are up to 10^15 of
+    them: the selection ends after a few solves, with one group fewer."""
+    import scipy.optimize
+    milp, solves = scipy.optimize.milp, []
+
+    def counted(*a, **kw):
+        solves.append(1)
+        assert len(solves) < 100
+        return milp(*a, **kw)
+    monkeypatch.setattr(scipy.optimize, "milp", counted)
+    omega, Q = np.tile([1.0, 0.0], (L, 1)), unit * np.tile([1.0, 2.0], (L, 1))
+    limit = 1.5 * L * unit * (1 - 1e-11)
+    # beside a second limit that holds anyway, which must not be lowered with the first
+    choice, obj = bs.solve(omega, size=Q, latency=Q, size_limit=1.5 * L * unit, latency_limit=limit)
+    assert Q[np.arange(L), choice].sum() <= limit
+    assert choice.sum() == L // 2 - 1 and obj == L - (L // 2 - 1)
+
+
+def test_a_choice_at_the_limit_beside_a_better_one_just_above_it():
+    omega = np.array([[2.0, 0.0], [2.0, 1.0]])
+    Q = np.array([[1.0, 3.0 + 1e-10], [1.0, 3.0]])
+    choice, obj = bs.solve(omega, latency=Q, latency_limit=4.0)      # (the better one exceeds it by 10^-10)
+    assert list(choice) == [0, 1] and obj == 3.0
+
+
+@pytest.mark.parametrize("bad", [np.inf, np.nan])
+def test_cost_tables_are_finite(bad):
+    with pytest.raises(ValueError):
+        bs.solve(np.ones((2, 2)), latency=np.array([[1.0, bad], [1.0, 2.0]]), latency_limit=3.0)
+
+
+def test_a_table_with_one_very_large_entry():
+    omega, Q = np.array([[1.0, 0.0], [1.0, 0.0], [2.0, 0.0]]), np.array([[1.0, 1e10], [1.0, 2.0], [1.0, 2.0]])
+    choice, obj = bs.solve(omega, latency=Q, latency_limit=4.0)
+    assert list(choice) == [0, 0, 1] and obj == 2.0
