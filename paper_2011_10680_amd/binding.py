@@ -1,5 +1,5 @@
 """Python binding with the same names as the C entry points.  Argument marshalling only: ctypes, and for the per-layer entry
-points on tensors of the usual types the same in C (``_fastcall.so``, csrc/fastcall.cpp).
+points on tensors of the usual types the same in C (module ``_fastcall``, csrc/fastcall.cpp).
 
 Tensors are ``torch`` CUDA (HIP) tensors; the binding passes ``data_ptr()`` and the current
 stream handle.  The library is loaded from ``libhawq.so`` next to this file; if it is missing

@@ -7,7 +7,9 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libhawq.so")
-FASTCALL = os.path.join(HERE, "_fastcall.so")     # CPython module: argument marshalling in C (host code only)
+# CPython module: argument marshalling in C (host code only).  It is compiled against this interpreter's object layouts, and its
+# name says so: another interpreter does not find it and the binding stays with ctypes.
+FASTCALL = os.path.join(HERE, "_fastcall" + sysconfig.get_config_var("EXT_SUFFIX"))
 OBJ_DIR = os.path.join(HERE, "_build")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -36,6 +38,9 @@ def _compile(src):
 
 
 def _compile_fastcall():
+    plain = os.path.join(HERE, "_fastcall.so")        # (the name of earlier builds, which every interpreter would load)
+    if os.path.exists(plain):
+        os.remove(plain)
     subprocess.check_call(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-I", sysconfig.get_paths()["include"],
                            "-o", FASTCALL, os.path.join(CSRC, "fastcall.cpp")])
 

@@ -233,3 +233,16 @@ def test_net_create_rejects_bad_parameters_before_touching_the_gpu(lib):
     with pytest.raises(hawq.HawqError) as e:                      # wrong layer count
         hawq.HawqNet(18, net["layers"][:-1], net["pool_b"], net["pool_c"], image_hw=64, num_classes=10)
     assert e.value.status == 2
+
+
+def test_native_marshalling_is_named_for_its_interpreter(lib):
+    """The module holds this interpreter's object layouts: a name that any other would import is not left in the package."""
+    import importlib.machinery
+    import sysconfig
+    from paper_2011_10680_amd import build
+    tag = sysconfig.get_config_var("EXT_SUFFIX")
+    assert "cpython" in tag and build.FASTCALL.endswith("_fastcall" + tag) and tag in importlib.machinery.EXTENSION_SUFFIXES
+    here = os.path.dirname(build.FASTCALL)
+    assert not os.path.exists(os.path.join(here, "_fastcall.so"))
+    from paper_2011_10680_amd import _fastcall
+    assert os.path.samefile(_fastcall.__file__, build.FASTCALL)
