@@ -2,6 +2,7 @@
 import os
 import subprocess
 import sysconfig
+import warnings
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -20,12 +21,15 @@ def sources():
     return sorted(os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith(".hip"))
 
 
+def _older(target, deps):
+    return not os.path.exists(target) or any(os.path.getmtime(d) > os.path.getmtime(target) for d in deps)
+
+
 def is_stale():
-    if not (os.path.exists(LIB) and os.path.exists(FASTCALL)):
-        return True
-    t = min(os.path.getmtime(LIB), os.path.getmtime(FASTCALL))
-    deps = [os.path.join(CSRC, f) for f in os.listdir(CSRC)] + [os.path.join(HERE, "..", "include", "hawq.h")]
-    return any(os.path.getmtime(d) > t for d in deps)
+    """Whether the library, or a native module that was built with it, is older than its sources."""
+    header = os.path.join(HERE, "..", "include", "hawq.h")
+    deps = [os.path.join(CSRC, f) for f in os.listdir(CSRC)] + [header]
+    return _older(LIB, deps) or (os.path.exists(FASTCALL) and _older(FASTCALL, [os.path.join(CSRC, "fastcall.cpp"), header]))
 
 
 def _compile(src):
@@ -38,23 +42,32 @@ def _compile(src):
 
 
 def _compile_fastcall():
-    plain = os.path.join(HERE, "_fastcall.so")        # (the name of earlier builds, which every interpreter would load)
-    if os.path.exists(plain):
-        os.remove(plain)
-    subprocess.check_call(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-I", sysconfig.get_paths()["include"],
-                           "-o", FASTCALL, os.path.join(CSRC, "fastcall.cpp")])
+    """Returns None, or why there is no native module: without a host compiler or Python's headers the binding does without."""
+    for old in (os.path.join(HERE, "_fastcall.so"), FASTCALL):     # (the first: the name of earlier builds, which every interpreter would load)
+        if os.path.exists(old):
+            os.remove(old)
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-I", sysconfig.get_paths()["include"],
+           "-o", FASTCALL, os.path.join(CSRC, "fastcall.cpp")]
+    try:
+        r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    except OSError as e:
+        return str(e)
+    return None if r.returncode == 0 else r.stdout
 
 
 def build(force=True, jobs=8):
-    """Compile every .hip source and link the shared library.  Returns its path."""
+    """Compile every .hip source and link the shared library; compile the native module, or warn that there is none.  Returns the
+    library's path."""
     if not force and not is_stale():
         return LIB
     os.makedirs(OBJ_DIR, exist_ok=True)
     with ThreadPoolExecutor(max_workers=jobs) as ex:
         fast = ex.submit(_compile_fastcall)
         objs = list(ex.map(_compile, sources()))
-        fast.result()
+        missing = fast.result()
     subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs)
+    if missing is not None:
+        warnings.warn("the native marshalling module was not built, calls go through ctypes:\n" + missing)
     return LIB
 
 

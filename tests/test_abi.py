@@ -3,6 +3,7 @@ declares, and rejects bad arguments on the host before anything is launched."""
 import ctypes
 import os
 import re
+import sys
 
 import pytest
 
@@ -246,3 +247,35 @@ def test_native_marshalling_is_named_for_its_interpreter(lib):
     assert not os.path.exists(os.path.join(here, "_fastcall.so"))
     from paper_2011_10680_amd import _fastcall
     assert os.path.samefile(_fastcall.__file__, build.FASTCALL)
+
+
+def test_the_library_is_built_without_the_native_marshalling(tmp_path, monkeypatch):
+    """No host C++ compiler, or no Python headers: the library is linked all the same, a warning says what is missing, and the
+    tree counts as built."""
+    from paper_2011_10680_amd import build
+    pkg, header = tmp_path / "package", tmp_path / "include" / "hawq.h"
+    pkg.mkdir()
+    header.parent.mkdir()
+    header.write_text("")
+    os.utime(header, (1, 1))
+    stub = tmp_path / "hipcc"                                     # (stands for hipcc: makes the files it is asked for)
+    stub.write_text("#!/bin/sh\nwhile [ $# -gt 0 ]; do [ \"$1\" = -o ] && : > \"$2\"; shift; done\n")
+    stub.chmod(0o755)
+    for name, value in (("HERE", pkg), ("LIB", pkg / "libhawq.so"), ("FASTCALL", pkg / "_fastcall.so"), ("OBJ_DIR", pkg / "_build"),
+                        ("HIPCC", stub)):
+        monkeypatch.setattr(build, name, str(value))
+    run = build.subprocess.run
+
+    def no_compiler(cmd, **kw):
+        if cmd[0] == "g++":
+            raise FileNotFoundError("g++")
+        return run(cmd, **kw)
+
+    def no_headers(cmd, **kw):
+        return run([sys.executable, "-c", "print('Python.h: no such file'); raise SystemExit(1)"] if cmd[0] == "g++" else cmd, **kw)
+    for fault, what in ((no_compiler, "g[+][+]"), (no_headers, "Python.h")):
+        monkeypatch.setattr(build.subprocess, "run", fault)
+        with pytest.warns(UserWarning, match=what):
+            assert build.build() == build.LIB
+        assert os.path.exists(build.LIB) and not os.path.exists(build.FASTCALL) and not build.is_stale()
+        os.remove(build.LIB)
