@@ -176,15 +176,6 @@ __device__ __forceinline__ uint32_t clamp_u8x4(uint32_t a, uint32_t lo, uint32_t
     return e | o;
 }
 
-// XCD-aware remap of a linear workgroup id.  Workgroups are dealt round-robin to the 8 XCDs
-// (each with its own L2); this gives every XCD one contiguous range of logical tile ids so
-// neighbouring tiles (shared input halo, shared activation rows) meet in the same L2.
-__device__ __forceinline__ uint32_t xcd_remap(uint32_t bid, uint32_t nblocks) {
-    const uint32_t per = nblocks >> 3, rem = nblocks & 7u;
-    const uint32_t xcd = bid & 7u, idx = bid >> 3;
-    return xcd < rem ? xcd * (per + 1) + idx : rem * (per + 1) + (xcd - rem) * per + idx;
-}
-
 // ---- launchers (host) ----
 hawq_status launch_conv_mfma(const ConvArgs &a, hipStream_t s);     // requires conv_mfma_eligible
 bool conv_mfma_eligible(const ConvArgs &a, int x_hi);

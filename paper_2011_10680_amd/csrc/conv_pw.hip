@@ -44,12 +44,11 @@ conv_pw_kernel(const ConvArgs a, const int n_ct, const int n_seq, const int n_gr
 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     // workgroups that share pixels (consecutive channel tiles of one sequence) stay on one XCD and its L2
-    const int g = (int)(blockIdx.x >> 3) * 4 + wave;
-    const int ct = g % n_ct, seq = g / n_ct;
-    const TileWalk gr = xcd_walk(blockIdx.x & 7 | (uint32_t)seq << 3, (uint32_t)n_seq, n_groups, xcd_eighths(a.M));   // (seq: within the XCD)
-    if (seq >= n_seq >> 3 || gr.first >= gr.end) return;   // whole wave; the kernel has no workgroup barrier
+    const StreamWave sw = stream_wave(blockIdx.x, gridDim.x, wave, n_ct, n_seq, n_groups, xcd_eighths(a.M));
+    const TileWalk gr = sw.groups;
+    if (sw.spare || gr.first >= gr.end) return;      // whole wave; the kernel has no workgroup barrier
     const int rho = lane & 31, khalf = lane >> 5;
-    const int k0 = ct * 32;
+    const int k0 = sw.ct * 32;
     const int Cb = INT4 ? a.C / 2 : a.C;
 
     // ---- parameters of this wave's 32 channels -> wave-private LDS ----
@@ -290,13 +289,11 @@ conv_pws_kernel(const ConvArgs a, const int n_ct, const int n_seq, const int n_g
     __shared__ __attribute__((aligned(1024))) uint8_t xs3[STAGE];
 
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // the launch makes n_ct a multiple of 4 and the grid exactly n_seq * n_ct / 4 workgroups: the four waves
-    // of a workgroup share `seq` (so every wave reaches every barrier the same number of times)
-    const int g = (int)(blockIdx.x >> 3) * 4 + wave;
-    const int ct = g % n_ct, seq = g / n_ct;
-    const TileWalk gr = xcd_walk(blockIdx.x & 7 | (uint32_t)seq << 3, (uint32_t)n_seq, n_groups, xcd_eighths(a.M));   // (seq: within the XCD)
+    // n_ct is a multiple of 4, so the four waves of a workgroup share a sequence (and reach every barrier the same number of times)
+    const StreamWave sw = stream_wave(blockIdx.x, gridDim.x, wave, n_ct, n_seq, n_groups, xcd_eighths(a.M));
+    const TileWalk gr = sw.groups;
     const int rho = lane & 31, khalf = lane >> 5;
-    const int k0 = ct * 32;
+    const int k0 = sw.ct * 32;
     const int Cb = a.C;
 
     int wide = 0;
@@ -484,11 +481,10 @@ conv_pws_dual_kernel(const ConvArgs a, const int n_ct, const int n_seq, const in
     __shared__ __attribute__((aligned(1024))) uint8_t xs3[STAGE];
 
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int g = (int)(blockIdx.x >> 3) * 4 + wave;
-    const int ct = g % n_ct, seq = g / n_ct;        // the four waves of a workgroup share `seq` (n_ct is a multiple of 4)
-    const TileWalk gr = xcd_walk(blockIdx.x & 7 | (uint32_t)seq << 3, (uint32_t)n_seq, n_groups, xcd_eighths(a.M));   // (seq: within the XCD)
+    const StreamWave sw = stream_wave(blockIdx.x, gridDim.x, wave, n_ct, n_seq, n_groups, xcd_eighths(a.M));   // (the four waves of a workgroup share a sequence: n_ct is a multiple of 4)
+    const TileWalk gr = sw.groups;
     const int rho = lane & 31, khalf = lane >> 5;
-    const int k0 = ct * 32;
+    const int k0 = sw.ct * 32;
 
     int wide = 0;
     if (khalf == 0) {
@@ -662,11 +658,8 @@ static hawq_status launch_pw_res(const ConvArgs &a, hipStream_t s) {
     const int n_groups = (a.M + 32 * TP - 1) / (32 * TP);
     // fill every SIMD of the 256 CUs with as many waves as the register budget allows, each walking over
     // several pixel groups
-    int n_seq = (WPE * 4 * 256) / n_ct;   // (rounded down: one workgroup past the last slot would be a round of its own)
-    n_seq = n_seq < 8 ? 8 : n_seq / 8 * 8;
-    if (n_seq > (n_groups + 7) / 8 * 8) n_seq = (n_groups + 7) / 8 * 8;
-    const int waves = n_seq / 8 * n_ct;                  // of an XCD
-    const uint32_t blocks = (uint32_t)((waves + 3) / 4) * 8;
+    const int n_seq = stream_sequences(WPE * 4 * 256, n_ct, n_groups, true);
+    const uint32_t blocks = stream_grid(n_ct, n_seq);
     if (is4(a.x_dt)) conv_pw_kernel<KC, TP, NS, WPE, RES, true><<<blocks, 256, 0, s>>>(a, n_ct, n_seq, n_groups);
     else conv_pw_kernel<KC, TP, NS, WPE, RES, false><<<blocks, 256, 0, s>>>(a, n_ct, n_seq, n_groups);
     return check_launch();
@@ -693,10 +686,8 @@ template <int KC, int WPE>
 static hawq_status launch_pws(const ConvArgs &a, hipStream_t s) {
     const int n_ct = a.K / 32;                           // a multiple of 4
     const int n_groups = (a.M + 31) / 32;
-    int n_seq = (WPE * 4 * 256) / n_ct;
-    n_seq = n_seq < 8 ? 8 : n_seq / 8 * 8;
-    if (n_seq > (n_groups + 7) / 8 * 8) n_seq = (n_groups + 7) / 8 * 8;
-    const uint32_t blocks = (uint32_t)(n_seq * (n_ct / 4));   // exactly: every wave of the grid has work
+    const int n_seq = stream_sequences(WPE * 4 * 256, n_ct, n_groups, false);
+    const uint32_t blocks = stream_grid(n_ct, n_seq);    // = n_seq * n_ct / 4: no spare wave
     if (a.res != nullptr) conv_pws_kernel<KC, WPE, true><<<blocks, 256, 0, s>>>(a, n_ct, n_seq, n_groups);
     else conv_pws_kernel<KC, WPE, false><<<blocks, 256, 0, s>>>(a, n_ct, n_seq, n_groups);
     return check_launch();
@@ -726,10 +717,8 @@ template <int KC1, int KC2, int WPE>
 static hawq_status launch_pws_dual(const ConvArgs &a, hipStream_t s) {
     const int n_ct = a.K / 32;                           // a multiple of 4
     const int n_groups = (a.M + 31) / 32;
-    int n_seq = (WPE * 4 * 256) / n_ct;
-    n_seq = n_seq < 8 ? 8 : n_seq / 8 * 8;
-    if (n_seq > (n_groups + 7) / 8 * 8) n_seq = (n_groups + 7) / 8 * 8;
-    const uint32_t blocks = (uint32_t)(n_seq * (n_ct / 4));
+    const int n_seq = stream_sequences(WPE * 4 * 256, n_ct, n_groups, false);
+    const uint32_t blocks = stream_grid(n_ct, n_seq);
     if (a.mid_s8) conv_pws_dual_kernel<KC1, KC2, WPE, true><<<blocks, 256, 0, s>>>(a, n_ct, n_seq, n_groups);
     else conv_pws_dual_kernel<KC1, KC2, WPE, false><<<blocks, 256, 0, s>>>(a, n_ct, n_seq, n_groups);
     return check_launch();

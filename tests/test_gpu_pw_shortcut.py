@@ -1,5 +1,6 @@
-"""GPU parity of the streaming 1x1 kernel with 128 input channels and a shortcut, bit-exact: ragged pixel groups and channel
-tiles, both operand widths, every shortcut type, at the fewest pixels the kernel takes and beyond one round of its waves."""
+"""GPU parity of the streaming 1x1 kernels, bit-exact: 128 input channels with a shortcut (ragged pixel groups and channel tiles, both
+operand widths, every shortcut type, at the fewest pixels the kernel takes and beyond one round of its waves), and the walks of
+the persistent kernels' waves over the XCDs."""
 import numpy as np
 import pytest
 
@@ -38,7 +39,7 @@ def test_128_channels_with_shortcut_in_one_round_of_tile_pairs(N, H, W, K, bits,
 @pytest.mark.parametrize("N,H,W,C,K,R,bits,res", [(1, 57, 144, 64, 64, 1, 8, False), (1, 57, 144, 64, 96, 1, 4, True), (1, 59, 141, 128, 96, 1, 8, False),
                                                   (1, 57, 144, 256, 64, 1, 4, False), (1, 57, 144, 256, 384, 1, 8, True), (11, 55, 55, 64, 64, 3, 8, True),
                                                   (13, 53, 51, 64, 64, 3, 4, False)])
-def test_walks_with_uneven_eighths(N, H, W, C, K, R, bits, res):
+def test_turns_with_uneven_shares(N, H, W, C, K, R, bits, res):
     import torch
     assert torch.cuda.is_available(), "GPU tests need a GPU"
     import paper_2011_10680_amd as hawq
@@ -48,3 +49,31 @@ def test_walks_with_uneven_eighths(N, H, W, C, K, R, bits, res):
     x_dt, w_dt, hi = (hawq.U8, hawq.S8, 127) if bits == 8 else (hawq.U4, hawq.S4, 15)
     got, want = run_conv_gpu(case, x_dt, w_dt, x_dt, res_dt=x_dt, y_lo=0, y_hi=hi, x_hi=127 if bits == 8 else 0)
     assert_same(got, want, str((N, H, W, C, K, R, bits, res)))
+
+
+def _sequences(slots, n_ct, groups, even):
+    """How many walks over the pixel groups a launch makes (stream_sequences of csrc/xcd_walk.h)."""
+    n = max(1, min(slots // n_ct, groups))
+    if slots // n_ct >= groups:
+        return -(-groups // 8) * 8 if even and slots // n_ct >= -(-groups // 8) * 8 else groups
+    return n // 8 * 8 if even and 33 * (n // 8 * 8) >= 32 * n else n
+
+
+# a number of sequences that is no multiple of 8, so that they are not dealt evenly over the XCDs: (pixels, C, K, bits, shortcut, the
+# launch's waves, pixels of a group)
+@pytest.mark.parametrize("M,C,K,bits,res,slots,px", [(8777, 64, 1184, 8, False, 4096, 32), (13801, 128, 624, 8, False, 2048, 64), (9001, 128, 832, 4, False, 2048, 64),
+                                                     (8713, 128, 832, 8, True, 2048, 32), (8713, 128, 1264, 4, True, 3072, 32),
+                                                     (8207, 256, 1408, 8, True, 2048, 32), (9747, 256, 640, 8, False, 3072, 32)])
+def test_sequences_not_dealt_evenly(M, C, K, bits, res, slots, px):
+    assert _sequences(slots, (K + 31) // 32, -(-M // px), C < 256) % 8 != 0
+    test_turns_with_uneven_shares(1, 1, M, C, K, 1, bits, res)
+
+
+@pytest.mark.parametrize("N,H,C,K,Cs,ss,slots", [(2, 68, 64, 896, 64, 1, 4096), (3, 60, 128, 384, 256, 2, 2048)])
+def test_two_convolutions_with_sequences_not_dealt_evenly(N, H, C, K, Cs, ss, slots):
+    import paper_2011_10680_amd as hawq
+    from gpu_util import assert_same
+    from test_gpu_dual import _case, _run
+    assert _sequences(slots, K // 32, -(-N * H * H // 32), False) % 8 != 0
+    got, want = _run(hawq, _case(N + H + K, N, H, C, K, 1, Cs, ss), hawq.U8, 1, 0, 127)
+    assert_same(got, want, str((N, H, C, K, Cs, ss)))
