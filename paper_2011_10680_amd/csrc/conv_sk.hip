@@ -440,14 +440,17 @@ hawq_status launch_conv_sk(const ConvArgs &a_in, int x_hi, hipStream_t s) {
     // 3x3 at batch 16: 12.4 against 13.9).  Past one round the number of waves in flight counts more than the operand bytes:
     // four waves a tile for long reductions (64 x 64; packed 5x5 240 -> 208 at 3267 pixels 22.4 us, with two 26.0), else two, 32 channels x
     // 64 pixels a workgroup, from 512 of those on 32 x 128 (packed 1x1 272 -> 288 at 39200 pixels 24 us,
-    // with 64 x 128 tiles or four waves a tile 27 to 42; packed 3x3 48 -> 64 8.3 and 9.8).
+    // with 64 x 128 tiles or four waves a tile 27 to 42; packed 3x3 48 -> 64 8.3 and 9.8) -- of more than 32 channels in their last 64,
+    // between one round of the small tiles and two, only reductions of a few steps (1x1 544 -> 36 at 12887 pixels with a shortcut 5.6 us, in small
+    // tiles 6.7; 3x3 96 -> 42 at 11025 6.7 and 7.6; with up to 4 steps, packed 6, the small ones are the faster or equal).
     auto tiles = [&](int tc, int tp) { return (int64_t)((a.K + 16 * tc - 1) / (16 * tc)) * ((a.M + 16 * tp - 1) / (16 * tp)); };
     if (tiles(1, 1) <= 256) return sk_launch<1, 1, 8, 1>(a, e, xf, s);
     if (tiles(1, 2) <= 256) return sk_launch<1, 2, 8, 1>(a, e, xf, s);
     if (tiles(2, 2) <= 256) return sk_launch<2, 2, 8, 1>(a, e, xf, s);
     const int steps = (a.R * a.S * (is4(a.x_dt) ? a.C / 2 : a.C) + 63) / 64;
     if (tiles(2, 4) <= 256) return steps < 32 ? sk_launch<2, 2, 4, 2>(a, e, xf, s) : sk_launch<2, 4, 8, 1>(a, e, xf, s);
-    if (tiles(4, 4) <= 512 && steps >= 16) return sk_launch<4, 2, 4, 2>(a, e, xf, s);
+    const bool whole = (a.K - 1) % 64 >= 32 && tiles(2, 4) > 272 && tiles(2, 4) <= 512 && steps >= (is4(a.x_dt) ? 7 : 5);
+    if (tiles(4, 4) <= 512 && (steps >= 16 || whole)) return sk_launch<4, 2, 4, 2>(a, e, xf, s);
     return tiles(2, 4) <= 512 ? sk_launch<2, 2, 2, 2>(a, e, xf, s) : sk_launch<2, 4, 2, 2>(a, e, xf, s);
 }
 
