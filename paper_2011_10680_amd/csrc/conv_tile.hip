@@ -501,16 +501,32 @@ static int tile_choice(const ConvArgs &a) {
     return best;
 }
 
+static int64_t tiles_of(const ConvArgs &a, int bm, int bn) { return ((int64_t)a.M + bm - 1) / bm * ((a.K + bn - 1) / bn); }
+
+// A handful of output channels, a long 3x3 or 1x1 reduction and very many pixels: most of a 32-channel tile's products are for nothing,
+// and this kernel fetches more for them than the other two (3x3 592 -> 8 at 90944 pixels 70 us, the split-reduction kernel 54; 512 -> 10
+// at 122304 74 and, conv_mfma.hip, 53; with fewer pixels it is no slower: 560 -> 11 at 68502 42.8 and 48.5).
+static bool tile_narrow(const ConvArgs &a) {
+    return !is4(a.x_dt) && a.K <= 12 && a.R * a.S <= 9 && tile_steps(a) >= 64 && tiles_of(a, 64, 64) >= 1280;
+}
+
 // Over the split-reduction kernel below its line of 2^19 outputs: matrix products and 1x1 layers of no more than 24 steps.  From
 // 2^18 outputs on with 8-bit operands and 8 steps or more, or with ragged rows (300 x 1000 x 1024 6.7 -> 4.6 us, 300 x 1003 x 256 4.9 ->
-// 3.4; with 64 steps 14.4 and 15.1), from 3 * 2^17 on with fewer (8670 pixels of packed 288 -> 48 4.6 -> 4.2; 7350 3.8 and 4.1).  A 3x3
-// window stays there (4624 pixels of 64 -> 96 4.2 us, here 5.8), and so do
-// longer packed reductions (1024 -> 2048 / 2 at 196 pixels 5.3 us, here 6.3; 2048 -> 512 at 784 7.4 and 8.2).
+// 3.4; with 64 steps 14.4 and 15.1), from 3 * 2^17 on with fewer (8670 pixels of packed 288 -> 48 4.6 -> 4.2; 7350 3.8 and 4.1).  Packed
+// operands stay there while its 32 x 64 tiles are no more than one to a CU (3136 pixels of 448 -> 132 3.8 us, here 4.4; 2450 of
+// 704 -> 176 4.3 and 4.9; above that 0.92 of its time in the mean of 85 shapes), but for ragged rows of one or two steps (4900 of
+// 128 -> 66 4.0 and 3.7).  A 3x3 window stays there (4624 pixels of 64 -> 96 4.2 us, here 5.8), and so do longer packed reductions (1024 ->
+// 2048 / 2 at 196 pixels 5.3 us, here 6.3; 2048 -> 512 at 784 7.4 and 8.2).  8-bit reductions of more than 64 steps over a few channels
+// come here with more than two rounds of tiles (5x5 / 2 416 -> 7 at 34496 pixels 84 -> 54 us; 3x3 496 -> 4 at 35258 28.3 -> 21.8), with many
+// more of them they stay (5x5 608 -> 3 at 98980 132 us, here 174).
 bool conv_tile_over_sk(const ConvArgs &a) {
     if (a.res != nullptr) return false;
+    const bool four = is4(a.x_dt);
     const int64_t out = (int64_t)a.M * a.K, steps = tile_steps(a);
+    if (!four && steps > 64 && tiles_of(a, 64, 64) > 512) return tiles_of(a, 64, 64) <= 896;
     const bool ragged = a.K % 4 != 0;
-    if (a.R * a.S != 1 || steps > 24 || (is4(a.x_dt) && steps >= 8 && !ragged)) return false;
+    const bool round = four && tiles_of(a, 64, 32) <= 256 && (steps >= 3 || !ragged);
+    if (a.R * a.S != 1 || steps > 24 || round || (four && steps >= 8 && !ragged)) return false;
     return out > (steps >= 8 || ragged ? 1 << 18 : 3 << 17);
 }
 
@@ -519,7 +535,7 @@ bool conv_tile_over_sk(const ConvArgs &a) {
 // 16: 6.2 and 6.6).  With more tiles or steps the larger tiles' fewer bytes count (512 x 4096 x 4096 22.7 us, with 64 x 64 23.8; shortcut,
 // packed 3x3 256 -> 256 at 14 x 14, batch 48, 588 tiles of 18 steps: 16.9, conv_mfma.hip 16.4).
 static bool few_tiles(const ConvArgs &a) {
-    const int64_t steps = tile_steps(a), tiles = ((int64_t)a.M + 63) / 64 * ((a.K + 63) / 64);
+    const int64_t steps = tile_steps(a), tiles = tiles_of(a, 64, 64);
     return tiles <= (steps < 16 ? 768 : steps < 32 ? 512 : 0);
 }
 
@@ -532,17 +548,29 @@ static bool few_tiles(const ConvArgs &a) {
 // results and no quarter of a 128-channel tile to spare, and every shortcut: its epilogue stores 16 bytes a lane (1x1 512 -> 128 at
 // 28x28, batch 64 11.2 us, here 10.8; 3x3 / 2 256 -> 512 at 14x14, batch 128 13.3 and 14.8); this one takes INT32 results
 // (4096 x 1000 x 256 25 -> 7.3), ragged ones (19 -> 5.5), 96 or 192 channels (3x3 64 -> 96 at 35x35, batch 32 12.9 -> 9.3) and products
-// large enough for 256 x 256 tiles.  The split-reduction kernel keeps long packed reductions just above its line (5x5 224 -> 112 at
-// 7350 pixels 13.0 us, here 16.0; at 8670 24.3 and 20.2).
+// large enough for 256 x 256 tiles.  Of the launches of few tiles it keeps, too, shortcut layers of fewer than 1024 pixels, no more than
+// a tile to a CU and more than 16 steps, packed 8 (3x3 384 -> 688 at 784 pixels, packed, 11.2 us, here 12.5; 192 -> 960 8.8 and 9.4), and 8-bit
+// ones of more than two tiles a CU and 12 steps on whose weights have no blocked copy (1x1 896 -> 928 at 3136 pixels 7.5 and 8.9;
+// 768 -> 704 6.7 and 7.5).
+// The split-reduction kernel keeps long packed reductions just above its line (5x5 224 -> 112 at 7350 pixels 13.0 us, here 16.0; at
+// 8670 24.3 and 20.2) and all of 13 steps or more, with a shortcut 8, whose 64 x 64 tiles are no more than one to a CU (3x3 224 -> 560 at
+// 1225 pixels with a shortcut 8.0 us, here 9.3; 5x5 96 -> 576 8.0 and 8.7), and shortcuts of up to 16 channels, 8-bit 12 (packed
+// 3x3 608 -> 8 at 159250 pixels 52 and 74, 8-bit 5x5 96 -> 4 at 194775 35 and 45, but 3x3 592 -> 16 at 43512 40 and 31).
 bool conv_tile_preferred(const ConvArgs &a, bool mfma) {
-    const int64_t steps = tile_steps(a);
+    const bool four = is4(a.x_dt), res = a.res != nullptr;
+    const int64_t steps = tile_steps(a), tiles = tiles_of(a, 64, 64), out = (int64_t)a.M * a.K;
+    if (!res && tile_narrow(a)) return false;
     if (mfma) {
-        if (a.y_dt != HAWQ_S32 && a.M >= 448 && few_tiles(a) && !(is4(a.x_dt) && a.res != nullptr && a.K > 1024)) return true;
-        if (a.res != nullptr) return false;
-        if (a.K % 16 == 0 && a.M < 1024 && steps >= 32 && ((int64_t)a.M + 63) / 64 * ((a.K + 63) / 64) <= 256) return false;
+        const bool kept = (res && a.M < 1024 && tiles <= 256 && (four ? steps >= 8 && a.C % 128 == 0 : steps > 16)) ||
+                          (!four && a.w_t == nullptr && a.K >= 128 && steps >= 12 && steps < 16 && tiles > 512);
+        if (a.y_dt != HAWQ_S32 && a.M >= 448 && few_tiles(a) && !(four && res && a.K > 1024) && !(kept && a.K % 16 == 0)) return true;
+        if (res) return false;
+        if (a.K % 16 == 0 && a.M < 1024 && steps >= 32 && tiles <= 256) return false;
         return a.K % 16 != 0 || a.y_dt == HAWQ_S32 || (a.K > 64 && (a.K < 128 || (a.R * a.S == 1 && (a.K + 127) / 128 * 512 >= 5 * a.K))) || (steps >= 16 && tile_choice(a) == 0);
     }
-    return !(is4(a.x_dt) ? steps >= 20 && (int64_t)a.M * a.K <= 7 << 17 : steps >= 32 && (int64_t)a.M * a.K <= 5 << 17);
+    if (res && (four ? a.K <= 16 && steps >= 12 : a.K <= 12 && steps >= 25)) return false;
+    if (four) return !((steps >= 20 && out <= 7 << 17) || (steps >= (res ? 8 : 13) && tiles <= 256));
+    return !(steps >= 32 && out <= 5 << 17 && (steps <= 64 || tiles <= 512 || tiles > 896));
 }
 
 // Two convolutions in one launch.  Packed operands always, the direct kernel is what else takes them (56 x 56, 64 -> 256 plus 64, batch
@@ -553,7 +581,7 @@ bool conv_tile_preferred(const ConvArgs &a, bool mfma) {
 // 221.0 us, ResNet18 at 8 140.3 -> 138.1; at 32, with 392 tiles of 38 steps, 207 and 213).
 bool conv_tile_dual_preferred(const ConvArgs &a) {
     if (is4(a.x_dt)) return true;
-    const int64_t steps = tile_steps(a) + (a.Cs + 63) / 64, tiles = ((int64_t)a.M + 63) / 64 * ((a.K + 63) / 64);
+    const int64_t steps = tile_steps(a) + (a.Cs + 63) / 64, tiles = tiles_of(a, 64, 64);
     return tiles <= (a.dual16 ? (steps < 32 ? 256 : 0) : steps < 16 ? 768 : steps < 64 ? 512 : 0);
 }
 

@@ -167,3 +167,26 @@ def test_two_convolutions(hawq, shape):
     assert_same(got, want, str(shape))
     v = want.astype(np.int32) if y_dt in (oracle.U8, oracle.S8) else oracle.unpack(want, y_dt)
     assert len(np.unique(v)) > 8
+
+
+# (pixels, C, K, R, bits, shortcut): either side of the lines between this kernel, the split-reduction kernel and the one with pixels along
+# the lanes: packed operands with a 32 x 64 tile per CU and one more; packed windows with a 64 x 64 tile per CU and one more, with
+# and without a shortcut; narrow shortcuts; a long reduction over few channels; a shortcut of fewer than 1024 pixels; the split-reduction
+# kernel's small tiles (one round and its end, two) and whole 64 channels
+_LINES = [
+    ((52, 64), 448, 148, 1, 4, False), ((52, 63), 448, 148, 1, 4, False), ((49, 64), 224, 320, 3, 4, False), ((49, 84), 224, 256, 3, 4, False),
+    ((41, 64), 96, 384, 3, 4, True), ((43, 65), 96, 384, 3, 4, True), ((201, 177), 192, 16, 3, 4, True), ((201, 220), 192, 12, 3, 8, True),
+    ((181, 193), 464, 12, 3, 8, False), ((31, 33), 384, 512, 3, 4, True), ((31, 33), 192, 512, 3, 8, True), ((136, 64), 544, 36, 1, 8, True),
+    ((137, 64), 544, 36, 1, 8, True), ((255, 64), 96, 32, 3, 8, False),
+]
+
+
+@pytest.mark.parametrize("shape", _LINES)
+def test_lines_of_the_dispatch(hawq, shape):
+    from gpu_util import run_conv_gpu, assert_same
+    from test_gpu_conv import _scale_c
+    (H, W), C, K, R, bits, res = shape
+    case = _scale_c(wl.conv_case(seed=H + W + C + K, N=1, H=H, W=W, C=C, K=K, R=R, S=R, stride=1, pad=R // 2, bits=bits, with_residual=res), bits)
+    x_dt, w_dt, hi = (hawq.U8, hawq.S8, 127) if bits == 8 else (hawq.U4, hawq.S4, 15)
+    got, want = run_conv_gpu(case, x_dt, w_dt, x_dt, res_dt=x_dt, y_lo=0, y_hi=hi, x_hi=127 if bits == 8 else 0)
+    assert_same(got, want, str(shape))
