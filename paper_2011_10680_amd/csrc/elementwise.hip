@@ -139,7 +139,7 @@ residual_add_stream_kernel(const uint32_t units, const uint32_t groups, const vo
         const bool four = u + (U - 1) * T < units;
         if (four)
 #pragma unroll
-            for (int i = 0; i < U; ++i) { a[i] = load4<MD, true>(m, u + i * T); b[i] = load4<RD, true>(r, u + i * T); }
+            for (int i = 0; i < U; ++i) { a[i] = load4<MD, NT>(m, u + i * T); b[i] = load4<RD, NT>(r, u + i * T); }
         return four;
     };
     bool four = fetch();               // (in flight while the parameters arrive and their form is decided)
@@ -157,8 +157,8 @@ residual_add_stream_kernel(const uint32_t units, const uint32_t groups, const vo
                 if constexpr (decltype(nc)::value) o[j] = med3(pm.narrow(a[j], j, half) + pr.narrow(b[j], j, half), vlo, vhi);
                 else o[j] = clamp64(pm.wide(a[j], j) + pr.wide(b[j], j), lo, hi);
             }
-            if (Y32) __builtin_nontemporal_store(o, (v4i *)y + at);
-            else __builtin_nontemporal_store(pack4(o), (uint32_t *)y + at);
+            if (Y32) ((v4i *)y)[at] = o;
+            else ((uint32_t *)y)[at] = pack4(o);
         };
         while (four) {
 #pragma unroll
@@ -167,7 +167,7 @@ residual_add_stream_kernel(const uint32_t units, const uint32_t groups, const vo
             four = fetch();
         }
         for (; u < units; u += T) {
-            const v4i a1 = load4<MD, true>(m, u), b1 = load4<RD, true>(r, u);
+            const v4i a1 = load4<MD, NT>(m, u), b1 = load4<RD, NT>(r, u);
             finish(a1, b1, u);
         }
     };
@@ -189,7 +189,7 @@ static uint32_t grouped_blocks(int64_t units, uint32_t groups, int64_t large = 1
     if (step > 4096) return 0;
     const int64_t want = one <= large ? one : large;
     const int64_t n = (want + step - 1) / step * step;
-    return (uint32_t)(n > 4096 || (stream && n > large && 8 * (n - step) >= 7 * large) ? n - step : n);
+    return (uint32_t)(n > 4096 || (stream && n > large && 8 * (n - step) >= 7 * large) ? n - step : n);   // (4096: at most that many)
 }
 
 hawq_status launch_residual_add(int64_t n_pixels, int K, int m_dt, int r_dt, int y_dt, const void *m, const int32_t *m_b,
@@ -202,13 +202,20 @@ hawq_status launch_residual_add(int64_t n_pixels, int K, int m_dt, int r_dt, int
         // The streaming form from the size on at which its few, long-lived workgroups are no slower (operands not in L2, this form
         // against the other): with an INT32 operand 23 / 27 / 36 / 72 MB 6.5 / 7.3 / 7.8 / 13.5 us (7.0 / 7.6 / 9.0 / 16.2), but
         // 14 / 19 MB 5.3 / 5.6 (4.7 / 5.5); 8 bits both 4.8 / 9.6 / 19 MB 3.19 / 4.3 / 5.8 (3.26 / 4.75 / 7.1), 1.2 MB 2.70 (2.57).
-        const bool stream = vu >= (m_dt == HAWQ_S32 || r_dt == HAWQ_S32 ? 900000 : 400000);
+        // INT32 operands past the caches from 128 MB in all on: between a layer that makes the INT32 operand and one that reads the sum,
+        // 100 to 160 MB 4 % less of the three's time than with ordinary loads, above 160 2 to 13 %; below, the operands are still
+        // in the caches (60 to 100 MB the addition by itself 1.15 times the ordinary loads' time, the three 1.00 to 1.05).
+        auto bytes = [](int dt) { return dt == HAWQ_S32 ? 4 : 1; };
+        const bool wide = m_dt == HAWQ_S32 || r_dt == HAWQ_S32, stream = vu >= (wide ? 900000 : 400000);
+        const bool past = wide && vu * 4 * (bytes(m_dt) + bytes(r_dt) + bytes(y_dt)) >= 128000000;
         const uint32_t nb = grouped_blocks(vu, K / 4, stream ? 768 : 1024, stream);
         if (nb != 0) {
             auto go = [&](auto md, auto rd) {
                 constexpr int MD = decltype(md)::value, RD = decltype(rd)::value;
                 auto run = [&](auto kernel) { kernel<<<nb, 256, 0, s>>>((uint32_t)vu, K / 4, m, m_b, m_c, r, r_b, r_c, lo, hi, y); };
-                if (stream) y_dt == HAWQ_S32 ? run(residual_add_stream_kernel<MD, RD, true>) : run(residual_add_stream_kernel<MD, RD, false>);
+                if constexpr (MD == HAWQ_S32 || RD == HAWQ_S32)
+                    if (stream && past) return y_dt == HAWQ_S32 ? run(residual_add_stream_kernel<MD, RD, true, true>) : run(residual_add_stream_kernel<MD, RD, false, true>);
+                if (stream) y_dt == HAWQ_S32 ? run(residual_add_stream_kernel<MD, RD, true, false>) : run(residual_add_stream_kernel<MD, RD, false, false>);
                 else y_dt == HAWQ_S32 ? run(residual_add_vec_kernel<MD, RD, true>) : run(residual_add_vec_kernel<MD, RD, false>);
             };
             auto on_r = [&](auto md) {

@@ -88,6 +88,13 @@ def test_concat_wide_parameters(hawq, P):
     assert_same(y.cpu().numpy(), np.asarray(want).reshape(tuple(y.shape)))
 
 
+# INT32 operands past the caches: from 128 MB in all on; one group of four below and above, results of either width
+@pytest.mark.parametrize("P,K,m_dt,r_dt,y_dt", [(41666, 512, oracle.S32, oracle.U8, oracle.U8), (41667, 512, oracle.S8, oracle.S32, oracle.U8),
+                                                (26044, 4 * 103, oracle.S32, oracle.S32, oracle.S32)])
+def test_residual_add_past_the_caches(hawq, P, K, m_dt, r_dt, y_dt):
+    test_residual_add_streaming_form(hawq, P, K, m_dt, r_dt, y_dt, "c")
+
+
 @pytest.mark.parametrize("P,spec,y_dt", [(1, [(4, oracle.S32)], oracle.U8), (777, [(64, oracle.S32), (12, oracle.U8), (4, oracle.S8)], oracle.U8),
                                          (9000, [(64, oracle.S32), (64, oracle.S32), (96, oracle.S32), (288, oracle.S32)], oracle.U8),
                                          (50, [(4, oracle.S32)] * 8, oracle.S32), (50, [(8, oracle.U8)] * 9, oracle.U8),
