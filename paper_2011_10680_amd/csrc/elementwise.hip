@@ -121,9 +121,11 @@ __device__ __forceinline__ uint32_t pack4(const v4i &o) {   // low bytes of four
     return __builtin_amdgcn_perm((uint32_t)o[1], (uint32_t)o[0], 0x0c0c0400u) | __builtin_amdgcn_perm((uint32_t)o[3], (uint32_t)o[2], 0x04000c0cu);
 }
 
-// The form for tensors that many rounds of the grid stream through: narrow evaluation, non-temporal loads and stores (nothing here
-// is read twice), three workgroups a compute unit.
-template <int MD, int RD, bool Y32>
+// The form for tensors that many rounds of the grid stream through: narrow evaluation, three workgroups a compute unit.  NT: INT32
+// operands pass the caches by (non-temporal loads).  Results do not: the layer that reads them next would find them in HBM (a
+// convolution behind the addition 5 to 14 % slower over all sizes, 64 -> 512 at 236463 pixels 51 us for both, with non-temporal
+// stores 75).
+template <int MD, int RD, bool Y32, bool NT>
 __global__ void __launch_bounds__(256)
 residual_add_stream_kernel(const uint32_t units, const uint32_t groups, const void *m, const int32_t *__restrict__ m_b,
                         const uint8_t *__restrict__ m_c, const void *r, const int32_t *__restrict__ r_b,
@@ -176,9 +178,9 @@ residual_add_stream_kernel(const uint32_t units, const uint32_t groups, const vo
 }
 
 // Workgroups of 256 threads such that their threads are a multiple of `groups` (every thread keeps its channel group): a
-// multiple of groups / gcd(groups, 256), one unit per thread up to `large` workgroups (four to a compute unit), which then walk:
-// a grid of more, one to each four units up to 4096, has its last round half empty (32 x 35 x 35 x 288 INT32 to 4 bits 11.1 us,
-// with 1024 workgroups 10.2; four branches of 512 channels in all to 8 bits 19.9 and 18.7).  At most 4096.  0: no such grid.
+// multiple of groups / gcd(groups, 256), one unit per thread up to `large` workgroups, which then walk.  0: no such grid.
+// 1024 (four to a compute unit) and not one to each four units: that grid has its last round half empty (32 x 35 x 35 x 288 INT32 to
+// 4 bits 11.1 us, with 1024 workgroups 10.2; four branches of 512 channels in all to 8 bits 19.9 and 18.7).
 // stream: no more than `large` where a multiple at most an eighth below it exists, for a few compute units with one workgroup more than
 // the others set the end (200704 pixels of 100 channels, INT32 and bytes, 775 workgroups 23.6 us, 750 21.2; 60000 of 300 21.7 and
 // 19.6; 25088 of 1028 771 workgroups 29.2 us, 514 31.5).  The concatenation gains nothing from it (288 channels to 4 bits 10.7, 10.9).
@@ -618,8 +620,11 @@ struct ConcatArgs {
     uint32_t end[kConcatMax];      // first channel group past the branch
     int32_t dt[kConcatMax];
 };
-template <int YB>   // bits of an output element
-__global__ void __launch_bounds__(256)
+// MANY: the form of large tensors, which eight waves a SIMD walk: its 64-bit evaluation has two pixels in flight, not four, and
+// the kernel 64 registers instead of 94 (with five waves a SIMD see launch_concat_all; with c > 32 in every channel it is 2 to
+// 12 % slower than four pixels in flight at eight waves were, 60 to 130 MB).
+template <int YB, bool MANY>   // bits of an output element
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MANY ? 8 : 5)))
 concat_vec_kernel(const ConcatArgs a, const int n, const uint32_t units, const uint32_t groups, const int lo, const int hi, void *y) {
     constexpr int U = 4;
     const uint32_t T = gridDim.x * 256;
@@ -660,6 +665,11 @@ concat_vec_kernel(const ConcatArgs a, const int n, const uint32_t units, const u
     int32_t vlo = lo, vhi = hi;
     int64_t half = (int64_t)1 << 31;
     asm volatile("" : "+v"(vlo), "+v"(vhi), "+v"(half));
+    auto put = [&](const v4i &o, uint32_t at) {
+        if constexpr (YB == 32) ((v4i *)y)[at] = o;
+        else if constexpr (YB == 8) ((uint32_t *)y)[at] = pack4(o);
+        else ((uint16_t *)y)[at] = (uint16_t)((o[0] & 0xf) | ((o[1] & 0xf) << 4) | ((o[2] & 0xf) << 8) | ((o[3] & 0xf) << 12));
+    };
     auto walk = [&](auto nc) {
         auto finish = [&](const v4i &v, uint32_t at) {
             v4i o;
@@ -668,9 +678,7 @@ concat_vec_kernel(const ConcatArgs a, const int n, const uint32_t units, const u
                 if constexpr (decltype(nc)::value) o[j] = med3(pq.narrow(v[j], j, half), vlo, vhi);
                 else o[j] = clamp64(pq.wide(v[j], j), lo, hi);
             }
-            if constexpr (YB == 32) ((v4i *)y)[at] = o;
-            else if constexpr (YB == 8) ((uint32_t *)y)[at] = pack4(o);
-            else ((uint16_t *)y)[at] = (uint16_t)((o[0] & 0xf) | ((o[1] & 0xf) << 4) | ((o[2] & 0xf) << 8) | ((o[3] & 0xf) << 12));
+            put(o, at);
         };
         while (four) {
 #pragma unroll
@@ -687,7 +695,24 @@ concat_vec_kernel(const ConcatArgs a, const int n, const uint32_t units, const u
         }
     };
     if (__all(narrow)) walk(std::true_type{});
-    else walk(std::false_type{});
+    else if constexpr (!MANY) walk(std::false_type{});
+    else {
+        auto unit = [&](const v4i &t, uint32_t at) {
+            v4i o;
+            uint32_t cs = c;
+            asm volatile("" : "+v"(cs));       // (kept over the loop, the shifts' 64-bit roundings alone are sixteen registers)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) o[j] = clamp64(rq64(t[j], b[j], (cs >> (8 * j)) & 0xff), lo, hi);
+            put(o, at);
+        };
+#pragma unroll 1
+        for (; u + T < units; u += 2 * T, e += 2 * de) {
+            const v4i t0 = load(e), t1 = load(e + de);
+            unit(t0, u);
+            unit(t1, u + T);
+        }
+        if (u < units) unit(load(e), u);
+    }
 }
 
 bool launch_concat_all(int64_t n_pixels, int n, const hawq_concat_branch *br, int Kt, int y_dt, int lo, int hi, void *y, hipStream_t s,
@@ -705,12 +730,18 @@ bool launch_concat_all(int64_t n_pixels, int n, const hawq_concat_branch *br, in
         end += br[i].K / 4;
         a.q[i] = br[i].q; a.b[i] = br[i].b; a.c[i] = br[i].c; a.end[i] = end; a.dt[i] = br[i].dtype;
     }
+    // From 2^22 groups on (some 60 MB) 4096 workgroups of the form with eight waves a SIMD: the others' five have too few bytes in
+    // flight there, of 8-bit branches above all.  285 shapes against the 64-bit form with a workgroup to each four units: 60 to 80 MB
+    // 0.97 -> 0.91 of its time, 80 to 160 1.02 to 1.05 -> 0.91, above 1.07 -> 0.95 (single shapes 1.21 -> 1.00).  Below, the fewer
+    // workgroups are as fast or faster (20 to 40 MB 0.84 of that time, with 4096 0.88).
     const int64_t units = n_pixels * (Kt / 4);
-    const uint32_t nb = grouped_blocks(units, Kt / 4);
+    const bool many = units >= 1 << 22;
+    const uint32_t nb = grouped_blocks(units, Kt / 4, many ? 4096 : 1024);
     if (nb == 0) return false;
-    if (y_dt == HAWQ_S32) concat_vec_kernel<32><<<nb, 256, 0, s>>>(a, n, (uint32_t)units, Kt / 4, lo, hi, y);
-    else if (is4(y_dt)) concat_vec_kernel<4><<<nb, 256, 0, s>>>(a, n, (uint32_t)units, Kt / 4, lo, hi, y);
-    else concat_vec_kernel<8><<<nb, 256, 0, s>>>(a, n, (uint32_t)units, Kt / 4, lo, hi, y);
+    auto run = [&](auto kernel) { kernel<<<nb, 256, 0, s>>>(a, n, (uint32_t)units, Kt / 4, lo, hi, y); };
+    if (y_dt == HAWQ_S32) many ? run(concat_vec_kernel<32, true>) : run(concat_vec_kernel<32, false>);
+    else if (is4(y_dt)) many ? run(concat_vec_kernel<4, true>) : run(concat_vec_kernel<4, false>);
+    else many ? run(concat_vec_kernel<8, true>) : run(concat_vec_kernel<8, false>);
     st = check_launch();
     return true;
 }

@@ -95,6 +95,32 @@ def test_residual_add_past_the_caches(hawq, P, K, m_dt, r_dt, y_dt):
     test_residual_add_streaming_form(hawq, P, K, m_dt, r_dt, y_dt, "c")
 
 
+# the form of large tensors, from 2^22 groups of four on: narrow parameters, and waves that hold a channel outside their range beside
+# others; an even and an odd number of pixels left to a thread
+@pytest.mark.parametrize("P,y_dt", [(43701, oracle.U8), (43700, oracle.U4), (54613, oracle.S32)])
+@pytest.mark.parametrize("wide", [False, True])
+def test_concat_large_form(hawq, P, y_dt, wide):
+    import torch
+    from gpu_util import to_dev, assert_same
+    g = np.random.default_rng(P)
+    host, dev = [], []
+    for K, dt in ((228, oracle.S32), (100, oracle.U8), (56, oracle.S8)):
+        q = _draw(g, (P, K), dt)
+        b = g.integers(1 << 14, 1 << 15, size=K).astype(np.int32)
+        c = np.full(K, 27 if dt == oracle.S32 else 15, dtype=np.uint8)
+        if wide:
+            b[K // 2], c[K // 2] = (1 << 30) + 12345, 44 if dt == oracle.S32 else 31
+        host.append((q, dt, b, c))
+        dev.append((to_dev(q), dt, to_dev(b), to_dev(c)))
+    lo, hi = {oracle.U8: (0, 127), oracle.U4: (0, 15), oracle.S32: (-1000, 1000)}[y_dt]
+    assert P * 96 >= 1 << 22
+    y = torch.full((P, 192 if y_dt == oracle.U4 else 384), 0x5A, dtype=torch.int32 if y_dt == oracle.S32 else torch.uint8, device="cuda")
+    hawq.hawq_concat_dyadic(P, dev, y_dt, lo, hi, y)
+    torch.cuda.synchronize()
+    want = oracle.concat_dyadic(host, n_pixels=P, y_dt=y_dt, y_lo=lo, y_hi=hi)
+    assert_same(y.cpu().numpy(), np.asarray(want).reshape(tuple(y.shape)))
+
+
 @pytest.mark.parametrize("P,spec,y_dt", [(1, [(4, oracle.S32)], oracle.U8), (777, [(64, oracle.S32), (12, oracle.U8), (4, oracle.S8)], oracle.U8),
                                          (9000, [(64, oracle.S32), (64, oracle.S32), (96, oracle.S32), (288, oracle.S32)], oracle.U8),
                                          (50, [(4, oracle.S32)] * 8, oracle.S32), (50, [(8, oracle.U8)] * 9, oracle.U8),
