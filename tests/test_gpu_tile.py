@@ -109,6 +109,59 @@ def test_blocked_weights(hawq):
         assert_same(y.cpu().numpy(), want, str((bits, C, K)))
 
 
+def _tile(M, C, K, R, bits):
+    """The tile of a launch without a shortcut (tile_choice and few_tiles of csrc/conv_tile.hip)."""
+    steps = (R * R * C * bits // 8 + 63) // 64
+    costs = []
+    for bm, bn, chain in ((256, 256, 75), (128, 128, 37), (128, 64, 27), (64, 64, 20), (64, 32, 17)):
+        per_cu = (-(-M // bm) * -(-K // bn) + 255) // 256
+        costs.append((steps * max(per_cu * (bm + bn) * 64 // 512, chain) + per_cu * bm * bn // 150, len(costs)))
+    best = min(costs)[1]
+    if best < 3 and -(-M // 64) * -(-K // 64) <= (768 if steps < 16 else 512 if steps < 32 else 0):
+        best = 3
+    return ((256, 256), (128, 128), (128, 64), (64, 64), (64, 32))[best]
+
+
+# the larger tiles over windows, several steps and one, ragged in pixels and channels: (N, H, W, C, K, R, bits, what, tile, blocked weights)
+_LARGE = [
+    (1, 223, 222, 48, 33, 3, 8, "", (128, 64), False), (1, 223, 222, 16, 34, 5, 8, "byte", (128, 64), False), (3, 129, 131, 96, 35, 3, 4, "", (128, 64), False),
+    (1, 159, 161, 80, 97, 3, 8, "", (128, 128), False), (1, 159, 161, 112, 99, 3, 8, "byte", (128, 128), False), (1, 201, 201, 160, 97, 3, 4, "", (128, 128), False),
+    (2, 113, 115, 16, 67, 5, 8, "s", (128, 128), False), (1, 159, 161, 64, 97, 3, 8, "", (128, 128), True), (1, 201, 203, 128, 97, 3, 4, "", (128, 128), True),
+    (1, 235, 237, 48, 161, 3, 8, "", (256, 256), False), (1, 183, 182, 48, 194, 5, 8, "byte", (256, 256), False), (1, 245, 245, 32, 163, 5, 4, "", (256, 256), False),
+    (1, 235, 237, 96, 161, 3, 4, "s", (256, 256), False), (1, 235, 237, 64, 161, 3, 8, "", (256, 256), True), (1, 245, 243, 128, 163, 3, 4, "", (256, 256), True),
+]
+
+
+@pytest.mark.parametrize("shape", _LARGE)
+def test_large_tiles_over_windows(hawq, shape):
+    import torch
+    from gpu_util import to_dev, assert_same
+    from test_gpu_conv import _scale_c
+    N, H, W, C, K, R, bits, what, tile, block = shape
+    assert _tile(N * H * W, C, K, R, bits) == tile
+    case = _scale_c(wl.conv_case(seed=sum(shape[:7]), N=N, H=H, W=W, C=C, K=K, R=R, S=R, stride=1, pad=R // 2, bits=bits), bits)
+    if what == "byte":
+        case["x"] = np.random.default_rng(K).integers(0, 256, size=case["x"].shape).astype(np.uint8)
+        case["c"] = case["c"] + np.uint8(1)
+    x_dt, w_dt = (hawq.U8, hawq.S8) if bits == 8 else (hawq.U4, hawq.S4)
+    y_dt = {(8, True): hawq.S8, (8, False): hawq.U8, (4, True): hawq.S8, (4, False): hawq.U8}[bits, what == "s"]
+    lo, hi, relu = (-128, 127, 0) if what == "s" else (0, 127, 1)
+    d = hawq.ConvDesc(N=N, H=H, W=W, C=C, K=K, R=R, S=R, stride_h=1, stride_w=1, pad_h=R // 2, pad_w=R // 2, x_dtype=x_dt, w_dtype=w_dt,
+                      y_dtype=y_dt, res_dtype=hawq.U8, relu=relu, y_lo=lo, y_hi=hi, x_hi=127 if bits == 8 and what != "byte" else 0)
+    w = to_dev(case["w"])
+    if block:
+        blocked = torch.empty(hawq.hawq_conv_blocked_weights_bytes(d), dtype=torch.uint8, device="cuda")
+        hawq.hawq_conv_block_weights(d, w, blocked)
+        d.w_blocked = blocked.data_ptr()
+    y = torch.full((N, H, W, K), 0x5A, dtype=torch.uint8, device="cuda")
+    hawq.hawq_conv2d_int(d, to_dev(case["x"]), w, to_dev(case["bias"]), to_dev(case["b"]), to_dev(case["c"]), None, None, None, y)
+    torch.cuda.synchronize()
+    want = oracle.conv2d_int(case["x"], case["w"], case["bias"], case["b"], case["c"], N=N, H=H, W=W, C=C, K=K, R=R, S=R, stride=1, pad=R // 2,
+                             x_dt=x_dt, w_dt=w_dt, y_dt=y_dt, relu=relu, y_lo=lo, y_hi=hi)
+    assert_same(y.cpu().numpy().view(want.dtype), want, str(shape))
+    assert len(np.unique(want)) > 8
+
+
 # (N, H, W, C, K, R, stride, bits, shortcut's type, what): 64x64 tiles with remainders in pixels and channels, one K-step and
 # many, channel counts of 4, 8 and 12 past a group of 16, results of either sign and width; what: "wide" (one channel's main and
 # another's shortcut parameters outside the narrow evaluation's range), "s" (signed result)
