@@ -35,7 +35,8 @@ def test_128_channels_with_shortcut_in_one_round_of_tile_pairs(N, H, W, K, bits,
 
 
 # 8200-odd pixels: fewer groups than waves, so that some waves of an XCD have none; a channel count whose tiles do not divide a
-# workgroup's waves; the form with shared stages; the resident-weight 3x3 with an uneven number of tiles per XCD
+# workgroup's waves; the form with shared stages; the resident-weight 3x3, a number of tiles that is no multiple of 8.  All of them
+# below the line of the eighths: their waves take turns.
 @pytest.mark.parametrize("N,H,W,C,K,R,bits,res", [(1, 57, 144, 64, 64, 1, 8, False), (1, 57, 144, 64, 96, 1, 4, True), (1, 59, 141, 128, 96, 1, 8, False),
                                                   (1, 57, 144, 256, 64, 1, 4, False), (1, 57, 144, 256, 384, 1, 8, True), (11, 55, 55, 64, 64, 3, 8, True),
                                                   (13, 53, 51, 64, 64, 3, 4, False)])
@@ -75,5 +76,36 @@ def test_two_convolutions_with_sequences_not_dealt_evenly(N, H, C, K, Cs, ss, sl
     from gpu_util import assert_same
     from test_gpu_dual import _case, _run
     assert _sequences(slots, K // 32, -(-N * H * H // 32), False) % 8 != 0
+    got, want = _run(hawq, _case(N + H + K, N, H, C, K, 1, Cs, ss), hawq.U8, 1, 0, 127)
+    assert_same(got, want, str((N, H, C, K, Cs, ss)))
+
+
+def _line():
+    """Output pixels from which the persistent kernels walk an XCD's own eighth (xcd_eighths of csrc/xcd_walk.h)."""
+    import pathlib
+    import re
+    import paper_2011_10680_amd as hawq
+    return int(re.search(r"bool xcd_eighths\(int64_t pixels\) { return pixels >= (\d+); }",
+                         (pathlib.Path(hawq.__file__).parent / "csrc" / "xcd_walk.h").read_text())[1])
+
+
+# eighths of unequal size: 397 and 403 tiles of 128 pixels, 1587 and 1611 groups of 32 (no multiple of 8), ragged at the end; the 3x3 with
+# resident weights, the kernel with stages of a wave's own, the ones with shared stages
+@pytest.mark.parametrize("N,H,W,C,K,R,bits,res", [
+    (13, 63, 62, 64, 64, 3, 8, False), (13, 63, 62, 64, 64, 3, 8, True), (13, 63, 62, 64, 64, 3, 4, False), (13, 63, 62, 64, 64, 3, 4, True),
+    (13, 63, 62, 64, 64, 1, 8, False), (13, 63, 62, 64, 96, 1, 4, False), (13, 63, 62, 64, 256, 1, 4, True), (4, 113, 114, 128, 128, 1, 8, True),
+    (4, 113, 114, 256, 384, 1, 8, False), (4, 113, 114, 256, 128, 1, 4, True),
+])
+def test_eighths_of_unequal_size(N, H, W, C, K, R, bits, res):
+    assert N * H * W >= _line() and -(-N * H * W // 128) % 8 and -(-N * H * W // 32) % 8
+    test_turns_with_uneven_shares(N, H, W, C, K, R, bits, res)
+
+
+@pytest.mark.parametrize("N,H,C,K,Cs,ss", [(13, 63, 64, 256, 64, 1), (13, 63, 64, 256, 64, 2), (13, 63, 128, 512, 256, 2)])
+def test_two_convolutions_in_eighths(N, H, C, K, Cs, ss):
+    import paper_2011_10680_amd as hawq
+    from gpu_util import assert_same
+    from test_gpu_dual import _case, _run
+    assert N * H * H >= _line() and -(-N * H * H // 32) % 8
     got, want = _run(hawq, _case(N + H + K, N, H, C, K, 1, Cs, ss), hawq.U8, 1, 0, 127)
     assert_same(got, want, str((N, H, C, K, Cs, ss)))
