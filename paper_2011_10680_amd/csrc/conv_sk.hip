@@ -442,7 +442,8 @@ hawq_status launch_conv_sk(const ConvArgs &a_in, int x_hi, hipStream_t s) {
     // 64 pixels a workgroup, from 512 of those on 32 x 128 (packed 1x1 272 -> 288 at 39200 pixels 24 us,
     // with 64 x 128 tiles or four waves a tile 27 to 42; packed 3x3 48 -> 64 8.3 and 9.8) -- of more than 32 channels in their last 64,
     // between one round of the small tiles and two, only reductions of a few steps (1x1 544 -> 36 at 12887 pixels with a shortcut 5.6 us, in small
-    // tiles 6.7; 3x3 96 -> 42 at 11025 6.7 and 7.6; with up to 4 steps, packed 6, the small ones are the faster or equal).
+    // tiles 6.7; 3x3 96 -> 42 at 11025 6.7 and 7.6; with up to 4 steps, packed 6, the small ones are the faster or equal) and
+    // two convolutions always (56 x 56, 160 -> 256 plus 1024 / 2 8.9 us, in small tiles 10.9; 32 x 32, 64 -> 756 plus 1024 / 2 10.6 and 11.9).
     auto tiles = [&](int tc, int tp) { return (int64_t)((a.K + 16 * tc - 1) / (16 * tc)) * ((a.M + 16 * tp - 1) / (16 * tp)); };
     if (tiles(1, 1) <= 256) return sk_launch<1, 1, 8, 1>(a, e, xf, s);
     if (tiles(1, 2) <= 256) return sk_launch<1, 2, 8, 1>(a, e, xf, s);
@@ -450,7 +451,7 @@ hawq_status launch_conv_sk(const ConvArgs &a_in, int x_hi, hipStream_t s) {
     const int steps = (a.R * a.S * (is4(a.x_dt) ? a.C / 2 : a.C) + 63) / 64;
     if (tiles(2, 4) <= 256) return steps < 32 ? sk_launch<2, 2, 4, 2>(a, e, xf, s) : sk_launch<2, 4, 8, 1>(a, e, xf, s);
     const bool whole = (a.K - 1) % 64 >= 32 && tiles(2, 4) > 272 && tiles(2, 4) <= 512 && steps >= (is4(a.x_dt) ? 7 : 5);
-    if (tiles(4, 4) <= 512 && (steps >= 16 || whole)) return sk_launch<4, 2, 4, 2>(a, e, xf, s);
+    if (tiles(4, 4) <= 512 && (steps >= 16 || whole || a.xs)) return sk_launch<4, 2, 4, 2>(a, e, xf, s);
     return tiles(2, 4) <= 512 ? sk_launch<2, 2, 2, 2>(a, e, xf, s) : sk_launch<2, 4, 2, 2>(a, e, xf, s);
 }
 
