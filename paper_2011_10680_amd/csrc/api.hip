@@ -240,8 +240,9 @@ hawq_status dispatch_conv_dual(const ConvArgs &a, int x_hi, int xs_hi, hipStream
         Rp1Args r1;
         if (make_rp1_args(a, x_hi, xs_hi, r1)) return launch_conv_rp1(r1, s);
     }
-    if (tile && conv_tile_dual_preferred(a)) return launch_conv_tile(a, x_hi, s);
-    if (conv_mfma_dual_eligible(a, x_hi, xs_hi)) return launch_conv_mfma_dual(a, s);
+    const bool mfma = conv_mfma_dual_eligible(a, x_hi, xs_hi);
+    if (tile && conv_tile_dual_preferred(a, mfma)) return launch_conv_tile(a, x_hi, s);
+    if (mfma) return launch_conv_mfma_dual(a, s);
     if (sk) return launch_conv_sk(a, x_hi, s);
     if (tile) return launch_conv_tile(a, x_hi, s);
     return launch_conv_direct(a, s);

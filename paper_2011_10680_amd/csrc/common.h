@@ -194,7 +194,7 @@ bool conv_tile_eligible(const ConvArgs &a, int x_hi);
 bool conv_tile_over_sk(const ConvArgs &a);                 // preferred below the split-reduction kernel's line
 bool conv_tile_preferred(const ConvArgs &a, bool mfma);    // ... over conv_mfma (mfma: it is eligible) or that kernel above its line
 bool conv_tile_dual_eligible(const ConvArgs &a, int x_hi, int xs_hi);
-bool conv_tile_dual_preferred(const ConvArgs &a);          // over conv_mfma's form
+bool conv_tile_dual_preferred(const ConvArgs &a, bool mfma);   // over conv_mfma's form (mfma: it is eligible) or the split-reduction kernel
 hawq_status launch_conv_tile(const ConvArgs &a, int x_hi, hipStream_t s);   // (one or two convolutions)
 // 3x3, 64 input channels, stride 1 or 2, on whole output rows (fragment-ordered weights in registers)
 bool conv3x3_rows_eligible(const ConvArgs &a, int x_hi);

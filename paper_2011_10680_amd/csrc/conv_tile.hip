@@ -576,13 +576,19 @@ bool conv_tile_preferred(const ConvArgs &a, bool mfma) {
 // Two convolutions in one launch.  Packed operands always, the direct kernel is what else takes them (56 x 56, 64 -> 256 plus 64, batch
 // 1 267 us, here 5.4, batch 64 11700 and 63).  Bytes with few tiles, as few_tiles counts them over both branches' steps; conv_mfma.hip
 // keeps a larger tile's sums twice and has one workgroup of it on a CU (56 x 56, 64 -> 256 plus 64, batch 1 8.2 -> 5.2 us; 28 x 28, 128 ->
-// 512 plus 256 / 2, batch 2 9.5 -> 6.2, 8 10.6 -> 9.4; 3x3 256 -> 256 at 14 x 14 plus 128 / 2, batch 16 24.2 -> 19.1, 48 24.4 and 26.4).
-// Where the main branch's term fits 16 bits its eight-wave form is better than that: up to a tile per CU (ResNet50 at batch 1 223.4 ->
+// 512 plus 256 / 2, batch 2 9.5 -> 6.2, 8 10.6 -> 9.4; 3x3 256 -> 256 at 14 x 14 plus 128 / 2, batch 16 24.2 -> 19.1, 48 24.4 and 26.4),
+// from 41 steps on up to 320 tiles (3x3 256 -> 512 plus 512 / 2 at 7 x 7, batch 53, 328 tiles of 44 steps 21.1 us, here 22.8).  Where
+// the main branch's term fits 16 bits its eight-wave form is better than that: up to a tile per CU (ResNet50 at batch 1 223.4 ->
 // 221.0 us, ResNet18 at 8 140.3 -> 138.1; at 32, with 392 tiles of 38 steps, 207 and 213).
-bool conv_tile_dual_preferred(const ConvArgs &a) {
+// What conv_mfma.hip does not take (mfma: it does) comes here from more than one 64 x 64 tile to a CU on, below that with few steps: the
+// split-reduction kernel is the other one, held up only by a long shortcut without blocked weights (up to 256 tiles of 17 to 20 steps
+// 9.0 us here, 10.5 there; windows of 13 to 18 steps 9.0 to 10.2 and 7.3 to 7.7; of 25 to 64 steps 1.3 to 1.4 times its time; over
+// 256 tiles 0.46 to 0.94 of it by steps and tiles, up to 1.1 with more than 32 steps; 700 shapes).
+bool conv_tile_dual_preferred(const ConvArgs &a, bool mfma) {
     if (is4(a.x_dt)) return true;
     const int64_t steps = tile_steps(a) + (a.Cs + 63) / 64, tiles = tiles_of(a, 64, 64);
-    return tiles <= (a.dual16 ? (steps < 32 ? 256 : 0) : steps < 16 ? 768 : steps < 64 ? 512 : 0);
+    if (!mfma) return tiles > 256 || steps <= (a.R * a.S > 1 || a.ws_t ? 12 : 20);
+    return tiles <= (a.dual16 ? (steps < 32 ? 256 : 0) : steps < 16 ? 768 : steps < 41 ? 512 : steps < 64 ? 320 : 0);
 }
 
 hawq_status launch_conv_tile(const ConvArgs &a_in, int x_hi, hipStream_t s) {

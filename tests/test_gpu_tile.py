@@ -222,6 +222,14 @@ def test_two_convolutions(hawq, shape):
     assert len(np.unique(v)) > 8
 
 
+# two convolutions that the kernel of whole 64-channel steps does not take, either side of the lines to the split-reduction kernel
+# (a 64 x 64 tile per CU with a step more than this kernel takes there, one fewer, more tiles) and that kernel's 64-channel tiles
+@pytest.mark.parametrize("N,H,C,K,R,Cs,ss", [(1, 32, 256, 1020, 1, 1024, 1), (1, 32, 320, 1020, 1, 1024, 1), (1, 33, 320, 1020, 1, 1024, 1),
+                                             (1, 56, 128, 1024, 3, 48, 2), (1, 56, 336, 256, 1, 1024, 2)])
+def test_two_convolutions_at_the_lines(hawq, N, H, C, K, R, Cs, ss):
+    test_two_convolutions(hawq, (N, H, C, K, R, Cs, ss, 8, False, oracle.U8))
+
+
 # (pixels, C, K, R, bits, shortcut): either side of the lines between this kernel, the split-reduction kernel and the one with pixels along
 # the lanes: packed operands with a 32 x 64 tile per CU and one more; packed windows with a 64 x 64 tile per CU and one more, with
 # and without a shortcut; narrow shortcuts; a long reduction over few channels; a shortcut of fewer than 1024 pixels; the split-reduction
