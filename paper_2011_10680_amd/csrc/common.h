@@ -49,7 +49,8 @@ struct ConvArgs {
     // ws_f (optional): the shortcut convolution's weights in the same fragment order (two-convolution form of conv_rp1.hip)
     const void *ws_f;
     // corun: kernels of another stream share the chip with this launch (the forward's two half-batches): configurations
-    // meant for a launch that is alone (small tiles with a deep LDS ring when there are few tiles) are not chosen
+    // meant for a launch that is alone (small tiles with a deep LDS ring when there are few tiles) are not chosen.  The kernel with
+    // channels along the lanes (conv_tile.hip) does not look at it
     int32_t corun;
     // dual16 (two-convolution form, set by the network plan from host data): every (b, c) and (b_s, c_s) is in the narrow
     // evaluation's range and |rq(acc + bias, b, c)| of the main branch cannot exceed 32767 for any input

@@ -534,6 +534,9 @@ bool conv_tile_over_sk(const ConvArgs &a) {
 // products and epilogues overlap (shortcut, 64 -> 256 at 56 x 56, packed, batch 2: 5.0 us, with 128 x 64 6.2; 3x3 / 2 64 -> 128, batch
 // 16: 6.2 and 6.6).  With more tiles or steps the larger tiles' fewer bytes count (512 x 4096 x 4096 22.7 us, with 64 x 64 23.8; shortcut,
 // packed 3x3 256 -> 256 at 14 x 14, batch 48, 588 tiles of 18 steps: 16.9, conv_mfma.hip 16.4).
+// Beside another part's kernels (corun) the same: with and without the larger tiles there ResNet50 at batch 96, 128, 192 and 256 takes 875
+// and 880 us, 1038 and 1038, 1475 and 1468, 1812 and 1808, mixed at 256 1783 and 1776, ResNet18 at 128 367 and 369, all within what
+// two runs of one side differ by.
 static bool few_tiles(const ConvArgs &a) {
     const int64_t steps = tile_steps(a), tiles = tiles_of(a, 64, 64);
     return tiles <= (steps < 16 ? 768 : steps < 32 ? 512 : 0);

@@ -35,7 +35,7 @@ residual_add_kernel(const int64_t units, const int K, const int per, const int m
 // Vector form: K % 4 == 0, 8-bit or INT32 operands and output.  A thread keeps one group of four channels (the grid's thread
 // count is a multiple of K / 4), so its parameters sit in registers, and has four pixels' loads in flight.  Bound: HBM
 // (m, r and y once); 32 x 56 x 56 x 256 INT32 + u8 -> u8 (154 MB): 103 us in the element-wise form above, whose sixteen
-// parameter loads per thread outnumbered its two data loads, 37 us (4.2 TB/s) in the exact 64-bit form below, 25.5 us (6.0 TB/s)
+// parameter loads per thread outnumbered its two data loads, 37 us (4.2 TB/s) in the exact 64-bit form below, 25.8 us (6.0 TB/s)
 // in the streaming form after it.
 template <int DT, bool NT = false>
 __device__ __forceinline__ v4i load4(const void *p, int64_t unit) {   // elements 4 unit .. 4 unit + 3

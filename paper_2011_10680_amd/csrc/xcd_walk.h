@@ -17,7 +17,8 @@ constexpr uint32_t xcd_remap(uint32_t bid, uint32_t nblocks) {
 // XCD's workgroups in turn.  The kernels of a network that share this map (or xcd_remap's, which gives the same eighths) read most of
 // what the kernel before them wrote from their own XCD's L2.  Measured by two plain kernels, a tensor written and read back with
 // one map: 16 MB 6.6 us, 32 MB 9.7, 64 MB 21; every eighth read on another XCD than the one that wrote it: 13.9, 24.9, 31.  In the
-// networks, whose kernels wait for other things as well, 1 % (ResNet50 at batch 128 1055 -> 1048 us, mixed at 256 1773 -> 1756).
+// networks, whose kernels wait for other things as well, 1.4 to 1.8 % of ResNet50 at batch 256 (8-bit 1837 -> 1812 us, mixed 1816 -> 1783),
+// nothing up to 192 (128 1035 and 1038, 192 1473 and 1475, 96 879 and 875; mixed at 96 and 128 and ResNet18 at 256 equal too).
 // (A contiguous run per workgroup instead of turns is 2 % slower: the neighbours' walk no longer shares L2 lines.)
 // Otherwise: turns over all tiles, an XCD's workgroups side by side.
 struct TileWalk { int32_t first, end, step; };
@@ -30,7 +31,9 @@ constexpr TileWalk xcd_walk(uint32_t b, uint32_t gx, int32_t n_tiles, bool eight
 // Eighths from 49152 output pixels on.  Below, with a round or two of tiles per workgroup, the 28 x 28 and 14 x 14 layers of ResNet50
 // gain nothing and their readers lose (batch 48, 512 -> 128 at 28 x 28 behind such a layer 11.9 us, with eighths 14.1; the forward at
 // batch 20 410 us, with eighths throughout 415, at 48 621 and 629; at 256, mixed widths, whose 14 x 14 layers have 50176, 1801 with
-// them and 1817 with a line of 65536).
+// them and 1817 with a line of 65536; 37632 pixels, the 28 x 28 layers of batch 48, are the next ones below that were measured, so the
+// line could lie anywhere between).  One layer alone, above the line: the kernel with stages of a wave's own is 3 to 5 %
+// faster in eighths, those with shared stages equal to 2 % slower.  conv1 + pool walks in eighths at every size.
 constexpr bool xcd_eighths(int64_t pixels) { return pixels >= 49152; }
 // grid for it: at most `most` (a multiple of 8) workgroups, no more than the largest eighth needs
 constexpr uint32_t xcd_walk_grid(int64_t n_tiles, uint32_t most) {
