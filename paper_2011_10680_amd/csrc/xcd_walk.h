@@ -31,9 +31,10 @@ constexpr TileWalk xcd_walk(uint32_t b, uint32_t gx, int32_t n_tiles, bool eight
 // Eighths from 49152 output pixels on.  Below, with a round or two of tiles per workgroup, the 28 x 28 and 14 x 14 layers of ResNet50
 // gain nothing and their readers lose (batch 48, 512 -> 128 at 28 x 28 behind such a layer 11.9 us, with eighths 14.1; the forward at
 // batch 20 410 us, with eighths throughout 415, at 48 621 and 629; at 256, mixed widths, whose 14 x 14 layers have 50176, 1801 with
-// them and 1817 with a line of 65536; 37632 pixels, the 28 x 28 layers of batch 48, are the next ones below that were measured, so the
-// line could lie anywhere between).  One layer alone, above the line: the kernel with stages of a wave's own is 3 to 5 %
-// faster in eighths, those with shared stages equal to 2 % slower.  conv1 + pool walks in eighths at every size.
+// them and 1817 with a line of 65536; with a line of 38000, which takes in the 28 x 28 layers of batches up to 62, batch 52 603 and, here,
+// 598, 56 620 and 615, 60 632 and 629; 104 to 240, in two parts, equal within 0.5 %).  One layer alone, above the line: the kernel
+// with stages of a wave's own is 3 to 5 % faster in eighths, those with shared stages equal to 2 % slower.  conv1 + pool walks in
+// eighths at every size (in turns the forward of batches 1 to 15 takes the same time, ResNet18 at 8 135.7 us, in eighths 135.1).
 constexpr bool xcd_eighths(int64_t pixels) { return pixels >= 49152; }
 // grid for it: at most `most` (a multiple of 8) workgroups, no more than the largest eighth needs
 constexpr uint32_t xcd_walk_grid(int64_t n_tiles, uint32_t most) {
