@@ -237,7 +237,7 @@ def test_two_convolutions_at_the_lines(hawq, N, H, C, K, R, Cs, ss):
 _LINES = [
     ((52, 64), 448, 148, 1, 4, False), ((52, 63), 448, 148, 1, 4, False), ((49, 64), 224, 320, 3, 4, False), ((49, 84), 224, 256, 3, 4, False),
     ((41, 64), 96, 384, 3, 4, True), ((43, 65), 96, 384, 3, 4, True), ((201, 177), 192, 16, 3, 4, True), ((201, 220), 192, 12, 3, 8, True),
-    ((181, 193), 464, 12, 3, 8, False), ((31, 33), 384, 512, 3, 4, True), ((31, 33), 192, 512, 3, 8, True), ((136, 64), 544, 36, 1, 8, True),
+    ((181, 193), 464, 12, 3, 8, False), ((397, 247), 432, 12, 3, 8, False), ((31, 33), 384, 512, 3, 4, True), ((31, 33), 192, 512, 3, 8, True), ((136, 64), 544, 36, 1, 8, True),
     ((137, 64), 544, 36, 1, 8, True), ((255, 64), 96, 32, 3, 8, False),
 ]
 
