@@ -506,8 +506,8 @@ static int64_t tiles_of(const ConvArgs &a, int bm, int bn) { return ((int64_t)a.
 // A handful of output channels, a long 3x3 or 1x1 reduction and very many pixels: most of a 32-channel tile's products are for nothing,
 // and this kernel fetches more for them than the other two (3x3 592 -> 8 at 90944 pixels 70 us, the split-reduction kernel 54; 512 -> 10
 // at 122304 74 and, conv_mfma.hip, 53; with fewer pixels it is no slower: 560 -> 11 at 68502 42.8 and 48.5).  From 58 steps on with still more
-// pixels (448 -> 10 at 107800 57.7 and, conv_mfma.hip, 46; 432 -> 12 at 98049 45 and 38.7; over 130 layers of 59 to 63 steps
-// the others need 0.93 of this kernel's time above that line).
+// pixels (448 -> 10 at 107800 57.7 and, conv_mfma.hip, 46; 432 -> 12 at 98049 45 and 38.7; over 117 layers of 59 to 63 steps
+// above that line the others need 0.94 of this kernel's time).
 static bool tile_narrow(const ConvArgs &a) {
     return !is4(a.x_dt) && a.K <= 12 && a.R * a.S <= 9 && tiles_of(a, 64, 64) >= (tile_steps(a) >= 64 ? 1280 : tile_steps(a) >= 58 ? 1500 : INT64_MAX);
 }
