@@ -251,9 +251,10 @@ hawq_status launch_conv_rp1k(const ConvArgs &a, hipStream_t s);
 bool conv_rp1_shape_ok(const Rp1Args &a);
 bool make_rp1_args(const ConvArgs &a, int x_hi, int xs_hi, Rp1Args &r);
 hawq_status launch_conv_rp1(const Rp1Args &a, hipStream_t s);
-// [K][row bytes] weights -> MFMA fragment order for that kernel (four: packed 4-bit rows, expanded to bytes on the way);
+// [K][row bytes] weights -> MFMA fragment order for that kernel (four: packed 4-bit rows, expanded to bytes on the way, in the order
+// in which the kernels split packed activations, or, natural, in that of the elements);
 // out: ceil(K/32) * 32 * (bytes of an expanded row)
-hawq_status launch_fragment_weights(const void *w, void *w_frag, int K, int64_t row, bool four, hipStream_t s);
+hawq_status launch_fragment_weights(const void *w, void *w_frag, int K, int64_t row, bool four, hipStream_t s, bool natural = false);
 
 // [K][row bytes] weights -> the implicit-GEMM kernel's blocked order (ConvArgs::w_t); row a multiple of 64
 hawq_status launch_block_weights(const void *w, void *w_blocked, int K, int64_t row, hipStream_t s);

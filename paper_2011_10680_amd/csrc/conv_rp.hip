@@ -468,8 +468,9 @@ hawq_status launch_conv_rp(const RpArgs &a, bool fused, hipStream_t s) {
 // FOUR: the source rows are packed 4-bit (row bytes = R*S*C / 2, a multiple of 32) and are expanded to signed bytes on
 // the way: 16-byte chunk 2q of the expanded row holds the sign-extended low nibbles of packed bytes 16q .. 16q + 15 (the
 // even elements), chunk 2q + 1 their high nibbles (the odd elements) -- the order in which the kernel's patch fill
-// splits the packed activations.  The copy then has the size and the layout of an 8-bit layer's.
-template <bool FOUR>
+// splits the packed activations.  The copy then has the size and the layout of an 8-bit layer's.  NATURAL: the elements in their
+// own order, for pixels held as bytes.
+template <bool FOUR, bool NATURAL>
 __global__ void __launch_bounds__(256) fragment_weights_kernel(const uint8_t *__restrict__ w, uint8_t *__restrict__ out, const int K,
                                                                const int64_t row, const int64_t chunks) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;   // index of a 16-byte chunk of the output
@@ -483,7 +484,15 @@ __global__ void __launch_bounds__(256) fragment_weights_kernel(const uint8_t *__
     v4i v = {0, 0, 0, 0};
     if (k < K) {
         const int64_t ci = t * 4 + kk * 2 + khalf;   // 16-byte chunk of the (expanded) row
-        if (FOUR) {
+        if (FOUR && NATURAL) {
+            const v2i p = *(const v2i *)(w + (int64_t)k * row + ci * 8);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const uint32_t h = ((uint32_t)p[e >> 1] >> (16 * (e & 1))) & 0xffffu;
+                const uint32_t u = (h & 0xfu) | ((h & 0xf0u) << 4) | ((h & 0xf00u) << 8) | ((h & 0xf000u) << 12);
+                v[e] = (int)(u | ((u & 0x08080808u) * 0x1Eu));
+            }
+        } else if (FOUR) {
             const v4i p = *(const v4i *)(w + (int64_t)k * row + (ci >> 1) * 16);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
@@ -499,13 +508,14 @@ __global__ void __launch_bounds__(256) fragment_weights_kernel(const uint8_t *__
 }
 
 // row: bytes of a weight row as stored (packed 4-bit when four)
-hawq_status launch_fragment_weights(const void *w, void *w_frag, int K, int64_t row, bool four, hipStream_t s) {
+hawq_status launch_fragment_weights(const void *w, void *w_frag, int K, int64_t row, bool four, hipStream_t s, bool natural) {
     const int64_t chunks = (int64_t)((K + 31) / 32) * ((four ? 2 * row : row) / 64) * 128;
     if (chunks == 0) return HAWQ_OK;
     const int64_t blocks = (chunks + 255) / 256;
     if (blocks > 0x7fffffff) return HAWQ_ERR_UNSUPPORTED;
-    if (four) fragment_weights_kernel<true><<<(uint32_t)blocks, 256, 0, s>>>((const uint8_t *)w, (uint8_t *)w_frag, K, row, chunks);
-    else fragment_weights_kernel<false><<<(uint32_t)blocks, 256, 0, s>>>((const uint8_t *)w, (uint8_t *)w_frag, K, row, chunks);
+    if (four && natural) fragment_weights_kernel<true, true><<<(uint32_t)blocks, 256, 0, s>>>((const uint8_t *)w, (uint8_t *)w_frag, K, row, chunks);
+    else if (four) fragment_weights_kernel<true, false><<<(uint32_t)blocks, 256, 0, s>>>((const uint8_t *)w, (uint8_t *)w_frag, K, row, chunks);
+    else fragment_weights_kernel<false, false><<<(uint32_t)blocks, 256, 0, s>>>((const uint8_t *)w, (uint8_t *)w_frag, K, row, chunks);
     return check_launch();
 }
 

@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "common.h"
+#include "conv_block.h"
 
 // Workspace of hawq_forward_resnet_noalloc: a fixed array in device memory that belongs to the library's code object (one
 // copy per GPU the library is loaded on, held until the process ends).  In host code this name is only a handle for
@@ -121,6 +122,9 @@ struct Step {
     // them is never stored): the 3x3 step launches nothing (tail_next = index of the 1x1 step), the 1x1 step launches both
     // (tail_prev = index of the 3x3 step).
     int tail_next = -1, tail_prev = -1;
+    // A bottleneck block at 64 channels as one launch (conv_block.hip): at its last step (block: index of its arguments), the others
+    // launch nothing (block_last: index of that step)
+    int block = -1, block_last = -1, block_in = -1;
     bool fused_pool = false;      // conv1 step: the max pool is computed in the same kernel (writes the pool's tensor)
     bool skip = false;            // max-pool step when conv1 has absorbed it: nothing to launch
 };
@@ -152,6 +156,7 @@ struct hawq_net {
     std::vector<Tensor> tensors;
     std::vector<Step> steps;
     std::vector<int64_t> slot_bytes_per_image;
+    std::vector<BlockArgs> blocks;   // (x, y and N filled per call)
     void *arena = nullptr;
     // a large batch runs as two parts on two streams (see hawq_forward_resnet): the second stream and the fork / join events
     hipStream_t aux_stream = nullptr;
@@ -213,6 +218,17 @@ bool pair_runs_fused(const hawq_net *net, int N, int ds_step) {
     // the eight-wave 16-bit form applies (ResNet18 batch 64, stored form: 189 k four-wave, 202 k two launches, 210 k).
     if (net->steps[d.pair_last].desc.R == 3 && !net->steps[d.pair_last].dual16) return false;
     return true;   // 8-bit operands on both branches (checked when the plan was made): one of the two-convolution kernels applies
+}
+
+// Does a 64-channel bottleneck block run as one launch at batch N?  Wherever its tensors' offsets fit 31 bits: of 96 measured nets
+// (64 x 64 to 448 x 448 pixels, batch 1 to 256, 8-bit and mixed) all but one were faster so, by 4 to 12 % (ResNet50 at 224 x 224,
+// three launches a block -> one: batch 1 227 -> 218 us, 8 326 -> 302, 64 649 -> 597, 256 1779 -> 1583), that one equal
+// (64 x 64, batch 1 mixed: 185 -> 187, where images of 16 x 16 pixels leave a fourteenth to the second tile of a row).
+bool block_runs(const hawq_net *net, int N, int last_step) {
+    const Step &st = net->steps[last_step];
+    if (st.block < 0) return false;
+    const BlockArgs &b = net->blocks[st.block];
+    return (int64_t)N * b.H * b.W * 256 < 0x80000000ll;
 }
 
 size_t slot_offset(const hawq_net *net, int slot, int N) {
@@ -338,8 +354,40 @@ hawq_status hawq_net_create(int32_t arch, int32_t image_hw, int32_t num_classes,
     auto is8 = [&](int i) { return lp[i].bits == 8 || expand[i]; };      // operands in 8-bit form
     auto cont_dt = [&](int i) { return is8(i) ? HAWQ_U8 : HAWQ_U4; };     // container of the tensor layer i reads
 
+    // ---- bottleneck blocks at 64 channels that can run as one launch: the layers' indices, and a common shift for the shortcut's
+    // multipliers.  Every multiplier in the narrow evaluation's range, and no accumulator with its bias beyond 32 bits ----
+    struct Block { int c1, c2, c3, ds, t, rescaled; size_t par; };
+    std::vector<Block> block64;
+    auto sums_fit = [&](int i, int in_hi) {
+        const int64_t row = (int64_t)L[i].R * L[i].S * L[i].C;
+        for (int k = 0; k < L[i].K; ++k) {
+            int64_t sum = 0;
+            for (int64_t e = k * row; e < (k + 1) * row; ++e) {
+                int v = lp[i].bits == 8 ? ((const int8_t *)lp[i].w)[e] : (((const uint8_t *)lp[i].w)[e >> 1] >> (4 * (e & 1))) & 0xF;
+                if (lp[i].bits == 4 && v >= 8) v -= 16;
+                sum += v < 0 ? -v : v;
+            }
+            const int64_t bias = lp[i].bias[k];
+            if (in_hi * sum + (bias < 0 ? -bias : bias) > INT32_MAX) return false;
+            if (lp[i].c[k] > 32 || ((int64_t)lp[i].b[k] >> (lp[i].c[k] - 1)) != 0) return false;
+        }
+        return true;
+    };
+    for (int i = 1; i < nl && !net->keep && g_fuse_tails >= 0 && arch == 50 && L[i].block >= 0 && L[i].K == 64; ) {
+        Block b{i, i + 1, i + 2, L[i + 3].is_ds ? i + 3 : -1, 1, 0, 0};
+        b.rescaled = b.ds < 0 || !(lp[b.ds].flags & HAWQ_LAYER_INT32_SHORTCUT);   // the shortcut is a stored byte's value
+        bool ok = sums_fit(b.c1, act_hi(lp[b.c1].bits)) && sums_fit(b.c2, act_hi(lp[b.c2].bits)) && sums_fit(b.c3, act_hi(lp[b.c3].bits)) &&
+                  (b.ds < 0 || (sums_fit(b.ds, act_hi(lp[b.ds].bits)) && is8(b.c1) && is8(b.c3) && is8(b.ds)));   // (then the input's place is kept to the last step)
+        if (b.rescaled) {
+            for (int k = 0; k < 256; ++k) b.t = lp[b.c3].res_c[k] > b.t ? lp[b.c3].res_c[k] : b.t;
+            for (int k = 0; k < 256 && ok; ++k) ok = b.t <= 30 && ((int64_t)lp[b.c3].res_b[k] << (b.t - lp[b.c3].res_c[k])) < (1 << 22);
+        }
+        if (ok) block64.push_back(b);
+        i += b.ds >= 0 ? 4 : 3;
+    }
+
     // ---- parameter arena layout ----
-    struct Off { size_t w, wt, wf, bias, b, c, rb, rc; };
+    struct Off { size_t w, wt, wf, wn, bias, b, c, rb, rc; };
     // row of the [K][R*S*C] weight matrix in bytes as stored, and whether a blocked copy is made for the implicit-GEMM
     // kernel (64-byte K-steps: 8-bit form with C % 64 == 0, packed 4-bit form with C % 128 == 0)
     auto wrow = [&](int i) { return (int64_t)tensor_bytes((int64_t)L[i].R * L[i].S * L[i].C, is8(i) ? HAWQ_S8 : HAWQ_S4); };
@@ -363,11 +411,17 @@ hawq_status hawq_net_create(int32_t arch, int32_t image_hw, int32_t num_classes,
     }
     const size_t off_pb = take(4 * (size_t)c_last), off_pc = take((size_t)c_last);
     const size_t off_ws = take(64 * 256), off_bs = take(4 * 64);
+    for (Block &b : block64) b.par = take(4 * BLOCK64_PAR);
     const size_t host_bytes = total;   // the reordered copies behind this are made on the device
     for (int i = 0; i < nl; ++i) {
         off[i].wt = blocked(i) ? take((size_t)((L[i].K + 63) / 64) * (size_t)wrow(i) * 64) : 0;
         off[i].wf = fragmented(i) ? take((size_t)((L[i].K + 31) / 32) * 32 * (size_t)L[i].R * L[i].S * L[i].C) : 0;   // (always bytes: 4-bit weights are expanded)
+        off[i].wn = off[i].wf;
     }
+    // fragments of bytes in the elements' own order, which the blocks read -- but a packed input's convolution in that input's
+    for (const Block &b : block64)
+        for (int i : {b.c1, b.c2, b.c3, b.ds})
+            if (i >= 0 && !(fragmented(i) && (is8(i) || i == b.c1))) off[i].wn = take((size_t)L[i].K * L[i].R * L[i].S * L[i].C);
     std::vector<uint8_t> host(host_bytes, 0);
     for (int i = 0; i < nl; ++i) {
         const int64_t nw = (int64_t)L[i].K * L[i].R * L[i].S * L[i].C;
@@ -401,6 +455,18 @@ hawq_status hawq_net_create(int32_t arch, int32_t image_hw, int32_t num_classes,
             bs[k] = (int32_t)(lp[0].bias[k] + 128 * sum);
         }
     }
+    for (const Block &b : block64) {
+        int32_t *par = (int32_t *)&host[b.par];
+        auto put = [&](int i, int at) {
+            for (int k = 0; k < L[i].K; ++k) {
+                par[at + k] = lp[i].bias[k];
+                par[at + L[i].K + k] = (int32_t)((uint32_t)lp[i].b[k] << (32 - lp[i].c[k]));
+            }
+        };
+        put(b.c1, 0); put(b.c2, 128); put(b.c3, 256);
+        if (b.ds >= 0) put(b.ds, 1024);
+        for (int k = 0; k < 256 && b.rescaled; ++k) par[768 + k] = (int32_t)((uint32_t)lp[b.c3].res_b[k] << (b.t - lp[b.c3].res_c[k]));
+    }
     memcpy(&host[off_pb], pool_b, 4 * (size_t)c_last);
     memcpy(&host[off_pc], pool_c, (size_t)c_last);
     if (scratch_base() == nullptr) return fail(HAWQ_ERR_DEVICE);   // (address of the fixed workspace on this device, for hawq_forward_resnet_noalloc)
@@ -418,6 +484,8 @@ hawq_status hawq_net_create(int32_t arch, int32_t image_hw, int32_t num_classes,
         if (blocked(i)) st = launch_block_weights(A + off[i].w, (uint8_t *)net->arena + off[i].wt, L[i].K, wrow(i), net->aux_stream);
         if (st == HAWQ_OK && fragmented(i))
             st = launch_fragment_weights(A + off[i].w, (uint8_t *)net->arena + off[i].wf, L[i].K, wrow(i), !is8(i), net->aux_stream);
+        if (st == HAWQ_OK && off[i].wn != off[i].wf)
+            st = launch_fragment_weights(A + off[i].w, (uint8_t *)net->arena + off[i].wn, L[i].K, wrow(i), !is8(i), net->aux_stream, true);
         if (st != HAWQ_OK) return fail(st);
     }
     if (hipStreamSynchronize(net->aux_stream) != hipSuccess) return fail(HAWQ_ERR_DEVICE);
@@ -531,6 +599,25 @@ hawq_status hawq_net_create(int32_t arch, int32_t image_hw, int32_t num_classes,
         if (lp[mids[0]].bits != in_bits) return fail(HAWQ_ERR_DTYPE);  // cannot happen: in_bits derives from it
         const int out_bits = reader_bits_after(j - 1), out_dt = reader_dt_after(j - 1);
         const int block_in = t, block_in_dt = cont_dt(mids[0]);
+        const size_t first_step = net->steps.size();
+        auto as_one_launch = [&]() {         // at 64 channels: all of the block's steps can run at the last one
+            const size_t s1 = net->steps.size() - 1;
+            for (const Block &b : block64) {
+                if (b.c1 != mids[0]) continue;
+                BlockArgs a{};
+                a.H = L[b.c1].H; a.W = L[b.c1].W;
+                a.w1 = A + off[b.c1].wn; a.w2 = A + off[b.c2].wn; a.w3 = A + off[b.c3].wn;
+                if (b.ds >= 0) a.w4 = A + off[b.ds].wn;
+                a.par = (const int32_t *)(A + b.par);
+                a.hi1 = act_hi(lp[b.c2].bits); a.hi2 = act_hi(lp[b.c3].bits); a.lo3 = 0; a.hi3 = act_hi(out_bits);
+                a.t = b.t; a.mid8 = b.ds >= 0 && b.rescaled;
+                a.x4 = !is8(b.c1); a.y4 = out_dt == HAWQ_U4;
+                for (size_t q = first_step; q < s1; ++q) net->steps[q].block_last = (int)s1;
+                net->steps[s1].block = (int)net->blocks.size();
+                net->steps[s1].block_in = block_in;
+                net->blocks.push_back(a);
+            }
+        };
         int u = block_in, u_dt = block_in_dt, u_bits = in_bits;
         std::vector<int> chain = mids;
         chain.push_back(last);
@@ -577,6 +664,7 @@ hawq_status hawq_net_create(int32_t arch, int32_t image_hw, int32_t num_classes,
                 net->steps.push_back(st);
                 t = st.out;
             }
+            as_one_launch();
             in_bits = out_bits;
             li = j;
             continue;
@@ -613,6 +701,7 @@ hawq_status hawq_net_create(int32_t arch, int32_t image_hw, int32_t num_classes,
             net->steps.back().pair_ds = ds_step;
             net->steps.back().dual16 = fits16(last, ds, u_bits, true);
         }
+        as_one_launch();
         in_bits = out_bits;
         li = j;
     }
@@ -699,6 +788,16 @@ hawq_status hawq_net_step_cost(const hawq_net *net, int32_t N, int32_t step, dou
     const Step &st = net->steps[step];
     *macs = st.macs_per_image * N;
     *bytes = st.bytes_per_image * N + st.bytes_fixed;
+    // a block that runs as one launch: all its work, its input, its output and its weights on the last step
+    if (st.block_last >= 0 && block_runs(net, N, st.block_last)) { *macs = 0; *bytes = 0; return HAWQ_OK; }
+    if (block_runs(net, N, step)) {
+        const BlockArgs &b = net->blocks[st.block];
+        const double px = (double)b.H * b.W;
+        *bytes = px * ((b.w4 ? 64.0 : 256.0) / (b.x4 ? 2 : 1) + 256.0 / (b.y4 ? 2 : 1)) * N + st.bytes_fixed;
+        for (int q = 0; q < step; ++q)
+            if (net->steps[q].block_last == step) { *macs += net->steps[q].macs_per_image * N; *bytes += net->steps[q].bytes_fixed; }
+        return HAWQ_OK;
+    }
     // a transition / last convolution pair that runs as one launch: all the work and the traffic it still needs (both
     // inputs, both parameter sets, the block output) are reported on the last convolution's step
     if (st.pair_last >= 0 && pair_runs_fused(net, N, step)) { *macs = 0; *bytes = 0; }
@@ -748,6 +847,16 @@ static hawq_status run_parts(const hawq_net *net, Part *parts, int n_parts, hipE
         const Step &st = net->steps[s];
         if (ev && hipEventRecord(ev[2 * s], stream) != hipSuccess) return HAWQ_ERR_DEVICE;
         hawq_status rc = HAWQ_OK;
+        if (st.block_last >= 0 ? block_runs(net, N, st.block_last) : block_runs(net, N, (int)s)) {
+            if (st.block >= 0) {
+                BlockArgs b = net->blocks[st.block];
+                b.x = tptr(st.block_in); b.y = tptr(st.out); b.N = N;
+                rc = launch_block64(b, stream);
+                if (rc != HAWQ_OK) return rc;
+            }
+            if (ev && hipEventRecord(ev[2 * s + 1], stream) != hipSuccess) return HAWQ_ERR_DEVICE;
+            continue;
+        }
         if (st.kind == STEP_CONV && (st.pair_last >= 0 || (st.pair_ds >= 0 && deferred[st.pair_ds]))) {
             const Step &l = st.pair_last >= 0 ? net->steps[st.pair_last] : st;
             const Step &d = st.pair_last >= 0 ? st : net->steps[st.pair_ds];

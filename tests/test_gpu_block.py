@@ -1,0 +1,84 @@
+"""GPU parity: ResNet50's 64-channel bottleneck blocks as one launch each, vs the CPU oracle, bit-exact, at the sizes where a tile of
+14 x 8 pixels, the walk over the tiles or a second workgroup on a compute unit can go wrong, and in every storage form."""
+import numpy as np
+import pytest
+
+from oracle import resnet as onet
+import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def hawq():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import paper_2011_10680_amd as h
+    h.load_library()
+    return h
+
+
+def _bits(four):
+    """All 8-bit but the named groups of stage 1 (block, convolution) and whatever follows it."""
+    b = {g: 8 for g in wl.resnet_group_names(50)}
+    if four == "all":
+        return {g: (8 if g in ("conv1", "fc") else 4) for g in b}
+    for g in four:
+        assert g in b, sorted(b)[:12]
+        b[g] = 4
+    return b
+
+
+def _forward(hawq, net, x, mode=0):
+    """(logits, how many of stage 1's steps do work)"""
+    import torch
+    N = x.shape[0]
+    try:
+        hawq.hawq_tune_set_fusion(mode)
+        hn = hawq.HawqNet(50, net["layers"], net["pool_b"], net["pool_c"], image_hw=net["image_hw"])
+    finally:
+        hawq.hawq_tune_set_fusion(0)
+    ws = torch.full((hn.workspace_bytes(N),), 0x7B, dtype=torch.uint8, device="cuda")
+    logits = torch.zeros((N, 1000), dtype=torch.int32, device="cuda")
+    xd = torch.from_numpy(x).cuda()
+    for _ in range(2):
+        hn.hawq_forward_resnet(xd, N, logits, ws)
+    torch.cuda.synchronize()
+    working = sum(hn.step_cost(N, s)[0] > 0 for s in range(hn.num_steps()) if hn.step_output(N, s)["name"].startswith("layer1"))
+    out = logits.cpu().numpy()
+    hn.close()
+    return out, working
+
+
+# map side = image side / 4: 8 (one tile, 8 of 14 columns), 16 (2 columns in the second tile), 25 (11 columns, one row), 56 (exact);
+# tiles: up to 256 (one workgroup a unit), 280 (some units two), 672 (a walk of more than one tile); 33 x 33 at 80 images: 1200
+@pytest.mark.parametrize("hw,N,four,int32_sc", [
+    (32, 1, (), True), (64, 3, (), False), (100, 2, "all", True), (100, 3, "all", False), (224, 10, (), True), (224, 24, (), False),
+    (132, 80, "all", False), (224, 1, ("layer1.1.in",), True), (64, 5, ("layer1.0.c2", "layer1.2.in", "layer1.2.c3"), False),
+    (100, 4, ("layer2.0.in", "layer1.1.c3"), False), (64, 260, (), True)])
+def test_blocks_as_one_launch(hawq, hw, N, four, int32_sc):
+    net = wl.make_resnet(50, seed=900 + hw + N, bits=_bits(four), image_hw=hw, int32_shortcut=int32_sc)
+    x = wl.make_image_batch(901 + N, N, image_hw=hw)
+    got, working = _forward(hawq, net, x)
+    assert np.array_equal(got, onet.forward(net, x))
+    assert working == 3, working
+
+
+@pytest.mark.parametrize("int32_sc", [True, False])
+@pytest.mark.parametrize("what", ["wide", "bias"])
+def test_blocks_beyond_the_narrow_evaluation(hawq, what, int32_sc):
+    """A multiplier beyond the narrow evaluation's range, or a bias with which an accumulator may pass 32 bits: that block keeps its
+    own launches, the others do not; same logits as the plan without fusion."""
+    net = wl.make_resnet(50, seed=77, image_hw=64, int32_shortcut=int32_sc)
+    l = next(l for l in net["layers"] if l["name"] == "layer1.1.c2")
+    if what == "wide":
+        l["b"] = np.where(np.arange(64) == 5, l["b"].astype(np.int64) << 15, l["b"]).astype(np.int32)
+        l["c"] = np.where(np.arange(64) == 5, l["c"].astype(np.int32) + 15, l["c"]).astype(np.uint8)
+    else:
+        l["bias"] = np.where(np.arange(64) == 5, 2 ** 31 - 1000, l["bias"]).astype(np.int32)
+    x = wl.make_image_batch(78, 2, image_hw=64)
+    got, working = _forward(hawq, net, x)
+    plain, separate = _forward(hawq, net, x, -1)
+    assert np.array_equal(got, plain) and working == 5 and separate >= 9, (working, separate)
+    if what == "wide":
+        assert np.array_equal(got, onet.forward(net, x))
