@@ -138,35 +138,104 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) c
 // For that a pooling window's nine accumulators must meet in one lane.  The MFMA leaves a lane with one column and
 // sixteen rows of the 32x32 result, so here the *pixels* are the row operand and the channels the column operand (the
 // other way round from every other kernel of the library): lane (n, h) ends up with channel n and the sixteen pixels in
-// rows {8j + 4h + q}.  Which conv1 pixel feeds which row is the kernel's choice: the sixteen rows of a lane half hold a
-// block of 3 x 5 conv1 outputs (one slot spare) -- the windows of two horizontally adjacent pooled pixels, which share
-// their middle column.  One MFMA tile thus yields four pooled pixels per channel; 15 conv1 outputs per two pooled pixels
-// instead of the 9 of perfect sharing is 1.7 times the multiply-accumulates of the plain tiling, on matrix pipes that
-// were one fifth busy, in exchange for a quarter of the vector arithmetic and no pooling pass over LDS.
+// rows {8j + 4h + q}.  Which conv1 pixel feeds which row is the kernel's choice: the 48 rows that a lane half has in three
+// MFMA tiles hold a block of 5 x 9 conv1 outputs (three slots spare) -- the windows of 2 x 4 pooled pixels.  6 slots a
+// pooled pixel, where 9 conv1 outputs without sharing and 4 at best would be needed, and one MFMA tile alone, 3 x 5 outputs
+// for two pooled pixels, took 8.
 //
-// A workgroup (four waves) makes 8 x 8 tiles of pooled pixels from a 39 x 40 input patch staged once in LDS (pixels
-// widened to RGB0 dwords; a filter row = 8 pixels x 4 B = one K = 32 MFMA step): sixteen MFMA tiles, four per wave.  The
-// 64 x 7 x 32 weight bytes a lane needs as column operand (two channels) stay in registers for the life of the
-// (persistent) workgroup.  Results go through a 4 KB LDS tile to become 16-byte NHWC stores.
+// What bounds it: the matrix pipes have 42 instructions for 16 pooled pixels of 64 channels, 14 us at batch 128 (224 x 224); the
+// image and the pooled tensor are 45 MB, 9 us.  56 -> 41 us at batch 128, 102 -> 70 at 256, 30 -> 24 at 64, 7.9 and 8.0 at
+// batch 1 against a tile of 3 x 5 conv1 outputs at a time (14 instructions for four pooled pixels; three waves on a SIMD where
+// this has two).  Of that 45 us came with the larger block, 3 with fragment reads free of bank conflicts, branch-free loads and
+// places in the image that are stepped and not divided.  Matrix pipes 40 %, vector ALU 30 %, LDS half of the cycles: what is
+// left is each wave's own chain of multiplying, taking maxima and staging, with two of them on a SIMD to overlap.
+//
+// A workgroup (four waves) makes 8 x 8 tiles of pooled pixels from a 39 x 41 input patch staged in LDS (pixels widened to
+// RGB0 dwords; a filter row = 8 pixels x 4 B = one K = 32 MFMA step), two pooled rows to a wave: the addresses of a lane's
+// row operands are the same for every tile.  The 64 x 7 x 32 weight bytes a lane needs as column operand (two channels)
+// stay in registers for the life of the (persistent) workgroup.  Results go through an LDS tile to become 16-byte NHWC
+// stores.  Patch and result tile have two places each: one barrier a tile, behind which a wave stores its share of this
+// tile and goes on to the next.
 constexpr int FUSE_PT = 8;                         // pooled tile edge
 constexpr int FUSE_CT = 2 * FUSE_PT + 1;           // 17 conv rows / columns under it
 constexpr int FUSE_ROWS = 2 * FUSE_CT + 5;         // 39 input rows
-// patch width in pixels (41 used; origin = image column 4*pq0 - 5).  42: the 32 lanes of one pass of a fragment read touch
-// three conv1 rows (two patch rows apart) x 18 consecutive dwords each; 2 x 42 = 20 (mod 64 banks) lays the three spans side
-// by side, where 44 wrapped the third onto the first (every pass a two-way conflict: half of all LDS cycles)
-constexpr int FUSE_COLS = 42;
+// The patch is 41 pixels wide (origin = image column 4*pq0 - 5), its rows in pairs of 98 dwords, the second of a pair 48 behind the
+// first: the 32 lanes of one pass of a fragment read touch parts of up to three conv1 rows (a pair each), 34 consecutive dwords a
+// whole row, and 98 = 34 (mod 64 banks) lays them side by side without an overlap in all three tiles (rows of 48: an overlap of
+// two dwords in each pass, every one two cycles)
+constexpr int FUSE_PAIR = 98, FUSE_ODD = 48;
+constexpr int FUSE_PATCH = (FUSE_ROWS + 1) / 2 * FUSE_PAIR + 4;   // (four dwords before the first row, which staging may write)
+constexpr int FUSE_PITCH = 80;                     // bytes of a pooled pixel in LDS (64: both lane halves in the same banks)
 constexpr int FUSE_GROUPS = 11;                    // 4-pixel groups fetched per patch row (patch columns -3 .. 40)
 
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
 conv_stem_pool_kernel(const ConvArgs a, const int pool_P, const int pool_Q, const int pool_y_dt, const int pool_lo,
                       const int pool_hi, uint8_t *__restrict__ pool_y, const int tiles_q, const int tiles_p, const int n_tiles) {
-    __shared__ __attribute__((aligned(16))) uint32_t lx[FUSE_ROWS * FUSE_COLS];
-    __shared__ __attribute__((aligned(16))) uint8_t lp[FUSE_PT * FUSE_PT * 64];   // pooled tile [row][column][channel]
+    __shared__ __attribute__((aligned(16))) uint32_t lx[2][FUSE_PATCH];
+    __shared__ __attribute__((aligned(16))) uint8_t lp[2][FUSE_PT * FUSE_PT * FUSE_PITCH];   // pooled tile [row][column][channel]
     __shared__ ChanMain par_m[64];
     __shared__ ChanRes par_r[64];
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 31, half = lane >> 5;
+    // input patch of a tile: row rl <-> image row 4*pp0 - 5 + rl, column c <-> image column 4*pq0 - 5 + c; groups of 4
+    // pixels (12 bytes) start at image column 4*pq0 - 8 + 4g, i.e. patch column 4g - 3.  A thread owns work items tid
+    // and tid + 256 of the FUSE_ROWS * FUSE_GROUPS groups.
+    constexpr int NITEM = (FUSE_ROWS * FUSE_GROUPS + 255) / 256;
+    // (items beyond the last and the first three columns of a row's first group go to places that nobody reads)
+    const int row_bytes = a.W * 3;
+    int it_row[NITEM], it_col[NITEM], it_off[NITEM];
+    uint32_t *it_dst[NITEM];
+#pragma unroll
+    for (int it = 0; it < NITEM; ++it) {
+        const int i = tid + it * 256, rl = i / FUSE_GROUPS, g = i - rl * FUSE_GROUPS;
+        it_row[it] = rl < FUSE_ROWS ? rl - 5 : -(1 << 30);        // (a row that no image has)
+        it_col[it] = 4 * g - 8;
+        it_off[it] = rl * row_bytes + 12 * g;
+        const int to = min(rl, FUSE_ROWS);
+        it_dst[it] = &lx[0][4] + (to >> 1) * FUSE_PAIR + (to & 1) * FUSE_ODD + 4 * g - 3;
+    }
+    typedef uint32_t v3u __attribute__((ext_vector_type(3)));
+    v3u raw[NITEM];
+    const TileWalk walk = xcd_walk(blockIdx.x, gridDim.x, n_tiles);
+    // a tile's place: column, row of its image, image; and what a step of the walk adds
+    struct Place { int q, p, n; };
+    auto place = [&](int tile) { Place c; c.q = tile % tiles_q; tile /= tiles_q; c.p = tile % tiles_p; c.n = tile / tiles_p; return c; };
+    const Place step = place(walk.step);
+    auto advance = [&](Place c) {
+        c.q += step.q; c.p += step.p; c.n += step.n;
+        if (c.q >= tiles_q) { c.q -= tiles_q; ++c.p; }
+        if (c.p >= tiles_p) { c.p -= tiles_p; ++c.n; }
+        return c;
+    };
+    auto fetch = [&](const Place &c) {
+        // (offsets from the patch's first group, which may lie outside the image: every lane that does reads zeros)
+        const int y0 = 4 * c.p * FUSE_PT, x0 = 4 * c.q * FUSE_PT;
+        const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc((void *)(a.x + (((int64_t)c.n * a.H + y0 - 5) * a.W + x0 - 8) * 3), 0, 0x7fffffff, 0x00020000);
+#pragma unroll
+        for (int it = 0; it < NITEM; ++it) {
+            const bool in = ((unsigned)(y0 + it_row[it]) < (unsigned)a.H) & ((unsigned)(x0 + it_col[it]) < (unsigned)a.W);   // (a.W is a multiple of 4, so is a group's column)
+            raw[it] = __builtin_amdgcn_raw_buffer_load_b96(rx, in ? it_off[it] : (int)0x80000000u, 0, 0);
+        }
+    };
+    // widen the fetched RGB triples to RGB0 dwords, offset by -128 (XOR 0x80 per byte), into the LDS patch;
+    // out-of-image positions are raw zeros and get the same offset (the bias correction assumes it everywhere)
+    auto stage = [&](int to) {
+#pragma unroll
+        for (int it = 0; it < NITEM; ++it) {
+            const uint32_t d0 = raw[it][0], d1 = raw[it][1], d2 = raw[it][2];
+            uint32_t *dst = it_dst[it] + to * FUSE_PATCH;
+            dst[0] = (d0 & 0x00ffffffu) ^ 0x00808080u;
+            dst[1] = (__builtin_amdgcn_alignbyte(d1, d0, 3) & 0x00ffffffu) ^ 0x00808080u;
+            dst[2] = (__builtin_amdgcn_alignbyte(d2, d1, 2) & 0x00ffffffu) ^ 0x00808080u;
+            dst[3] = (d2 >> 8) ^ 0x00808080u;
+        }
+    };
+    // (the first tile's bytes are under way while the parameters come)
+    if (walk.first >= walk.end) return;    // (the whole workgroup)
+    int tile = walk.first;
+    Place cur = place(tile), nxt = advance(cur);
+    fetch(cur);
     int wide = stage_params(a, 0, 64, par_m, par_r);
     wide = __syncthreads_or(wide);
     // column operand: channel col + 32 tc, K-step r (filter row), this lane half's 16 bytes (filter columns 4 half .. + 3)
@@ -175,168 +244,126 @@ conv_stem_pool_kernel(const ConvArgs a, const int pool_P, const int pool_Q, cons
     for (int r = 0; r < 7; ++r)
 #pragma unroll
         for (int tc = 0; tc < 2; ++tc) wf[r][tc] = *(const v4i *)(a.w + (((col + 32 * tc) * 8 + r) * 8 + 4 * half) * 4);
-    // the two channels' requantisation: narrow form  high word of t * bs + Rs  (bias inside Rs), else the exact 64-bit form
-    int32_t q_bs[2], q_b[2], q_c[2], q_bias[2];
-    int64_t q_Rs[2];
+    // row operand: MFMA row rho of tile mt is slot 16 mt + 4 (rho >> 3) + (rho & 3) of the block of lane half (rho >> 2) & 1;
+    // slot s < 45 is conv1 pixel (s / 9, s % 9) of the 5 x 9 block (the rest repeat slot 44 and are never looked at)
+    int bb[3];
 #pragma unroll
-    for (int tc = 0; tc < 2; ++tc) {
-        const ChanMain m = par_m[col + 32 * tc];
-        q_bs[tc] = m.bs; q_Rs[tc] = m.Rs; q_b[tc] = m.b; q_c[tc] = m.c; q_bias[tc] = m.bias;
+    for (int mt = 0; mt < 3; ++mt) {
+        const int s = min(16 * mt + 4 * (col >> 3) + (col & 3), 44), br = s / 9, bc = s - 9 * br;
+        bb[mt] = 4 + (4 * wave + br) * FUSE_PAIR + 2 * (8 * ((col >> 2) & 1) + bc) + 4 * half;
     }
+    // the convolution's clamp and the pool's as one
+    int32_t lo_c = min(max(a.lo, pool_lo), pool_hi), hi_c = min(max(a.hi, pool_lo), pool_hi);
+    asm volatile("" : "+v"(lo_c), "+v"(hi_c));
 
-    // input patch of a tile: row rl <-> image row 4*pp0 - 5 + rl, column c <-> image column 4*pq0 - 5 + c; groups of 4
-    // pixels (12 bytes) start at image column 4*pq0 - 8 + 4g, i.e. patch column 4g - 3.  A thread owns work items tid
-    // and tid + 256 of the FUSE_ROWS * FUSE_GROUPS groups.
-    constexpr int NITEM = (FUSE_ROWS * FUSE_GROUPS + 255) / 256;
-    uint32_t raw[NITEM][3];
-    const TileWalk walk = xcd_walk(blockIdx.x, gridDim.x, n_tiles);
-    auto fetch = [&](int tile) {
-        int t = tile;
-        const int tq = t % tiles_q; t /= tiles_q;
-        const int tp_ = t % tiles_p;
-        const int n = t / tiles_p;
-        const uint8_t *img = a.x + (int64_t)n * a.H * a.W * 3;
-#pragma unroll
-        for (int it = 0; it < NITEM; ++it) {
-            const int i = tid + it * 256;
-            const int rl = i / FUSE_GROUPS, g = i - rl * FUSE_GROUPS;
-            const int ih = 4 * tp_ * FUSE_PT - 5 + rl;
-            const int iw = 4 * tq * FUSE_PT - 8 + 4 * g;
-            raw[it][0] = raw[it][1] = raw[it][2] = 0;
-            if (tile < walk.end && i < FUSE_ROWS * FUSE_GROUPS && (unsigned)ih < (unsigned)a.H && iw >= 0 && iw + 3 < a.W) {
-                const uint32_t *src = (const uint32_t *)(img + ((int64_t)ih * a.W + iw) * 3);
-                raw[it][0] = src[0]; raw[it][1] = src[1]; raw[it][2] = src[2];
-            }
-        }
-    };
-    // widen the fetched RGB triples to RGB0 dwords, offset by -128 (XOR 0x80 per byte), into the LDS patch;
-    // out-of-image positions are raw zeros and get the same offset (the bias correction assumes it everywhere)
-    auto stage = [&]() {
-#pragma unroll
-        for (int it = 0; it < NITEM; ++it) {
-            const int i = tid + it * 256;
-            const int rl = i / FUSE_GROUPS, g = i - rl * FUSE_GROUPS;
-            const uint32_t d0 = raw[it][0], d1 = raw[it][1], d2 = raw[it][2];
-            const uint32_t p0 = d0 & 0x00ffffffu;
-            const uint32_t p1 = ((d0 >> 24) | (d1 << 8)) & 0x00ffffffu;
-            const uint32_t p2 = ((d1 >> 16) | (d2 << 16)) & 0x00ffffffu;
-            const uint32_t p3 = d2 >> 8;
-            const int c0 = 4 * g - 3;          // -3, 1, 5, ... 37: patch columns c0 .. c0 + 3
-            if (i < FUSE_ROWS * FUSE_GROUPS) {
-                uint32_t *dst = lx + rl * FUSE_COLS + c0;
-                if (c0 >= 0) { dst[0] = p0 ^ 0x00808080u; dst[1] = p1 ^ 0x00808080u; dst[2] = p2 ^ 0x00808080u; }
-                dst[3] = p3 ^ 0x00808080u;
-            }
-        }
-    };
-    // row operand: MFMA row rho of a tile is slot 4 (rho >> 3) + (rho & 3) of the block of lane half (rho >> 2) & 1;
-    // slot s < 15 is conv1 pixel (s / 5, s % 5) of the 3 x 5 block (slot 15 repeats slot 14 and is never looked at)
-    const int a_h = (col >> 2) & 1;
-    const int a_s = min(4 * (col >> 3) + (col & 3), 14);
-    const int a_br = a_s / 5, a_bc = a_s - 5 * a_br;
-    int32_t lo_c = a.lo, hi_c = a.hi, lo_p = pool_lo, hi_p = pool_hi;
-    asm volatile("" : "+v"(lo_c), "+v"(hi_c), "+v"(lo_p), "+v"(hi_p));
+    const uint32_t st_off = (uint32_t)(((tid >> 5) * pool_Q + (tid >> 2 & 7)) * 64 + (tid & 3) * 16);   // a thread's pixel and channels in the pooled tensor
 
-    int tile = walk.first;
-    fetch(tile);
-    for (; tile < walk.end; tile += walk.step) {
-        int t = tile;
-        const int tq = t % tiles_q; t /= tiles_q;
-        const int tp_ = t % tiles_p;
-        const int n = t / tiles_p;
-        const int pp0 = tp_ * FUSE_PT, pq0 = tq * FUSE_PT;       // pooled tile origin
-        stage();
-        fetch(tile + walk.step);
-        __syncthreads();              // patch complete; the previous tile's output reads are done
-
-        // ---- wave w: MFMA tiles 4w .. 4w + 3, one after the other; tile wt = pooled row wt / 2 of the pooled tile, column
-        // pairs 2 (wt % 2) and 2 (wt % 2) + 1 (lane halves 0 and 1) ----
-#pragma nounroll
-        for (int it = 0; it < 4; ++it) {
-            const int wt = 4 * wave + it;
-            const int pr = wt >> 1;
+    auto run = [&](auto wide_c) {
+        int buf = 0;
+        stage(0);
+        if (tile + walk.step < walk.end) fetch(nxt);
+        __syncthreads();
+        for (;;) {
+            const int pp0 = cur.p * FUSE_PT, pq0 = cur.q * FUSE_PT;       // pooled tile origin
+            v16i acc[3][2];
             {
-                // the row this lane feeds: conv1 pixel (2 pr + br, 4 pcp + bc) of the 17 x 17 under the pooled tile
-                const int pcp = 2 * (wt & 1) + a_h;
-                const int bb = (2 * (2 * pr + a_br)) * FUSE_COLS + 2 * (4 * pcp + a_bc) + 4 * half;
-                v16i acc[2];
+                const uint32_t *patch = lx[buf];
+                auto frag = [&](int r, int mt) {
+                    const uint32_t *p = patch + bb[mt] + (r >> 1) * FUSE_PAIR + (r & 1) * FUSE_ODD;
+                    const uint2 l0 = *(const uint2 *)p;
+                    const uint2 h0 = *(const uint2 *)(p + 2);
+                    return (v4i){(int)l0.x, (int)l0.y, (int)h0.x, (int)h0.y};
+                };
+                v4i pf[2][3];
 #pragma unroll
-                for (int tc = 0; tc < 2; ++tc)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) acc[tc][i] = 0;
+                for (int mt = 0; mt < 3; ++mt) pf[0][mt] = frag(0, mt);
 #pragma unroll
                 for (int r = 0; r < 7; ++r) {   // the 8th K-step multiplies zero weights: skipped
-                    const uint2 l0 = *(const uint2 *)(lx + bb + r * FUSE_COLS);
-                    const uint2 h0 = *(const uint2 *)(lx + bb + r * FUSE_COLS + 2);
-                    const v4i pf = (v4i){(int)l0.x, (int)l0.y, (int)h0.x, (int)h0.y};
+                    if (r < 6)
 #pragma unroll
-                    for (int tc = 0; tc < 2; ++tc) acc[tc] = __builtin_amdgcn_mfma_i32_32x32x32_i8(pf, wf[r][tc], acc[tc], 0, 0, 0);
+                        for (int mt = 0; mt < 3; ++mt) pf[(r + 1) & 1][mt] = frag(r + 1, mt);
+#pragma unroll
+                    for (int mt = 0; mt < 3; ++mt)
+#pragma unroll
+                        for (int tc = 0; tc < 2; ++tc)
+                            acc[mt][tc] = __builtin_amdgcn_mfma_i32_32x32x32_i8(pf[r & 1][mt], wf[r][tc], r == 0 ? (v16i){} : acc[mt][tc], 0, 0, 0);
                 }
-                // ---- this lane: channels col, col + 32 of the block (pr, pcp = 2 (wt % 2) + half): two pooled pixels ----
-                const int pcq = 2 * (2 * (wt & 1) + half);            // first pooled column of the block within the tile
-                const int cr0 = 2 * (pp0 + pr) - 1, cq0 = 2 * (pq0 + pcq) - 1;   // conv1 coordinates of block pixel (0, 0)
-                bool rv[3], cv[5];
-                bool all = true;
+            }
+            const int next = tile + walk.step;
+            const bool more = next < walk.end;
+            const Place after = advance(nxt);
+            if (more) {
+                stage(buf ^ 1);
+                if (next + walk.step < walk.end) fetch(after);
+            }
+            // ---- this lane: channels col, col + 32; pooled pixels (2 wave + 0..1, 4 half + 0..3) of the tile ----
+            auto at = [&](int tc, int r, int c) -> int32_t { return acc[(9 * r + c) / 16][tc][(9 * r + c) % 16]; };
+            // taps outside the image do not take part: rows are the same for the wave, columns for a lane half
+            const int cr0 = 2 * (pp0 + 2 * wave) - 1;                // conv1 row of the block's first
+            if (cr0 < 0 || cr0 + 4 >= a.P)
 #pragma unroll
-                for (int i = 0; i < 3; ++i) { rv[i] = (unsigned)(cr0 + i) < (unsigned)a.P; all = all && rv[i]; }
+            for (int r = 0; r < 5; ++r)
+                if ((unsigned)(cr0 + r) >= (unsigned)a.P)
 #pragma unroll
-                for (int i = 0; i < 5; ++i) { cv[i] = (unsigned)(cq0 + i) < (unsigned)a.Q; all = all && cv[i]; }
-                if (!__all(all)) {   // a window reaches over the image's edge: those taps do not take part
+                    for (int s = 9 * r; s < 9 * r + 9; ++s) acc[s / 16][0][s % 16] = acc[s / 16][1][s % 16] = INT32_MIN;
+            if (cur.q == 0 || 2 * (pq0 + FUSE_PT) > a.Q) {
+                const int cq0 = 2 * (pq0 + 4 * half) - 1;
 #pragma unroll
-                    for (int tc = 0; tc < 2; ++tc)
+                for (int c = 0; c < 9; ++c) {
+                    const bool in = (unsigned)(cq0 + c) < (unsigned)a.Q;
 #pragma unroll
-                        for (int i = 0; i < 15; ++i)
-                            if (!(rv[i / 5] && cv[i % 5])) acc[tc][i] = INT32_MIN;
+                    for (int s = c; s < 45; s += 9)
+#pragma unroll
+                        for (int tc = 0; tc < 2; ++tc) acc[s / 16][tc][s % 16] = in ? acc[s / 16][tc][s % 16] : INT32_MIN;
                 }
-                uint32_t yb[2][2];
+            }
+            uint8_t *out = lp[buf] + (2 * wave * FUSE_PT + 4 * half) * FUSE_PITCH + col;
 #pragma unroll
-                for (int tc = 0; tc < 2; ++tc) {
-                    // columns 0..2 -> first pooled pixel, 2..4 -> second; the shared middle column once
-                    const int32_t mid = max(acc[tc][2], max(acc[tc][7], acc[tc][12]));
-                    int32_t m0 = max(max(acc[tc][0], acc[tc][1]), max(acc[tc][5], acc[tc][6]));
-                    m0 = max(max(m0, mid), max(acc[tc][10], acc[tc][11]));
-                    int32_t m1 = max(max(acc[tc][3], acc[tc][4]), max(acc[tc][8], acc[tc][9]));
-                    m1 = max(max(m1, mid), max(acc[tc][13], acc[tc][14]));
-                    const int32_t mm[2] = {m0, m1};
+            for (int tc = 0; tc < 2; ++tc) {
+                // the channel's requantisation: narrow form  high word of t * bs + Rs  (bias inside Rs), else the exact 64-bit form
+                const ChanMain &q = par_m[col + 32 * tc];
+                int32_t m[5][4];           // maxima over a row's three columns
 #pragma unroll
-                    for (int j = 0; j < 2; ++j) {
+                for (int r = 0; r < 5; ++r)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) m[r][c] = max(max(at(tc, r, 2 * c), at(tc, r, 2 * c + 1)), at(tc, r, 2 * c + 2));
+#pragma unroll
+                for (int r = 0; r < 2; ++r)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        const int32_t mm = max(max(m[2 * r][c], m[2 * r + 1][c]), m[2 * r + 2][c]);
                         int32_t y;
                         // (wrapping sum: a pooled pixel outside the tensor carries INT32_MIN and is never stored)
-                        if (wide) y = clamp64(rq64((int32_t)((uint32_t)mm[j] + (uint32_t)q_bias[tc]), q_b[tc], q_c[tc]), lo_c, hi_c);
+                        if (decltype(wide_c)::value) y = clamp64(rq64((int32_t)((uint32_t)mm + (uint32_t)q.bias), q.b, q.c), lo_c, hi_c);
                         else {
-                            const int32_t v = (int32_t)(((int64_t)mm[j] * (int64_t)q_bs[tc] + q_Rs[tc]) >> 32);
+                            const int32_t v = (int32_t)(((int64_t)mm * (int64_t)q.bs + q.Rs) >> 32);
                             asm("v_med3_i32 %0, %1, %2, %3" : "=v"(y) : "v"(v), "v"(lo_c), "v"(hi_c));
                         }
-                        int32_t z;
-                        asm("v_med3_i32 %0, %1, %2, %3" : "=v"(z) : "v"(y), "v"(lo_p), "v"(hi_p));
-                        yb[tc][j] = (uint32_t)z;
+                        out[(r * FUSE_PT + c) * FUSE_PITCH + 32 * tc] = (uint8_t)y;
                     }
-                }
-#pragma unroll
-                for (int tc = 0; tc < 2; ++tc)
-#pragma unroll
-                    for (int j = 0; j < 2; ++j) lp[(pr * FUSE_PT + pcq + j) * 64 + col + 32 * tc] = (uint8_t)yb[tc][j];
             }
-        }
-        __syncthreads();              // pooled tile complete; patch reads are done
+            __syncthreads();              // pooled tile and the next patch complete
 
-        // ---- 16 channels of one pooled pixel per thread: 16-byte NHWC stores ----
-        {
-            const int pg = tid & 3, pi = tid >> 2;
-            const int pp = pp0 + (pi >> 3), pq = pq0 + (pi & 7);
-            if (pp < pool_P && pq < pool_Q) {
-                const uint4 v = *(const uint4 *)(lp + pi * 64 + pg * 16);
-                const int64_t oe = (((int64_t)n * pool_P + pp) * pool_Q + pq) * 64 + pg * 16;
+            // ---- 16 channels of one pooled pixel per thread: 16-byte NHWC stores ----
+            if (pp0 + (tid >> 5) < pool_P && pq0 + (tid >> 2 & 7) < pool_Q) {
+                const uint4 v = *(const uint4 *)(lp[buf] + (tid >> 2) * FUSE_PITCH + (tid & 3) * 16);
+                const int64_t oe = (((int64_t)cur.n * pool_P + pp0) * pool_Q + pq0) * 64;
                 if (is4(pool_y_dt)) {
                     // low nibbles of the four bytes of a dword -> 16 bits (values <= 15 by the clamp)
                     auto nib = [](uint32_t d) { return (d & 0xfu) | ((d >> 4) & 0xf0u) | ((d >> 8) & 0xf00u) | ((d >> 12) & 0xf000u); };
-                    *(uint2 *)(pool_y + (oe >> 1)) = make_uint2(nib(v.x) | (nib(v.y) << 16), nib(v.z) | (nib(v.w) << 16));
+                    *(uint2 *)(pool_y + (oe >> 1) + (st_off >> 1)) = make_uint2(nib(v.x) | (nib(v.y) << 16), nib(v.z) | (nib(v.w) << 16));
                 } else {
-                    *(uint4 *)(pool_y + oe) = v;
+                    *(uint4 *)(pool_y + oe + st_off) = v;
                 }
             }
+            if (!more) break;
+            tile = next;
+            cur = nxt; nxt = after;
+            buf ^= 1;
         }
-    }
+    };
+    if (wide) run(std::true_type{});
+    else run(std::false_type{});
 }
 
 hawq_status launch_conv_stem_pool(const ConvArgs &a, int pool_y_dt, int pool_lo, int pool_hi, void *pool_y, hipStream_t s) {
@@ -345,7 +372,7 @@ hawq_status launch_conv_stem_pool(const ConvArgs &a, int pool_y_dt, int pool_lo,
     const int tiles_p = (pool_P + FUSE_PT - 1) / FUSE_PT, tiles_q = (pool_Q + FUSE_PT - 1) / FUSE_PT;
     const int64_t n_tiles = (int64_t)a.N * tiles_p * tiles_q;
     if (n_tiles > 0x7fffffff) return HAWQ_ERR_UNSUPPORTED;
-    const uint32_t grid = xcd_walk_grid(n_tiles, 3 * 256);         // persistent: three workgroups per CU
+    const uint32_t grid = xcd_walk_grid(n_tiles, 2 * 256);         // persistent: two workgroups per CU
     // the pooled bytes are unsigned: bounds outside 0..255 never bind
     pool_lo = pool_lo < 0 ? 0 : pool_lo;
     pool_hi = pool_hi > 255 ? 255 : pool_hi;
