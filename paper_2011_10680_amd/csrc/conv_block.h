@@ -15,9 +15,21 @@ struct BlockArgs {
     int32_t hi1, hi2, lo3, hi3;  // clamps (the first two from 0)
     int32_t t, mid8;             // shift of the shortcut's multipliers; w4: its result passes through a signed byte first
     int32_t x4, y4;
+    int32_t flt;                 // without w4, bytes: the shortcut's multipliers are floats (res_float), t is not looked at
     int32_t tiles_x, tiles_y, n_tiles;  // set by the launcher
 };
 constexpr int BLOCK64_PAR = 1536;       // words of par
+
+// The shortcut of an unsigned byte in floating point, exactly:  (r*rb + 2^(rc-1)) >> rc  is the integer nearest to
+// x = r*rb / 2^rc, a half rounded up.  With the multiplier raised to (256 rb + 1) / 2^(rc+8) the product is x + r / 2^(rc+8):
+// nothing that is a multiple of 2^-rc lies between the two (r < 256), a half is no tie any more, and one fused multiply-add with
+// 1.5 * 2^23 rounds to the nearest integer -- the result's bits are kResMagic + the term.  24 bits hold 256 rb + 1 for rb < 2^16,
+// and rc >= 2 keeps the term below 2^22.
+constexpr int32_t kResMagic = 0x4B400000;
+inline bool res_float_ok(int32_t rb, int32_t rc) { return rb < 65536 && rc >= 2; }
+inline int32_t res_float(int32_t rb, int32_t rc) {
+    return __builtin_bit_cast(int32_t, __builtin_ldexpf((float)(256 * rb + 1), -(rc + 8)));
+}
 
 hawq_status launch_block64(const BlockArgs &a, hipStream_t s);
 

@@ -356,7 +356,7 @@ hawq_status hawq_net_create(int32_t arch, int32_t image_hw, int32_t num_classes,
 
     // ---- bottleneck blocks at 64 channels that can run as one launch: the layers' indices, and a common shift for the shortcut's
     // multipliers.  Every multiplier in the narrow evaluation's range, and no accumulator with its bias beyond 32 bits ----
-    struct Block { int c1, c2, c3, ds, t, rescaled; size_t par; };
+    struct Block { int c1, c2, c3, ds, t, rescaled; bool flt; size_t par; };
     std::vector<Block> block64;
     auto sums_fit = [&](int i, int in_hi) {
         const int64_t row = (int64_t)L[i].R * L[i].S * L[i].C;
@@ -374,7 +374,7 @@ hawq_status hawq_net_create(int32_t arch, int32_t image_hw, int32_t num_classes,
         return true;
     };
     for (int i = 1; i < nl && !net->keep && g_fuse_tails >= 0 && arch == 50 && L[i].block >= 0 && L[i].K == 64; ) {
-        Block b{i, i + 1, i + 2, L[i + 3].is_ds ? i + 3 : -1, 1, 0, 0};
+        Block b{i, i + 1, i + 2, L[i + 3].is_ds ? i + 3 : -1, 1, 0, false, 0};
         b.rescaled = b.ds < 0 || !(lp[b.ds].flags & HAWQ_LAYER_INT32_SHORTCUT);   // the shortcut is a stored byte's value
         bool ok = sums_fit(b.c1, act_hi(lp[b.c1].bits)) && sums_fit(b.c2, act_hi(lp[b.c2].bits)) && sums_fit(b.c3, act_hi(lp[b.c3].bits)) &&
                   (b.ds < 0 || (sums_fit(b.ds, act_hi(lp[b.ds].bits)) && is8(b.c1) && is8(b.c3) && is8(b.ds)));   // (then the input's place is kept to the last step)
@@ -382,6 +382,8 @@ hawq_status hawq_net_create(int32_t arch, int32_t image_hw, int32_t num_classes,
             for (int k = 0; k < 256; ++k) b.t = lp[b.c3].res_c[k] > b.t ? lp[b.c3].res_c[k] : b.t;
             for (int k = 0; k < 256 && ok; ++k) ok = b.t <= 30 && ((int64_t)lp[b.c3].res_b[k] << (b.t - lp[b.c3].res_c[k])) < (1 << 22);
         }
+        b.flt = b.ds < 0 && is8(b.c1);
+        for (int k = 0; k < 256 && b.flt; ++k) b.flt = res_float_ok(lp[b.c3].res_b[k], lp[b.c3].res_c[k]);
         if (ok) block64.push_back(b);
         i += b.ds >= 0 ? 4 : 3;
     }
@@ -465,7 +467,7 @@ hawq_status hawq_net_create(int32_t arch, int32_t image_hw, int32_t num_classes,
         };
         put(b.c1, 0); put(b.c2, 128); put(b.c3, 256);
         if (b.ds >= 0) put(b.ds, 1024);
-        for (int k = 0; k < 256 && b.rescaled; ++k) par[768 + k] = (int32_t)((uint32_t)lp[b.c3].res_b[k] << (b.t - lp[b.c3].res_c[k]));
+        for (int k = 0; k < 256 && b.rescaled; ++k) par[768 + k] = b.flt ? res_float(lp[b.c3].res_b[k], lp[b.c3].res_c[k]) : (int32_t)((uint32_t)lp[b.c3].res_b[k] << (b.t - lp[b.c3].res_c[k]));
     }
     memcpy(&host[off_pb], pool_b, 4 * (size_t)c_last);
     memcpy(&host[off_pc], pool_c, (size_t)c_last);
@@ -611,7 +613,7 @@ hawq_status hawq_net_create(int32_t arch, int32_t image_hw, int32_t num_classes,
                 a.par = (const int32_t *)(A + b.par);
                 a.hi1 = act_hi(lp[b.c2].bits); a.hi2 = act_hi(lp[b.c3].bits); a.lo3 = 0; a.hi3 = act_hi(out_bits);
                 a.t = b.t; a.mid8 = b.ds >= 0 && b.rescaled;
-                a.x4 = !is8(b.c1); a.y4 = out_dt == HAWQ_U4;
+                a.x4 = !is8(b.c1); a.y4 = out_dt == HAWQ_U4; a.flt = b.flt;
                 for (size_t q = first_step; q < s1; ++q) net->steps[q].block_last = (int)s1;
                 net->steps[s1].block = (int)net->blocks.size();
                 net->steps[s1].block_in = block_in;

@@ -64,6 +64,20 @@ def test_blocks_as_one_launch(hawq, hw, N, four, int32_sc):
     assert working == 3, working
 
 
+def test_blocks_with_large_shortcut_multipliers(hawq):
+    """Shortcut multipliers of 16 bits and more: the integer form of that term, still as one launch."""
+    net = wl.make_resnet(50, seed=79, image_hw=64)
+    for name in ("layer1.1.c3", "layer1.2.c3"):
+        l = next(l for l in net["layers"] if l["name"] == name)
+        sel = np.arange(256) % 9 == 4
+        l["res_b"] = np.where(sel, l["res_b"].astype(np.int64) << 3, l["res_b"]).astype(np.int32)
+        l["res_c"] = np.where(sel, l["res_c"].astype(np.int32) + 3, l["res_c"]).astype(np.uint8)
+        assert l["res_b"].max() >= 65536
+    x = wl.make_image_batch(80, 3, image_hw=64)
+    got, working = _forward(hawq, net, x)
+    assert np.array_equal(got, onet.forward(net, x)) and working == 3, working
+
+
 @pytest.mark.parametrize("int32_sc", [True, False])
 @pytest.mark.parametrize("what", ["wide", "bias"])
 def test_blocks_beyond_the_narrow_evaluation(hawq, what, int32_sc):
