@@ -111,7 +111,7 @@ def measure_group_latencies(net_by_choice, batch, image, repeats=5):
     """Measured latency table Q [G, B] in milliseconds for one batch size: net_by_choice maps a bit choice to a
     HawqNet in which every selectable group runs at that width; the per-launch device times of the library's timed
     forward are summed per group (a transition convolution into its block's first group; conv1 carries the fused max
-    pool).  Returns (group names, Q)."""
+    pool); the time of a block that runs as one launch goes to its groups by their multiply-accumulates.  Returns (group names, Q)."""
     import torch
     names = None
     cols = []
@@ -122,14 +122,23 @@ def measure_group_latencies(net_by_choice, batch, image, repeats=5):
         for _ in range(2):
             hn.hawq_forward_resnet(image, batch, logits, ws)
         per = np.median(np.array([hn.hawq_forward_resnet_timed(image, batch, logits, ws) for _ in range(repeats)]), axis=0)
-        acc, order = {}, []
+        acc, order, idle = {}, [], set()
         for s in range(hn.num_steps()):
             nm = hn.step_output(batch, s)["name"]
+            if hn.step_cost(batch, s)[0] == 0:
+                idle.add(nm)                             # (no convolution, or computed in the launch at a later step)
             g = "conv1" if nm == "pool" else ("fc" if nm == "avgpool" else group_of(nm))
             if g not in acc:
                 acc[g] = 0.0
                 order.append(g)
             acc[g] += float(per[s])
+        cost_names, _, ops = layer_costs(hn.arch, hn.image_hw, hn.num_classes, (8,))
+        costs = dict(zip(cost_names, ops[:, 0]))
+        for blk in [nm[:-3] for nm in idle if nm.endswith(".c1") and nm[:-1] + "2" in idle]:
+            mine = [g for g in order if g.startswith(blk + ".")]
+            total, work = sum(acc[g] for g in mine), sum(costs[g] for g in mine)
+            for g in mine:
+                acc[g] = total * costs[g] / work
         if names is None:
             names = order
         cols.append([acc[g] for g in names])

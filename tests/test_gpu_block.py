@@ -96,3 +96,22 @@ def test_blocks_beyond_the_narrow_evaluation(hawq, what, int32_sc):
     assert np.array_equal(got, plain) and working == 5 and separate >= 9, (working, separate)
     if what == "wide":
         assert np.array_equal(got, onet.forward(net, x))
+
+
+def test_measured_latencies_of_a_joined_block(hawq):
+    """A block's launch has one time; the table of the bit selection gives each of its groups the part that its work is."""
+    import torch
+    from paper_2011_10680_amd import bitselect as bs
+    N, hw = 2, 64
+    nets = {}
+    for b in (4, 8):
+        net = wl.make_resnet(50, seed=5, bits=_bits("all" if b == 4 else ()), image_hw=hw)
+        nets[b] = hawq.HawqNet(50, net["layers"], net["pool_b"], net["pool_c"], image_hw=hw)
+    names, Q = bs.measure_group_latencies(nets, N, torch.from_numpy(wl.make_image_batch(6, N, image_hw=hw)).cuda(), repeats=2)
+    cost_names, _, G = bs.layer_costs(50, image_hw=hw, choices=(8,))
+    for hn in nets.values():
+        hn.close()
+    assert names == cost_names and np.all(Q > 0)
+    rows = [names.index("layer1.1." + c) for c in ("c1", "c2", "c3")]
+    share = Q[rows] / Q[rows].sum(axis=0)
+    assert np.allclose(share, (G[rows] / G[rows].sum()).repeat(2, axis=1))
