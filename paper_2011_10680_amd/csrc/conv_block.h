@@ -1,6 +1,7 @@
 // A bottleneck block at 64 channels as one launch (conv_block.hip).
 #pragma once
 #include "common.h"
+#include "conv_block_plan.h"
 
 namespace hawq {
 

@@ -26,7 +26,7 @@ namespace hawq {
 
 namespace {
 
-constexpr int TW = 14, TH = 8, HW16 = 16, HROWS = TH + 2, HALO = HW16 * HROWS;   // 160 input pixels
+constexpr int TW = BLOCK_TW, TH = BLOCK_TH, HW16 = BLOCK_HW, HALO = HW16 * BLOCK_HROWS;   // 160 input pixels
 constexpr uint32_t kOut = 0x80000000u;
 constexpr float kResMagicF = 12582912.f;                  // 1.5 * 2^23, whose bits are kResMagic
 
@@ -163,7 +163,7 @@ __global__ void __launch_bounds__(256, 2) block64_kernel(const BlockArgs a) {
             const int y = y0 + k / IPR;
             const uint32_t off = (unsigned)y < (unsigned)a.H ? col : kOut;
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (__attribute__((address_space(3))) void *)(xs + to + k * 1024), 16, (int)off,
-                                                     (n * a.H + max(y, 0)) * a.W * XB, 0, 0);
+                                                     block_input_row(n, y, a.H, a.W, XB), 0, 0);
         }
     };
 
