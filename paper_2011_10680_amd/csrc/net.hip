@@ -326,8 +326,13 @@ hawq_status hawq_net_create(int32_t arch, int32_t image_hw, int32_t num_classes,
     // 4-bit layer's input in an 8-bit container (values 0..15, written so by the producer's epilogue) and its weights expanded
     // to INT8 in the arena, and the layer runs on the INT8 kernels at INT8 speed -- same integers, other storage.  A block's
     // transition layer and first convolution read the same tensor and go together; in a block with a transition layer
-    // the last convolution and the transition layer are expanded so that they can run as one launch.  With kept
-    // activations every tensor stays in the documented packed form.
+    // the last convolution and the transition layer are expanded so that they can run as one launch.  Where the transition layer
+    // has 8 bits itself, a last convolution of 4 is expanded too if its shortcut stays INT32 (else both raw accumulators pass through
+    // memory: ResNet50 batch 128, layer2.0.c3 at 4 bits 1134 -> 984 us, ResNet18 layer2.0.c2 407 -> 361) and in the 64-channel
+    // bottleneck block, which runs as one launch then (layer1.0.c3, INT32 1272 -> 988, stored 1052 -> 1012).  Other stored shortcuts
+    // keep the packed form: alone among 8-bit layers it loses 1 to 10 %, but among 4-bit ones it wins up to 3 (layer2.0.c1 alone
+    // at 8 bits: ResNet18 batch 8 135 against 138, 128 396 against 403; ResNet50 128 955 against 966).  With kept activations
+    // every tensor stays in the documented packed form.
     std::vector<char> expand(nl, 0);
     if (!net->keep) {
         auto packed_pays = [&](const LayerShape &l) {
@@ -342,13 +347,16 @@ hawq_status hawq_net_create(int32_t arch, int32_t image_hw, int32_t num_classes,
         for (int i = 0; i < nl; ++i)
             if (lp[i].bits == 4 && !L[i].is_stem && !L[i].is_fc) expand[i] = !packed_pays(L[i]);
         for (int i = 0; i < nl; ++i) {
-            if (!L[i].is_ds || lp[i].bits != 4) continue;
+            if (!L[i].is_ds) continue;
             int c1 = i, last = i;
             while (c1 >= 0 && !(L[c1].is_c1 && L[c1].block == L[i].block)) --c1;
             while (last >= 0 && !(L[last].has_residual && L[last].block == L[i].block)) --last;
-            expand[i] = 1;
-            if (c1 >= 0) expand[c1] = 1;                              // (same width as the transition layer: validated above)
-            if (last >= 0 && lp[last].bits == 4) expand[last] = 1;
+            if (lp[i].bits == 4) {
+                expand[i] = 1;
+                if (c1 >= 0) expand[c1] = 1;                          // (same width as the transition layer: validated above)
+            }
+            if (last >= 0 && lp[last].bits == 4 &&
+                (lp[i].bits == 4 || (lp[i].flags & HAWQ_LAYER_INT32_SHORTCUT) || (L[last].R == 1 && L[last].C == 64))) expand[last] = 1;
         }
     }
     auto is8 = [&](int i) { return lp[i].bits == 8 || expand[i]; };      // operands in 8-bit form

@@ -55,13 +55,35 @@ def _forward(hawq, net, x, mode=0):
 @pytest.mark.parametrize("hw,N,four,int32_sc", [
     (32, 1, (), True), (64, 3, (), False), (100, 2, "all", True), (100, 3, "all", False), (224, 10, (), True), (224, 24, (), False),
     (132, 80, "all", False), (224, 1, ("layer1.1.in",), True), (64, 5, ("layer1.0.c2", "layer1.2.in", "layer1.2.c3"), False),
-    (100, 4, ("layer2.0.in", "layer1.1.c3"), False), (64, 260, (), True)])
+    (100, 4, ("layer2.0.in", "layer1.1.c3"), False), (64, 260, (), True),
+    (100, 3, ("layer1.0.c3",), True), (100, 3, ("layer1.0.c2", "layer1.0.c3"), False)])
 def test_blocks_as_one_launch(hawq, hw, N, four, int32_sc):
     net = wl.make_resnet(50, seed=900 + hw + N, bits=_bits(four), image_hw=hw, int32_shortcut=int32_sc)
     x = wl.make_image_batch(901 + N, N, image_hw=hw)
     got, working = _forward(hawq, net, x)
     assert np.array_equal(got, onet.forward(net, x))
     assert working == 3, working
+
+
+@pytest.mark.parametrize("arch", [18, 50])
+def test_last_convolutions_of_four_bits_with_an_int32_shortcut(hawq, arch):
+    """A transition layer of 8 bits and a last convolution of 4, both branches INT32: one launch, no raw accumulators in memory."""
+    import torch
+    last = "c3" if arch == 50 else "c2"
+    bits = {g: (4 if g.endswith(".0." + last) else 8) for g in wl.resnet_group_names(arch)}
+    assert sum(b == 4 for b in bits.values()) == 4
+    net = wl.make_resnet(arch, seed=83 + arch, bits=bits, image_hw=64, int32_shortcut=True)
+    x = wl.make_image_batch(84, 3, image_hw=64)
+    hn = hawq.HawqNet(arch, net["layers"], net["pool_b"], net["pool_c"], image_hw=64)
+    ws = torch.full((hn.workspace_bytes(3),), 0x7B, dtype=torch.uint8, device="cuda")
+    logits = torch.zeros((3, 1000), dtype=torch.int32, device="cuda")
+    hn.hawq_forward_resnet(torch.from_numpy(x).cuda(), 3, logits, ws)
+    torch.cuda.synchronize()
+    names = [hn.step_output(3, s)["name"] for s in range(hn.num_steps())]
+    got = logits.cpu().numpy()
+    hn.close()
+    assert not [n for n in names if n.endswith(".acc")], names
+    assert np.array_equal(got, onet.forward(net, x))
 
 
 def test_blocks_with_large_shortcut_multipliers(hawq):
