@@ -107,14 +107,30 @@ def solve(omega, size=None, bops=None, latency=None, size_limit=None, bops_limit
     return choice, float(omega[np.arange(L), choice].sum())
 
 
+def share_block_time(times, work, stored):
+    """Time of a block that runs as one launch, per bit choice, as its groups' shares: {group: [B]}.  The launch computes on bytes at
+    every width and keeps what lies between its convolutions on the chip, so a width changes its time only where it changes how
+    the block's input or output is stored.  What every choice takes is dealt to the block's groups by their work ({group:
+    multiply-accumulates}), what one takes beyond that in equal parts to `stored`, the groups whose widths set that storage."""
+    times = np.asarray(times, dtype=np.float64)
+    least, total = times.min(), float(sum(work.values()))
+    out = {g: np.zeros(len(times)) for g in list(work) + list(stored)}
+    for g in work:
+        out[g] += least * work[g] / total
+    for g in stored:
+        out[g] += (times - least) / len(stored)
+    return out
+
+
 def measure_group_latencies(net_by_choice, batch, image, repeats=5):
     """Measured latency table Q [G, B] in milliseconds for one batch size: net_by_choice maps a bit choice to a
     HawqNet in which every selectable group runs at that width; the per-launch device times of the library's timed
     forward are summed per group (a transition convolution into its block's first group; conv1 carries the fused max
-    pool); the time of a block that runs as one launch goes to its groups by their multiply-accumulates.  Returns (group names, Q)."""
+    pool); the time of a block that runs as one launch goes to the groups as share_block_time has it, with the first
+    convolution of the next block among those whose width sets its storage.  Returns (group names, Q)."""
     import torch
     names = None
-    cols = []
+    cols, blocks = [], []
     for b in sorted(net_by_choice):
         hn = net_by_choice[b]
         ws = torch.empty(hn.workspace_bytes(batch), dtype=torch.uint8, device="cuda")
@@ -122,9 +138,10 @@ def measure_group_latencies(net_by_choice, batch, image, repeats=5):
         for _ in range(2):
             hn.hawq_forward_resnet(image, batch, logits, ws)
         per = np.median(np.array([hn.hawq_forward_resnet_timed(image, batch, logits, ws) for _ in range(repeats)]), axis=0)
+        steps = [hn.step_output(batch, s) for s in range(hn.num_steps())]
         acc, order, idle = {}, [], set()
-        for s in range(hn.num_steps()):
-            nm = hn.step_output(batch, s)["name"]
+        for s, st in enumerate(steps):
+            nm = st["name"]
             if hn.step_cost(batch, s)[0] == 0:
                 idle.add(nm)                             # (no convolution, or computed in the launch at a later step)
             g = "conv1" if nm == "pool" else ("fc" if nm == "avgpool" else group_of(nm))
@@ -132,14 +149,29 @@ def measure_group_latencies(net_by_choice, batch, image, repeats=5):
                 acc[g] = 0.0
                 order.append(g)
             acc[g] += float(per[s])
-        cost_names, _, ops = layer_costs(hn.arch, hn.image_hw, hn.num_classes, (8,))
-        costs = dict(zip(cost_names, ops[:, 0]))
-        for blk in [nm[:-3] for nm in idle if nm.endswith(".c1") and nm[:-1] + "2" in idle]:
-            mine = [g for g in order if g.startswith(blk + ".")]
-            total, work = sum(acc[g] for g in mine), sum(costs[g] for g in mine)
-            for g in mine:
-                acc[g] = total * costs[g] / work
+        joined = {}                                      # block: (storage of its input, of its output, the group that reads that)
+        for s, st in enumerate(steps):
+            blk = st["name"][:-3]
+            if st["name"] == blk + ".c1" and st["name"] in idle and blk + ".c2" in idle:
+                last = max(i for i, o in enumerate(steps) if o["name"].startswith(blk + "."))
+                joined[blk] = (steps[s - 1]["dtype"], steps[last]["dtype"], group_of(steps[last + 1]["name"]))
         if names is None:
             names = order
-        cols.append([acc[g] for g in names])
-    return names, np.array(cols).T
+        cols.append(acc)
+        blocks.append(joined)
+    cost_names, _, ops = layer_costs(hn.arch, hn.image_hw, hn.num_classes, (8,))
+    costs = dict(zip(cost_names, ops[:, 0]))
+    Q = {g: np.array([acc[g] for acc in cols]) for g in names}
+    extra = {g: np.zeros(len(cols)) for g in names}
+    for blk in sorted(set().union(*blocks)):
+        work = {g: costs[g] for g in names if g.startswith(blk + ".")}
+        times = sum(Q[g] for g in work)
+        first, here = blk + ".c1", [j for j in range(len(cols)) if blk in blocks[j]]
+        inputs, outputs = ({blocks[j][blk][i] for j in here} for i in (0, 1))
+        stored = ([first] if len(inputs) > 1 else []) + ([blocks[here[0]][blk][2]] if len(outputs) > 1 else [])
+        shares = share_block_time(times[here], work, stored or [first])
+        for g in work:
+            Q[g][here] = 0                               # (a choice with separate launches keeps their times)
+        for g in shares:
+            extra[g][here] += shares[g]
+    return names, np.array([Q[g] + extra[g] for g in names])

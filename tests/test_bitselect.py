@@ -75,6 +75,19 @@ def test_quantization_perturbation_grows_as_bits_shrink():
     assert 0 < p8 < p4 and 100 < p4 / p8 < 600           # step ratio 255/15 = 17, squared 289
 
 
+@pytest.mark.parametrize("times", [(60.0, 72.0), (75.0, 64.0), (5.0, 5.0), (3.0, 30.0)])
+def test_time_of_a_joined_block_goes_where_a_width_changes_it(times):
+    """Groups whose width the launch does not see cost the same at every width; the sum is the launch's time and every share positive."""
+    work = {"b.c1": 4.0, "b.c2": 9.0, "b.c3": 4.0}
+    for stored in (["b.c1"], ["n.c1"], ["b.c1", "n.c1"]):
+        q = bs.share_block_time(times, work, stored)
+        assert np.allclose(sum(q.values()), times) and all((q[g] > 0).all() for g in work)
+        for g in work:
+            assert g in stored or q[g][0] == q[g][1]
+        parts = [q[g] - min(times) * work.get(g, 0) / 17 for g in stored]
+        assert all(np.allclose(p, (np.array(times) - min(times)) / len(stored)) for p in parts)
+
+
 @pytest.mark.gpu
 def test_latency_table_measured_on_the_gpu_and_selection_under_a_latency_limit():
     import torch
