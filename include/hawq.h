@@ -328,12 +328,14 @@ size_t hawq_net_workspace_bytes(const hawq_net *net, int32_t N);
 /* Images in the first of the two parts hawq_forward_resnet runs a batch of N as (see there); 0: one part. */
 int32_t hawq_net_split_first(const hawq_net *net, int32_t N);
 
-/* Number of launches of one forward: conv1, max pool, the convolutions, average pool, fc. */
+/* Number of steps of one forward: conv1, max pool, the convolutions, average pool, fc.  A step is one launch or none: a later step's
+ * launch may do its work (hawq_net_step_cost reports no multiply-accumulates for such a convolution), and conv1's does the pool's. */
 int32_t hawq_net_num_steps(const hawq_net *net);
 
 /*
  * Where step `step` leaves its output inside the workspace for batch N, and what it is
- * (valid until a later step reuses the slot; permanent with keep_activations).
+ * (valid until a later step reuses the slot; permanent with keep_activations).  bytes = 0: it leaves none -- conv1 where the
+ * max pool is computed with it, and every step whose work is done in a later step's launch.
  * name: at least 24 bytes.  dtype: hawq_dtype of the stored tensor.
  * The offsets describe a batch that runs as one part (always the case with keep_activations); when
  * hawq_net_split_first(net, N) is not 0 the two parts have their own regions of the workspace, the first laid out
@@ -347,7 +349,8 @@ hawq_status hawq_net_step_output(const hawq_net *net, int32_t N, int32_t step, c
  * [N,num_classes].  x, logits and workspace are device memory; workspace must hold
  * hawq_net_workspace_bytes(net, N) bytes, 256-byte aligned; x must be 16-byte aligned.  Enqueues every layer on
  * `stream`.  Unless the network keeps its activations, conv1 and the max pool run as one kernel and the conv1
- * tensor is never written to memory (its step reports an empty output).
+ * tensor is never written to memory; likewise ResNet50's 64-channel bottleneck blocks, whose inner tensors stay on the chip, and
+ * transition layers that run with their block's last convolution (all these steps report an empty output).
  * Stream semantics: as if every launch were on `stream` -- the forward starts after all work queued on `stream`
  * before the call and work queued after the call sees the finished logits.  Inside, a batch of 96 images or more
  * (without kept activations) runs as two halves, the second on a stream the network owns (default priority, created
@@ -398,8 +401,9 @@ void hawq_tune_set_split(int32_t n_first);
 
 /* Measurement hook for the network plan: networks created by later hawq_net_create calls run the 3x3 and the closing 1x1 of
  * an identity-shortcut bottleneck block as one launch (the kernel of hawq_bottleneck_tail_int) wherever it applies (1),
- * only where the 3x3 has 256 input channels (2), or by the plan's own rule (0, default: the rule keeps two launches on the
- * ResNet50 shapes, where one launch measured slower).
+ * only where the 3x3 has 256 input channels (2), by the plan's own rule (0, default: the rule keeps two launches on the
+ * ResNet50 shapes, where one launch measured slower) or nowhere (-1).  With -1 the 64-channel bottleneck blocks, which otherwise run
+ * as one launch each, keep a launch per convolution too.
  * Process-wide state, as hawq_tune_set_tile.  Results are identical for every setting. */
 void hawq_tune_set_fusion(int32_t mode);
 

@@ -306,7 +306,7 @@ def hawq_noalloc_workspace_limit():
 
 def hawq_tune_set_fusion(mode):
     """Measurement hook: 1 = later networks fuse bottleneck tails wherever the kernel applies, 2 = only at 256 input
-    channels, 0 = the plan's rule."""
+    channels, 0 = the plan's rule, -1 = nowhere, and the 64-channel blocks keep a launch per convolution too."""
     load_library().hawq_tune_set_fusion(int(mode))
 
 

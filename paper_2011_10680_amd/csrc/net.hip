@@ -231,6 +231,12 @@ bool block_runs(const hawq_net *net, int N, int last_step) {
     return (int64_t)N * b.H * b.W * 256 < 0x80000000ll;
 }
 
+// Does a later step's launch do this step's work at batch N?  Its output is stored nowhere then.
+bool done_later(const hawq_net *net, int N, int step) {
+    const Step &st = net->steps[step];
+    return (st.block_last >= 0 && block_runs(net, N, st.block_last)) || (st.pair_last >= 0 && pair_runs_fused(net, N, step)) || st.tail_next >= 0;
+}
+
 size_t slot_offset(const hawq_net *net, int slot, int N) {
     size_t off = 0;
     for (int i = 0; i < slot; ++i) off += align_up((size_t)net->slot_bytes_per_image[i] * N, 256);
@@ -786,7 +792,7 @@ hawq_status hawq_net_step_output(const hawq_net *net, int32_t N, int32_t step, c
     }
     const Tensor &t = net->tensors[st.out];
     *offset = slot_offset(net, t.slot, N);
-    *bytes = (size_t)tensor_bytes(t.elems_per_image * N, t.dt);
+    *bytes = done_later(net, N, step) ? 0 : (size_t)tensor_bytes(t.elems_per_image * N, t.dt);
     *dtype = t.dt;
     dims4[0] = N; dims4[1] = t.dims[0]; dims4[2] = t.dims[1]; dims4[3] = t.dims[2];
     return HAWQ_OK;
@@ -798,8 +804,8 @@ hawq_status hawq_net_step_cost(const hawq_net *net, int32_t N, int32_t step, dou
     const Step &st = net->steps[step];
     *macs = st.macs_per_image * N;
     *bytes = st.bytes_per_image * N + st.bytes_fixed;
+    if (done_later(net, N, step)) { *macs = 0; *bytes = 0; return HAWQ_OK; }
     // a block that runs as one launch: all its work, its input, its output and its weights on the last step
-    if (st.block_last >= 0 && block_runs(net, N, st.block_last)) { *macs = 0; *bytes = 0; return HAWQ_OK; }
     if (block_runs(net, N, step)) {
         const BlockArgs &b = net->blocks[st.block];
         const double px = (double)b.H * b.W;
@@ -808,18 +814,16 @@ hawq_status hawq_net_step_cost(const hawq_net *net, int32_t N, int32_t step, dou
             if (net->steps[q].block_last == step) { *macs += net->steps[q].macs_per_image * N; *bytes += net->steps[q].bytes_fixed; }
         return HAWQ_OK;
     }
-    // a transition / last convolution pair that runs as one launch: all the work and the traffic it still needs (both
-    // inputs, both parameter sets, the block output) are reported on the last convolution's step
-    if (st.pair_last >= 0 && pair_runs_fused(net, N, step)) { *macs = 0; *bytes = 0; }
     // a 3x3 convolution that runs inside the launch of the 1x1 that follows it: work and traffic (the 3x3's input, the
     // shortcut, the block output, both weight sets) are reported on that step; the tensor in between moves no bytes
-    if (st.tail_next >= 0) { *macs = 0; *bytes = 0; }
     if (st.tail_prev >= 0) {
         const Step &p = net->steps[st.tail_prev];
         const double px = (double)st.desc.H * st.desc.W;
         *macs += p.macs_per_image * N;
         *bytes = (px * p.desc.C + 2.0 * px * st.desc.K) * N + st.bytes_fixed + p.bytes_fixed;
     }
+    // a transition / last convolution pair that runs as one launch: all the work and the traffic it still needs (both
+    // inputs, both parameter sets, the block output) are reported on the last convolution's step
     if (st.pair_ds >= 0 && pair_runs_fused(net, N, st.pair_ds)) {
         const Step &d = net->steps[st.pair_ds];
         const hawq_conv_desc &c = st.desc, &e = d.desc;

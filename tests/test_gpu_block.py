@@ -86,6 +86,26 @@ def test_last_convolutions_of_four_bits_with_an_int32_shortcut(hawq, arch):
     assert np.array_equal(got, onet.forward(net, x))
 
 
+@pytest.mark.parametrize("int32_sc", [True, False])
+@pytest.mark.parametrize("mode", [0, -1])
+def test_steps_that_leave_no_output_say_so(hawq, mode, int32_sc):
+    """A convolution whose work a later step's launch does reports an empty output, every other one (conv1, whose pool is computed with it,
+    and the classifier aside) where it is."""
+    net = wl.make_resnet(50, seed=85, image_hw=64, int32_shortcut=int32_sc)
+    try:
+        hawq.hawq_tune_set_fusion(mode)
+        hn = hawq.HawqNet(50, net["layers"], net["pool_b"], net["pool_c"], image_hw=64)
+    finally:
+        hawq.hawq_tune_set_fusion(0)
+    steps = [(hn.step_output(3, s), hn.step_cost(3, s)[0]) for s in range(hn.num_steps())]
+    hn.close()
+    empty = [o["name"] for o, _ in steps if o["bytes"] == 0]
+    inner = ["layer1.%d.c%d" % (b, c) for b in range(3) for c in (1, 2)] if mode == 0 else []
+    ds = [] if int32_sc else ["layer%d.0.ds" % l for l in (1, 2, 3, 4)]
+    assert sorted(empty) == sorted(["conv1", "fc"] + inner + ds)
+    assert all(o["bytes"] == 0 for o, macs in steps if macs == 0 and o["name"] not in ("pool", "avgpool"))
+
+
 def test_blocks_with_large_shortcut_multipliers(hawq):
     """Shortcut multipliers of 16 bits and more: the integer form of that term, still as one launch."""
     net = wl.make_resnet(50, seed=79, image_hw=64)

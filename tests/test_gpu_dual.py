@@ -179,7 +179,7 @@ def _forward_gpu(hawq, net, x, keep):
 @pytest.mark.parametrize("arch,mixed,N", [(18, False, 2), (50, False, 2), (50, True, 2)])
 def test_network_with_int32_shortcuts(hawq, arch, mixed, N):
     """Transition blocks in the two-accumulator form: all-8-bit networks run them as one launch each (no transition
-    tensor is stored); with 4-bit layers in a transition block the raw accumulators pass through the workspace."""
+    tensor is stored); with 4-bit layers in a transition block and kept activations the raw accumulators pass through the workspace."""
     bits = wl.draw_bits(arch, 4000 + arch) if mixed else None
     net = wl.make_resnet(arch, seed=1000 + arch, bits=bits, int32_shortcut=True)
     plain = wl.make_resnet(arch, seed=1000 + arch, bits=bits)
