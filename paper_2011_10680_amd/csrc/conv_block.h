@@ -21,17 +21,6 @@ struct BlockArgs {
 };
 constexpr int BLOCK64_PAR = 1536;       // words of par
 
-// The shortcut of an unsigned byte in floating point, exactly:  (r*rb + 2^(rc-1)) >> rc  is the integer nearest to
-// x = r*rb / 2^rc, a half rounded up.  With the multiplier raised to (256 rb + 1) / 2^(rc+8) the product is x + r / 2^(rc+8):
-// nothing that is a multiple of 2^-rc lies between the two (r < 256), a half is no tie any more, and one fused multiply-add with
-// 1.5 * 2^23 rounds to the nearest integer -- the result's bits are kResMagic + the term.  24 bits hold 256 rb + 1 for rb < 2^16,
-// and rc >= 2 keeps the term below 2^22.
-constexpr int32_t kResMagic = 0x4B400000;
-inline bool res_float_ok(int32_t rb, int32_t rc) { return rb < 65536 && rc >= 2; }
-inline int32_t res_float(int32_t rb, int32_t rc) {
-    return __builtin_bit_cast(int32_t, __builtin_ldexpf((float)(256 * rb + 1), -(rc + 8)));
-}
-
 hawq_status launch_block64(const BlockArgs &a, hipStream_t s);
 
 }  // namespace hawq

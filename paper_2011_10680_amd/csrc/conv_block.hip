@@ -28,7 +28,6 @@ namespace {
 
 constexpr int TW = BLOCK_TW, TH = BLOCK_TH, HW16 = BLOCK_HW, HALO = HW16 * BLOCK_HROWS;   // 160 input pixels
 constexpr uint32_t kOut = 0x80000000u;
-constexpr float kResMagicF = 12582912.f;                  // 1.5 * 2^23, whose bits are kResMagic
 
 __device__ __forceinline__ void lds_barrier() {
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -55,10 +54,10 @@ __device__ __forceinline__ v4i pack16(const int32_t (&y)[16]) {
     }
     return o;
 }
-// kResMagic + the shortcut of byte I in floating point (conv_block.h): two vector instructions, the conversion picks its byte
+// kResMagic + the shortcut of byte I in floating point (conv_block_plan.h): two vector instructions, the conversion picks its byte
 template <int I>
 __device__ __forceinline__ int32_t res_term(uint32_t bytes, int32_t rf) {
-    return __builtin_bit_cast(int32_t, __builtin_fmaf((float)((bytes >> (8 * I)) & 0xffu), __builtin_bit_cast(float, rf), kResMagicF));
+    return res_scaled((float)((bytes >> (8 * I)) & 0xffu), rf);
 }
 // sixteen words of a lane's channels; fresh: read here, not kept from an earlier use (accumulators start at the bias, and a copy
 // kept for all of them would be sixteen registers and sixteen moves for each)

@@ -120,6 +120,27 @@ def test_blocks_with_large_shortcut_multipliers(hawq):
     assert np.array_equal(got, onet.forward(net, x)) and working == 3, working
 
 
+@pytest.mark.parametrize("shifts,multipliers", [
+    (range(2, 9), lambda g, c: np.minimum(g.integers(0, 6, 256) << np.maximum(c - 4, 0), 65535)),          # the smallest shifts: sums of whole, half and quarter steps
+    (range(14, 18), lambda g, c: np.where(g.random(256) < 0.5, 1 << np.minimum(c - 1, 15), 65535 - g.integers(0, 3, 256))),   # halves; the largest multipliers
+    (range(22, 28), lambda g, c: g.choice([1 << 15, 65535, 65534, 0], 256)),                              # steps of a 128th of one and less
+    (range(24, 31), lambda g, c: g.choice([1 << 15, 65535, 65534, 0], 256))])                             # the largest shifts: nothing left
+def test_blocks_with_shortcut_multipliers_at_the_ends_of_the_float_form(hawq, shifts, multipliers):
+    """Shortcuts in floating point where a product meets a half, and at either end of its multipliers and shifts."""
+    net = wl.make_resnet(50, seed=87, image_hw=64)
+    g = np.random.default_rng(shifts[0])
+    for name in ("layer1.1.c3", "layer1.2.c3"):
+        l = next(l for l in net["layers"] if l["name"] == name)
+        c = g.choice(np.array(shifts), 256)
+        c[:len(shifts)] = shifts
+        l["res_c"], l["res_b"] = c.astype(np.uint8), multipliers(g, c).astype(np.int32)
+        # (one launch: multipliers raised to the largest shift stay below 2^22)
+        assert l["res_b"].max() < 65536 and (l["res_b"].astype(np.int64) << (c.max() - c)).max() < 1 << 22
+    x = wl.make_image_batch(88, 3, image_hw=64)
+    got, working = _forward(hawq, net, x)
+    assert np.array_equal(got, onet.forward(net, x)) and working == 3, working
+
+
 @pytest.mark.parametrize("int32_sc", [True, False])
 @pytest.mark.parametrize("what", ["wide", "bias"])
 def test_blocks_beyond_the_narrow_evaluation(hawq, what, int32_sc):
