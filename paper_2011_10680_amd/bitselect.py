@@ -107,6 +107,12 @@ def solve(omega, size=None, bops=None, latency=None, size_limit=None, bops_limit
     return choice, float(omega[np.arange(L), choice].sum())
 
 
+def least_cost(table, fixed=None):
+    """The least sum that any choice under `fixed` ({row: column}) has in a cost table [L, B]: a limit from there on can be met."""
+    table = np.asarray(table, dtype=np.float64)
+    return float(sum(table[i, fixed[i]] if i in (fixed or {}) else table[i].min() for i in range(len(table))))
+
+
 def share_block_time(times, work, stored):
     """Time of a block that runs as one launch, per bit choice, as its groups' shares: {group: [B]}.  The launch computes on bytes at
     every width and keeps what lies between its convolutions on the chip, so a width changes its time only where it changes how

@@ -90,7 +90,7 @@ def main():
     fixed = {0: 1, len(names) - 1: 1}                                   # conv1 and fc stay at 8 bits
     q4, q8 = Q[:, 0].sum(), Q[:, 1].sum()
     lo, hi = min(q4, q8), max(q4, q8)
-    floor = Q.min(axis=1).sum()                                        # the fastest any assignment can be, by the table
+    floor = bs.least_cost(Q, fixed)                                    # the fastest any assignment can be, by the table
     out = dict(arch=arch, batch=N, groups=names, latency_ms=Q.tolist(), omega=omega.tolist(), size_bytes=M.tolist(), bops=G.tolist(),
                sum_latency_int4_ms=q4, sum_latency_int8_ms=q8, sum_latency_fastest_ms=floor,
                forward_ms_all_int4=t_uniform[4], forward_ms_all_int8=t_uniform[8], selections=[])

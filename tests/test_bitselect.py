@@ -75,6 +75,18 @@ def test_quantization_perturbation_grows_as_bits_shrink():
     assert 0 < p8 < p4 and 100 < p4 / p8 < 600           # step ratio 255/15 = 17, squared 289
 
 
+def test_least_cost_under_fixed_rows_can_be_met():
+    """Fixed rows that were measured slower than their other column: the least sum without them is out of reach, the one with them met."""
+    Q = np.array([[5.0, 5.4], [4.0, 4.1], [3.0, 2.9], [2.0, 2.6]])
+    omega, fixed = np.array([[2.0, 0.0]] * 4), {0: 1, 3: 1}
+    least = bs.least_cost(Q, fixed)
+    assert abs(least - (5.4 + 4.0 + 2.9 + 2.6)) < 1e-12 and abs(bs.least_cost(Q) - Q.min(axis=1).sum()) < 1e-12
+    choice, _ = bs.solve(omega, latency=Q, latency_limit=least, fixed=fixed)
+    assert list(choice) == [1, 0, 1, 1]
+    with pytest.raises(ValueError):
+        bs.solve(omega, latency=Q, latency_limit=bs.least_cost(Q) + 0.5, fixed=fixed)
+
+
 @pytest.mark.parametrize("times", [(60.0, 72.0), (75.0, 64.0), (5.0, 5.0), (3.0, 30.0)])
 def test_time_of_a_joined_block_goes_where_a_width_changes_it(times):
     """Groups whose width the launch does not see cost the same at every width; the sum is the launch's time and every share positive."""
@@ -104,8 +116,9 @@ def test_latency_table_measured_on_the_gpu_and_selection_under_a_latency_limit()
     cost_names, M, G = bs.layer_costs(arch, image_hw=hw)
     assert names == cost_names and Q.shape == (len(names), 2) and np.all(Q > 0)
     omega = np.stack([np.linspace(2, 1, len(names)), np.zeros(len(names))], axis=1)
-    limit = 0.5 * (Q.min(axis=1).sum() + Q.max(axis=1).sum())
     fixed = {0: 1, len(names) - 1: 1}                                   # first and last layer stay at 8 bits
+    # halfway from the fastest choice that the fixed layers leave to the slowest: the fastest one holds it, whatever was measured
+    limit = 0.5 * (bs.least_cost(Q, fixed) - bs.least_cost(-Q, fixed))
     choice, obj = bs.solve(omega, latency=Q, latency_limit=limit, fixed=fixed)
     assert Q[np.arange(len(names)), choice].sum() <= limit + 1e-9
     for hn in nets.values():
