@@ -223,7 +223,7 @@ bool pair_runs_fused(const hawq_net *net, int N, int ds_step) {
 // Does a 64-channel bottleneck block run as one launch at batch N?  Wherever its tensors' offsets fit 31 bits: of 96 measured nets
 // (64 x 64 to 448 x 448 pixels, batch 1 to 256, 8-bit and mixed) all but one were faster so, by 4 to 12 % (ResNet50 at 224 x 224,
 // three launches a block -> one: batch 1 227 -> 218 us, 8 326 -> 302, 64 649 -> 597, 256 1779 -> 1583), that one equal
-// (64 x 64, batch 1 mixed: 185 -> 187, where images of 16 x 16 pixels leave a fourteenth to the second tile of a row).
+// (64 x 64, batch 1 mixed: 185 -> 187, where images of 16 x 16 pixels leave two of its fourteen columns to the second tile of a row).
 bool block_runs(const hawq_net *net, int N, int last_step) {
     const Step &st = net->steps[last_step];
     if (st.block < 0) return false;
@@ -248,7 +248,8 @@ size_t workspace_one_part(const hawq_net *net, int N) { return slot_offset(net, 
 // Batch split.  Every kernel of a forward pays a ramp-up and a tail in which part of the chip idles (tiles do not divide
 // evenly over 256 CUs, pipelines fill and drain), about a fifth of a ResNet50 forward at batch 128.  Images are
 // independent, so a large batch is run as two parts on two streams: the second part's kernels fill the first part's
-// gaps (measured 5 % on ResNet50 at batch 128 with equal parts; nothing at batch 64, a loss with three or four parts).
+// gaps (one part -> two equal ones, ResNet50: batch 96 898 -> 834 us, 128 984 -> 1000, mixed 1000 -> 990, 192 1538 -> 1358, 256
+// 1805 -> 1634; nothing at batch 64, a loss with three or four parts).
 // Returns the size of the first part, 0 for no split.
 int g_split_override = 0;   // 0: rule below; -1: never split; n > 0: first part of n images (measurement hook)
 int g_fuse_tails = 0;       // networks created from now on: 0 = the plan's rule for fused bottleneck tails, 1 = wherever the kernel applies, -1 = nowhere
@@ -391,7 +392,7 @@ hawq_status hawq_net_create(int32_t arch, int32_t image_hw, int32_t num_classes,
         Block b{i, i + 1, i + 2, L[i + 3].is_ds ? i + 3 : -1, 1, 0, false, 0};
         b.rescaled = b.ds < 0 || !(lp[b.ds].flags & HAWQ_LAYER_INT32_SHORTCUT);   // the shortcut is a stored byte's value
         bool ok = sums_fit(b.c1, act_hi(lp[b.c1].bits)) && sums_fit(b.c2, act_hi(lp[b.c2].bits)) && sums_fit(b.c3, act_hi(lp[b.c3].bits)) &&
-                  (b.ds < 0 || (sums_fit(b.ds, act_hi(lp[b.ds].bits)) && is8(b.c1) && is8(b.c3) && is8(b.ds)));   // (then the input's place is kept to the last step)
+                  (b.ds < 0 || sums_fit(b.ds, act_hi(lp[b.ds].bits)));   // (a transition block's operands are all bytes: see the expansion)
         if (b.rescaled) {
             for (int k = 0; k < 256; ++k) b.t = lp[b.c3].res_c[k] > b.t ? lp[b.c3].res_c[k] : b.t;
             for (int k = 0; k < 256 && ok; ++k) ok = b.t <= 30 && ((int64_t)lp[b.c3].res_b[k] << (b.t - lp[b.c3].res_c[k])) < (1 << 22);
