@@ -2,22 +2,25 @@
 // the shortcut -- the block's input itself or a 1x1 convolution of it (Figure 2, Section 3.3).
 //
 // As three launches these blocks move the input twice and both tensors in between, and each launch has a ramp-up and a tail:
-// 56 x 56 at batch 128 92 us with an identity shortcut, 81 us at the transition, of which input and output (206 and 128 MB) need
-// 40 and 25.  Here a workgroup walks over tiles of 14 x 8 output pixels; a tile's input with a border of one pixel, 16 x 10, comes
+// 56 x 56 at batch 128 91 to 94 us with an identity shortcut, 81 us at the transition, of which input and output (206 and 128 MB)
+// need 40 and 25.  Here a workgroup walks over tiles of 14 x 8 output pixels; a tile's input with a border of one pixel, 16 x 10, comes
 // to LDS once and serves as the first convolution's operand and as the shortcut, and what lies between the convolutions stays in
-// LDS.  The first convolution is computed on the border too (160 pixels for 112).  72 and 64 us; HBM reads 105 MB for the identity
-// block, each input byte once.  The vector pipe binds (half of all cycles at 256 rescaled outputs and as many shortcuts a pixel;
-// the matrix pipe a fifth), with the barriers between the three parts.
+// LDS.  The first convolution is computed on the border too (160 pixels for 112).  64 and 61 us (kernel trace, in the network); HBM
+// reads 105 MB for the identity block, each input byte once.  The vector pipe binds (half of all cycles at 256 rescaled outputs and
+// as many shortcuts a pixel; the matrix pipe a quarter), with the barriers between the three parts.
 //
 // Four waves to a workgroup, two workgroups to a CU, so that one fetches and multiplies while the other requantises.  The weights
 // of the second, third and shortcut convolutions live in registers, the first's in LDS (all in registers: 33 of them spilled at the
-// transition, 86 us; the shortcut's in LDS too: no faster, and batch 128 as a whole 25 us slower).  The next tile's input comes
+// transition, 86 us; the shortcut's in LDS too: no faster, and batch 128 as a whole 25 us slower).  Two waves a SIMD leave 256
+// registers, and only the floating-point form fits them: by the compiler's report the transition keeps 4 words a lane in scratch
+// memory, with a stored shortcut 10, the identity block of packed 4-bit pixels 10, that of bytes with integer shortcuts 6.  It
+// shows: batch 256, packed input 126 us and bytes 121, stored transition 149 with a packed output and 143 with bytes.  The next tile's input comes
 // while the second and third convolutions of this one run: the identity shortcut's bytes go to registers before, the transition's
 // small input has two places in LDS.  Sixteen columns to a tile's input row make every LDS address of the kernel a lane's constant
 // plus an immediate: pixel h of the input tile lies in row h, a tap's row distance is a multiple of sixteen rows and leaves the
 // bank permutation as it is.
 //
-// The identity shortcut of bytes is scaled in floating point, two instructions for three: 73 -> 69.5 us,
+// The identity shortcut of bytes is scaled in floating point, two instructions for three: 3.5 us of the identity block's 64,
 // ResNet50 as a whole 966 -> 959 at batch 128.  (The streaming 1x1 kernels with a shortcut gained
 // nothing by it: 32.3 us either way at 28 x 28, 21 at 14 x 14, batch 128.)
 #include "conv_block.h"

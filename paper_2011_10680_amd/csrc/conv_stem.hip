@@ -147,8 +147,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) c
 // image and the pooled tensor are 45 MB, 9 us.  56 -> 41 us at batch 128, 102 -> 70 at 256, 30 -> 24 at 64, 7.9 and 8.0 at
 // batch 1 against a tile of 3 x 5 conv1 outputs at a time (14 instructions for four pooled pixels; three waves on a SIMD where
 // this has two).  Of that 45 us came with the larger block, 3 with fragment reads free of bank conflicts, branch-free loads and
-// places in the image that are stepped and not divided.  Matrix pipes 40 %, vector ALU 30 %, LDS half of the cycles: what is
-// left is each wave's own chain of multiplying, taking maxima and staging, with two of them on a SIMD to overlap.
+// places in the image that are stepped and not divided.  Matrix pipes 40 %, vector ALU 30 %, LDS half of the cycles (a quarter
+// of the LDS's are still conflicts, of the staging's and the results' writes): what is left is each wave's own chain of multiplying,
+// taking maxima and staging, with two of them on a SIMD to overlap.
 //
 // A workgroup (four waves) makes 8 x 8 tiles of pooled pixels from a 39 x 41 input patch staged in LDS (pixels widened to
 // RGB0 dwords; a filter row = 8 pixels x 4 B = one K = 32 MFMA step), two pooled rows to a wave: the addresses of a lane's
