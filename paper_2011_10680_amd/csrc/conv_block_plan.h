@@ -10,10 +10,10 @@ constexpr int BLOCK_HW = 16, BLOCK_HROWS = BLOCK_TH + 2;               // its in
 
 // Byte offset of image n's row y (inside the image or not) as a load's scalar offset.  Rows outside the image are read at a lane
 // offset that is out of range, and the scalar offset stays inside the tensor all the same: the range check subtracts it from the
-// buffer's size, and what it does with a negative difference is documented nowhere.
+// buffer's size, and what it does with a negative difference is documented nowhere.  (The same test as the lane offset's: one
+// select; clamping the row cost two scalar instructions a load and 0.1 to 0.2 % of a ResNet50 forward.)
 constexpr int32_t block_input_row(int n, int y, int H, int W, int pixel_bytes) {
-    const int inside = y < 0 ? 0 : y < H ? y : H - 1;
-    return (n * H + inside) * W * pixel_bytes;
+    return (unsigned)y < (unsigned)H ? (n * H + y) * W * pixel_bytes : 0;
 }
 
 // The shortcut of an unsigned byte in floating point, exactly:  (r*rb + 2^(rc-1)) >> rc  is the integer nearest to
