@@ -11,14 +11,16 @@
 //
 // Four waves to a workgroup, two workgroups to a CU, so that one fetches and multiplies while the other requantises.  The weights
 // of the second, third and shortcut convolutions live in registers, the first's in LDS (all in registers: 33 of them spilled at the
-// transition, 86 us; the shortcut's in LDS too: no faster, and batch 128 as a whole 25 us slower).  Two waves a SIMD leave 256
-// registers, and only the floating-point form fits them: by the compiler's report the transition keeps 4 words a lane in scratch
-// memory, with a stored shortcut 10, the identity block of packed 4-bit pixels 10, that of bytes with integer shortcuts 6.  It
-// shows: batch 256, packed input 126 us and bytes 121, stored transition 149 with a packed output and 143 with bytes.  The next tile's input comes
+// transition, 86 us; the shortcut's in LDS too: no faster, and batch 128 as a whole 25 us slower).  The next tile's input comes
 // while the second and third convolutions of this one run: the identity shortcut's bytes go to registers before, the transition's
 // small input has two places in LDS.  Sixteen columns to a tile's input row make every LDS address of the kernel a lane's constant
 // plus an immediate: pixel h of the input tile lies in row h, a tap's row distance is a multiple of sixteen rows and leaves the
 // bank permutation as it is.
+//
+// Two waves a SIMD leave 256 registers, and not every form fits them: by the compiler's report the transition keeps 4 words a lane
+// in scratch memory, with a stored shortcut 10, the identity block of bytes with integer shortcuts 6; in floating point and of
+// packed 4-bit pixels none.  Batch 256: bytes 113 us, packed input 115, packed input and output 122, stored transition 132 (packed
+// output 138).
 //
 // The identity shortcut of bytes is scaled in floating point, two instructions for three: 3.5 us of the identity block's 64,
 // ResNet50 as a whole 966 -> 959 at batch 128.  (The streaming 1x1 kernels with a shortcut gained
